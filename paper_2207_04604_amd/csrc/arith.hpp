@@ -1,27 +1,32 @@
 // Modular arithmetic back-ends ("policies") for the transform engine on gfx950.
 //
 // On CDNA4 v_mad_u64_u32, v_mul_lo/hi_u32, v_lshl_add_u64 and v_fma_f64 all issue at full
-// rate, so the cost of a butterfly is its instruction count.  Three formulations, chosen
-// per context from the size of the largest modulus:
+// rate, so the cost of a butterfly is its instruction count.  Six formulations, chosen
+// per context from the size and the form of the moduli:
 //
 //   ArithF  (moduli < 2^44)  residues as signed doubles.  w*y mod q from an error-free
 //           product (mul + fma), one rounded quotient and one fma: 6 instructions, result
 //           in about (-q/2, q/2); butterflies add and subtract without any correction.
-//   ArithS  (moduli < 2^55)  64-bit integers, Shoup quotient ws = floor(w 2^63 / q).  The
+//   ArithS  (other moduli < 2^55)  64-bit integers, Shoup quotient ws = floor(w 2^63 / q).  The
 //           quotient estimate drops the low x low partial product (error <= 2), so the
 //           product lands in [0, 4q); values grow by at most 4q per forward stage and are
 //           never corrected inside a forward transform (65 q < 2^62).
-//   ArithB  (moduli < 2^61)  64-bit integers, exact 63-bit Shoup quotient, Harvey's lazy
+//   ArithB  (other moduli < 2^61)  64-bit integers, exact 63-bit Shoup quotient, Harvey's lazy
 //           butterflies: forward values in [0, 4q), inverse values in [0, 2q).
+//   ArithP  (moduli in [2^44, 2^55) just below a power of two) and
+//   ArithQ  (the same up to 2^60): q = 2^b - c with a small c.  Multiplicands are kept as w and
+//           w 2^32 mod q, both split at bit b - 31, so that a product needs no quotient: six
+//           multiply-adds give w*y + u directly (see pm_mul_add).  9 instructions per butterfly
+//           instead of 15 (ArithS) and 10.5 instead of 21 (ArithB).
 //   Arith32 (moduli < 2^30)  32-bit residues (one register and one 4-byte LDS word per
 //           coefficient), 32-bit Shoup quotient ws = floor(w 2^32 / q), Harvey's lazy butterflies
 //           in 8 instructions.  Used for whole contexts whose primes are below 2^30 and, in every
 //           context, for the transforms modulo the plaintext modulus t.
 //
-// Table entries (twiddles, per-modulus constants) are {w, floor(w 2^63 / q)} for the integer
-// policies and {bits of the double w, unused} for ArithF.  Prepared keys cross the library
-// boundary as values plus 64-bit quotients floor(v 2^64 / q); the integer policies shift
-// those right by one, ArithF converts the value and ignores the quotient.
+// Table entries (twiddles, per-modulus constants) are {w, floor(w 2^63 / q)} for ArithS and ArithB,
+// {bits of the double w, unused} for ArithF, the two split multiplicands for ArithP and ArithQ.
+// Prepared keys cross the library boundary as values plus 64-bit quotients floor(v 2^64 / q); ArithS and
+// ArithB shift those right by one, ArithF, ArithP and ArithQ read the value only.
 #pragma once
 #include <stdint.h>
 
@@ -333,14 +338,16 @@ struct ArithS {
     typedef uint64_t word;          // LDS word of an exchange
     typedef ModU Mod;
     typedef TwU Twid;
-    static constexpr int KIND = 1;
+    static constexpr int KIND = 1, INV_LIM = 0, INV_PROD = 0;
 
     D2_DEV static Mod mod(uint64_t q) { return Mod{q, 0 - q, 0}; }
     D2_DEV static Mod mod(uint64_t q, uint64_t one_s63) { return Mod{q, 0 - q, one_s63}; }
     D2_DEV static Twid tw(const Tw &t) { return Twid{t.w, t.ws}; }
     D2_DEV static Twid tw(uint64_t w, uint64_t ws64) { return Twid{w, ws64 >> 1}; }
     // element of a prepared key: values at v, 64-bit quotients at vs
-    D2_DEV static Twid key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
+    typedef Twid Key;
+    D2_DEV static Key key_of(uint64_t v, uint64_t vs) { return tw(v, vs); }
+    D2_DEV static Key key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
     {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
@@ -378,6 +385,9 @@ struct ArithS {
     }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
+    // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
+    D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
+    D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
     // x + v for a small signed v (|v| <= 32), as a forward input: q is added instead of mapping v into
     // [0, q) first (the forward range has room for it)
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + (m.q + (uint64_t)(int64_t)v); }
@@ -385,7 +395,7 @@ struct ArithS {
     // forward: no correction; each stage adds at most 4q to the bound.
     // x' = u + t comes out of the multiply-add chain itself, y' = u + 4q - t = (2u + 4q) - x'.
     template <bool SC = false>
-    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
     {
         const elem u = x;
         x = shoup_tail_add<SC>(y, w.w, qhat_approx<SC>(y, w.ws), m.nq, u);
@@ -407,7 +417,7 @@ struct ArithS {
     D2_DEV static void fwd_end(elem &, const Mod &) {}
     // inverse: values in [0, 4q)
     template <bool SC = false>
-    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool = false)
     {
         const elem four_q = 4 * m.q;
         const elem s = x + y, d = x + four_q - y;
@@ -446,14 +456,16 @@ struct ArithB {
     typedef uint64_t word;          // LDS word of an exchange
     typedef ModU Mod;
     typedef TwU Twid;
-    static constexpr int KIND = 2;
+    static constexpr int KIND = 2, INV_LIM = 0, INV_PROD = 0;
 
     D2_DEV static Mod mod(uint64_t q) { return Mod{q, 0 - q, 0}; }
     D2_DEV static Mod mod(uint64_t q, uint64_t one_s63) { return Mod{q, 0 - q, one_s63}; }
     D2_DEV static Twid tw(const Tw &t) { return Twid{t.w, t.ws}; }
     D2_DEV static Twid tw(uint64_t w, uint64_t ws64) { return Twid{w, ws64 >> 1}; }
     // element of a prepared key: values at v, 64-bit quotients at vs
-    D2_DEV static Twid key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
+    typedef Twid Key;
+    D2_DEV static Key key_of(uint64_t v, uint64_t vs) { return tw(v, vs); }
+    D2_DEV static Key key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
     {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
@@ -481,12 +493,15 @@ struct ArithB {
     }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
+    // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
+    D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
+    D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul(y, w, m); }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
 
     // x, y in [0, 4q) -> [0, 4q)
     template <bool SC = false>
-    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
     {
         const elem two_q = 2 * m.q;
         const elem u = csub(x, two_q);
@@ -505,7 +520,7 @@ struct ArithB {
     D2_DEV static void fwd_end(elem &, const Mod &) {}
     // x, y in [0, 2q) -> [0, 2q)
     template <bool SC = false>
-    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool = false)
     {
         const elem two_q = 2 * m.q;
         const elem s = x + y, d = x + two_q - y;
@@ -548,7 +563,7 @@ struct ArithF {
     struct Twid {
         double w;
     };
-    static constexpr int KIND = 0;
+    static constexpr int KIND = 0, INV_LIM = 0, INV_PROD = 0;
 
     D2_DEV static double u2d(uint64_t v)    // exact for v < 2^52
     {
@@ -568,7 +583,9 @@ struct ArithF {
     D2_DEV static Twid tw(const Tw &t) { return Twid{__longlong_as_double((long long)t.w)}; }
     D2_DEV static Twid tw(uint64_t w, uint64_t) { return Twid{u2d(w)}; }
     // element of a prepared key: only the values are read
-    D2_DEV static Twid key(const uint64_t *v, const uint64_t *, uint32_t lane_off, uint32_t slot_off)
+    typedef Twid Key;
+    D2_DEV static Key key_of(uint64_t v, uint64_t vs) { return tw(v, vs); }
+    D2_DEV static Key key(const uint64_t *v, const uint64_t *, uint32_t lane_off, uint32_t slot_off)
     {
         return Twid{u2d(ld64(v, lane_off, slot_off))};
     }
@@ -607,9 +624,12 @@ struct ArithF {
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul((double)y, w, m); }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &) { return x + (double)v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
+    // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
+    D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
+    D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
 
     template <bool SC = false>
-    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
     {
         const elem t = mul<SC>(y, w, m);
         const elem u = x;
@@ -631,7 +651,7 @@ struct ArithF {
     D2_DEV static void fwd_pass_begin(elem &, const Mod &) {}
     D2_DEV static void fwd_end(elem &, const Mod &) {}
     template <bool SC = false>
-    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool = false)
     {
         const elem s = x + y, d = x - y;
         x = s;
@@ -678,14 +698,16 @@ struct Arith32 {
     struct Twid {
         uint32_t w, ws;
     };
-    static constexpr int KIND = 3;
+    static constexpr int KIND = 3, INV_LIM = 0, INV_PROD = 0;
 
     D2_DEV static Mod mod(uint64_t q, uint64_t one_s32) { return Mod{(uint32_t)q, 2u * (uint32_t)q, 0u - (uint32_t)q, (uint32_t)one_s32}; }
     D2_DEV static Mod mod(uint64_t q) { return mod(q, (1ull << 32) / q); }
     D2_DEV static Twid tw(const Tw &t) { return Twid{lo32(t.w), hi32(t.w)}; }
     D2_DEV static Twid tw(uint64_t w, uint64_t ws64) { return Twid{(uint32_t)w, hi32(ws64)}; }
     // element of a prepared key: values at v, 64-bit quotients at vs (their high words are the 32-bit quotients)
-    D2_DEV static Twid key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
+    typedef Twid Key;
+    D2_DEV static Key key_of(uint64_t v, uint64_t vs) { return tw(v, vs); }
+    D2_DEV static Key key(const uint64_t *v, const uint64_t *vs, uint32_t lane_off, uint32_t slot_off)
     {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
@@ -717,12 +739,15 @@ struct Arith32 {
     D2_DEV static elem from_small(int32_t v, const Mod &m) { return v >= 0 ? (uint32_t)v : m.q - (uint32_t)(-v); }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return (uint32_t)v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
+    // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
+    D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
+    D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul(y, w, m); }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
 
     // x, y in [0, 4q) -> [0, 4q)
     template <bool SC = false>
-    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
     {
         const elem u = csub32(x, m.two_q);
         const elem t = mul<SC>(y, w, m);
@@ -742,7 +767,7 @@ struct Arith32 {
     D2_DEV static void fwd_end(elem &x, const Mod &m) { x = csub32(x, m.two_q); }
     // x, y in [0, 2q) -> [0, 2q)
     template <bool SC = false>
-    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m)
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool = false)
     {
         const elem s = x + y, d = x + m.two_q - y;
         x = csub32(s, m.two_q);
@@ -772,6 +797,302 @@ struct Arith32 {
     D2_DEV static uint64_t canon_acc(elem x, const Mod &m) { return canon_lazy(x, m); }
 };
 
+// ---------------------------------------------------------------------------------------
+// ArithP, ArithQ: moduli q = 2^b - c with a small c (b < 56 / b <= 60), the form in which RNS primes are
+// usually searched.  2^(b+1) = 2c (mod q), so the part of a product above bit b + 1 folds down with one
+// multiply-add and no quotient is ever estimated.
+//
+// A multiplicand w is kept as w and W = w 2^32 mod q, each split at bit s = b - 31:
+//     w = w01 2^s + w00,   W = w11 2^s + w10,   w01, w11 < 2^31.
+// For y = y1 2^32 + y0:  w y = w y0 + W y1 = A + B 2^s (mod q),  A = w00 y0 + w10 y1,  B = w01 y0 + w11 y1 < 2^64,
+// and B 2^s = B_lo 2^s + B_hi 2^(b+1) = B_lo 2^s + B_hi 2c.  Six multiply-adds in all; an addend u rides on the
+// first.  With kappa = y / 2^64 and gamma = c 2^32 / 2^b the result is below
+//     T = ((2 + gamma)(1 + kappa) + 2) 2^b <= G q,
+// G computed at context creation (8 for ArithP's 55-bit and 6 for ArithQ's 60-bit moduli; larger when c is).
+// The kernels are bound by instruction issue.  Measured, with the Shoup quotients and with this: round of 34,272
+// ciphertexts, N = 2^13, four 54-bit limbs, 28.7 -> 23.4 ms; N = 2^14, eight limbs, 20.7 -> 18.5 ms; transforms of
+// N = 2^16, 16 60-bit limbs, batch 64: forward 0.509 -> 0.426 ms, inverse 0.516 -> 0.435 ms.
+// ---------------------------------------------------------------------------------------
+struct ModPm {
+    uint64_t q;
+    uint64_t k;         // G q: what a difference adds to stay positive
+    uint64_t c64;       // c as a 64-bit addend
+    uint32_t c, c2;     // c, 2c
+    uint32_t p2s;       // 2^s
+    uint32_t sh;        // b - 32: bit b of a value as a bit of its high word
+};
+struct TwPm {
+    uint32_t w00, w01, w10, w11;
+};
+
+// One multiply-add per statement (the compiler orders them); its own selection from C splits some of them into
+// 32-bit multiplications.  mad_s: the first factor sits in a scalar register.
+D2_DEV uint64_t mad_v(uint32_t a, uint32_t b, uint64_t c)
+{
+#if D2_GCN_ASM
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c) : "vcc");
+    return r;
+#else
+    return (uint64_t)a * b + c;
+#endif
+}
+D2_DEV uint64_t mad_s(uint32_t a, uint32_t b, uint64_t c)
+{
+#if D2_GCN_ASM
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "s"(a), "v"(b), "v"(c) : "vcc");
+    return r;
+#else
+    return (uint64_t)a * b + c;
+#endif
+}
+template <bool SC>
+D2_DEV uint64_t mad_w(uint32_t a, uint32_t b, uint64_t c)
+{
+    if constexpr (SC) return mad_s(a, b, c);
+    else return mad_v(a, b, c);
+}
+template <bool SC>
+D2_DEV uint64_t mul_w(uint32_t a, uint32_t b)
+{
+#if D2_GCN_ASM
+    uint64_t r;
+    if constexpr (SC) asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "s"(a), "v"(b) : "vcc");
+    else asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b) : "vcc");
+    return r;
+#else
+    return (uint64_t)a * b;
+#endif
+}
+D2_DEV ModPm pm_mod(uint64_t q, uint64_t k)
+{
+    const uint32_t b = 64u - (uint32_t)__builtin_clzll(q);
+    const uint32_t c = (uint32_t)(((uint64_t)1 << b) - q);
+    return ModPm{q, k, c, c, 2 * c, 1u << (b - 31), b - 32};
+}
+D2_DEV TwPm pm_tw(const Tw &t) { return TwPm{lo32(t.w), hi32(t.w), lo32(t.ws), hi32(t.ws)}; }
+
+// w y + u in u + [0, G q), any y the policy's ranges allow; the low 64 bits are the value (nothing wraps)
+template <bool SC = false>
+D2_DEV uint64_t pm_mul_add(uint64_t y, const TwPm &w, uint64_t u, const ModPm &m)
+{
+    const uint32_t y0 = lo32(y), y1 = hi32(y);
+    uint64_t a = mad_w<SC>(w.w00, y0, u);
+    uint64_t b = mul_w<SC>(w.w01, y0);
+    a = mad_w<SC>(w.w10, y1, a);
+    b = mad_w<SC>(w.w11, y1, b);
+    a = mad_s(m.p2s, lo32(b), a);
+    return mad_s(m.c2, hi32(b), a);
+}
+template <bool SC = false>
+D2_DEV uint64_t pm_mul(uint64_t y, const TwPm &w, const ModPm &m)
+{
+    const uint32_t y0 = lo32(y), y1 = hi32(y);
+    uint64_t a = mul_w<SC>(w.w00, y0);
+    uint64_t b = mul_w<SC>(w.w01, y0);
+    a = mad_w<SC>(w.w10, y1, a);
+    b = mad_w<SC>(w.w11, y1, b);
+    a = mad_s(m.p2s, lo32(b), a);
+    return mad_s(m.c2, hi32(b), a);
+}
+// the same for a 32-bit y (a plaintext coefficient)
+D2_DEV uint64_t pm_mul_u32(uint32_t y, const TwPm &w, const ModPm &m)
+{
+    const uint64_t a = mul_w<false>(w.w00, y), b = mul_w<false>(w.w01, y);
+    return mad_s(m.c2, hi32(b), mad_s(m.p2s, lo32(b), a));
+}
+// bit b and above folded down: x < 2^64 -> below 2^b + (x >> b) c
+D2_DEV uint64_t pm_fold(uint64_t x, const ModPm &m)
+{
+    const uint32_t h = hi32(x) >> m.sh, top = hi32(x) & ((1u << m.sh) - 1u);
+    return mad_s(m.c, h, ((uint64_t)top << 32) | lo32(x));
+}
+// x -> [0, q) for x + (x / 2^b + 1) c < 2^64: the quotient is h = x >> b or h + 1, and h + 1 exactly when
+// x >= (h + 1) q, i.e. when x + (h + 1) c reaches (h + 1) 2^b
+D2_DEV uint64_t pm_canon(uint64_t x, const ModPm &m)
+{
+    const uint32_t h = hi32(x) >> m.sh;
+    const uint64_t z = mad_s(m.c, h, x + m.c64);
+    const uint64_t r = mad_s(m.c, hi32(z) >> m.sh, x);
+    return ((uint64_t)(hi32(r) & ((1u << m.sh) - 1u)) << 32) | lo32(r);
+}
+// A canonical value as a multiplicand: W = w 2^32 = w01 2^(b+1) + w00 2^32 = w01 2c + w00 2^32, folded once.
+D2_DEV TwPm pm_split(uint64_t w, const ModPm &m)
+{
+    const uint32_t s = m.sh + 1, mask = m.p2s - 1u;
+    TwPm t;
+    t.w00 = lo32(w) & mask;
+    t.w01 = (uint32_t)(w >> s);
+    const uint64_t W = pm_fold(mul_w<true>(m.c2, t.w01) + ((uint64_t)t.w00 << 32), m);
+    t.w10 = lo32(W) & mask;
+    t.w11 = (uint32_t)(W >> s);
+    return t;
+}
+
+// ---------------------------------------------------------------------------------------
+// ArithP: nothing is corrected inside a forward transform.  In units of q: a forward value is at most 64 + 16 G
+// (small first stage, 15 further stages, one product with a key); an inverse pass of at most four stages takes
+// values up to 8 G, folds the sums of its first stage (the first pass of all starts from canonical values and
+// folds nothing) and leaves at most 8 G.  All of it stays below 2^63.
+// A forward butterfly is 9 instructions (ArithS 15), an inverse one 11 (ArithS 20).
+// ---------------------------------------------------------------------------------------
+struct ArithP {
+    typedef uint64_t elem;
+    typedef uint64_t word;          // LDS word of an exchange
+    typedef ModPm Mod;
+    typedef TwPm Twid;
+    static constexpr int KIND = 4;
+    // bounds of inverse values in units of q (G = 8): a product, and what a pass takes and leaves
+    static constexpr int INV_PROD = 8, INV_LIM = 64;
+
+    D2_DEV static Mod mod(uint64_t q, uint64_t k) { return pm_mod(q, k); }
+    D2_DEV static Twid tw(const Tw &t) { return pm_tw(t); }
+    // element of a prepared key: only the value is read, its split form costs 9 instructions and saves
+    // half of the bytes
+    typedef uint64_t Key;
+    D2_DEV static Key key_of(uint64_t v, uint64_t) { return v; }
+    D2_DEV static Key key(const uint64_t *v, const uint64_t *, uint32_t lane_off, uint32_t slot_off)
+    {
+        return ld64(v, lane_off, slot_off);
+    }
+    static constexpr bool SCALAR_TW = true;
+    D2_DEV static Twid load_v(const Tw *table, uint32_t i)
+    {
+        const U128 e = ld128(table, 16u * i, 0);
+        return TwPm{lo32(e.lo), hi32(e.lo), lo32(e.hi), hi32(e.hi)};
+    }
+    D2_DEV static Twid load_u(const Tw *table, uint32_t i)
+    {
+        return pm_tw(Tw{const_ld64(table, 16u * i), const_ld64(table, 16u * i + 8u)});
+    }
+    template <bool SC = false>
+    D2_DEV static elem mul(elem y, const Twid &w, const Mod &m) { return pm_mul<SC>(y, w, m); }
+    D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return pm_mul_u32(y, w, m); }
+    D2_DEV static elem mul_key_add(elem u, Key k, elem x, const Mod &m) { return pm_mul_add(u, pm_split(k, m), x, m); }
+    D2_DEV static elem renorm(elem x, const Mod &) { return x; }
+    D2_DEV static elem from_small(int32_t v, const Mod &m)
+    {
+        return v >= 0 ? (uint64_t)v : m.q - (uint64_t)(uint32_t)(-v);
+    }
+    D2_DEV static elem from_canon(uint64_t v, const Mod &) { return v; }
+    D2_DEV static elem add(elem a, elem b) { return a + b; }
+    D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + (m.q + (uint64_t)(int64_t)v); }
+    // x' = u + t comes out of the multiply-adds, y' = u + G q - t = (2u + G q) - x'
+    template <bool SC = false>
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
+    {
+        const elem u = x;
+        x = pm_mul_add<SC>(y, w, u, m);
+        y = (2 * u + m.k) - x;
+    }
+    // first stage on small signed inputs (|v| <= 32): w yv is an exact 64-bit product, both results in (0, 64q + 32)
+    template <bool SC = false>
+    D2_DEV static void ct_small(int32_t xv, int32_t yv, elem &x, elem &y, const Twid &w, const Mod &m)
+    {
+        const uint64_t wv = ((uint64_t)w.w01 << (m.sh + 1)) + w.w00;
+        const int64_t t = (int64_t)wv * (int64_t)yv;
+        const uint64_t base = 32 * m.q + (uint64_t)(int64_t)xv;
+        x = base + (uint64_t)t;
+        y = base - (uint64_t)t;
+    }
+    D2_DEV static void fwd_end(elem &, const Mod &) {}
+    template <bool SC = false>
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool fold = true)
+    {
+        const elem s = x + y, d = x + 8 * m.k - y;
+        x = fold ? pm_fold(s, m) : s;
+        y = pm_mul<SC>(d, w, m);
+    }
+    template <bool SC = false>
+    D2_DEV static void gs_last(elem &x, elem &y, const Twid &ninv, const Twid &wn, const Mod &m)
+    {
+        const elem s = x + y, d = x + 8 * m.k - y;
+        x = pm_mul<SC>(s, ninv, m);
+        y = pm_mul<SC>(d, wn, m);
+    }
+    D2_DEV static void inv_pass_begin(elem &, const Mod &) {}
+    D2_DEV static elem inv_input(uint64_t canon, const Mod &) { return canon; }
+    D2_DEV static uint64_t canon_wide(elem x, const Mod &m) { return pm_canon(x, m); }
+    D2_DEV static uint64_t canon_lazy(elem x, const Mod &m) { return pm_canon(x, m); }
+    D2_DEV static uint64_t canon_fwd(elem x, const Mod &m) { return pm_canon(x, m); }
+    D2_DEV static uint64_t canon_inv(elem x, const Mod &m) { return pm_canon(x, m); }
+    D2_DEV static uint64_t canon_acc(elem x, const Mod &m) { return pm_canon(x, m); }
+};
+
+// ---------------------------------------------------------------------------------------
+// ArithQ: the same with 16 multiples of q or fewer in a word.  The odd stages of a forward transform fold u
+// first: values are at most 1 + G (and a bit) after them and 1 + 2 G after an even stage; the inputs of stage 0
+// may reach 1 + G.  Inverse values are at most G between the stages: a sum of two products is folded, sums
+// of folded values are not before they reach G.  A forward butterfly is 10.5 instructions on average, an inverse
+// one 12 (ArithB 21 and 22).
+// ---------------------------------------------------------------------------------------
+struct ArithQ : ArithP {
+    static constexpr int KIND = 5;
+    static constexpr int INV_PROD = 6, INV_LIM = 6;
+
+    // x may come from an even last stage (1 + 2 G): folded before the product is added
+    D2_DEV static elem mul_key_add(elem u, Key k, elem x, const Mod &m)
+    {
+        return pm_mul_add(u, pm_split(k, m), pm_fold(x, m), m);
+    }
+    D2_DEV static elem renorm(elem x, const Mod &m) { return pm_fold(x, m); }
+    template <bool SC = false>
+    D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int stage = 1)
+    {
+        const elem u = (stage & 1) ? pm_fold(x, m) : x;
+        x = pm_mul_add<SC>(y, w, u, m);
+        y = (2 * u + m.k) - x;
+    }
+    template <bool SC = false>
+    D2_DEV static void ct_small(int32_t xv, int32_t yv, elem &x, elem &y, const Twid &w, const Mod &m)
+    {
+        x = from_small(xv, m);
+        y = from_small(yv, m);
+        ct<SC>(x, y, w, m, 0);
+    }
+    D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
+    template <bool SC = false>
+    D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool fold = true)
+    {
+        const elem s = x + y, d = x + m.k - y;
+        x = fold ? pm_fold(s, m) : s;
+        y = pm_mul<SC>(d, w, m);
+    }
+    template <bool SC = false>
+    D2_DEV static void gs_last(elem &x, elem &y, const Twid &ninv, const Twid &wn, const Mod &m)
+    {
+        const elem s = x + y, d = x + m.k - y;
+        x = pm_mul<SC>(s, ninv, m);
+        y = pm_mul<SC>(d, wn, m);
+    }
+};
+
+// Which sums of an inverse pass a policy has to fold (bit 16 * stage + slot), from the bounds of its values in
+// units of q: a pass starts from canonical values (FIRST) or from values up to A::INV_LIM, a product is at
+// most A::INV_PROD, a sum at most the sum of its operands' bounds, and a sum that could exceed
+// A::INV_LIM is folded to 1.  INV_LIM = 0: the policy corrects its sums by itself.
+template <class A>
+constexpr uint64_t inv_folds(bool first, int stages, int slots)
+{
+    uint64_t mask = 0;
+    if (A::INV_LIM == 0) return mask;
+    int bound[16] = {};
+    for (int k = 0; k < slots; ++k) bound[k] = first ? 1 : A::INV_LIM;
+    for (int i = 0; i < stages; ++i)
+        for (int k = 0; k < slots; ++k) {
+            if (k & (1 << i)) continue;
+            int s = bound[k] + bound[k | (1 << i)];
+            if (s > A::INV_LIM) {
+                s = 1;
+                mask |= (uint64_t)1 << (16 * i + k);
+            }
+            bound[k] = s;
+            bound[k | (1 << i)] = A::INV_PROD;
+        }
+    return mask;
+}
+
 // canonical u64 helpers used outside the transforms
 D2_DEV uint64_t add_mod(uint64_t a, uint64_t b, uint64_t q) { return csub(a + b, q); }
 // w*y mod q, canonical, with the 64-bit Shoup quotient ws64 = floor(w 2^64 / q); any 64-bit y
@@ -790,6 +1111,10 @@ D2_DEV uint64_t to_bits<ArithS>(uint64_t v) { return v; }
 template <>
 D2_DEV uint64_t to_bits<ArithB>(uint64_t v) { return v; }
 template <>
+D2_DEV uint64_t to_bits<ArithP>(uint64_t v) { return v; }
+template <>
+D2_DEV uint64_t to_bits<ArithQ>(uint64_t v) { return v; }
+template <>
 D2_DEV uint64_t to_bits<ArithF>(double v) { return (uint64_t)__double_as_longlong(v); }
 
 template <>
@@ -803,6 +1128,10 @@ template <>
 D2_DEV uint64_t from_bits<ArithS>(uint64_t v) { return v; }
 template <>
 D2_DEV uint64_t from_bits<ArithB>(uint64_t v) { return v; }
+template <>
+D2_DEV uint64_t from_bits<ArithP>(uint64_t v) { return v; }
+template <>
+D2_DEV uint64_t from_bits<ArithQ>(uint64_t v) { return v; }
 template <>
 D2_DEV double from_bits<ArithF>(uint64_t v) { return __longlong_as_double((long long)v); }
 

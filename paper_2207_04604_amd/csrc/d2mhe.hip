@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ctx.hpp"
+#include "pm_growth.hpp"
 #include "stream_kernels.hpp"
 
 using namespace d2;
@@ -86,40 +87,55 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- engine shape per ring degree ----------------------------------------------------------
 typedef const EngineOps *(*OpsGetter)();
-const OpsGetter OPS_TABLE[4][7] = {
+const OpsGetter OPS_TABLE[6][7] = {
     {ops_f_10, ops_f_11, ops_f_12, ops_f_13, ops_f_14, ops_f_15, ops_f_16},
     {ops_s_10, ops_s_11, ops_s_12, ops_s_13, ops_s_14, ops_s_15, ops_s_16},
     {ops_b_10, ops_b_11, ops_b_12, ops_b_13, ops_b_14, ops_b_15, ops_b_16},
     {ops_w_10, ops_w_11, ops_w_12, ops_w_13, ops_w_14, ops_w_15, ops_w_16},
+    {ops_p_10, ops_p_11, ops_p_12, ops_p_13, ops_p_14, ops_p_15, ops_p_16},
+    {ops_q_10, ops_q_11, ops_q_12, ops_q_13, ops_q_14, ops_q_15, ops_q_16},
 };
-constexpr int ARITH_32 = 3;
+constexpr int ARITH_F = 0, ARITH_S = 1, ARITH_B = 2, ARITH_32 = 3, ARITH_P = 4, ARITH_Q = 5;
 
 const EngineOps *engine_ops(const d2mhe_ctx *ctx) { return OPS_TABLE[ctx->arith][ctx->log2n - 10](); }
 
-// Arithmetic back-end from the largest modulus: 32-bit residues below 2^30, doubles below 2^44,
-// 63-bit Shoup with an approximate quotient below 2^55, exact Harvey butterflies otherwise.
+// Arithmetic back-end from the moduli: 32-bit residues below 2^30, doubles below 2^44 (8 instructions per
+// butterfly each); above, moduli just below a power of two take ArithP or ArithQ (9 and 10.5), any
+// others the Shoup quotients of ArithS below 2^55 (15) and ArithB (21).
 // Transforms modulo the plaintext modulus (< 2^30) always use the 32-bit back-end.
 int arith_for(const d2mhe_params *p)
 {
     uint64_t qmax = 0;
-    for (uint32_t i = 0; i < p->num_limbs; ++i) qmax = p->q[i] > qmax ? p->q[i] : qmax;
+    bool narrow = true, wide = true;
+    for (uint32_t i = 0; i < p->num_limbs; ++i) {
+        qmax = p->q[i] > qmax ? p->q[i] : qmax;
+        narrow = narrow && pm_growth(p->q[i], false);
+        wide = wide && pm_growth(p->q[i], true);
+    }
     if (qmax < (1ull << 30)) return ARITH_32;
-    if (qmax < (1ull << 44)) return 0;
-    if (qmax < (1ull << 55)) return 1;
-    return 2;
+    if (qmax < (1ull << 44)) return ARITH_F;
+    if (narrow) return ARITH_P;
+    if (wide) return ARITH_Q;
+    if (qmax < (1ull << 55)) return ARITH_S;
+    return ARITH_B;
 }
 
 // table entry in the format of the back-end
 Tw h_entry(int arith, uint64_t w, uint64_t m)
 {
     Tw t;
-    if (arith == 0) {
+    if (arith == ARITH_F) {
         const double d = (double)w;          // exact: w < 2^44
         std::memcpy(&t.w, &d, sizeof(d));
         t.ws = 0;
     } else if (arith == ARITH_32) {
         t.w = w | ((w << 32) / m) << 32;     // value and floor(w 2^32 / m) in one 8-byte word
         t.ws = 0;
+    } else if (arith == ARITH_P || arith == ARITH_Q) {
+        const int s = 64 - __builtin_clzll(m) - 31;          // w and w 2^32 mod m, each split at bit s
+        const uint64_t low = ((uint64_t)1 << s) - 1, v = (uint64_t)(((u128)w << 32) % m);
+        t.w = (w & low) | (w >> s) << 32;
+        t.ws = (v & low) | (v >> s) << 32;
     } else {
         t.w = w;
         t.ws = (uint64_t)(((unsigned __int128)w << 63) / m);
@@ -290,11 +306,13 @@ d2mhe_status d2mhe_create(const d2mhe_params *p, void *dev_workspace, size_t byt
         for (size_t k = 0; k < N; ++k) inv[k] = h_entry(ar, pw[h_bitrev((uint32_t)k, (int)log2n)], m);
         LimbTab &tb = tabs[i < L ? i : L];
         tb.q = m;
-        if (ar == 0) {
+        if (ar == ARITH_F) {
             const double qinv = 1.0 / (double)m;
             std::memcpy(&tb.one_s, &qinv, sizeof(qinv));
         } else if (ar == ARITH_32) {
             tb.one_s = ((uint64_t)1 << 32) / m;
+        } else if (ar == ARITH_P || ar == ARITH_Q) {
+            tb.one_s = pm_growth(m, ar == ARITH_Q) * m;
         } else {
             tb.one_s = (uint64_t)(((u128)1 << 63) / m);
         }

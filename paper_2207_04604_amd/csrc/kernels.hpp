@@ -14,13 +14,14 @@ constexpr int MAX_LIMBS = 16;
 constexpr int MAX_GROUP = 64;
 
 // Per-modulus constants; entry L of the table array describes the plaintext modulus t.
-// Tw entries are in the context's arithmetic format ({w, floor(w 2^63/q)} for the 64-bit integer
-// policies, {bits of the double w, -} for the floating-point policy, {w | floor(w 2^32/q) << 32, -} for
+// Tw entries are in the context's arithmetic format ({w, floor(w 2^63/q)} for ArithS and ArithB, the split
+// multiplicands for ArithP and ArithQ, {bits of the double w, -} for the floating-point policy, {w | floor(w 2^32/q) << 32, -} for
 // the 32-bit policy; the entry of the plaintext modulus is always in the 32-bit format), except
 // `gamma` and `pow32`, which are always {w, floor(w 2^64/q)} (they work on canonical 64-bit integers).
 struct LimbTab {
     uint64_t q;
-    uint64_t one_s;     // floor(2^63 / q); floating-point policy: bits of the double 1/q; 32-bit policy: floor(2^32 / q)
+    uint64_t one_s;     // floor(2^63 / q); floating-point policy: bits of the double 1/q; 32-bit policy: floor(2^32 / q);
+                        // ArithP, ArithQ: G q
     Tw ninv;            // N^-1 mod q
     Tw wn;              // (inverse twiddle 1) * N^-1 mod q
     Tw lambda;          // floor(Q/t) mod q
@@ -201,7 +202,7 @@ __global__ void __launch_bounds__(256) k_head_forward(uint64_t *polys, const Lim
 #pragma unroll
             for (int j = 0; j < (1 << kb); ++j) {
                 const int k0 = (g << (kb + 1)) | j;
-                A::template ct<A::SCALAR_TW>(x[k0], x[k0 | (1 << kb)], w, md);
+                A::template ct<A::SCALAR_TW>(x[k0], x[k0 | (1 << kb)], w, md, s);
             }
         }
     }
@@ -220,6 +221,7 @@ __global__ void __launch_bounds__(256) k_head_inverse(uint64_t *polys, const Lim
     const typename A::Mod md = A::mod(tb.q, tb.one_s);
     const Tw *tw = tb.inv;
     uint64_t *p = polys + ((size_t)poly << LOGN) + (size_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr uint64_t folds = inv_folds<A>(false, LOGH, H);
     typename A::elem x[H];
 #pragma unroll
     for (int k = 0; k < H; ++k) {
@@ -239,7 +241,7 @@ __global__ void __launch_bounds__(256) k_head_inverse(uint64_t *polys, const Lim
 #pragma unroll
                 for (int j = 0; j < (1 << kb); ++j) {
                     const int k0 = (g << (kb + 1)) | j;
-                    A::template gs<A::SCALAR_TW>(x[k0], x[k0 | (1 << kb)], w, md);
+                    A::template gs<A::SCALAR_TW>(x[k0], x[k0 | (1 << kb)], w, md, (folds >> (16 * kb + k0)) & 1);
                 }
             }
         }
@@ -536,8 +538,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_keygen(uint32_t party, u
         const uint64_t sv = A::canon_fwd(s[k], md);
         sk[off + pos] = sv;
         sk[LN + off + pos] = shoup_quotient(sv, q);
-        const typename A::elem prod = A::mul(A::from_canon(sv, md), A::tw(p1[off + pos], p1[LN + off + pos]), md);
-        const uint64_t sum = A::canon_acc(A::add(prod, e[k]), md);      // p1 s + e
+        const typename A::Key pv = A::key_of(p1[off + pos], p1[LN + off + pos]);
+        const uint64_t sum = A::canon_acc(A::mul_key_add(A::from_canon(sv, md), pv, e[k], md), md);      // p1 s + e
         pk0[off + pos] = sum == 0 ? 0 : q - sum;
     }
 }
@@ -565,7 +567,7 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
     typedef typename ENG::A A;
     constexpr int E = ENG::E, BATCH = E < 8 ? E : 8, NB = E / BATCH;
     const uint32_t lo = 8u * (uint32_t)tl;
-    typename A::Twid kv[BATCH];
+    typename A::Key kv[BATCH];
     uint64_t ub[BATCH];
 #pragma unroll
     for (int k = 0; k < BATCH; ++k) {
@@ -582,10 +584,10 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
             else if constexpr (SRC == SRC_CANON) uu = A::from_canon(ub[k], md);
             else uu = u[b * BATCH + k];
             if constexpr (NEG) {
-                const uint64_t prod = A::canon_acc(A::mul(uu, kv[k], md), md);
+                const uint64_t prod = A::canon_acc(A::mul_key_add(uu, kv[k], A::from_canon(0, md), md), md);
                 r[k] = A::canon_acc(A::add(x[b * BATCH + k], A::from_canon(prod ? q - prod : 0, md)), md);
             } else {
-                r[k] = A::canon_acc(A::add(A::mul(uu, kv[k], md), x[b * BATCH + k]), md);
+                r[k] = A::canon_acc(A::mul_key_add(uu, kv[k], x[b * BATCH + k], md), md);
             }
         }
         if (b + 1 < NB) {
@@ -831,13 +833,13 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
 #pragma unroll
                 for (int k = 0; k < E; ++k) z[k] = add_mod(z[k], hv[k], q);
             }
-            typename A::Twid kv[E];
+            typename A::Key kv[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) kv[k] = A::key(skr + off, skr + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * k);
 #pragma unroll
             for (int k = 0; k < E; ++k) {
-                const typename A::elem prod = A::mul(A::from_canon(z[k], md), kv[k], md);
-                x[k] = A::inv_input(A::canon_acc(A::add(prod, A::from_canon(y[k], md)), md), md);
+                const typename A::elem sum = A::mul_key_add(A::from_canon(z[k], md), kv[k], A::from_canon(y[k], md), md);
+                x[k] = A::inv_input(A::canon_acc(sum, md), md);
             }
         } else {
 #pragma unroll
@@ -976,9 +978,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_receiver_keygen(uint32_t
 #pragma unroll
     for (int k = 0; k < E; ++k) {
         const int pos = ENG::eval_pos(k, tid);
-        const typename A::elem prod = A::mul(A::from_canon(sk[off + pos], md),
-                                             A::tw(pk[2 * LN + off + pos], pk[3 * LN + off + pos]), md);
-        const uint64_t sum = A::canon_acc(A::add(prod, x[k]), md);      // p1 s + e
+        const typename A::Key pv = A::key_of(pk[2 * LN + off + pos], pk[3 * LN + off + pos]);
+        const uint64_t sum = A::canon_acc(A::mul_key_add(A::from_canon(sk[off + pos], md), pv, x[k], md), md);      // p1 s + e
         const uint64_t p0 = sum == 0 ? 0 : q - sum;
         pk[off + pos] = p0;
         pk[LN + off + pos] = shoup_quotient(p0, q);
@@ -1035,7 +1036,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
         constexpr int BATCH = E < 8 ? E : 8;
 #pragma unroll
         for (int k0 = 0; k0 < E; k0 += BATCH) {
-            typename A::Twid kv[BATCH];
+            typename A::Key kv[BATCH];
             uint64_t cv[BATCH];
 #pragma unroll
             for (int k = 0; k < BATCH; ++k) {
@@ -1044,7 +1045,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
             }
 #pragma unroll
             for (int k = 0; k < BATCH; ++k)
-                x[k0 + k] = A::from_canon(A::canon_acc(A::add(A::mul(A::from_canon(cv[k], md), kv[k], md), x[k0 + k]), md), md);
+                x[k0 + k] = A::renorm(A::mul_key_add(A::from_canon(cv[k], md), kv[k], x[k0 + k], md), md);
         }
         mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, u, x, tl, md);
 #pragma unroll

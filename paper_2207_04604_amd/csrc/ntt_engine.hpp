@@ -204,9 +204,9 @@ struct Engine {
                 for (int j = 0; j < (1 << kb); ++j) {
                     const int k0 = (g << (kb + 1)) | j;
                     if constexpr (ahead<P>())
-                        A::template ct<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], w[tw_slot(kb, g)], md);
+                        A::template ct<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], w[tw_slot(kb, g)], md, LOGN - 1 - b);
                     else
-                        A::template ct<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], ws[b & 1][g], md);
+                        A::template ct<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], ws[b & 1][g], md, LOGN - 1 - b);
                 }
             }
         }
@@ -220,6 +220,8 @@ struct Engine {
                                 const Twid &ninv, const Twid &wn)
     {
         constexpr int wb = wbase(P), lo = sbit(P), r = stages(P);
+        static_assert(wb == lo, "fold mask counts stages from the lowest slot bit");
+        constexpr uint64_t folds = inv_folds<A>(P == NPASS - 1, r, E);
         const uint32_t hi = tw_hi<P>(tid);
         if (P != NPASS - 1) {
 #pragma unroll
@@ -248,10 +250,11 @@ struct Engine {
 #pragma unroll
                     for (int j = 0; j < (1 << kb); ++j) {
                         const int k0 = (g << (kb + 1)) | j;
+                        const bool fold = (folds >> (16 * (b - lo) + k0)) & 1;
                         if constexpr (ahead<P>())
-                            A::template gs<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], w[tw_slot(kb, g)], md);
+                            A::template gs<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], w[tw_slot(kb, g)], md, fold);
                         else
-                            A::template gs<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], ws[b & 1][g], md);
+                            A::template gs<uniform_tw<P>()>(x[k0], x[k0 | (1 << kb)], ws[b & 1][g], md, fold);
                     }
                 }
             }
