@@ -810,8 +810,8 @@ struct Arith32 {
 //     T = ((2 + gamma)(1 + kappa) + 2) 2^b <= G q,
 // G computed at context creation (8 for ArithP's 55-bit and 6 for ArithQ's 60-bit moduli; larger when c is).
 // The kernels are bound by instruction issue.  Measured, with the Shoup quotients and with this: round of 34,272
-// ciphertexts, N = 2^13, four 54-bit limbs, 28.7 -> 23.4 ms; N = 2^14, eight limbs, 20.7 -> 18.5 ms; transforms of
-// N = 2^16, 16 60-bit limbs, batch 64: forward 0.509 -> 0.426 ms, inverse 0.516 -> 0.435 ms.
+// ciphertexts, N = 2^13, four 54-bit limbs, 28.7 -> 22.6 ms; N = 2^14, eight limbs, 20.7 -> 17.5 ms; transforms of
+// N = 2^16, 16 60-bit limbs, batch 64: forward 0.509 -> 0.431 ms, inverse 0.516 -> 0.437 ms.
 // ---------------------------------------------------------------------------------------
 struct ModPm {
     uint64_t q;
@@ -825,96 +825,60 @@ struct TwPm {
     uint32_t w00, w01, w10, w11;
 };
 
-// One multiply-add per statement (the compiler orders them); its own selection from C splits some of them into
-// 32-bit multiplications.  mad_s: the first factor sits in a scalar register.
-D2_DEV uint64_t mad_v(uint32_t a, uint32_t b, uint64_t c)
-{
-#if D2_GCN_ASM
-    uint64_t r;
-    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c) : "vcc");
-    return r;
-#else
-    return (uint64_t)a * b + c;
-#endif
-}
-D2_DEV uint64_t mad_s(uint32_t a, uint32_t b, uint64_t c)
-{
-#if D2_GCN_ASM
-    uint64_t r;
-    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "s"(a), "v"(b), "v"(c) : "vcc");
-    return r;
-#else
-    return (uint64_t)a * b + c;
-#endif
-}
-template <bool SC>
-D2_DEV uint64_t mad_w(uint32_t a, uint32_t b, uint64_t c)
-{
-    if constexpr (SC) return mad_s(a, b, c);
-    else return mad_v(a, b, c);
-}
-template <bool SC>
-D2_DEV uint64_t mul_w(uint32_t a, uint32_t b)
-{
-#if D2_GCN_ASM
-    uint64_t r;
-    if constexpr (SC) asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "s"(a), "v"(b) : "vcc");
-    else asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b) : "vcc");
-    return r;
-#else
-    return (uint64_t)a * b;
-#endif
-}
+// Written as C: the compiler selects one v_mad_u64_u32 for each of these multiply-adds and interleaves independent
+// butterflies.  (As single-instruction assembly statements every dependent pair cost a wait state on top,
+// 762 in k_encrypt for N = 2^13 instead of 118, and 116 registers instead of 90.)
 D2_DEV ModPm pm_mod(uint64_t q, uint64_t k)
 {
     const uint32_t b = 64u - (uint32_t)__builtin_clzll(q);
     const uint32_t c = (uint32_t)(((uint64_t)1 << b) - q);
-    return ModPm{q, k, c, c, 2 * c, 1u << (b - 31), b - 32};
+    uint32_t p2s = 1u << (b - 31);
+#if D2_GCN_ASM
+    asm("" : "+s"(p2s));        // or a multiplication by it becomes a shift, a move and an addition
+#endif
+    return ModPm{q, k, c, c, 2 * c, p2s, b - 32};
 }
 D2_DEV TwPm pm_tw(const Tw &t) { return TwPm{lo32(t.w), hi32(t.w), lo32(t.ws), hi32(t.ws)}; }
 
 // w y + u in u + [0, G q), any y the policy's ranges allow; the low 64 bits are the value (nothing wraps)
-template <bool SC = false>
 D2_DEV uint64_t pm_mul_add(uint64_t y, const TwPm &w, uint64_t u, const ModPm &m)
 {
-    const uint32_t y0 = lo32(y), y1 = hi32(y);
-    uint64_t a = mad_w<SC>(w.w00, y0, u);
-    uint64_t b = mul_w<SC>(w.w01, y0);
-    a = mad_w<SC>(w.w10, y1, a);
-    b = mad_w<SC>(w.w11, y1, b);
-    a = mad_s(m.p2s, lo32(b), a);
-    return mad_s(m.c2, hi32(b), a);
+    const uint64_t a = mul32(w.w10, hi32(y)) + (mul32(w.w00, lo32(y)) + u);
+    const uint64_t b = mul32(w.w11, hi32(y)) + mul32(w.w01, lo32(y));
+    return mul32(m.c2, hi32(b)) + (mul32(m.p2s, lo32(b)) + a);
 }
-template <bool SC = false>
-D2_DEV uint64_t pm_mul(uint64_t y, const TwPm &w, const ModPm &m)
+D2_DEV uint64_t pm_mul(uint64_t y, const TwPm &w, const ModPm &m) { return pm_mul_add(y, w, 0, m); }
+// 2u + k, as the one instruction it is (as C it comes back as a shift and an addition in half of the butterflies:
+// the compiler moves the constant past the subtraction that follows)
+D2_DEV uint64_t pm_twice_plus(uint64_t u, uint64_t k)
 {
-    const uint32_t y0 = lo32(y), y1 = hi32(y);
-    uint64_t a = mul_w<SC>(w.w00, y0);
-    uint64_t b = mul_w<SC>(w.w01, y0);
-    a = mad_w<SC>(w.w10, y1, a);
-    b = mad_w<SC>(w.w11, y1, b);
-    a = mad_s(m.p2s, lo32(b), a);
-    return mad_s(m.c2, hi32(b), a);
+#if D2_GCN_ASM
+    uint64_t d;
+    asm("v_lshl_add_u64 %0, %1, 1, %2" : "=v"(d) : "v"(u), "s"(k));
+    return d;
+#else
+    return 2 * u + k;
+#endif
 }
 // the same for a 32-bit y (a plaintext coefficient)
 D2_DEV uint64_t pm_mul_u32(uint32_t y, const TwPm &w, const ModPm &m)
 {
-    const uint64_t a = mul_w<false>(w.w00, y), b = mul_w<false>(w.w01, y);
-    return mad_s(m.c2, hi32(b), mad_s(m.p2s, lo32(b), a));
+    const uint64_t b = mul32(w.w01, y);
+    return mul32(m.c2, hi32(b)) + (mul32(m.p2s, lo32(b)) + mul32(w.w00, y));
 }
 // bit b and above folded down: x < 2^64 -> below 2^b + (x >> b) c
 D2_DEV uint64_t pm_fold(uint64_t x, const ModPm &m)
 {
     const uint32_t h = hi32(x) >> m.sh, top = hi32(x) & ((1u << m.sh) - 1u);
-    return mad_s(m.c, h, ((uint64_t)top << 32) | lo32(x));
+    return mul32(m.c, h) + (((uint64_t)top << 32) | lo32(x));
 }
 // x -> [0, q) for x + (x / 2^b + 1) c < 2^64: the quotient is h = x >> b or h + 1, and h + 1 exactly when
 // x >= (h + 1) q, i.e. when x + (h + 1) c reaches (h + 1) 2^b
 D2_DEV uint64_t pm_canon(uint64_t x, const ModPm &m)
 {
     const uint32_t h = hi32(x) >> m.sh;
-    const uint64_t z = mad_s(m.c, h, x + m.c64);
-    const uint64_t r = mad_s(m.c, hi32(z) >> m.sh, x);
+    const uint64_t z = mul32(m.c, h) + (x + m.c64);
+    const uint64_t r = mul32(m.c, hi32(z) >> m.sh) + x;
     return ((uint64_t)(hi32(r) & ((1u << m.sh) - 1u)) << 32) | lo32(r);
 }
 // A canonical value as a multiplicand: W = w 2^32 = w01 2^(b+1) + w00 2^32 = w01 2c + w00 2^32, folded once.
@@ -924,7 +888,7 @@ D2_DEV TwPm pm_split(uint64_t w, const ModPm &m)
     TwPm t;
     t.w00 = lo32(w) & mask;
     t.w01 = (uint32_t)(w >> s);
-    const uint64_t W = pm_fold(mul_w<true>(m.c2, t.w01) + ((uint64_t)t.w00 << 32), m);
+    const uint64_t W = pm_fold(mul32(m.c2, t.w01) + ((uint64_t)t.w00 << 32), m);
     t.w10 = lo32(W) & mask;
     t.w11 = (uint32_t)(W >> s);
     return t;
@@ -967,7 +931,7 @@ struct ArithP {
         return pm_tw(Tw{const_ld64(table, 16u * i), const_ld64(table, 16u * i + 8u)});
     }
     template <bool SC = false>
-    D2_DEV static elem mul(elem y, const Twid &w, const Mod &m) { return pm_mul<SC>(y, w, m); }
+    D2_DEV static elem mul(elem y, const Twid &w, const Mod &m) { return pm_mul(y, w, m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return pm_mul_u32(y, w, m); }
     D2_DEV static elem mul_key_add(elem u, Key k, elem x, const Mod &m) { return pm_mul_add(u, pm_split(k, m), x, m); }
     D2_DEV static elem renorm(elem x, const Mod &) { return x; }
@@ -983,8 +947,8 @@ struct ArithP {
     D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
     {
         const elem u = x;
-        x = pm_mul_add<SC>(y, w, u, m);
-        y = (2 * u + m.k) - x;
+        x = pm_mul_add(y, w, u, m);
+        y = pm_twice_plus(u, m.k) - x;
     }
     // first stage on small signed inputs (|v| <= 32): w yv is an exact 64-bit product, both results in (0, 64q + 32)
     template <bool SC = false>
@@ -1002,14 +966,14 @@ struct ArithP {
     {
         const elem s = x + y, d = x + 8 * m.k - y;
         x = fold ? pm_fold(s, m) : s;
-        y = pm_mul<SC>(d, w, m);
+        y = pm_mul(d, w, m);
     }
     template <bool SC = false>
     D2_DEV static void gs_last(elem &x, elem &y, const Twid &ninv, const Twid &wn, const Mod &m)
     {
         const elem s = x + y, d = x + 8 * m.k - y;
-        x = pm_mul<SC>(s, ninv, m);
-        y = pm_mul<SC>(d, wn, m);
+        x = pm_mul(s, ninv, m);
+        y = pm_mul(d, wn, m);
     }
     D2_DEV static void inv_pass_begin(elem &, const Mod &) {}
     D2_DEV static elem inv_input(uint64_t canon, const Mod &) { return canon; }
@@ -1041,8 +1005,8 @@ struct ArithQ : ArithP {
     D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int stage = 1)
     {
         const elem u = (stage & 1) ? pm_fold(x, m) : x;
-        x = pm_mul_add<SC>(y, w, u, m);
-        y = (2 * u + m.k) - x;
+        x = pm_mul_add(y, w, u, m);
+        y = pm_twice_plus(u, m.k) - x;
     }
     template <bool SC = false>
     D2_DEV static void ct_small(int32_t xv, int32_t yv, elem &x, elem &y, const Twid &w, const Mod &m)
@@ -1057,14 +1021,14 @@ struct ArithQ : ArithP {
     {
         const elem s = x + y, d = x + m.k - y;
         x = fold ? pm_fold(s, m) : s;
-        y = pm_mul<SC>(d, w, m);
+        y = pm_mul(d, w, m);
     }
     template <bool SC = false>
     D2_DEV static void gs_last(elem &x, elem &y, const Twid &ninv, const Twid &wn, const Mod &m)
     {
         const elem s = x + y, d = x + m.k - y;
-        x = pm_mul<SC>(s, ninv, m);
-        y = pm_mul<SC>(d, wn, m);
+        x = pm_mul(s, ninv, m);
+        y = pm_mul(d, wn, m);
     }
 };
 
@@ -1091,6 +1055,20 @@ constexpr uint64_t inv_folds(bool first, int stages, int slots)
             bound[k | (1 << i)] = A::INV_PROD;
         }
     return mask;
+}
+
+// A multiplicand in vector registers that a loop keeps: nothing is derived from it outside the loop (the compiler
+// would hold its words zero-extended to 64 bits there, twice the registers).
+template <class T>
+D2_DEV void pin_multiplicand(T &) {}
+template <>
+D2_DEV void pin_multiplicand<TwPm>(TwPm &w)
+{
+#if D2_GCN_ASM
+    asm volatile("" : "+v"(w.w00), "+v"(w.w01), "+v"(w.w10), "+v"(w.w11));
+#else
+    (void)w;
+#endif
 }
 
 // canonical u64 helpers used outside the transforms

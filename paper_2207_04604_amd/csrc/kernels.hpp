@@ -299,6 +299,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_tail_forward(uint64_t *p
 #pragma unroll
     for (int k = 0; k < E; ++k) nx[k] = ld64(p, 8u * (uint32_t)tid, 8u * ENG::T * k);
     for (uint32_t m = tt.m0; m < tt.m1; ++m, p += stride) {
+        ENG::pin(tw);
         typename A::elem x[E];
 #pragma unroll
         for (int k = 0; k < E; ++k) x[k] = from_bits<A>(nx[k]);
@@ -333,6 +334,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_tail_inverse(uint64_t *p
 #pragma unroll
     for (int k = 0; k < E; ++k) nx[k] = ld64(p, 8u * (uint32_t)tid, 8u * ENG::T * k);
     for (uint32_t m = tt.m0; m < tt.m1; ++m, p += stride) {
+        ENG::pin(tw);
         typename A::elem x[E];
 #pragma unroll
         for (int k = 0; k < E; ++k) x[k] = A::inv_input(nx[k], md);

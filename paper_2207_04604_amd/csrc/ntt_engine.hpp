@@ -53,6 +53,15 @@ D2_DEV void sched_fence()
 #endif
 }
 
+// The same pointer, as one the compiler knows nothing about: loads through it are not shared with earlier ones.
+D2_DEV const Tw *fresh_table(const Tw *tw)
+{
+#if D2_GCN_ASM
+    asm volatile("" : "+s"(tw));
+#endif
+    return tw;
+}
+
 // table entry with an index that is uniform over the workgroup
 template <class A>
 D2_DEV typename A::Twid load_tw_uniform(const Tw *tw, uint32_t i)
@@ -351,9 +360,13 @@ struct Engine {
     }
 
     // The next forward transform of a chain (see PINGPONG); `lds` holds LDS_CHAIN_WORDS words.
+    // With 16 coefficients per thread the scalar twiddles of two passes fill the scalar registers: transforms that
+    // follow one another fetch them again (the constant cache has them) instead of keeping them in lanes
+    // of vector registers (290 of 6,290 vector instructions of k_encrypt for N = 2^14 moved them there and back).
     D2_DEV static void forward_chained(elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid, uint32_t blk, const Tw *tw,
                                        const Mod &md)
     {
+        if constexpr (E > 8) tw = fresh_table(tw);
         Twid w[E];
         load_tw<0, false, true>(w, tid, blk, tw);
         fwd_from<0, PINGPONG>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
@@ -368,6 +381,7 @@ struct Engine {
                                              const Tw *tw, const Mod &md)
     {
         static_assert(LOGB == LOGN && stages(0) >= 2 && ahead<0>(), "shape without a separable first stage");
+        if constexpr (E > 8) tw = fresh_table(tw);
         Twid w[E];
         load_tw<0, false, true>(w, tid, 0, tw);
         constexpr int kb = ELOG - 1;                      // the first stage pairs slots k and k + E/2, one twiddle
@@ -391,6 +405,17 @@ struct Engine {
     {
         load_tw<P, FOLD, !INV>(t.w[P], tid, blk, tw);
         if constexpr (P + 1 < NPASS) load_all<INV, FOLD, P + 1>(t, tid, blk, tw);
+    }
+
+    // at the top of a loop over transforms that share `t`
+    template <int P = 0>
+    D2_DEV static void pin(Twiddles &t)
+    {
+        if constexpr (!uniform_tw<P>()) {
+#pragma unroll
+            for (int i = 0; i < E - 1; ++i) pin_multiplicand(t.w[P][i]);
+        }
+        if constexpr (P + 1 < NPASS) pin<P + 1>(t);
     }
 
     template <int P = 0, bool FRESH = false>
