@@ -327,7 +327,8 @@ def main():
                   "create_ms": w.create_ms, "keys_ms": w.keys_ms},
         "phase_ms": fig["phase_ms"],
         "phase_roofline": fig["phase_roofline"],
-        "phase_ms_from": f"{nph} further steps with an event after every phase (of the timed steps every "
+        "phase_ms_from": f"{nph} further steps with an event after every phase, which runs the last three as separate "
+                         f"launches (the timed steps run them in one; of the timed steps every "
                          f"{EVENT_EVERY}th records two events, around the dominant kernel's launches)",
         "round_algorithmic": fig["round_algorithmic"],
         "roofline": {"kernel": f"k_encrypt (fused encode + encrypt), {w.launches} launch(es) per round", "bound": "alu",

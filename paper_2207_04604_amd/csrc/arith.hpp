@@ -379,6 +379,9 @@ struct ArithS {
         const uint32_t cross = hi32(w.w) * y + h * hi32(m.nq);
         return acc + ((uint64_t)cross << 32);
     }
+    // sums of canonical words (at most 65 of them), left unreduced until sum_end
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t) { return a + b; }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &m) { return canon_wide(s, m); }
     D2_DEV static elem from_small(int32_t v, const Mod &m)
     {
         return v >= 0 ? (uint64_t)v : m.q - (uint64_t)(uint32_t)(-v);
@@ -487,6 +490,9 @@ struct ArithB {
     {
         return shoup_tail<SC>(y, w.w, qhat_exact<SC>(y, w.ws), m.nq);
     }
+    // sums of canonical words, canonical at every step
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t q) { return csub(a + b, q); }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &) { return s; }
     D2_DEV static elem from_small(int32_t v, const Mod &m)
     {
         return v >= 0 ? (uint64_t)v : m.q - (uint64_t)(uint32_t)(-v);
@@ -619,6 +625,9 @@ struct ArithF {
         const double r = __builtin_fma(-b, m.q, h);
         return r + l;
     }
+    // sums of canonical words (at most 65 of them), left unreduced until sum_end
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t) { return a + b; }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &m) { return canon_wide(u2d(s), m); }
     D2_DEV static elem from_small(int32_t v, const Mod &) { return (double)v; }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return u2d(v); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul((double)y, w, m); }
@@ -736,6 +745,9 @@ struct Arith32 {
         const uint32_t qh = __umulhi(y, w.ws);
         return (uint32_t)(mul32(w.w, y) + mul32(qh, m.nq));
     }
+    // sums of canonical words, canonical at every step
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t q) { return csub(a + b, q); }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &) { return s; }
     D2_DEV static elem from_small(int32_t v, const Mod &m) { return v >= 0 ? (uint32_t)v : m.q - (uint32_t)(-v); }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return (uint32_t)v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
@@ -935,6 +947,9 @@ struct ArithP {
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return pm_mul_u32(y, w, m); }
     D2_DEV static elem mul_key_add(elem u, Key k, elem x, const Mod &m) { return pm_mul_add(u, pm_split(k, m), x, m); }
     D2_DEV static elem renorm(elem x, const Mod &) { return x; }
+    // sums of canonical words (at most 65 of them), left unreduced until sum_end
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t) { return a + b; }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &m) { return pm_canon(s, m); }
     D2_DEV static elem from_small(int32_t v, const Mod &m)
     {
         return v >= 0 ? (uint64_t)v : m.q - (uint64_t)(uint32_t)(-v);
@@ -1015,6 +1030,9 @@ struct ArithQ : ArithP {
         y = from_small(yv, m);
         ct<SC>(x, y, w, m, 0);
     }
+    // sums of canonical words, canonical at every step
+    D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t q) { return csub(a + b, q); }
+    D2_DEV static uint64_t sum_end(uint64_t s, const Mod &) { return s; }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
     template <bool SC = false>
     D2_DEV static void gs(elem &x, elem &y, const Twid &w, const Mod &m, bool fold = true)

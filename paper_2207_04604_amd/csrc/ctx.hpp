@@ -53,6 +53,9 @@ struct EngineOps {
                             uint64_t *pt, hipStream_t);
     d2mhe_status (*combine_decode)(d2mhe_ctx *, const GroupJobs &jobs, uint32_t njobs, size_t stride, uint32_t C,
                                    uint64_t n_values, hipStream_t);
+    // sum, shares, combine and decode of whole groups in one launch; null where the shape has no such kernel
+    d2mhe_status (*finish)(d2mhe_ctx *, const FinishJobs &jobs, uint32_t ngroups, const uint64_t *cts, uint64_t *agg,
+                           uint64_t *shares, uint32_t ct_base, uint32_t C, uint64_t n_values, hipStream_t);
     // MBFV.Convert
     d2mhe_status (*receiver_keygen)(d2mhe_ctx *, uint32_t party, uint64_t *sk, uint64_t *pk, hipStream_t);
     d2mhe_status (*convert_share)(d2mhe_ctx *, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,

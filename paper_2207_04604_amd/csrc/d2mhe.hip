@@ -330,7 +330,9 @@ d2mhe_status d2mhe_create(const d2mhe_params *p, void *dev_workspace, size_t byt
             uint64_t others = 1;
             for (uint32_t j = 0; j < L; ++j)
                 if (j != i) others = h_mul(others, p->q[j] % m, m);
-            tb.gamma = h_tw(h_inv(others, m), m);      // always the integer pair
+            const uint64_t gamma = h_inv(others, m);
+            tb.ninvg = h_entry(ar, h_mul(ninv, gamma, m), m);
+            tb.wng = h_entry(ar, h_mul(h_mul(pw[h_bitrev(1u, (int)log2n)], ninv, m), gamma, m), m);
             const u128 num = (u128)p->t << 64;
             tb.theta_hi = (uint64_t)(num / m);
             tb.theta_lo = (uint64_t)(((num % m) << 64) / m);
@@ -743,6 +745,36 @@ size_t round_words(const d2mhe_ctx *ctx, uint64_t J, uint64_t G, uint64_t S, uin
     return (size_t)C * ((size_t)J * 2 * LN + (size_t)G * 2 * LN + shares);
 }
 
+// The table of a k_finish launch: groups g0, g0 + 1, ... as far as it holds them; returns their number (at least
+// one).  slot: scratch of num_parties entries (1 + a party's place in this table).
+uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, uint32_t g0, std::vector<uint16_t> &slot)
+{
+    static_assert(MAX_GROUP <= FIN_PARTIES && MAX_GROUP <= FIN_MEMBERS, "a group must fit one launch");
+    uint32_t n = 0, members = 0, parties = 0;
+    std::fill(slot.begin(), slot.end(), (uint16_t)0);
+    jobs.first[0] = 0;
+    for (; g0 + n < d->num_groups && n < (uint32_t)FIN_GROUPS; ++n) {
+        const uint32_t g = g0 + n, first = d->group_offsets[g], K = d->group_offsets[g + 1] - first;
+        uint32_t fresh = 0;
+        for (uint32_t i = 0; i < K; ++i) fresh += slot[d->members[first + i]] == 0;
+        if (members + K > (uint32_t)FIN_MEMBERS || parties + fresh > (uint32_t)FIN_PARTIES) break;
+        for (uint32_t i = 0; i < K; ++i) {
+            const uint32_t party = d->members[first + i];
+            if (!slot[party]) {
+                jobs.sk[parties] = d->sk_shares[party];
+                jobs.party[parties] = (uint16_t)party;
+                slot[party] = (uint16_t)++parties;
+            }
+            jobs.member[members + i] = (uint8_t)(slot[party] - 1);
+        }
+        members += K;
+        jobs.first[n + 1] = (uint16_t)members;
+        jobs.out[n] = d->out_sums[g];
+        jobs.group[n] = (uint16_t)(d->group_ids ? d->group_ids[g] : g);
+    }
+    return n;
+}
+
 // One exchange round; conv == nullptr: collective decryption of every aggregate, otherwise key
 // switching to every receiver (MBFV.Convert) and single-key decryption.
 d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_convert_desc *conv, void *scratch,
@@ -841,6 +873,32 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
         if (s != D2MHE_OK) return s;
     }
     if (ev && ev[1]) D2_HIP(ctx, hipEventRecord(ev[1], st));
+
+    // Phases 2 to 4 in one launch, or in as many as its table needs, unless the caller wants an event between them.
+    // One workgroup then walks through the K + 1 transforms of every limb of its ciphertext index, which pays where the
+    // launch fills the chip.  Measured over groups of 3 to 15 members, one launch against three: N = 8192 with 128 / 256 /
+    // 1024 workgroups 0.95-1.01 / 1.09-1.15 / 1.10-1.23 times as fast, N = 4096 0.87-0.95 / 1.05-1.09 / 1.04-1.07, N = 2048
+    // 0.82-0.93 / 0.99-1.05 / 1.05-1.08, N = 1024 with 512 / 1024 workgroups 0.90-0.99 / 1.02-1.10.
+    // A table that does not hold all groups means one launch after the other: each then has to be twice as large.
+    const bool split = ev && (ev[2] || ev[3]);
+    const uint64_t full = ctx->N >= 2048 ? 256 : 1024;
+    if (!conv && ops->finish && !split && (uint64_t)G * C >= full) {
+        FinishJobs jobs;
+        std::vector<uint16_t> slot(d->num_parties);
+        uint32_t n = fill_finish_jobs(jobs, d, 0, slot), launches = 1;
+        for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, g0, slot);
+        if (launches == 1 || (uint64_t)G * C >= 2 * full * launches) {
+            for (uint32_t g0 = 0; g0 < G; g0 += n) {
+                if (launches > 1) n = fill_finish_jobs(jobs, d, g0, slot);
+                const size_t j0 = d->group_offsets[g0];
+                d2mhe_status s = ops->finish(ctx, jobs, n, cts + j0 * ct_words, agg + (size_t)g0 * ct_words,
+                                             shares + j0 * sh_words, d->ct_base, C, d->n_values, st);
+                if (s != D2MHE_OK) return s;
+            }
+            if (ev && ev[4]) D2_HIP(ctx, hipEventRecord(ev[4], st));
+            return D2MHE_OK;
+        }
+    }
 
     // phase 2: homomorphic sum per group
     for (uint32_t g0 = 0; g0 < G; g0 += JOB_CHUNK) {

@@ -104,6 +104,21 @@ struct Launch {
         return D2MHE_OK;
     }
 
+    static d2mhe_status finish(d2mhe_ctx *ctx, const FinishJobs &jobs, uint32_t ngroups, const uint64_t *cts,
+                               uint64_t *agg, uint64_t *shares, uint32_t ct_base, uint32_t C, uint64_t n_values,
+                               hipStream_t st)
+    {
+        hipLaunchKernelGGL(k_finish<ENG>, dim3(C, ngroups), dim3(ENG::T), 0, st, jobs, cts, agg, shares,
+                           (size_t)C * 2 * ctx->L * ENG::NB, ct_base, n_values, ctx->d_tabs, ctx->rc);
+        D2_LAUNCHED(ctx);
+        return D2MHE_OK;
+    }
+    static constexpr auto finish_or_null()
+    {
+        if constexpr (ENG::E == 8) return &finish;
+        else return nullptr;
+    }
+
     static d2mhe_status receiver_keygen(d2mhe_ctx *ctx, uint32_t party, uint64_t *sk, uint64_t *pk, hipStream_t st)
     {
         hipLaunchKernelGGL(k_receiver_keygen<ENG>, dim3(ctx->L), dim3(ENG::T), 0, st, party, sk, pk, ctx->d_tabs,
@@ -170,7 +185,7 @@ struct Launch {
     static EngineOps full()
     {
         return EngineOps{ENG::ELOG, ENG::LOGB, &ntt, &keygen, &encode, &decode, &encrypt, &share, &combine,
-                         &combine_decode, &receiver_keygen, &convert_share, &convert_combine,
+                         &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &convert_combine,
                          &convert_combine_decode, &bootstrap_alpha, &bootstrap_share, &bootstrap_combine};
     }
     // transforms only (longer rings)

@@ -17,7 +17,7 @@ constexpr int MAX_GROUP = 64;
 // Tw entries are in the context's arithmetic format ({w, floor(w 2^63/q)} for ArithS and ArithB, the split
 // multiplicands for ArithP and ArithQ, {bits of the double w, -} for the floating-point policy, {w | floor(w 2^32/q) << 32, -} for
 // the 32-bit policy; the entry of the plaintext modulus is always in the 32-bit format), except
-// `gamma` and `pow32`, which are always {w, floor(w 2^64/q)} (they work on canonical 64-bit integers).
+// `pow32`, which is always {w, floor(w 2^64/q)} (it works on canonical 64-bit integers).
 struct LimbTab {
     uint64_t q;
     uint64_t one_s;     // floor(2^63 / q); floating-point policy: bits of the double 1/q; 32-bit policy: floor(2^32 / q);
@@ -25,10 +25,10 @@ struct LimbTab {
     Tw ninv;            // N^-1 mod q
     Tw wn;              // (inverse twiddle 1) * N^-1 mod q
     Tw lambda;          // floor(Q/t) mod q
-    Tw gamma;           // (Q/q)^-1 mod q, integer pair
+    Tw ninvg, wng;      // ninv and wn times (Q/q)^-1 mod q: an inverse transform scaled for the rounding of a decryption
     uint64_t theta_hi;  // floor(t * 2^128 / q), high and low words
     uint64_t theta_lo;
-    Tw pow32;           // 2^32 mod q, integer pair like gamma (reduction of 128-bit uniform blocks)
+    Tw pow32;           // 2^32 mod q, integer pair (reduction of 128-bit uniform blocks)
     uint64_t inv64;     // floor(2^64 / q)
     const Tw *fwd;      // forward twiddles, N entries
     const Tw *inv;      // inverse twiddles, N entries
@@ -45,7 +45,8 @@ D2_DEV LimbTab load_tab(const LimbTab *tabs, uint32_t i)
     r.ninv = Tw{const_ld64(e, offsetof(LimbTab, ninv)), const_ld64(e, offsetof(LimbTab, ninv) + 8)};
     r.wn = Tw{const_ld64(e, offsetof(LimbTab, wn)), const_ld64(e, offsetof(LimbTab, wn) + 8)};
     r.lambda = Tw{const_ld64(e, offsetof(LimbTab, lambda)), const_ld64(e, offsetof(LimbTab, lambda) + 8)};
-    r.gamma = Tw{const_ld64(e, offsetof(LimbTab, gamma)), const_ld64(e, offsetof(LimbTab, gamma) + 8)};
+    r.ninvg = Tw{const_ld64(e, offsetof(LimbTab, ninvg)), const_ld64(e, offsetof(LimbTab, ninvg) + 8)};
+    r.wng = Tw{const_ld64(e, offsetof(LimbTab, wng)), const_ld64(e, offsetof(LimbTab, wng) + 8)};
     r.theta_hi = const_ld64(e, offsetof(LimbTab, theta_hi));
     r.theta_lo = const_ld64(e, offsetof(LimbTab, theta_lo));
     r.pow32 = Tw{const_ld64(e, offsetof(LimbTab, pow32)), const_ld64(e, offsetof(LimbTab, pow32) + 8)};
@@ -113,6 +114,15 @@ struct GroupJobs {                     // one job = one group: K buffers laid ou
     const uint64_t *ct[JOB_CHUNK];     // aggregate (combine) / unused (sum)
     void *out[JOB_CHUNK];              // aggregate (sum) / decoded floats (combine)
     uint32_t K[JOB_CHUNK];
+};
+constexpr int FIN_PARTIES = 128, FIN_MEMBERS = 1400, FIN_GROUPS = 64;   // 3.6 KB of table; any group fits
+struct FinishJobs {                    // one job = one group
+    const uint64_t *sk[FIN_PARTIES];   // prepared secret shares of the parties of this launch
+    float *out[FIN_GROUPS];            // decoded floats
+    uint16_t party[FIN_PARTIES];
+    uint16_t group[FIN_GROUPS];
+    uint16_t first[FIN_GROUPS + 2];    // members of group g: entries [first[g], first[g + 1]) of
+    uint8_t member[FIN_MEMBERS];       // indices into sk and party
 };
 struct RecvJobs {                      // one job = one receiver of one group (MBFV.Convert)
     const uint64_t *first[CONV_CHUNK]; // conversion shares of the group's first member for this receiver
@@ -381,6 +391,36 @@ D2_DEV void stage_cbd(uint32_t *lds32, int tid, uint32_t domain, uint32_t party,
         cbd2(philox4x32_10(j, ct, party, counter_tag(domain, 0, group), rc.key), rc.eta_mask, e);
         lds32[2 * j] = (uint32_t)e[0];
         lds32[2 * j + 1] = (uint32_t)e[1];
+    }
+}
+
+// v of the neighbouring lane (lane ^ 1)
+D2_DEV int32_t lane_xor1(int32_t v)
+{
+#if D2_GCN_ASM
+    return __builtin_amdgcn_update_dpp(0, v, 0xb1 /* quad_perm [1,0,3,2] */, 0xf, 0xf, true);
+#else
+    return __shfl_xor(v, 1);
+#endif
+}
+
+// Centred-binomial coefficients of a polynomial, delivered to their pass-0 owners (slot k of thread tid: coefficient
+// k T + tid) without going through LDS.  A block holds two adjacent coefficients, i.e. the same slot of two
+// adjacent lanes: of two slots the even lane draws the block of the first, the odd lane that of the second, and
+// each hands over the half that is not its own.
+template <class ENG>
+D2_DEV void cbd_own(int32_t (&v)[ENG::E], int tid, uint32_t domain, uint32_t party, uint32_t group, uint32_t ct,
+                    const RoundConst &rc)
+{
+    const int odd = tid & 1;
+#pragma unroll
+    for (int k = 0; k < ENG::E; k += 2) {
+        int32_t e[2];
+        const uint32_t j = (uint32_t)((k + odd) * ENG::T + (tid & ~1)) / 2;
+        cbd2(philox4x32_10(j, ct, party, counter_tag(domain, 0, group), rc.key), rc.eta_mask, e);
+        const int32_t own = odd ? e[1] : e[0], got = lane_xor1(odd ? e[0] : e[1]);
+        v[k] = odd ? got : own;
+        v[k + 1] = odd ? own : got;
     }
 }
 
@@ -697,7 +737,6 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(ShareJobs jobs, ui
     typedef typename ENG::A A;
     __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
     uint32_t turn = 0;
-    uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x, job = blockIdx.y, L = rc.L;
@@ -705,11 +744,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(ShareJobs jobs, ui
     const uint64_t *sk = jobs.sk[job];
     const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = jobs.out[job] + (size_t)c * LN;
-    int e[E];
-    stage_cbd<ENG>(lds32, tid, DOM_DEC_E, jobs.party[job], jobs.group[job], ct_base + c, rc);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < E; ++k) e[k] = (int)lds32[ENG::coef_pos(k, tid)];
+    int32_t e[E];
+    cbd_own<ENG>(e, tid, DOM_DEC_E, jobs.party[job], jobs.group[job], ct_base + c, rc);
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
@@ -738,31 +774,22 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(ShareJobs jobs, ui
 // to x in R_t, and the refreshed ciphertext (Lambda x + sum eta1_k, alpha) goes to ct_out.
 // aux: alpha [C][L][N] in evaluation form.
 // -------------------------------------------------------------------------------------
-// One limb's term of round(t y / Q) = round(sum_i t y_i' / q_i): y_i' = y_i (Q/q_i)^-1 mod q_i, then
-// y_i' * theta / 2^128 = integer part, next 64 bits = fraction (theta = floor(t 2^128 / q_i)); added to the
-// running integer part and 64-bit fraction of a coefficient.
-D2_DEV void scale_term(uint64_t y_canon, const LimbTab &tb, uint64_t &acc_int, uint64_t &acc_frac)
+// One limb's term of round(t y / Q) = round(sum_i t y_i' / q_i) with y_i' = y_i (Q/q_i)^-1 mod q_i, which the inverse
+// transform delivers (ninvg, wng): y_i' * theta / 2^128 = integer part, next 64 bits = fraction (theta =
+// floor(t 2^128 / q_i)); added to the running integer part (kept below t) and 64-bit fraction of a coefficient.
+D2_DEV void scale_term(uint64_t yi, const LimbTab &tb, uint32_t t, uint32_t &acc_int, uint64_t &acc_frac)
 {
-    const uint64_t yi = mul_shoup64(y_canon, tb.gamma.w, tb.gamma.ws, tb.q);
-    uint64_t hi_lo = yi * tb.theta_hi, hi_hi = __umul64hi(yi, tb.theta_hi);
-    uint64_t lo_hi = __umul64hi(yi, tb.theta_lo);
-    uint64_t frac = hi_lo + lo_hi;
-    uint64_t ip = hi_hi + (frac < hi_lo ? 1 : 0);
-    uint64_t nf = acc_frac + frac;
-    acc_int += ip + (nf < frac ? 1 : 0);
+    const uint64_t hi_lo = yi * tb.theta_hi, hi_hi = __umul64hi(yi, tb.theta_hi);
+    const uint64_t frac = hi_lo + __umul64hi(yi, tb.theta_lo), nf = acc_frac + frac;
+    const uint32_t v = acc_int + (uint32_t)hi_hi + (frac < hi_lo ? 1u : 0u) + (nf < frac ? 1u : 0u);   // <= 2t
+    acc_int = v - t < v ? v - t : v;
     acc_frac = nf;
 }
-// + 1/2, floor, mod t.  The sum is below (L + 1) t < 2^35: reduced in doubles (exact on integers; the
-// quotient estimate can be off by one in either direction).
-D2_DEV uint32_t round_mod_t(uint64_t acc_int, uint64_t acc_frac, const RoundConst &rc)
+// + 1/2, floor, mod t
+D2_DEV uint32_t round_mod_t(uint32_t acc_int, uint64_t acc_frac, uint32_t t)
 {
-    const double td = (double)(uint32_t)rc.t, tinv = 1.0 / td;
-    const uint64_t v = acc_int + (acc_frac >> 63);
-    const double vd = (double)(uint32_t)v + 4294967296.0 * (double)(uint32_t)(v >> 32);
-    double r = __builtin_fma(-__builtin_floor(vd * tinv), td, vd);
-    r = r < 0.0 ? r + td : r;
-    r = r >= td ? r - td : r;
-    return (uint32_t)r;
+    const uint32_t v = acc_int + (uint32_t)(acc_frac >> 63);
+    return v >= t ? v - t : v;
 }
 
 enum { COMBINE_COLLECTIVE = 0, COMBINE_CONVERT = 1, COMBINE_BOOTSTRAP = 2 };
@@ -782,9 +809,14 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
     const size_t LN = (size_t)L * ENG::NB;
     const size_t share_ct = (MODE == COMBINE_COLLECTIVE ? 1 : 2) * LN;       // words of one share per ciphertext index
     const uint64_t *c0 = ct + (size_t)c * 2 * LN;
-    uint64_t acc_int[E], acc_frac[E];
+    const uint32_t t = (uint32_t)rc.t;
+    // (a zero of its own: shared with the limb counter's it would move the counter, and with it every buffer
+    // descriptor, to vector registers)
+    const uint32_t zero = opaque(0u);
+    uint32_t acc_int[E];
+    uint64_t acc_frac[E];
 #pragma unroll
-    for (int k = 0; k < E; ++k) { acc_int[k] = 0; acc_frac[k] = 0; }
+    for (int k = 0; k < E; ++k) { acc_int[k] = zero; acc_frac[k] = 0; }
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;
@@ -847,13 +879,13 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
 #pragma unroll
             for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
         }
-        ENG::template inverse<true>(x, lds, tl, 0, tb.inv, md, A::tw(tb.ninv), A::tw(tb.wn));
+        ENG::template inverse<true>(x, lds, tl, 0, tb.inv, md, A::tw(tb.ninvg), A::tw(tb.wng));
 #pragma unroll
-        for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), tb, acc_int[k], acc_frac[k]);
+        for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), tb, t, acc_int[k], acc_frac[k]);
     }
     uint32_t m[E];
 #pragma unroll
-    for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], rc);
+    for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], t);
     if constexpr (MODE == COMBINE_BOOTSTRAP) {
         // x sits where a forward transform takes its input: c0' = NTT(Lambda x) + sum eta1_k, c1' = alpha
         uint64_t *ct_out = pt + (size_t)c * 2 * LN;
@@ -915,6 +947,141 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine_decode(GroupJobs
     combine_body<ENG, true, COMBINE_COLLECTIVE>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
                                    jobs.K[job], (const uint64_t *)nullptr, false, (uint64_t *)nullptr,
                                    (float *)jobs.out[job], n_values, tabs, rc);
+}
+
+// Sum of K canonical polynomials `stride` words apart, canonical, for the slots of a thread: the next one's words are
+// in flight while one's are added.
+template <class ENG>
+D2_DEV void sum_members(uint64_t (&s)[ENG::E], const uint64_t *p, size_t stride, uint32_t K, uint32_t lo,
+                        const typename ENG::A::Mod &md, uint64_t q)
+{
+    typedef typename ENG::A A;
+    constexpr int E = ENG::E;
+    uint64_t v[E], n[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) s[k] = ld64_stream(p, lo, 8u * ENG::T * k);
+    if (K > 1) {
+        p += stride;
+#pragma unroll
+        for (int k = 0; k < E; ++k) v[k] = ld64_stream(p, lo, 8u * ENG::T * k);
+    }
+    for (uint32_t j = 1; j < K; ++j) {
+        if (j + 1 < K) {
+            p += stride;
+#pragma unroll
+            for (int k = 0; k < E; ++k) n[k] = ld64_stream(p, lo, 8u * ENG::T * k);
+        }
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            s[k] = A::sum(s[k], v[k], q);
+            v[k] = n[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < E; ++k) s[k] = A::sum_end(s[k], md);
+}
+
+// -------------------------------------------------------------------------------------
+// Sum, decryption shares, combine and decode of one ciphertext index of one group in one workgroup; grid = (C, groups).
+// The separate kernels are bound by memory (sum, combine) or alternate memory and transforms (share), and read
+// every aggregate K times and every share once more; here the aggregate's c1 stays in registers for the K shares,
+// the shares are added up as they are made, and only what the protocol sends is written.
+//   cts: fresh ciphertexts of the first member of the launch's first group, the others ct_words apart; agg and shares:
+//   aggregate of the first group, shares of its first member.
+// The error samples of a member are drawn once and kept as bytes where its share of the last limb will go.
+// Measured (sum + shares + combine, 32 groups of 7, N = 8192, 4 limbs, 153 indices): 10.3 ms as three launches, 7.0 ms
+// in one.  The chain of K + 1 transforms per limb in one workgroup needs a full chip: see the rule in run_round.
+// -------------------------------------------------------------------------------------
+template <class ENG>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, const uint64_t *cts, uint64_t *agg,
+                                                               uint64_t *shares, size_t ct_words, uint32_t ct_base,
+                                                               uint64_t n_values, const LimbTab *tabs, RoundConst rc)
+{
+    typedef typename ENG::A A;
+    constexpr int E = ENG::E;
+    static_assert(E == 8, "the samples of a thread are kept in one 8-byte word");
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
+    const int tid = threadIdx.x;
+    uint32_t turn = 0;
+    // from the last to the first: what the encryption wrote last is still in the memory-side cache
+    const uint32_t c = gridDim.x - 1 - blockIdx.x, job = gridDim.y - 1 - blockIdx.y, L = rc.L, t = (uint32_t)rc.t;
+    const uint32_t m0 = jobs.first[job], K = jobs.first[job + 1] - m0, group = jobs.group[job];
+    const size_t LN = (size_t)L * ENG::NB, sh_words = ct_words / 2;
+    cts += (size_t)m0 * ct_words + (size_t)c * 2 * LN;
+    agg += (size_t)job * ct_words + (size_t)c * 2 * LN;
+    shares += (size_t)m0 * sh_words + (size_t)c * LN;
+    // (a zero of its own: shared with the limb counter's it would move the counter, and with it every buffer
+    // descriptor, to vector registers)
+    const uint32_t zero = opaque(0u);
+    uint32_t acc_int[E];
+    uint64_t acc_frac[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) { acc_int[k] = zero; acc_frac[k] = 0; }
+    for (uint32_t limb = 0; limb < L; ++limb) {
+        const LimbTab tb = load_tab(tabs, limb);
+        const uint64_t q = tb.q;
+        const typename A::Mod md = A::mod(q, tb.one_s);
+        const size_t off = (size_t)limb * ENG::NB;
+        const uint32_t lo = 8u * (uint32_t)opaque(tid);
+        uint64_t y[E], z[E];                        // sums of c0 (and of the shares) and of c1
+        sum_members<ENG>(z, cts + LN + off, ct_words, K, lo, md, q);
+        sum_members<ENG>(y, cts + off, ct_words, K, lo, md, q);
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            st64_stream(agg + off, lo, 8u * ENG::T * k, y[k]);
+            st64_stream(agg + LN + off, lo, 8u * ENG::T * k, z[k]);
+        }
+        for (uint32_t j = 0; j < K; ++j) {
+            const uint32_t who = jobs.member[m0 + j];
+            uint64_t *share = shares + (size_t)j * sh_words, *kept = share + (size_t)(L - 1) * ENG::NB;
+            int32_t e[E];
+            if (limb == 0) {
+                cbd_own<ENG>(e, opaque(tid), DOM_DEC_E, jobs.party[who], group, ct_base + c, rc);
+                if (L > 1) {
+                    uint32_t w[2] = {0, 0};
+#pragma unroll
+                    for (int k = 0; k < E; ++k) w[k / 4] |= ((uint32_t)e[k] & 0xffu) << (8 * (k % 4));
+                    st64(kept, lo, 0, ((uint64_t)w[1] << 32) | w[0]);
+                }
+            } else {
+                const uint64_t w = ld64(kept, lo, 0);
+#pragma unroll
+                for (int k = 0; k < E; ++k) e[k] = sbyte(k < 4 ? lo32(w) : hi32(w), k % 4);
+            }
+            typename A::elem x[E];
+            ENG::forward_chained_small(e, x, lds, turn, opaque(tid), tb.fwd, md);
+            const uint64_t *sk = jobs.sk[who];
+            typename A::Key kv[E];
+#pragma unroll
+            for (int k = 0; k < E; ++k) kv[k] = A::key(sk + off, sk + LN + off, lo, 8u * ENG::T * k);
+            uint64_t h[E];
+#pragma unroll
+            for (int k = 0; k < E; ++k) h[k] = A::canon_acc(A::mul_key_add(A::from_canon(z[k], md), kv[k], x[k], md), md);
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                st64_stream(share + off, lo, 8u * ENG::T * k, h[k]);
+                y[k] = A::sum(y[k], h[k], q);
+            }
+            if (j == 31) {                          // a sum never holds more than 33 terms
+#pragma unroll
+                for (int k = 0; k < E; ++k) y[k] = A::sum_end(y[k], md);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < E; ++k) y[k] = A::sum_end(y[k], md);
+        // the inverse side of the table, fetched here so that it is not held in scalar registers across the shares
+        const LimbTab ti = load_tab(fresh_table(tabs), limb);
+        typename A::elem x[E];
+#pragma unroll
+        for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
+        ENG::template inverse<true>(x, ENG::next_buffer(lds, turn), opaque(tid), 0, ti.inv, md, A::tw(ti.ninvg), A::tw(ti.wng));
+#pragma unroll
+        for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), ti, t, acc_int[k], acc_frac[k]);
+    }
+    uint32_t m[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], t);
+    decode_from_regs<ENG>(m, lds, tid, jobs.out[job], (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
 }
 
 // -------------------------------------------------------------------------------------

@@ -54,7 +54,8 @@ D2_DEV void sched_fence()
 }
 
 // The same pointer, as one the compiler knows nothing about: loads through it are not shared with earlier ones.
-D2_DEV const Tw *fresh_table(const Tw *tw)
+template <class T>
+D2_DEV const T *fresh_table(const T *tw)
 {
 #if D2_GCN_ASM
     asm volatile("" : "+s"(tw));
