@@ -44,10 +44,13 @@ struct EngineOps {
     d2mhe_status (*keygen)(d2mhe_ctx *, uint32_t party, uint64_t *sk, uint64_t *pk0, hipStream_t);
     d2mhe_status (*encode)(d2mhe_ctx *, const float *grad, uint64_t n_values, uint64_t *pt, uint32_t C, hipStream_t);
     d2mhe_status (*decode)(d2mhe_ctx *, const uint64_t *pt, uint32_t C, uint64_t n_values, float *out, hipStream_t);
-    // from_float: jobs.src holds gradients (encoded on the fly), otherwise plaintext polynomials
-    d2mhe_status (*encrypt)(d2mhe_ctx *, bool from_float, const EncJobs &jobs, uint32_t njobs, uint32_t ct_base,
+    // plaintexts of several parties, 32-bit words [parties][C][N]
+    d2mhe_status (*encode_parties)(d2mhe_ctx *, const EncodeJobs &jobs, uint32_t nparties, uint64_t n_values, uint32_t *pt,
+                                   uint32_t C, hipStream_t);
+    // from: FROM_VECTOR, FROM_WORDS32, FROM_WORDS64
+    d2mhe_status (*encrypt)(d2mhe_ctx *, int from, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base,
                             uint64_t n_values, uint32_t C, hipStream_t);
-    d2mhe_status (*share)(d2mhe_ctx *, const ShareJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
+    d2mhe_status (*share)(d2mhe_ctx *, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
                           hipStream_t);
     d2mhe_status (*combine)(d2mhe_ctx *, const uint64_t *ct, const PtrList &shares, uint32_t K, uint32_t C,
                             uint64_t *pt, hipStream_t);

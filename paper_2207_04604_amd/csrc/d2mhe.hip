@@ -189,6 +189,16 @@ namespace {
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
 
+// the table of a launch for one (party, group) pair
+void one_job(RoundJobs &jobs, const void *src, uint32_t party, const uint64_t *key, uint32_t group, uint64_t *out)
+{
+    jobs.out = out;
+    jobs.stride = 0;
+    jobs.set_party(0, src, party);
+    jobs.set_group(0, key, group);
+    jobs.set_job(0, 0, 0);
+}
+
 d2mhe_status launch_ntt(d2mhe_ctx *ctx, uint64_t *polys, uint32_t B, bool forward, hipStream_t st)
 {
     return engine_ops(ctx)->ntt(ctx, polys, B, forward, st);
@@ -537,13 +547,9 @@ d2mhe_status d2mhe_encrypt(d2mhe_ctx *ctx, const uint64_t *pk, const uint64_t *p
     if (misaligned(pk) || misaligned(pt) || misaligned(ct)) return D2MHE_ERR_ALIGN;
     if (party > 0xffffu || group > 0xffffu || (uint64_t)ct_base + C > 0xffffffffull) return D2MHE_ERR_RANGE;
     if (C == 0) return D2MHE_OK;
-    EncJobs jobs;
-    jobs.src[0] = pt;
-    jobs.pk[0] = pk;
-    jobs.out[0] = ct;
-    jobs.party[0] = party;
-    jobs.group[0] = group;
-    return engine_ops(ctx)->encrypt(ctx, false, jobs, 1, ct_base, 0, C, (hipStream_t)stream);
+    RoundJobs jobs;
+    one_job(jobs, pt, party, pk, group, ct);
+    return engine_ops(ctx)->encrypt(ctx, FROM_WORDS64, jobs, 1, ct_base, 0, C, (hipStream_t)stream);
 }
 
 d2mhe_status d2mhe_add(d2mhe_ctx *ctx, uint64_t *ct_acc, const uint64_t *ct_in, uint32_t C, void *stream)
@@ -570,12 +576,8 @@ d2mhe_status d2mhe_partial_decrypt(d2mhe_ctx *ctx, const uint64_t *sk_share, con
     if (misaligned(sk_share) || misaligned(ct) || misaligned(share)) return D2MHE_ERR_ALIGN;
     if (party > 0xffffu || group > 0xffffu || (uint64_t)ct_base + C > 0xffffffffull) return D2MHE_ERR_RANGE;
     if (C == 0) return D2MHE_OK;
-    ShareJobs jobs;
-    jobs.sk[0] = sk_share;
-    jobs.ct[0] = ct;
-    jobs.out[0] = share;
-    jobs.party[0] = party;
-    jobs.group[0] = group;
+    RoundJobs jobs;
+    one_job(jobs, sk_share, party, ct, group, share);
     return engine_ops(ctx)->share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
 }
 
@@ -745,6 +747,42 @@ size_t round_words(const d2mhe_ctx *ctx, uint64_t J, uint64_t G, uint64_t S, uin
     return (size_t)C * ((size_t)J * 2 * LN + (size_t)G * 2 * LN + shares);
 }
 
+// A round's J jobs in as few launches as their table allows, of equal size.
+uint32_t jobs_per_launch(uint32_t J)
+{
+    const uint32_t launches = (J + RJ_JOBS - 1) / RJ_JOBS;
+    return (J + launches - 1) / launches;
+}
+
+// The table of a launch over jobs j0, j0 + 1, ..., at most `limit` of them and as far as it holds their parties and
+// groups; returns their number (at least one).  src(party) and key(group index): the pointers of a job.  slot: scratch
+// of num_parties entries (1 + a party's place in this table).
+extern "C++" template <class SRC, class KEY>
+uint32_t fill_round_jobs(RoundJobs &jobs, const d2mhe_round_desc *d, uint32_t j0, uint32_t limit,
+                         std::vector<uint16_t> &slot, uint64_t *out, size_t stride, SRC src, KEY key)
+{
+    const uint32_t J = d->group_offsets[d->num_groups];
+    uint32_t n = 0, parties = 0, groups = 0, g = 0, listed = d->num_groups;
+    std::fill(slot.begin(), slot.end(), (uint16_t)0);
+    jobs.out = out;
+    jobs.stride = stride;
+    for (; n < limit && j0 + n < J; ++n) {
+        const uint32_t party = d->members[j0 + n];
+        while (d->group_offsets[g + 1] <= j0 + n) ++g;
+        if ((g != listed && groups == (uint32_t)RJ_GROUPS) || (!slot[party] && parties == (uint32_t)RJ_PARTIES)) break;
+        if (g != listed) {
+            jobs.set_group(groups++, key(g), d->group_ids ? d->group_ids[g] : g);
+            listed = g;
+        }
+        if (!slot[party]) {
+            jobs.set_party(parties, src(party), party);
+            slot[party] = (uint16_t)++parties;
+        }
+        jobs.set_job(n, slot[party] - 1u, groups - 1);
+    }
+    return n;
+}
+
 // The table of a k_finish launch: groups g0, g0 + 1, ... as far as it holds them; returns their number (at least
 // one).  slot: scratch of num_parties entries (1 + a party's place in this table).
 uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, uint32_t g0, std::vector<uint16_t> &slot)
@@ -854,22 +892,40 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     hipEvent_t *ev = (hipEvent_t *)phase_events;
     if (ev && ev[0]) D2_HIP(ctx, hipEventRecord(ev[0], st));
 
-    // phase 1: every member of every group encodes and encrypts its gradient
-    std::vector<uint32_t> group_of(J);
-    for (uint32_t g = 0; g < G; ++g)
-        for (uint32_t j = d->group_offsets[g]; j < d->group_offsets[g + 1]; ++j) group_of[j] = g;
-    for (uint32_t j0 = 0; j0 < J; j0 += JOB_CHUNK) {
-        const uint32_t n = J - j0 < (uint32_t)JOB_CHUNK ? J - j0 : (uint32_t)JOB_CHUNK;
-        EncJobs jobs;
-        for (uint32_t i = 0; i < n; ++i) {
-            const uint32_t j = j0 + i, g = group_of[j];
-            jobs.src[i] = d->grads[d->members[j]];
-            jobs.pk[i] = d->pks[g];
-            jobs.out[i] = cts + (size_t)j * ct_words;
-            jobs.party[i] = d->members[j];
-            jobs.group[i] = d->group_ids ? d->group_ids[g] : g;
+    // phase 1: every member of every group encodes and encrypts its gradient.  A party in many groups encrypts one
+    // vector many times: its plaintexts are then made first, in the space the shares take later, and read from there.
+    // Measured, encoded per group and ahead: 32 parties in 7 groups each, N = 8192, 4 limbs 20.2 / 19.1 ms; 16 in 5, N =
+    // 4096, 3 limbs 0.391 / 0.375 ms.  Below two groups per party, or where the launches do not fill the chip, the
+    // extra launch costs what it saves.
+    const uint32_t ids = std::min(d->num_parties, 0x10000u);
+    std::vector<uint16_t> slot(ids);
+    std::vector<uint32_t> order(ids, ~0u);               // a party's place among those that take part
+    std::vector<const float *> vectors;
+    for (uint32_t j = 0; j < J; ++j)
+        if (order[d->members[j]] == ~0u) {
+            order[d->members[j]] = (uint32_t)vectors.size();
+            vectors.push_back(d->grads[d->members[j]]);
         }
-        d2mhe_status s = ops->encrypt(ctx, true, jobs, n, d->ct_base, d->n_values, C, st);
+    const bool ahead = !ctx->rc.coeff_packing && J >= 2 * vectors.size() && (uint64_t)J * C >= 1024;
+    uint32_t *pt = (uint32_t *)shares;
+    if (ahead) {
+        for (size_t p0 = 0; p0 < vectors.size(); p0 += ENCODE_CHUNK) {
+            const uint32_t n = (uint32_t)std::min(vectors.size() - p0, (size_t)ENCODE_CHUNK);
+            EncodeJobs jobs;
+            std::copy(vectors.begin() + p0, vectors.begin() + p0 + n, jobs.src);
+            d2mhe_status s = ops->encode_parties(ctx, jobs, n, d->n_values, pt + p0 * C * ctx->N, C, st);
+            if (s != D2MHE_OK) return s;
+        }
+    }
+    const uint32_t per_launch = jobs_per_launch(J);
+    for (uint32_t j0 = 0, n; j0 < J; j0 += n) {
+        RoundJobs jobs;
+        n = fill_round_jobs(jobs, d, j0, per_launch, slot, cts + j0 * ct_words, ct_words,
+                            [&](uint32_t party) -> const void * {
+                                return ahead ? (const void *)(pt + (size_t)order[party] * C * ctx->N) : d->grads[party];
+                            },
+                            [&](uint32_t g) { return d->pks[g]; });
+        d2mhe_status s = ops->encrypt(ctx, ahead ? FROM_WORDS32 : FROM_VECTOR, jobs, n, d->ct_base, d->n_values, C, st);
         if (s != D2MHE_OK) return s;
     }
     if (ev && ev[1]) D2_HIP(ctx, hipEventRecord(ev[1], st));
@@ -884,7 +940,6 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     const uint64_t full = ctx->N >= 2048 ? 256 : 1024;
     if (!conv && ops->finish && !split && (uint64_t)G * C >= full) {
         FinishJobs jobs;
-        std::vector<uint16_t> slot(d->num_parties);
         uint32_t n = fill_finish_jobs(jobs, d, 0, slot), launches = 1;
         for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, g0, slot);
         if (launches == 1 || (uint64_t)G * C >= 2 * full * launches) {
@@ -919,17 +974,11 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
 
     if (!conv) {
         // phase 3: every member's decryption share of its group's aggregate
-        for (uint32_t j0 = 0; j0 < J; j0 += JOB_CHUNK) {
-            const uint32_t n = J - j0 < (uint32_t)JOB_CHUNK ? J - j0 : (uint32_t)JOB_CHUNK;
-            ShareJobs jobs;
-            for (uint32_t i = 0; i < n; ++i) {
-                const uint32_t j = j0 + i, g = group_of[j];
-                jobs.sk[i] = d->sk_shares[d->members[j]];
-                jobs.ct[i] = agg + (size_t)g * ct_words;
-                jobs.out[i] = shares + (size_t)j * sh_words;
-                jobs.party[i] = d->members[j];
-                jobs.group[i] = d->group_ids ? d->group_ids[g] : g;
-            }
+        for (uint32_t j0 = 0, n; j0 < J; j0 += n) {
+            RoundJobs jobs;
+            n = fill_round_jobs(jobs, d, j0, per_launch, slot, shares + j0 * sh_words, sh_words,
+                                [&](uint32_t party) -> const void * { return d->sk_shares[party]; },
+                                [&](uint32_t g) { return agg + (size_t)g * ct_words; });
             d2mhe_status s = ops->share(ctx, jobs, n, d->ct_base, C, st);
             if (s != D2MHE_OK) return s;
         }
@@ -1097,7 +1146,7 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     D2_NEED_SCHEME(ctx);
     if (!pk || !sk_shares || !grads || !members || !out_sum) return D2MHE_ERR_NULL;
     if (K == 0 || K > (uint32_t)MAX_GROUP || K > ctx->max_group || group > 0xffffu) return D2MHE_ERR_RANGE;
-    static_assert(MAX_GROUP <= JOB_CHUNK, "a group must fit one launch");
+    static_assert(MAX_GROUP <= RJ_PARTIES && MAX_GROUP <= JOB_CHUNK, "a group must fit one launch");
     if (misaligned(pk) || misaligned(out_sum)) return D2MHE_ERR_ALIGN;
     for (uint32_t k = 0; k < K; ++k) {
         if (members[k] > 0xffffu) return D2MHE_ERR_RANGE;
@@ -1123,19 +1172,20 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     d2mhe_ctx local = *ctx;                  // slot packing, whatever a concurrent call sets in its own copy
     local.rc.coeff_packing = 0;
 
-    EncJobs enc;
-    ShareJobs shr;
+    RoundJobs enc, shr;
+    enc.out = cts;
+    enc.stride = ct_words;
+    enc.set_group(0, pk, group);
+    shr.out = shares;
+    shr.stride = sh_words;
+    shr.set_group(0, agg, group);
     for (uint32_t k = 0; k < K; ++k) {
-        enc.src[k] = grads[k];
-        enc.pk[k] = pk;
-        enc.out[k] = cts + (size_t)k * ct_words;
-        enc.party[k] = shr.party[k] = members[k];
-        enc.group[k] = shr.group[k] = group;
-        shr.sk[k] = sk_shares[k];
-        shr.ct[k] = agg;
-        shr.out[k] = shares + (size_t)k * sh_words;
+        enc.set_party(k, grads[k], members[k]);
+        enc.set_job(k, k, 0);
+        shr.set_party(k, sk_shares[k], members[k]);
+        shr.set_job(k, k, 0);
     }
-    d2mhe_status s = ops->encrypt(&local, true, enc, K, 0, n_values, C, st);
+    d2mhe_status s = ops->encrypt(&local, FROM_VECTOR, enc, K, 0, n_values, C, st);
     if (s == D2MHE_OK) {
         GroupJobs sum;
         sum.first[0] = cts;

@@ -58,6 +58,15 @@ struct Launch {
         return D2MHE_OK;
     }
 
+    static d2mhe_status encode_parties(d2mhe_ctx *ctx, const EncodeJobs &jobs, uint32_t nparties, uint64_t n_values,
+                                       uint32_t *pt, uint32_t C, hipStream_t st)
+    {
+        hipLaunchKernelGGL(k_encode_parties<ENG>, dim3(C, nparties), dim3(ENG::T), 0, st, jobs, n_values, pt, ctx->d_tabs,
+                           ctx->rc);
+        D2_LAUNCHED(ctx);
+        return D2MHE_OK;
+    }
+
     static d2mhe_status decode(d2mhe_ctx *ctx, const uint64_t *pt, uint32_t C, uint64_t n_values, float *out,
                                hipStream_t st)
     {
@@ -66,20 +75,21 @@ struct Launch {
         return D2MHE_OK;
     }
 
-    static d2mhe_status encrypt(d2mhe_ctx *ctx, bool from_float, const EncJobs &jobs, uint32_t njobs,
+    static d2mhe_status encrypt(d2mhe_ctx *ctx, int from, const RoundJobs &jobs, uint32_t njobs,
                                 uint32_t ct_base, uint64_t n_values, uint32_t C, hipStream_t st)
     {
-        if (from_float)
-            hipLaunchKernelGGL((k_encrypt<ENG, true>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, n_values,
-                               ctx->d_tabs, ctx->rc);
+        const dim3 grid(C, njobs), block(ENG::T);
+        if (from == FROM_VECTOR)
+            hipLaunchKernelGGL((k_encrypt<ENG, FROM_VECTOR>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+        else if (from == FROM_WORDS32)
+            hipLaunchKernelGGL((k_encrypt<ENG, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
         else
-            hipLaunchKernelGGL((k_encrypt<ENG, false>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, n_values,
-                               ctx->d_tabs, ctx->rc);
+            hipLaunchKernelGGL((k_encrypt<ENG, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
 
-    static d2mhe_status share(d2mhe_ctx *ctx, const ShareJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
+    static d2mhe_status share(d2mhe_ctx *ctx, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
                               hipStream_t st)
     {
         hipLaunchKernelGGL(k_share<ENG>, dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
@@ -184,14 +194,14 @@ struct Launch {
     // full set (ring degrees a single workgroup can hold)
     static EngineOps full()
     {
-        return EngineOps{ENG::ELOG, ENG::LOGB, &ntt, &keygen, &encode, &decode, &encrypt, &share, &combine,
-                         &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &convert_combine,
+        return EngineOps{ENG::ELOG, ENG::LOGB, &ntt, &keygen, &encode, &decode, &encode_parties, &encrypt, &share,
+                         &combine, &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &convert_combine,
                          &convert_combine_decode, &bootstrap_alpha, &bootstrap_share, &bootstrap_combine};
     }
     // transforms only (longer rings)
     static EngineOps transforms_only()
     {
-        return EngineOps{ENG::ELOG, ENG::LOGB, &ntt,    nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+        return EngineOps{ENG::ELOG, ENG::LOGB, &ntt,    nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                          nullptr,   nullptr,   nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     }
 };

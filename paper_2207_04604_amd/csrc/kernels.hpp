@@ -4,6 +4,7 @@
 #include "ntt_engine.hpp"
 #include "philox.hpp"
 #include <stddef.h>
+#include <type_traits>
 
 // no fused multiply-add unless written out: float results here are compared bit for bit
 #pragma clang fp contract(off)
@@ -86,19 +87,43 @@ struct PtrList {
 
 // Job tables passed by value in the kernel arguments; grid.y indexes the job.
 constexpr int JOB_CHUNK = 112;   // 112 * 32 B of table + the other arguments stay under the 4 KB argument limit
-struct EncJobs {                       // one job = one (party, group) pair encrypting C ciphertexts
-    const void *src[JOB_CHUNK];        // gradient (float) or plaintext polynomials (uint64)
-    const uint64_t *pk[JOB_CHUNK];     // prepared public key of the group
-    uint64_t *out[JOB_CHUNK];          // ciphertexts [C][2][L][N]
-    uint32_t party[JOB_CHUNK];
-    uint32_t group[JOB_CHUNK];
+// Jobs of Encrypt and of the decryption shares: one job = one (party, group) pair, its C results at out + job * stride.
+// What belongs to a party or to a group is listed once and a job is two indices, so that one launch takes a whole
+// round: with a row of pointers per job (112 to a launch) the 2,060 jobs of 100 users in 100 groups were 19 launches of
+// barely more than one chip's worth of workgroups each.
+// Measured, that round (N = 4096, 5 indices, 2 limbs of 54 bits), with the vectors encoded ahead: 1.98 -> 1.42 ms.
+constexpr int RJ_PARTIES = 112, RJ_GROUPS = 112, RJ_JOBS = 880;      // 4,016 bytes
+struct RoundJobs {
+    const void *src[RJ_PARTIES];       // gradient, plaintext polynomials or prepared secret share of a party
+    const uint64_t *key[RJ_GROUPS];    // prepared public key or aggregate of a group
+    uint64_t *out;
+    size_t stride;                     // words
+    uint32_t party[RJ_PARTIES / 2];    // ids, two to a word (scalar loads come in words)
+    uint32_t group[RJ_GROUPS / 2];
+    uint32_t job[RJ_JOBS / 2];         // index into src | index into key << 8, two to a word
+
+    static constexpr uint32_t half(uint32_t v, uint32_t i, uint32_t old) { return i & 1 ? (old & 0xffffu) | (v << 16) : v; }
+    void set_party(uint32_t i, const void *p, uint32_t id) { src[i] = p; party[i / 2] = half(id, i, party[i / 2]); }
+    void set_group(uint32_t i, const uint64_t *p, uint32_t id) { key[i] = p; group[i / 2] = half(id, i, group[i / 2]); }
+    void set_job(uint32_t i, uint32_t si, uint32_t ki) { job[i / 2] = half(si | (ki << 8), i, job[i / 2]); }
 };
-struct ShareJobs {                     // one job = one member's shares of C aggregated ciphertexts
-    const uint64_t *sk[JOB_CHUNK];     // prepared secret share
-    const uint64_t *ct[JOB_CHUNK];     // aggregate [C][2][L][N]
-    uint64_t *out[JOB_CHUNK];          // shares [C][L][N]
-    uint32_t party[JOB_CHUNK];
-    uint32_t group[JOB_CHUNK];
+static_assert(sizeof(RoundJobs) <= 4016, "with the other arguments of a launch under 4 KB");
+struct RoundJob {                      // one entry, uniform over the workgroup
+    const void *src;
+    const uint64_t *key;
+    uint64_t *out;
+    uint32_t party, group;
+};
+D2_DEV RoundJob round_job(const RoundJobs &t, uint32_t i)
+{
+    auto half = [](const uint32_t *v, uint32_t k) { return (v[k >> 1] >> (16 * (k & 1))) & 0xffffu; };
+    const uint32_t e = half(t.job, i), si = e & 0xffu, ki = e >> 8;
+    return RoundJob{t.src[si], t.key[ki], t.out + (size_t)i * t.stride, half(t.party, si), half(t.group, ki)};
+}
+enum { FROM_WORDS64 = 0, FROM_WORDS32 = 1, FROM_VECTOR = 2 };   // what Encrypt reads
+constexpr int ENCODE_CHUNK = 448;
+struct EncodeJobs {                    // one job = one party's vector
+    const float *src[ENCODE_CHUNK];
 };
 constexpr int CONV_CHUNK = 80;         // 80 * 40 B of table
 struct ConvJobs {                      // one job = one member's conversion shares towards one receiver
@@ -525,6 +550,23 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encode(const float *grad
     for (int k = 0; k < ENG::E; ++k) pt[(size_t)c * ENG::NB + ENG::coef_pos(k, tid)] = m[k];
 }
 
+// The plaintexts of a whole round: grid = (C, parties), one 32-bit word per coefficient.  A party encrypts the same
+// vector for every group it is in; encoding it in k_encrypt (an inverse transform modulo t and four barriers) repeats
+// the work per group.  See the rule in run_round.
+template <class ENG>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encode_parties(EncodeJobs jobs, uint64_t n_values, uint32_t *pt,
+                                                                       const LimbTab *tabs, RoundConst rc)
+{
+    __shared__ uint64_t lds[ENG::LDS_WORDS];
+    const int tid = threadIdx.x;
+    const uint32_t c = blockIdx.x;
+    uint32_t m[ENG::E];
+    encode_to_regs<ENG>(m, lds, tid, jobs.src[blockIdx.y], (uint64_t)c * ENG::NB, n_values, load_tab(tabs, rc.L), rc);
+    pt += ((size_t)blockIdx.y * gridDim.x + c) * ENG::NB;
+#pragma unroll
+    for (int k = 0; k < ENG::E; ++k) pt[ENG::coef_pos(k, tid)] = m[k];
+}
+
 template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_decode(const uint64_t *pt, uint64_t n_values, float *out,
                                                    const LimbTab *tabs, RoundConst rc)
@@ -647,11 +689,11 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
 // -------------------------------------------------------------------------------------
 // BFV.Encrypt in evaluation form.  grid = (C, jobs); one workgroup per ciphertext.
 //   c0 = NTT(Lambda m + e0) + NTT(mu) * p0,   c1 = NTT(e1) + NTT(mu) * p1.
-// FROM_FLOAT: the plaintext is encoded on the fly from the member's gradient;
-// otherwise it is read from pt [C][N].
+// FROM says what a job's source is: plaintext polynomials [C][N], the same in 32-bit words (k_encode_parties), or the
+// member's gradient, encoded on the fly.
 // -------------------------------------------------------------------------------------
-template <class ENG, bool FROM_FLOAT>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(EncJobs jobs, uint32_t ct_base, uint64_t n_values,
+template <class ENG, int FROM>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, uint32_t ct_base, uint64_t n_values,
                                                     const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
@@ -661,11 +703,12 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(EncJobs jobs, ui
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, job = blockIdx.y, L = rc.L;
-    const uint32_t party = jobs.party[job], group = jobs.group[job];
-    const uint64_t *pk = jobs.pk[job];
+    const uint32_t c = blockIdx.x, L = rc.L;
+    const RoundJob job = round_job(jobs, blockIdx.y);
+    const uint32_t party = job.party, group = job.group;
+    const uint64_t *pk = job.key;
     const size_t LN = (size_t)L * ENG::NB;
-    uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
+    uint64_t *out = job.out + (size_t)c * 2 * LN;
 
     // With two buffers the samples are staged in the second one, next to the encoding in the first:
     // one barrier then makes them visible and also ends the encoding's reads of the first buffer,
@@ -676,10 +719,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(EncJobs jobs, ui
         turn = 1;
     }
     uint32_t m[E];
-    if (FROM_FLOAT) {
-        encode_to_regs<ENG>(m, lds, tid, (const float *)jobs.src[job], (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
+    if constexpr (FROM == FROM_VECTOR) {
+        encode_to_regs<ENG>(m, lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
     } else {
-        const uint64_t *pt = (const uint64_t *)jobs.src[job] + (size_t)c * ENG::NB;
+        typedef typename std::conditional<FROM == FROM_WORDS32, uint32_t, uint64_t>::type word;
+        const word *pt = (const word *)job.src + (size_t)c * ENG::NB;
 #pragma unroll
         for (int k = 0; k < E; ++k) m[k] = (uint32_t)pt[ENG::coef_pos(k, tid)];
     }
@@ -732,20 +776,21 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(EncJobs jobs, ui
 // Decryption share h = s c1 + e in evaluation form.  grid = (C, jobs).
 // -------------------------------------------------------------------------------------
 template <class ENG>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(ShareJobs jobs, uint32_t ct_base, const LimbTab *tabs, RoundConst rc)
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, uint32_t ct_base, const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
     __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
     uint32_t turn = 0;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, job = blockIdx.y, L = rc.L;
+    const uint32_t c = blockIdx.x, L = rc.L;
+    const RoundJob job = round_job(jobs, blockIdx.y);
     const size_t LN = (size_t)L * ENG::NB;
-    const uint64_t *sk = jobs.sk[job];
-    const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
-    uint64_t *out = jobs.out[job] + (size_t)c * LN;
+    const uint64_t *sk = (const uint64_t *)job.src;
+    const uint64_t *c1 = job.key + ((size_t)c * 2 + 1) * LN;
+    uint64_t *out = job.out + (size_t)c * LN;
     int32_t e[E];
-    cbd_own<ENG>(e, tid, DOM_DEC_E, jobs.party[job], jobs.group[job], ct_base + c, rc);
+    cbd_own<ENG>(e, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);

@@ -1,0 +1,81 @@
+"""Rounds whose job tables do not fit one launch (880 jobs, 112 parties, 112 groups) and rounds whose parties are in
+many groups, so that their vectors are encoded once ahead of the encryption: every message against the per-call entry
+points, which the other tests hold to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import oracle as O
+
+from gpu_util import DEV, dzeros, make_ctx, to_dev
+
+
+def ring(parties, reach):
+    return [sorted((i + d) % parties for d in range(-reach, reach + 1)) for i in range(parties)]
+
+
+def shuffled(groups, seed):
+    rng = np.random.default_rng(seed)
+    return [[int(k) for k in rng.permutation(g)] for g in groups]
+
+
+# (prime bits, log2 N, limbs, groups, ciphertexts, packing, one event between the phases)
+@pytest.mark.parametrize("bits,log2n,L,groups,C,packing,split", [
+    (54, 10, 1, ring(200, 4), 1, 0, True),                      # 1,800 jobs, more parties and groups than a table lists
+    (36, 10, 2, shuffled(ring(41, 10), 1), 2, 0, True),         # 861 jobs: one launch; members in any order
+    (30, 10, 1, shuffled(ring(42, 10), 2), 2, 0, True),         # 882: two
+    (54, 11, 1, ring(125, 3), 2, 0, False),                     # 875 jobs, parties beyond the table before the jobs are
+    (60, 13, 1, ring(26, 19), 1, 0, False),                     # exactly 39 members each
+    (54, 14, 1, ring(23, 5), 5, 0, False),                      # 16 coefficients per thread
+    (44, 11, 1, ring(130, 3), 2, 1, True),                      # coefficient packing: never encoded ahead
+    (54, 10, 1, [[0, 1, 2], [3, 4]], 300, 0, True),             # nobody in two groups
+])
+def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
+    N = 1 << log2n
+    groups = [list(dict.fromkeys(g)) for g in groups]
+    K = max(len(g) for g in groups)
+    q, t = O.find_primes(bits, log2n, L), 12289 if log2n <= 11 else 65537
+    P, J, G = 1 + max(max(g) for g in groups), sum(len(g) for g in groups), len(groups)
+    n, LN = C * N - 5, L * N
+    ctx = make_ctx(log2n, q, t, f=3, max_group=K, seed=5)
+    sk, pk0 = [dzeros(2 * LN) for _ in range(P)], [dzeros(LN) for _ in range(P)]
+    for k in range(P):
+        ctx.keygen_share(k, sk[k], pk0[k])
+    pks = [dzeros(4 * LN) for _ in groups]
+    for g, pk in zip(groups, pks):
+        ctx.aggregate_pk([pk0[k] for k in g], pk)
+    vec = to_dev(np.random.default_rng(bits).normal(0, 2.0, n + 4 * P).astype(np.float32))
+    grads = [vec[4 * k:4 * k + n] for k in range(P)]
+    outs = [torch.zeros((n + 3) // 4 * 4, dtype=torch.float32, device=DEV) for _ in groups]
+    nbytes = ctx.round_scratch_bytes(J, G, n)
+    scratch = dzeros(nbytes // 8)
+    ids = [3 + 2 * g for g in range(G)]
+    desc = ctx.make_round(groups, pks, sk, grads, outs, n, group_ids=ids, ct_base=7, packing=packing)
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+    for e in events:
+        e.record()
+    ctx.round(desc, scratch, nbytes, [e.cuda_event for e in events] if split else None)
+    cts = scratch[:J * C * 2 * LN].view(J, C * 2 * LN)
+    agg = scratch[J * C * 2 * LN:(J + G) * C * 2 * LN].view(G, C * 2 * LN)
+    shares = scratch[(J + G) * C * 2 * LN:].view(J, C * LN)
+    pts = [dzeros(C * N) for _ in range(P)]
+    for k in range(P):
+        (ctx.encode_coefficients if packing else ctx.encode)(grads[k], n, pts[k], C)
+    ct, share, j = dzeros(C * 2 * LN), dzeros(C * LN), 0
+    for g, members in enumerate(groups):
+        total = None
+        for k in members:
+            ctx.encrypt(pks[g], pts[k], C, k, ids[g], 7, ct)
+            assert torch.equal(ct, cts[j]), f"ciphertext of party {k} in group {g}"
+            if total is None:
+                total = ct.clone()
+            else:
+                ctx.add(total, ct, C)
+            ctx.partial_decrypt(sk[k], agg[g], C, k, ids[g], 7, share)
+            assert torch.equal(share, shares[j]), f"share of party {k} in group {g}"
+            j += 1
+        assert torch.equal(total, agg[g]), f"aggregate of group {g}"
+    torch.cuda.synchronize()
+    ctx.close()
