@@ -352,6 +352,7 @@ struct ArithS {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
     // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
+    static constexpr bool SUM_SMALL = false;
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
     {
@@ -473,6 +474,7 @@ struct ArithB {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
     // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
+    static constexpr bool SUM_SMALL = false;
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
     {
@@ -645,6 +647,26 @@ struct ArithF {
         x = u + t;
         y = u - t;
     }
+    // s[0] + sum of c[j] s[j], |s| <= 32: the first stages of a transform on small inputs, taken together.  The multiplicands
+    // are signed representatives: one product is at most 16 q, three 48 q, and twelve or nine further stages keep
+    // either below the 64 q of canon_wide (see ct_small).
+    static constexpr bool SUM_SMALL = true;
+    struct Small {
+        double w;
+    };
+    D2_DEV static Small small(const Twid &t, bool neg, const Mod &m)
+    {
+        const double w = t.w + t.w > m.q ? t.w - m.q : t.w;
+        return Small{neg ? -w : w};
+    }
+    template <int SS>
+    D2_DEV static elem sum_small(const int32_t (&s)[SS], const Small (&c)[SS], const Mod &)
+    {
+        double x = (double)s[0];
+#pragma unroll
+        for (int j = 1; j < SS; ++j) x = __builtin_fma(c[j].w, (double)s[j], x);
+        return x;
+    }
     // First stage on small signed inputs (|xv|, |yv| <= 32): w*yv is exact in a double (< 2^49), so the
     // stage is one multiplication and two additions.  The values then reach 32q; every later stage adds one
     // product (see mul), i.e. takes a bound of c q to (1 + 1.5 q 2^-52) c q + q/2: 41.3 q after the 13 further
@@ -774,6 +796,24 @@ struct Arith32 {
         y = from_small(yv, m);
         ct<SC>(x, y, w, m);
     }
+    // s[0] + sum of c[j] s[j], |s| <= 32, in [0, 4q)
+    static constexpr bool SUM_SMALL = true;
+    struct Small {
+        Twid w;
+        bool neg;
+    };
+    D2_DEV static Small small(const Twid &t, bool neg, const Mod &) { return Small{t, neg}; }
+    template <int SS>
+    D2_DEV static elem sum_small(const int32_t (&s)[SS], const Small (&c)[SS], const Mod &m)
+    {
+        uint32_t x = from_small(s[0], m);
+#pragma unroll
+        for (int j = 1; j < SS; ++j) {
+            const uint32_t t = mul(from_small(c[j].neg ? -s[j] : s[j], m), c[j].w, m);
+            x = (j > 1 ? csub32(x, m.two_q) : x) + t;
+        }
+        return x;
+    }
     D2_DEV static void fwd_pass_begin(elem &, const Mod &) {}
     // the last step of a forward transform: [0, 4q) -> [0, 2q)
     D2_DEV static void fwd_end(elem &x, const Mod &m) { x = csub32(x, m.two_q); }
@@ -878,6 +918,27 @@ D2_DEV uint64_t pm_mul_u32(uint32_t y, const TwPm &w, const ModPm &m)
     const uint64_t b = mul32(w.w01, y);
     return mul32(m.c2, hi32(b)) + (mul32(m.p2s, lo32(b)) + mul32(w.w00, y));
 }
+// s[0] + sum of +-w[j] s[j], |s| <= 32 and at most three products, as pm_mul with signed multiply-adds: the sums of the
+// halves are A and B, |B| < 2^38, and 2^40 added to B keeps it positive; 2^40 2^s = 2^(b + 9) = 512 c is taken off
+// again.  The result is in (0, 4q).
+struct SmallPm {
+    int32_t w0, w1;     // the halves of +-w
+};
+D2_DEV SmallPm pm_small(const TwPm &w, bool neg)
+{
+    return neg ? SmallPm{-(int32_t)w.w00, -(int32_t)w.w01} : SmallPm{(int32_t)w.w00, (int32_t)w.w01};
+}
+template <int SS>
+D2_DEV uint64_t pm_sum_small(const int32_t (&s)[SS], const SmallPm (&c)[SS], const ModPm &m)
+{
+    int64_t a = (int64_t)(m.q - 512 * m.c64) + s[0], b = (int64_t)1 << 40;
+#pragma unroll
+    for (int j = 1; j < SS; ++j) {
+        a = (int64_t)c[j].w0 * s[j] + a;
+        b = (int64_t)c[j].w1 * s[j] + b;
+    }
+    return mul32(m.c2, hi32((uint64_t)b)) + (mul32(m.p2s, lo32((uint64_t)b)) + (uint64_t)a);
+}
 // bit b and above folded down: x < 2^64 -> below 2^b + (x >> b) c
 D2_DEV uint64_t pm_fold(uint64_t x, const ModPm &m)
 {
@@ -957,6 +1018,11 @@ struct ArithP {
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + (m.q + (uint64_t)(int64_t)v); }
+    static constexpr bool SUM_SMALL = true;
+    typedef SmallPm Small;
+    D2_DEV static Small small(const Twid &t, bool neg, const Mod &) { return pm_small(t, neg); }
+    template <int SS>
+    D2_DEV static elem sum_small(const int32_t (&s)[SS], const Small (&c)[SS], const Mod &m) { return pm_sum_small(s, c, m); }
     // x' = u + t comes out of the multiply-adds, y' = u + G q - t = (2u + G q) - x'
     template <bool SC = false>
     D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)
@@ -1055,7 +1121,7 @@ struct ArithQ : ArithP {
 // most A::INV_PROD, a sum at most the sum of its operands' bounds, and a sum that could exceed
 // A::INV_LIM is folded to 1.  INV_LIM = 0: the policy corrects its sums by itself.
 template <class A>
-constexpr uint64_t inv_folds(bool first, int stages, int slots)
+constexpr uint64_t inv_folds(bool first, int stages, int slots, int bit0 = 0 /* slot bit of the first stage */)
 {
     uint64_t mask = 0;
     if (A::INV_LIM == 0) return mask;
@@ -1063,14 +1129,15 @@ constexpr uint64_t inv_folds(bool first, int stages, int slots)
     for (int k = 0; k < slots; ++k) bound[k] = first ? 1 : A::INV_LIM;
     for (int i = 0; i < stages; ++i)
         for (int k = 0; k < slots; ++k) {
-            if (k & (1 << i)) continue;
-            int s = bound[k] + bound[k | (1 << i)];
+            const int other = k | (1 << (bit0 + i));
+            if (other == k) continue;
+            int s = bound[k] + bound[other];
             if (s > A::INV_LIM) {
                 s = 1;
                 mask |= (uint64_t)1 << (16 * i + k);
             }
             bound[k] = s;
-            bound[k | (1 << i)] = A::INV_PROD;
+            bound[other] = A::INV_PROD;
         }
     return mask;
 }

@@ -429,27 +429,125 @@ D2_DEV int32_t lane_xor1(int32_t v)
 #endif
 }
 
-// Centred-binomial coefficients of a polynomial, delivered to their pass-0 owners (slot k of thread tid: coefficient
-// k T + tid) without going through LDS.  A block holds two adjacent coefficients, i.e. the same slot of two
-// adjacent lanes: of two slots the even lane draws the block of the first, the odd lane that of the second, and
-// each hands over the half that is not its own.
+D2_DEV int32_t sbyte(uint32_t w, int i) { return (int32_t)(int8_t)(w >> (8 * i)); }
+
+// The samples of a small polynomial that a thread's part of a transform starts from: packed bytes where they are more than
+// its coefficients (FUSE).
+template <class ENG, bool PACKED = (ENG::FUSE > 0)>
+struct SmallPoly {
+    static_assert(ENG::E == 8, "one 8-byte word per part");
+    uint32_t w[ENG::SS][2];
+    D2_DEV void set(int j, int k, uint32_t byte)
+    {
+        if (k % 4 == 0) w[j][k / 4] = byte & 0xffu;
+        else w[j][k / 4] |= (byte & 0xffu) << (8 * (k % 4));
+    }
+    D2_DEV void get(int32_t (&v)[ENG::SS][ENG::E]) const
+    {
+#pragma unroll
+        for (int j = 0; j < ENG::SS; ++j)
+#pragma unroll
+            for (int k = 0; k < ENG::E; k += 4) {
+                const uint32_t b = opaque(w[j][k / 4]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[j][k + i] = sbyte(b, i);
+            }
+    }
+    D2_DEV uint64_t word(int j) const { return ((uint64_t)w[j][1] << 32) | w[j][0]; }
+    D2_DEV void set_word(int j, uint64_t v)
+    {
+        w[j][0] = lo32(v);
+        w[j][1] = hi32(v);
+    }
+};
 template <class ENG>
-D2_DEV void cbd_own(int32_t (&v)[ENG::E], int tid, uint32_t domain, uint32_t party, uint32_t group, uint32_t ct,
-                    const RoundConst &rc)
+struct SmallPoly<ENG, false> {
+    int32_t v[ENG::E];
+    D2_DEV void set(int, int k, uint32_t sample) { v[k] = (int32_t)sample; }
+    D2_DEV void get(int32_t (&out)[1][ENG::E]) const
+    {
+#pragma unroll
+        for (int k = 0; k < ENG::E; ++k) out[0][k] = opaque(v[k]);
+    }
+    D2_DEV uint64_t word(int) const            // 8 coefficients per thread
+    {
+        uint32_t w[2] = {0, 0};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k / 4] |= ((uint32_t)v[k] & 0xffu) << (8 * (k % 4));
+        return ((uint64_t)w[1] << 32) | w[0];
+    }
+    D2_DEV void set_word(int, uint64_t w)
+    {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = sbyte(k < 4 ? lo32(w) : hi32(w), k % 4);
+    }
+};
+// The three small polynomials of an encryption or a conversion share (mu, e0, e1), as stage_encrypt_samples left them
+template <class ENG, bool PACKED = (ENG::FUSE > 0)>
+struct SmallTriple {
+    SmallPoly<ENG> p[3];
+    D2_DEV void load(const uint32_t *stage, int tid)
+    {
+#pragma unroll
+        for (int k = 0; k < ENG::E; ++k)
+#pragma unroll
+            for (int j = 0; j < ENG::SS; ++j) {
+                const uint32_t v = stage[ENG::small_pos(j, k, tid)];
+                p[0].set(j, k, v);
+                p[1].set(j, k, v >> 8);
+                p[2].set(j, k, v >> 16);
+            }
+    }
+    template <int I>
+    D2_DEV void get(int32_t (&v)[ENG::SS][ENG::E]) const { p[I].get(v); }
+};
+template <class ENG>
+struct SmallTriple<ENG, false> {
+    uint32_t w[ENG::E];
+    D2_DEV void load(const uint32_t *stage, int tid)
+    {
+#pragma unroll
+        for (int k = 0; k < ENG::E; ++k) w[k] = stage[ENG::coef_pos(k, tid)];
+    }
+    template <int I>
+    D2_DEV void get(int32_t (&v)[1][ENG::E]) const
+    {
+#pragma unroll
+        for (int k = 0; k < ENG::E; ++k) v[0][k] = sbyte(opaque(w[k]), I);
+    }
+};
+// words of LDS that small_cbd exchanges samples through
+template <class ENG>
+constexpr int SMALL_LDS_WORDS = ENG::FUSE > 0 ? ENG::T * ENG::E / 8 : 0;
+
+// Centred-binomial coefficients of a polynomial, every one drawn by its owner (own_pos).  A block holds two
+// adjacent coefficients, i.e. the same slot of two adjacent lanes: of two slots the even lane draws the block of the
+// first, the odd lane that of the second, and each hands over the half that is not its own.  The other
+// samples a thread needs are those of the threads that own the same slots of the other parts of the polynomial,
+// which pass their bytes through `buf` (SMALL_LDS_WORDS, used for nothing else).
+template <class ENG>
+D2_DEV void small_cbd(SmallPoly<ENG> &s, uint64_t *buf, int tid, uint32_t domain, uint32_t party, uint32_t group,
+                      uint32_t ct, const RoundConst &rc)
 {
     const int odd = tid & 1;
 #pragma unroll
     for (int k = 0; k < ENG::E; k += 2) {
         int32_t e[2];
-        const uint32_t j = (uint32_t)((k + odd) * ENG::T + (tid & ~1)) / 2;
+        const uint32_t j = (uint32_t)ENG::own_pos(k + odd, tid & ~1) / 2;
         cbd2(philox4x32_10(j, ct, party, counter_tag(domain, 0, group), rc.key), rc.eta_mask, e);
-        const int32_t own = odd ? e[1] : e[0], got = lane_xor1(odd ? e[0] : e[1]);
-        v[k] = odd ? got : own;
-        v[k + 1] = odd ? own : got;
+        const int32_t mine = odd ? e[1] : e[0], got = lane_xor1(odd ? e[0] : e[1]);
+        s.set(0, k, (uint32_t)(odd ? got : mine));
+        s.set(0, k + 1, (uint32_t)(odd ? mine : got));
+    }
+    if constexpr (ENG::FUSE > 0) {
+        constexpr int PART = ENG::T / ENG::SS;           // threads per part of the polynomial
+        __syncthreads();                                 // readers of an earlier polynomial
+        buf[tid] = s.word(0);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < ENG::SS; ++j) s.set_word(j, buf[j * PART + (tid & (PART - 1))]);
     }
 }
-
-D2_DEV int32_t sbyte(uint32_t w, int i) { return (int32_t)(int8_t)(w >> (8 * i)); }
 
 // -------------------------------------------------------------------------------------
 // Fixed point + slots (encode) as a device step: leaves the plaintext polynomial of
@@ -727,14 +825,22 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
 #pragma unroll
         for (int k = 0; k < E; ++k) m[k] = (uint32_t)pt[ENG::coef_pos(k, tid)];
     }
-    uint32_t smp[E];
     if (!ENG::PINGPONG) {
         __syncthreads();
         stage_encrypt_samples<ENG>(stage, tid, DOM_ENC_U, party, group, ct_base + c, rc);
     }
     __syncthreads();
+    SmallTriple<ENG> smp;                   // of a fused transform's start; e0 of pass 0's otherwise
+    smp.load(stage, tid);
+    uint32_t e0[2];
+    if constexpr (ENG::FUSE > 0) {
 #pragma unroll
-    for (int k = 0; k < E; ++k) smp[k] = stage[ENG::coef_pos(k, tid)];
+        for (int k = 0; k < E; ++k) {
+            const uint32_t b = (stage[ENG::coef_pos(k, tid)] >> 8) & 0xffu;
+            e0[k / 4] = k % 4 ? e0[k / 4] | b << (8 * (k % 4)) : b;
+        }
+    }
+    if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
@@ -751,9 +857,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
         constexpr bool STASH = E > 8;
         uint64_t *stash = out + LN + off;
         elem u[E];
-        int32_t sv[E];          // the samples of this transform as plain small integers
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = sbyte(opaque(smp[k]), 0);
+        int32_t sv[ENG::SS][E];         // the samples of this transform as plain small integers
+        smp.template get<0>(sv);
         ENG::forward_chained_small(sv, u, lds, turn, tl, tb.fwd, md);
         if (STASH) {
 #pragma unroll
@@ -761,12 +866,15 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
         }
         elem x[E];
 #pragma unroll
-        for (int k = 0; k < E; ++k)
-            x[k] = A::add_small(A::mul_u32(opaque(m[k]), lam, md), sbyte(opaque(smp[k]), 1), md);
+        for (int k = 0; k < E; ++k) {
+            int32_t e;
+            if constexpr (ENG::FUSE > 0) e = sbyte(opaque(e0[k / 4]), k % 4);
+            else e = sbyte(opaque(smp.w[k]), 1);
+            x[k] = A::add_small(A::mul_u32(opaque(m[k]), lam, md), e, md);
+        }
         ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
         mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, u, x, tl, md);
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = sbyte(opaque(smp[k]), 2);
+        smp.template get<2>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
         mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, u, x, tl, md);
     }
@@ -779,7 +887,7 @@ template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, uint32_t ct_base, const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
-    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS + SMALL_LDS_WORDS<ENG>];
     uint32_t turn = 0;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
@@ -789,17 +897,16 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     const uint64_t *sk = (const uint64_t *)job.src;
     const uint64_t *c1 = job.key + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = job.out + (size_t)c * LN;
-    int32_t e[E];
-    cbd_own<ENG>(e, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
+    SmallPoly<ENG> e;
+    small_cbd<ENG>(e, lds + ENG::LDS_CHAIN_WORDS, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const size_t off = (size_t)limb * ENG::NB;
         const int tl = opaque(tid);
         typename A::elem x[E];
-        int32_t sv[E];
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = opaque(e[k]);
+        int32_t sv[ENG::SS][E];
+        e.get(sv);
         ENG::forward_chained_small(sv, x, lds, turn, tl, tb.fwd, md);
         mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, x, x, tl, md);
     }
@@ -1044,8 +1151,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
 {
     typedef typename ENG::A A;
     constexpr int E = ENG::E;
-    static_assert(E == 8, "the samples of a thread are kept in one 8-byte word");
-    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
+    static_assert(E == 8, "the samples of a thread are kept in SS 8-byte words");
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS + SMALL_LDS_WORDS<ENG>];
     const int tid = threadIdx.x;
     uint32_t turn = 0;
     // from the last to the first: what the encryption wrote last is still in the memory-side cache
@@ -1079,22 +1186,22 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         for (uint32_t j = 0; j < K; ++j) {
             const uint32_t who = jobs.member[m0 + j];
             uint64_t *share = shares + (size_t)j * sh_words, *kept = share + (size_t)(L - 1) * ENG::NB;
-            int32_t e[E];
+            SmallPoly<ENG> e;
             if (limb == 0) {
-                cbd_own<ENG>(e, opaque(tid), DOM_DEC_E, jobs.party[who], group, ct_base + c, rc);
+                small_cbd<ENG>(e, lds + ENG::LDS_CHAIN_WORDS, opaque(tid), DOM_DEC_E, jobs.party[who], group, ct_base + c, rc);
                 if (L > 1) {
-                    uint32_t w[2] = {0, 0};
 #pragma unroll
-                    for (int k = 0; k < E; ++k) w[k / 4] |= ((uint32_t)e[k] & 0xffu) << (8 * (k % 4));
-                    st64(kept, lo, 0, ((uint64_t)w[1] << 32) | w[0]);
+                    for (int i = 0; i < ENG::SS; ++i)
+                        st64(kept, lo, 8u * ENG::T * i, e.word(i));
                 }
             } else {
-                const uint64_t w = ld64(kept, lo, 0);
 #pragma unroll
-                for (int k = 0; k < E; ++k) e[k] = sbyte(k < 4 ? lo32(w) : hi32(w), k % 4);
+                for (int i = 0; i < ENG::SS; ++i) e.set_word(i, ld64(kept, lo, 8u * ENG::T * i));
             }
+            int32_t sv[ENG::SS][E];
+            e.get(sv);
             typename A::elem x[E];
-            ENG::forward_chained_small(e, x, lds, turn, opaque(tid), tb.fwd, md);
+            ENG::forward_chained_small(sv, x, lds, turn, opaque(tid), tb.fwd, md);
             const uint64_t *sk = jobs.sk[who];
             typename A::Key kv[E];
 #pragma unroll
@@ -1122,6 +1229,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         ENG::template inverse<true>(x, ENG::next_buffer(lds, turn), opaque(tid), 0, ti.inv, md, A::tw(ti.ninvg), A::tw(ti.wng));
 #pragma unroll
         for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), ti, t, acc_int[k], acc_frac[k]);
+        if (ENG::WAVE_CHAIN) __syncthreads();       // the next shares' transforms have no barrier of their own
     }
     uint32_t m[E];
 #pragma unroll
@@ -1219,11 +1327,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     const uint64_t *sk = jobs.sk[job], *pk = jobs.pk[job];
     const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
-    uint32_t smp[E];
     stage_encrypt_samples<ENG>(lds32, tid, DOM_CVT_U, jobs.who[job], jobs.group[job], ct_base + c, rc);
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < E; ++k) smp[k] = lds32[ENG::coef_pos(k, tid)];
+    SmallTriple<ENG> smp;
+    smp.load(lds32, tid);
+    if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
@@ -1234,17 +1342,15 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
         constexpr bool STASH = E > 8;
         uint64_t *stash = out + LN + off;
         elem u[E];
-        int32_t sv[E];
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = sbyte(opaque(smp[k]), 0);
+        int32_t sv[ENG::SS][E];
+        smp.template get<0>(sv);
         ENG::forward_chained_small(sv, u, lds, turn, tl, tb.fwd, md);
         if (STASH) {
 #pragma unroll
             for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
         }
         elem x[E];
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = sbyte(opaque(smp[k]), 1);
+        smp.template get<1>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
         // h0: two products per slot, each reduced on its own; first x <- s c1 + x (loads only, eight slots at a time)
         constexpr int BATCH = E < 8 ? E : 8;
@@ -1262,8 +1368,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
                 x[k0 + k] = A::renorm(A::mul_key_add(A::from_canon(cv[k], md), kv[k], x[k0 + k], md), md);
         }
         mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, u, x, tl, md);
-#pragma unroll
-        for (int k = 0; k < E; ++k) sv[k] = sbyte(opaque(smp[k]), 2);
+        smp.template get<2>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
         mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, pk + 2 * LN + off, pk + 3 * LN + off, stash, u, x, tl, md);
     }

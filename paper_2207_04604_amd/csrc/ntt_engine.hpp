@@ -18,7 +18,8 @@
 //
 // Index of a coefficient inside the block during pass p with window base wb:
 //     idx = (tid >> wb) << (wb + ELOG) | k << wb | (tid & (2^wb - 1)),   k = register slot.
-// Pass 0 has wb = LOGB - ELOG (idx = k * T + tid: coalesced natural order); the last pass
+// Pass 0 has wb = LOGB - ELOG (idx = k * T + tid: coalesced natural order; where ELOG does not divide LOGB one pass has
+// fewer stages than its window is wide); the last pass
 // has wb = 0 (idx = tid * E + k), and evaluation-form data is stored at position
 // k * T + tid, so global accesses are coalesced on both sides.
 //
@@ -110,11 +111,39 @@ struct Engine {
     template <class B>
     using Rebind = Engine<B, LOGN_, ELOG_, LOGB_>;
 
-    // number of stages of pass p and the window base
-    static constexpr int stages(int p) { return p < NPASS - 1 ? ELOG : LOGB - ELOG * (NPASS - 1); }
-    static constexpr int wbase(int p) { return p < NPASS - 1 ? LOGB - ELOG * (p + 1) : 0; }
-    // lowest stage bit (position inside the block index) handled by pass p
-    static constexpr int sbit(int p) { return p < NPASS - 1 ? wbase(p) : 0; }
+    // Number of stages of pass p, lowest stage bit (position inside the block index) it handles, and its window
+    // base.  The pass with fewer than ELOG stages is, with 8 coefficients per thread, the first one: its twiddles are
+    // uniform over the wave, the per-lane ones of the last six stages come to 14 instead of 18 to 20, and on small
+    // inputs it takes no exchange at all (FUSE below).  With 16 it is the last but one: 3 + 15 per-lane twiddles
+    // instead of 15 + 12 (N = 2^14, 8 limbs, 8 nodes: round 17.34 -> 16.88 ms).
+    static constexpr int PARTIAL = LOGB % ELOG == 0 ? -1 : ELOG > 3 ? NPASS - 2 : 0;
+    static constexpr int stages(int p) { return p == PARTIAL ? LOGB % ELOG : ELOG; }
+    static constexpr int sbit(int p) { return p < PARTIAL ? LOGB - ELOG * (p + 1) : ELOG * (NPASS - 1 - p); }
+    static constexpr int wbase(int p) { return sbit(p) + stages(p) - ELOG; }
+
+    // FUSE = 1: a first pass of one stage, on small inputs, is one sum per coefficient, of SS = 2 samples with a
+    // multiplicand that is the same for the whole wave, in the ownership of pass 1: pass 0 and its exchange go away
+    // (N = 8192: one workgroup barrier per transform instead of three; N = 1024: none, see WAVE_CHAIN).
+    // Measured with the order of the passes, N = 8192, 4 limbs: rounds with key switching 7.87 -> 7.40 ms, without
+    // 19.3 -> 18.9 ms; one node's encryption and share 121 -> 118 us.
+    // Two stages taken together (N = 2048) cost three products per coefficient for the exchange they save: 117 us
+    // instead of 115 for an iteration of 12 nodes.
+    static constexpr int FUSE = A::SUM_SMALL && PARTIAL == 0 && LOGB == LOGN && wbase(1) >= 6 && LOGB % ELOG == 1 ? 1 : 0;
+    static constexpr int SS = 1 << FUSE;
+    // Such transforms never leave the wave: what brings other waves' data in or out has to put its own barriers
+    // around its use of the buffers.
+    static constexpr bool WAVE_CHAIN = FUSE > 0 && wbase(1) <= 6;
+    // Position of sample j (of SS) of slot k: the first is in the lower part of the polynomial; own_pos is the one
+    // among them that the thread owns.
+    D2_DEV static int own_pos(int k, int tid)
+    {
+        if constexpr (FUSE > 0) return index_of<1>(k, tid);
+        else return coef_pos(k, tid);
+    }
+    D2_DEV static int small_pos(int j, int k, int tid)
+    {
+        return FUSE > 0 ? (j << (LOGB - FUSE)) | (own_pos(k, tid) & ((1 << (LOGB - FUSE)) - 1)) : own_pos(k, tid);
+    }
 
     template <int P>
     D2_DEV static int index_of(int k, int tid)
@@ -230,8 +259,7 @@ struct Engine {
                                 const Twid &ninv, const Twid &wn)
     {
         constexpr int wb = wbase(P), lo = sbit(P), r = stages(P);
-        static_assert(wb == lo, "fold mask counts stages from the lowest slot bit");
-        constexpr uint64_t folds = inv_folds<A>(P == NPASS - 1, r, E);
+        constexpr uint64_t folds = inv_folds<A>(P == NPASS - 1, r, E, lo - wb);
         const uint32_t hi = tw_hi<P>(tid);
         if (P != NPASS - 1) {
 #pragma unroll
@@ -317,7 +345,8 @@ struct Engine {
         for (int k = 0; k < E; ++k) x[k] = from_word<A>(rd[slot_off<PT, X>(k)]);
     }
 
-    template <int P, bool FRESH = false, bool SKIP_FIRST = false>
+    // START: the pass the transform begins with
+    template <int P, bool FRESH = false, bool SKIP_FIRST = false, int START = 0>
     D2_DEV static void fwd_from(elem (&x)[E], const Twid (&w)[E], uint64_t *lds, int tid, uint32_t blk,
                                 const Tw *tw, const Mod &md)
     {
@@ -325,8 +354,8 @@ struct Engine {
             Twid wn[E];
             fwd_pass<P, SKIP_FIRST>(x, w, tid, blk, tw, md);
             load_tw<P + 1, false, true>(wn, tid, blk, tw);
-            exchange<P, P + 1, FRESH && P == 0>(x, lds, tid);      // later exchanges meet this transform's own readers
-            fwd_from<P + 1, FRESH>(x, wn, lds, tid, blk, tw, md);
+            exchange<P, P + 1, FRESH && P == START>(x, lds, tid);  // later exchanges meet this transform's own readers
+            fwd_from<P + 1, FRESH, false, START>(x, wn, lds, tid, blk, tw, md);
         } else {
             fwd_pass<P, SKIP_FIRST>(x, w, tid, blk, tw, md);
 #pragma unroll
@@ -370,26 +399,42 @@ struct Engine {
         if constexpr (E > 8) tw = fresh_table(tw);
         Twid w[E];
         load_tw<0, false, true>(w, tid, blk, tw);
-        fwd_from<0, PINGPONG>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
+        fwd_from<0, PINGPONG && !WAVE_CHAIN>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
     }
 
     // The next forward transform of a chain for a whole polynomial of small signed coefficients
-    // (|v[k]| <= 32: ternary or centred-binomial samples), given as plain integers in pass-0 ownership.
-    // Its first stage multiplies the twiddle by a small number: the policy does that without a modular
-    // reduction and without first mapping the inputs into [0, q) (ct_small); the remaining stages are
-    // the usual ones.  Needs at least two stages in the first pass and a whole-polynomial engine.
-    D2_DEV static void forward_chained_small(const int32_t (&v)[E], elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid,
+    // (|v| <= 32: ternary or centred-binomial samples), given as plain integers: v[j][k] is the one at
+    // small_pos(j, k, tid).  Without FUSE the first stage multiplies the twiddle by a small number: the policy does
+    // that without a modular reduction and without first mapping the inputs into [0, q) (ct_small).
+    // Whole-polynomial engines only.
+    D2_DEV static void forward_chained_small(const int32_t (&v)[SS][E], elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid,
                                              const Tw *tw, const Mod &md)
     {
-        static_assert(LOGB == LOGN && stages(0) >= 2 && ahead<0>(), "shape without a separable first stage");
+        static_assert(LOGB == LOGN && ahead<0>(), "shape without a separable first stage");
         if constexpr (E > 8) tw = fresh_table(tw);
         Twid w[E];
-        load_tw<0, false, true>(w, tid, 0, tw);
-        constexpr int kb = ELOG - 1;                      // the first stage pairs slots k and k + E/2, one twiddle
+        if constexpr (FUSE > 0) {
+            // The sample half a polynomial up is added in the lower half of the positions and subtracted in the upper one.
+            const uint32_t top = wave_uniform((uint32_t)threadIdx.x >> wbase(1));
+            typename A::Small c[SS];
+            c[1] = A::small(load_tw_uniform<A>(tw, 1), top != 0, md);
+            load_tw<1, false, true>(w, tid, 0, tw);
 #pragma unroll
-        for (int j = 0; j < (1 << kb); ++j)
-            A::template ct_small<uniform_tw<0>()>(v[j], v[j | (1 << kb)], x[j], x[j | (1 << kb)], w[tw_slot(kb, 0)], md);
-        fwd_from<0, PINGPONG, true>(x, w, next_buffer(lds, turn), tid, 0, tw, md);
+            for (int k = 0; k < E; ++k) {
+                int32_t s[SS];
+#pragma unroll
+                for (int j = 0; j < SS; ++j) s[j] = v[j][k];
+                x[k] = A::sum_small(s, c, md);
+            }
+            fwd_from<1, PINGPONG, false, 1>(x, w, next_buffer(lds, turn), tid, 0, tw, md);
+        } else {
+            load_tw<0, false, true>(w, tid, 0, tw);
+            constexpr int kb = ELOG - 1;                  // the first stage pairs slots k and k + E/2, one twiddle
+#pragma unroll
+            for (int j = 0; j < (1 << kb); ++j)
+                A::template ct_small<uniform_tw<0>()>(v[0][j], v[0][j | (1 << kb)], x[j], x[j | (1 << kb)], w[tw_slot(kb, 0)], md);
+            fwd_from<0, PINGPONG, true>(x, w, next_buffer(lds, turn), tid, 0, tw, md);
+        }
     }
 
     // All twiddles of one transform, for callers that run several transforms with the same table and
