@@ -352,6 +352,10 @@ struct ArithS {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
     // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
+    // a value that several keys multiply
+    typedef elem Factor;
+    D2_DEV static Factor factor(elem u, const Mod &) { return u; }
+    D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = false;
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
@@ -474,6 +478,10 @@ struct ArithB {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
     // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
+    // a value that several keys multiply
+    typedef elem Factor;
+    D2_DEV static Factor factor(elem u, const Mod &) { return u; }
+    D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = false;
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
@@ -650,6 +658,10 @@ struct ArithF {
     // s[0] + sum of c[j] s[j], |s| <= 32: the first stages of a transform on small inputs, taken together.  The multiplicands
     // are signed representatives: one product is at most 16 q, three 48 q, and twelve or nine further stages keep
     // either below the 64 q of canon_wide (see ct_small).
+    // a value that several keys multiply
+    typedef elem Factor;
+    D2_DEV static Factor factor(elem u, const Mod &) { return u; }
+    D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = true;
     struct Small {
         double w;
@@ -797,6 +809,10 @@ struct Arith32 {
         ct<SC>(x, y, w, m);
     }
     // s[0] + sum of c[j] s[j], |s| <= 32, in [0, 4q)
+    // a value that several keys multiply
+    typedef elem Factor;
+    D2_DEV static Factor factor(elem u, const Mod &) { return u; }
+    D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = true;
     struct Small {
         Twid w;
@@ -967,6 +983,11 @@ D2_DEV TwPm pm_split(uint64_t w, const ModPm &m)
     return t;
 }
 
+// A lazy value as a multiplicand of canonical ones: folded to 2^b + (x >> b) c, then split like a canonical one.  With
+// e = (x >> b) c / 2^b < 1 its halves are below 2^31 (1 + e), and a product with y < q is below
+// ((2 + gamma) (1 + e) + 2) 2^b, less than 2 G q (4 to 5 q for the moduli a prime search gives).
+D2_DEV TwPm pm_factor(uint64_t x, const ModPm &m) { return pm_split(pm_fold(x, m), m); }
+
 // ---------------------------------------------------------------------------------------
 // ArithP: nothing is corrected inside a forward transform.  In units of q: a forward value is at most 64 + 16 G
 // (small first stage, 15 further stages, one product with a key); an inverse pass of at most four stages takes
@@ -1007,6 +1028,10 @@ struct ArithP {
     D2_DEV static elem mul(elem y, const Twid &w, const Mod &m) { return pm_mul(y, w, m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return pm_mul_u32(y, w, m); }
     D2_DEV static elem mul_key_add(elem u, Key k, elem x, const Mod &m) { return pm_mul_add(u, pm_split(k, m), x, m); }
+    // a value that several keys multiply: split once instead of a key each time (4 + 9 instructions for 9 per key)
+    typedef TwPm Factor;
+    D2_DEV static Factor factor(elem u, const Mod &m) { return pm_factor(u, m); }
+    D2_DEV static elem factor_key_add(const Factor &u, Key k, elem x, const Mod &m) { return pm_mul_add(k, u, x, m); }
     D2_DEV static elem renorm(elem x, const Mod &) { return x; }
     // sums of canonical words (at most 65 of them), left unreduced until sum_end
     D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t) { return a + b; }
@@ -1081,6 +1106,7 @@ struct ArithQ : ArithP {
     {
         return pm_mul_add(u, pm_split(k, m), pm_fold(x, m), m);
     }
+    D2_DEV static elem factor_key_add(const Factor &u, Key k, elem x, const Mod &m) { return pm_mul_add(k, u, pm_fold(x, m), m); }
     D2_DEV static elem renorm(elem x, const Mod &m) { return pm_fold(x, m); }
     template <bool SC = false>
     D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int stage = 1)

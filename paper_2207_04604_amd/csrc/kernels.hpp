@@ -743,7 +743,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_keygen(uint32_t party, u
 enum { SRC_REGS = 0, SRC_PARKED = 1, SRC_CANON = 2 };
 template <class ENG, int SRC, bool NEG = false>
 D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps, const uint64_t *src,
-                          const typename ENG::A::elem (&u)[ENG::E], const typename ENG::A::elem (&x)[ENG::E], int tl,
+                          const typename ENG::A::Factor (&u)[ENG::E], const typename ENG::A::elem (&x)[ENG::E], int tl,
                           const typename ENG::A::Mod &md, uint64_t q = 0 /* the modulus, for NEG */)
 {
     typedef typename ENG::A A;
@@ -761,15 +761,20 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
         uint64_t r[BATCH];
 #pragma unroll
         for (int k = 0; k < BATCH; ++k) {
-            typename A::elem uu;
-            if constexpr (SRC == SRC_PARKED) uu = from_bits<A>(ub[k]);
-            else if constexpr (SRC == SRC_CANON) uu = A::from_canon(ub[k], md);
-            else uu = u[b * BATCH + k];
-            if constexpr (NEG) {
-                const uint64_t prod = A::canon_acc(A::mul_key_add(uu, kv[k], A::from_canon(0, md), md), md);
-                r[k] = A::canon_acc(A::add(x[b * BATCH + k], A::from_canon(prod ? q - prod : 0, md)), md);
+            const typename A::elem xx = x[b * BATCH + k];
+            if constexpr (SRC == SRC_REGS) {
+                static_assert(!NEG, "not needed");
+                r[k] = A::canon_acc(A::factor_key_add(u[b * BATCH + k], kv[k], xx, md), md);
             } else {
-                r[k] = A::canon_acc(A::mul_key_add(uu, kv[k], x[b * BATCH + k], md), md);
+                typename A::elem uu;
+                if constexpr (SRC == SRC_PARKED) uu = from_bits<A>(ub[k]);
+                else uu = A::from_canon(ub[k], md);
+                if constexpr (NEG) {
+                    const uint64_t prod = A::canon_acc(A::mul_key_add(uu, kv[k], A::from_canon(0, md), md), md);
+                    r[k] = A::canon_acc(A::add(xx, A::from_canon(prod ? q - prod : 0, md)), md);
+                } else {
+                    r[k] = A::canon_acc(A::mul_key_add(uu, kv[k], xx, md), md);
+                }
             }
         }
         if (b + 1 < NB) {
@@ -864,6 +869,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
 #pragma unroll
             for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
         }
+        typename A::Factor f[E];
+        if (!STASH) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) f[k] = A::factor(u[k], md);
+        }
         elem x[E];
 #pragma unroll
         for (int k = 0; k < E; ++k) {
@@ -873,10 +883,10 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
             x[k] = A::add_small(A::mul_u32(opaque(m[k]), lam, md), e, md);
         }
         ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, u, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, tl, md);
         smp.template get<2>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, u, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, tl, md);
     }
 }
 
@@ -906,9 +916,10 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
         const int tl = opaque(tid);
         typename A::elem x[E];
         int32_t sv[ENG::SS][E];
+        const typename A::Factor none[E] = {};
         e.get(sv);
         ENG::forward_chained_small(sv, x, lds, turn, tl, tb.fwd, md);
-        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, x, x, tl, md);
+        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, tl, md);
     }
 }
 
@@ -1349,6 +1360,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
 #pragma unroll
             for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
         }
+        typename A::Factor f[E];
+        if (!STASH) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) f[k] = A::factor(u[k], md);
+        }
         elem x[E];
         smp.template get<1>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
@@ -1367,10 +1383,10 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
             for (int k = 0; k < BATCH; ++k)
                 x[k0 + k] = A::renorm(A::mul_key_add(A::from_canon(cv[k], md), kv[k], x[k0 + k], md), md);
         }
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, u, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, f, x, tl, md);
         smp.template get<2>(sv);
         ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, pk + 2 * LN + off, pk + 3 * LN + off, stash, u, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, pk + 2 * LN + off, pk + 3 * LN + off, stash, f, x, tl, md);
     }
 }
 
@@ -1475,6 +1491,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
         const typename A::Twid lam = A::tw(tb.lambda);
         const size_t off = (size_t)limb * ENG::NB;
         const int tl = opaque(tid);
+        const typename A::Factor none[E] = {};
         uint64_t lm[E];                                     // Lambda M mod q, canonical
 #pragma unroll
         for (int k = 0; k < E; ++k) lm[k] = A::canon_acc(A::mul_u32(opaque(mv[k]), lam, md), md);
@@ -1483,13 +1500,13 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
         for (int k = 0; k < E; ++k)
             x[k] = A::add(A::from_canon(lm[k] ? q - lm[k] : 0, md), A::from_small(sbyte(opaque(ev[k]), 0), md));
         ENG::forward_chained(x, lds, turn, tl, 0, tb.fwd, md);
-        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, x, x, tl, md);
+        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, tl, md);
 #pragma unroll
         for (int k = 0; k < E; ++k)
             x[k] = A::add(A::from_canon(lm[k], md), A::from_small(sbyte(opaque(ev[k]), 1), md));
         ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
         // eta1 = Lambda M + e1 - s_k alpha
-        mul_add_store<ENG, SRC_CANON, true>(out + LN + off, sk + off, sk + LN + off, alpha + off, x, x, tl, md, q);
+        mul_add_store<ENG, SRC_CANON, true>(out + LN + off, sk + off, sk + LN + off, alpha + off, none, x, tl, md, q);
     }
 }
 

@@ -1,6 +1,6 @@
 // Host build of the sums that stand in for the first one or two stages of a transform on small inputs (sum_small of
 // the policies in paper_2207_04604_amd/csrc/arith.hpp) against 128-bit integers: the residue, and the bound the
-// stages that follow start from.  Compiled and run by tests/test_sum_small.py; exits non-zero on a violation.
+// stages that follow start from; and a lazy value as the multiplicand of keys (factor_key_add).  Compiled and run by tests/test_sum_small.py; exits non-zero on a violation.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -80,13 +80,32 @@ static void check(uint64_t q)
     }
 }
 
+template <class A>
+static void check_factor(uint64_t q, bool wide)
+{
+    const uint64_t G = pm_growth(q, wide), top = wide ? q + 2 * G * q + q / 4 : 64 * q + 16 * G * q;
+    const ModPm md = Of<A>::mod(q);
+    const uint64_t us[] = {top, top - 1, q, q - 1, 0, top & ~0xffffffffull, ((top >> 32) << 32) - 1};
+    const uint64_t ks[] = {q - 1, q - 2, 0, 1, 0xffffffffull, q & ~0xffffffffull, q / 2};
+    for (int rep = 0; rep < 40000; ++rep) {
+        const uint64_t u = rep % 3 ? us[rnd() % 7] : (uint64_t)(((u128)rnd() * top) >> 64);
+        const uint64_t k = rep % 4 ? ks[rnd() % 7] : rnd() % q, x = rep % 2 ? (wide ? top : 64 * q + 8 * G * q) : rnd() % q;
+        const uint64_t r = A::factor_key_add(A::factor(u, md), A::key_of(k, 0), x, md);
+        const uint64_t want = (uint64_t)(((u128)(u % q) * k + x) % q);
+        if (r % q != want || A::canon_acc(r, md) != want || (u128)r > (u128)x + 2 * G * (u128)q) {
+            std::printf("FAILED: factor, kind %d, q = %llu\n", A::KIND, (unsigned long long)q);
+            std::exit(1);
+        }
+    }
+}
+
 int main(int argc, char **argv)
 {
     for (int i = 1; i < argc; ++i) {
         const uint64_t q = std::strtoull(argv[i], nullptr, 10);
         int n = 0;
-        if (pm_growth(q, false)) { check<ArithP, 2>(q); check<ArithP, 4>(q); ++n; }
-        if (pm_growth(q, true)) { check<ArithQ, 2>(q); check<ArithQ, 4>(q); ++n; }
+        if (pm_growth(q, false)) { check<ArithP, 2>(q); check<ArithP, 4>(q); check_factor<ArithP>(q, false); ++n; }
+        if (pm_growth(q, true)) { check<ArithQ, 2>(q); check<ArithQ, 4>(q); check_factor<ArithQ>(q, true); ++n; }
         if (q < 1ull << 44) { check<ArithF, 2>(q); check<ArithF, 4>(q); ++n; }
         if (q < 1ull << 30) { check<Arith32, 2>(q); check<Arith32, 4>(q); ++n; }
         std::printf("%d ", n);
