@@ -655,13 +655,13 @@ struct ArithF {
         x = u + t;
         y = u - t;
     }
-    // s[0] + sum of c[j] s[j], |s| <= 32: the first stages of a transform on small inputs, taken together.  The multiplicands
-    // are signed representatives: one product is at most 16 q, three 48 q, and twelve or nine further stages keep
-    // either below the 64 q of canon_wide (see ct_small).
     // a value that several keys multiply
     typedef elem Factor;
     D2_DEV static Factor factor(elem u, const Mod &) { return u; }
     D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
+    // s[0] + sum of c[j] s[j], |s| <= 32: the first stages of a transform on small inputs, taken together.  The multiplicands
+    // are signed representatives: one product is at most 16 q, three 48 q; twelve further stages and a product with a
+    // key take that to 59 q at q = 2^44 (see ct_small), inside the 64 q of canon_wide.
     static constexpr bool SUM_SMALL = true;
     struct Small {
         double w;
@@ -678,6 +678,14 @@ struct ArithF {
 #pragma unroll
         for (int j = 1; j < SS; ++j) x = __builtin_fma(c[j].w, (double)s[j], x);
         return x;
+    }
+    // lam m[0] + e[0] +- I (lam m[1] + e[1]), m below 2^30: the first stage on an encoded message and its error; c as in
+    // sum_small, lam_i = I lam (neg: subtracted).  Two products and 16 q.
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
+                                   const Small (&c)[2], const Mod &m)
+    {
+        const elem t = mul_u32(mm[1], lam_i, m), s = sum_small(e, c, m) + mul_u32(mm[0], lam, m);
+        return neg ? s - t : s + t;
     }
     // First stage on small signed inputs (|xv|, |yv| <= 32): w*yv is exact in a double (< 2^49), so the
     // stage is one multiplication and two additions.  The values then reach 32q; every later stage adds one
@@ -830,6 +838,14 @@ struct Arith32 {
         }
         return x;
     }
+    // lam m[0] + e[0] +- I (lam m[1] + e[1]), in [0, 4q)
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
+                                   const Small (&c)[2], const Mod &m)
+    {
+        const uint32_t t = mul(mm[1], lam_i, m);
+        const uint32_t s = csub32(sum_small(e, c, m), m.two_q) + mul(mm[0], lam, m);
+        return csub32(s, m.two_q) + (neg ? m.two_q - t : t);
+    }
     D2_DEV static void fwd_pass_begin(elem &, const Mod &) {}
     // the last step of a forward transform: [0, 4q) -> [0, 2q)
     D2_DEV static void fwd_end(elem &x, const Mod &m) { x = csub32(x, m.two_q); }
@@ -955,6 +971,21 @@ D2_DEV uint64_t pm_sum_small(const int32_t (&s)[SS], const SmallPm (&c)[SS], con
     }
     return mul32(m.c2, hi32((uint64_t)b)) + (mul32(m.p2s, lo32((uint64_t)b)) + (uint64_t)a);
 }
+// lam m[0] + e[0] +- I (lam m[1] + e[1]), m below 2^30, |e| <= 32, in the same way (neg is in lam_i and c): here
+// -2^62 < B < 2^62 + 2^37, 2^62 is added, and 2^62 2^s = 2^(b + 31) = 2^31 c is less than k = G q.  The result is below
+// (G + 3 + gamma / 2) q.
+D2_DEV uint64_t pm_sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const SmallPm &lam, const SmallPm &lam_i,
+                               const SmallPm &c, const ModPm &m)
+{
+    uint64_t a = (m.k - (m.c64 << 31)) + (uint64_t)(int64_t)e[0], b = (uint64_t)1 << 62;
+    a = (uint64_t)((int64_t)c.w0 * e[1]) + a;
+    b = (uint64_t)((int64_t)c.w1 * e[1]) + b;
+    a = (uint64_t)((int64_t)lam.w0 * (int32_t)mm[0]) + a;
+    b = (uint64_t)((int64_t)lam.w1 * (int32_t)mm[0]) + b;
+    a = (uint64_t)((int64_t)lam_i.w0 * (int32_t)mm[1]) + a;
+    b = (uint64_t)((int64_t)lam_i.w1 * (int32_t)mm[1]) + b;
+    return mul32(m.c2, hi32(b)) + (mul32(m.p2s, lo32(b)) + a);
+}
 // bit b and above folded down: x < 2^64 -> below 2^b + (x >> b) c
 D2_DEV uint64_t pm_fold(uint64_t x, const ModPm &m)
 {
@@ -1048,6 +1079,11 @@ struct ArithP {
     D2_DEV static Small small(const Twid &t, bool neg, const Mod &) { return pm_small(t, neg); }
     template <int SS>
     D2_DEV static elem sum_small(const int32_t (&s)[SS], const Small (&c)[SS], const Mod &m) { return pm_sum_small(s, c, m); }
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
+                                   const Small (&c)[2], const Mod &m)
+    {
+        return pm_sum_encoded(mm, e, pm_small(lam, false), pm_small(lam_i, neg), c[1], m);
+    }
     // x' = u + t comes out of the multiply-adds, y' = u + G q - t = (2u + G q) - x'
     template <bool SC = false>
     D2_DEV static void ct(elem &x, elem &y, const Twid &w, const Mod &m, int = 0)

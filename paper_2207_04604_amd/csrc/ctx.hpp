@@ -40,6 +40,7 @@ inline d2mhe_status hip_fail(d2mhe_ctx *ctx, hipError_t e)
 // Kernel launchers of one ring degree (one engine shape); defined in inst_<log2n>.hip.
 struct EngineOps {
     int elog, logb;
+    bool encodes_ahead;     // encrypt takes plaintexts only: a round encodes its vectors first (encode_parties)
     d2mhe_status (*ntt)(d2mhe_ctx *, uint64_t *polys, uint32_t B, bool forward, hipStream_t);
     d2mhe_status (*keygen)(d2mhe_ctx *, uint32_t party, uint64_t *sk, uint64_t *pk0, hipStream_t);
     d2mhe_status (*encode)(d2mhe_ctx *, const float *grad, uint64_t n_values, uint64_t *pt, uint32_t C, hipStream_t);

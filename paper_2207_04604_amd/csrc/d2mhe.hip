@@ -337,6 +337,7 @@ d2mhe_status d2mhe_create(const d2mhe_params *p, void *dev_workspace, size_t byt
             // floor(Q/t) = (Q - (Q mod t)) / t  and  Q = 0 (mod q_i)  =>  floor(Q/t) = -(Q mod t) t^-1 (mod q_i)
             const uint64_t lam = h_mul((m - q_mod_t % m) % m, h_inv(p->t % m, m), m);
             tb.lambda = h_entry(ar, lam, m);
+            tb.lambda_i = h_entry(ar, h_mul(lam, h_pow(psi, N / 2, m), m), m);
             uint64_t others = 1;
             for (uint32_t j = 0; j < L; ++j)
                 if (j != i) others = h_mul(others, p->q[j] % m, m);
@@ -906,7 +907,8 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             order[d->members[j]] = (uint32_t)vectors.size();
             vectors.push_back(d->grads[d->members[j]]);
         }
-    const bool ahead = !ctx->rc.coeff_packing && J >= 2 * vectors.size() && (uint64_t)J * C >= 1024;
+    const bool ahead = ops->encodes_ahead ||
+                       (!ctx->rc.coeff_packing && J >= 2 * vectors.size() && (uint64_t)J * C >= 1024);
     uint32_t *pt = (uint32_t *)shares;
     if (ahead) {
         for (size_t p0 = 0; p0 < vectors.size(); p0 += ENCODE_CHUNK) {
@@ -1179,13 +1181,22 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     shr.out = shares;
     shr.stride = sh_words;
     shr.set_group(0, agg, group);
+    uint32_t *pt = (uint32_t *)shares;       // plaintexts made ahead wait in the space of the shares (see run_round)
     for (uint32_t k = 0; k < K; ++k) {
-        enc.set_party(k, grads[k], members[k]);
+        enc.set_party(k, ops->encodes_ahead ? (const void *)(pt + (size_t)k * C * ctx->N) : grads[k], members[k]);
         enc.set_job(k, k, 0);
         shr.set_party(k, sk_shares[k], members[k]);
         shr.set_job(k, k, 0);
     }
-    d2mhe_status s = ops->encrypt(&local, FROM_VECTOR, enc, K, 0, n_values, C, st);
+    d2mhe_status s = D2MHE_OK;
+    if (ops->encodes_ahead) {
+        static_assert(MAX_GROUP <= ENCODE_CHUNK, "a group must fit one launch");
+        EncodeJobs vectors;
+        std::copy(grads, grads + K, vectors.src);
+        s = ops->encode_parties(&local, vectors, K, n_values, pt, C, st);
+    }
+    if (s == D2MHE_OK)
+        s = ops->encrypt(&local, ops->encodes_ahead ? FROM_WORDS32 : FROM_VECTOR, enc, K, 0, n_values, C, st);
     if (s == D2MHE_OK) {
         GroupJobs sum;
         sum.first[0] = cts;

@@ -4,7 +4,7 @@
 namespace d2 {
 const EngineOps *ops_f_14()
 {
-    static const EngineOps ops = Launch<Engine<ArithF, 14, 4>>::full();
+    static const EngineOps ops = Launch<Engine<ArithF, 14, 4>, Engine<ArithF, 14, 3, 13>>::full();
     return &ops;
 }
 }

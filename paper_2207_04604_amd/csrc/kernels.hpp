@@ -26,6 +26,7 @@ struct LimbTab {
     Tw ninv;            // N^-1 mod q
     Tw wn;              // (inverse twiddle 1) * N^-1 mod q
     Tw lambda;          // floor(Q/t) mod q
+    Tw lambda_i;        // that times forward twiddle 1
     Tw ninvg, wng;      // ninv and wn times (Q/q)^-1 mod q: an inverse transform scaled for the rounding of a decryption
     uint64_t theta_hi;  // floor(t * 2^128 / q), high and low words
     uint64_t theta_lo;
@@ -45,6 +46,7 @@ D2_DEV LimbTab load_tab(const LimbTab *tabs, uint32_t i)
     r.one_s = const_ld64(e, offsetof(LimbTab, one_s));
     r.ninv = Tw{const_ld64(e, offsetof(LimbTab, ninv)), const_ld64(e, offsetof(LimbTab, ninv) + 8)};
     r.wn = Tw{const_ld64(e, offsetof(LimbTab, wn)), const_ld64(e, offsetof(LimbTab, wn) + 8)};
+    r.lambda_i = Tw{const_ld64(e, offsetof(LimbTab, lambda_i)), const_ld64(e, offsetof(LimbTab, lambda_i) + 8)};
     r.lambda = Tw{const_ld64(e, offsetof(LimbTab, lambda)), const_ld64(e, offsetof(LimbTab, lambda) + 8)};
     r.ninvg = Tw{const_ld64(e, offsetof(LimbTab, ninvg)), const_ld64(e, offsetof(LimbTab, ninvg) + 8)};
     r.wng = Tw{const_ld64(e, offsetof(LimbTab, wng)), const_ld64(e, offsetof(LimbTab, wng) + 8)};
@@ -393,7 +395,7 @@ template <class ENG>
 D2_DEV void stage_encrypt_samples(uint32_t *lds32, int tid, uint32_t dom, uint32_t party, uint32_t group,
                                   uint32_t ct, const RoundConst &rc)
 {
-    for (int j = tid; j < ENG::NB / 4; j += ENG::T) {
+    for (int j = tid; j < ENG::N / 4; j += ENG::T) {
         int32_t mu[4], e0[4], e1[4];
         ternary4(philox4x32_10(j, ct, party, counter_tag(dom, 0, group), rc.key), mu);
         cbd2(philox4x32_10(2 * j, ct, party, counter_tag(dom + 1, 0, group), rc.key), rc.eta_mask, e0);
@@ -518,34 +520,39 @@ struct SmallTriple<ENG, false> {
 };
 // words of LDS that small_cbd exchanges samples through
 template <class ENG>
-constexpr int SMALL_LDS_WORDS = ENG::FUSE > 0 ? ENG::T * ENG::E / 8 : 0;
+constexpr int SMALL_LDS_WORDS = ENG::FUSE > 0 ? ENG::N / 8 : 0;
 
-// Centred-binomial coefficients of a polynomial, every one drawn by its owner (own_pos).  A block holds two
-// adjacent coefficients, i.e. the same slot of two adjacent lanes: of two slots the even lane draws the block of the
-// first, the odd lane that of the second, and each hands over the half that is not its own.  The other
-// samples a thread needs are those of the threads that own the same slots of the other parts of the polynomial,
-// which pass their bytes through `buf` (SMALL_LDS_WORDS, used for nothing else).
+// Centred-binomial coefficients of a polynomial, drawn once by the workgroup.  A block holds two adjacent
+// coefficients, i.e. the same slot of two adjacent lanes: of two slots the even lane draws the block of the first,
+// the odd lane that of the second, and each hands over the half that is not its own.  A thread draws one or two of
+// the SS parts that it needs (draw_part); the rest comes from the threads with the same positions in the other
+// parts, which pass their bytes through `buf` (SMALL_LDS_WORDS; barriers in front of the write and of the read, none
+// after it).
 template <class ENG>
 D2_DEV void small_cbd(SmallPoly<ENG> &s, uint64_t *buf, int tid, uint32_t domain, uint32_t party, uint32_t group,
                       uint32_t ct, const RoundConst &rc)
 {
     const int odd = tid & 1;
+    if constexpr (ENG::FUSE > 0) __syncthreads();        // readers of an earlier polynomial
+    constexpr int ROW = ENG::PART / ENG::E;              // threads per part
 #pragma unroll
-    for (int k = 0; k < ENG::E; k += 2) {
-        int32_t e[2];
-        const uint32_t j = (uint32_t)ENG::own_pos(k + odd, tid & ~1) / 2;
-        cbd2(philox4x32_10(j, ct, party, counter_tag(domain, 0, group), rc.key), rc.eta_mask, e);
-        const int32_t mine = odd ? e[1] : e[0], got = lane_xor1(odd ? e[0] : e[1]);
-        s.set(0, k, (uint32_t)(odd ? got : mine));
-        s.set(0, k + 1, (uint32_t)(odd ? mine : got));
+    for (int r = 0; r < ENG::DRAW; ++r) {
+        const int part = ENG::draw_part(r, tid);
+#pragma unroll
+        for (int k = 0; k < ENG::E; k += 2) {
+            int32_t e[2];
+            const uint32_t j = (uint32_t)(part * ENG::PART + (ENG::small_pos(0, k + odd, tid & ~1))) / 2;
+            cbd2(philox4x32_10(j, ct, party, counter_tag(domain, 0, group), rc.key), rc.eta_mask, e);
+            const int32_t mine = odd ? e[1] : e[0], got = lane_xor1(odd ? e[0] : e[1]);
+            s.set(r, k, (uint32_t)(odd ? got : mine));
+            s.set(r, k + 1, (uint32_t)(odd ? mine : got));
+        }
+        if constexpr (ENG::FUSE > 0) buf[part * ROW + tid % ROW] = s.word(r);
     }
     if constexpr (ENG::FUSE > 0) {
-        constexpr int PART = ENG::T / ENG::SS;           // threads per part of the polynomial
-        __syncthreads();                                 // readers of an earlier polynomial
-        buf[tid] = s.word(0);
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < ENG::SS; ++j) s.set_word(j, buf[j * PART + (tid & (PART - 1))]);
+        for (int j = 0; j < ENG::SS; ++j) s.set_word(j, buf[j * ROW + tid % ROW]);
     }
 }
 
@@ -801,49 +808,61 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
 {
     typedef typename ENG::A A;
     typedef typename A::elem elem;
+    static_assert(FROM != FROM_VECTOR || ENG::LOGP == 0, "an encoding takes the whole polynomial");
     __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
     uint32_t turn = 0;      // the buffer used last; the transforms take the two buffers in turn
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
+    // The message's first stage as a sum (forward_chained_encoded) wants two coefficients from far apart: read from memory,
+    // not brought through LDS after an encoding in place (25.9 instead of 25.7 us for the smallest round).
+    constexpr bool SUMMED = ENG::FUSE > 0 && FROM != FROM_VECTOR;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, L = rc.L;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
     const RoundJob job = round_job(jobs, blockIdx.y);
     const uint32_t party = job.party, group = job.group;
     const uint64_t *pk = job.key;
-    const size_t LN = (size_t)L * ENG::NB;
+    const size_t LN = (size_t)L * ENG::N;
     uint64_t *out = job.out + (size_t)c * 2 * LN;
 
     // With two buffers the samples are staged in the second one, next to the encoding in the first:
     // one barrier then makes them visible and also ends the encoding's reads of the first buffer,
     // which the first transform of the chain takes.
+    static_assert(ENG::N <= 2 * ENG::LDS_WORDS, "one word per sample fits a buffer");
     uint32_t *stage = ENG::PINGPONG ? lds32 + 2 * ENG::LDS_WORDS : lds32;
     if (ENG::PINGPONG) {
         stage_encrypt_samples<ENG>(stage, tid, DOM_ENC_U, party, group, ct_base + c, rc);
         turn = 1;
     }
-    uint32_t m[E];
+    constexpr int MS = SUMMED ? 2 : 1;
+    uint32_t m[MS][E];
     if constexpr (FROM == FROM_VECTOR) {
-        encode_to_regs<ENG>(m, lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
+        encode_to_regs<ENG>(m[0], lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
     } else {
         typedef typename std::conditional<FROM == FROM_WORDS32, uint32_t, uint64_t>::type word;
-        const word *pt = (const word *)job.src + (size_t)c * ENG::NB;
+        const word *pt = (const word *)job.src + (size_t)c * ENG::N;
 #pragma unroll
-        for (int k = 0; k < E; ++k) m[k] = (uint32_t)pt[ENG::coef_pos(k, tid)];
+        for (int j = 0; j < MS; ++j)
+#pragma unroll
+            for (int k = 0; k < E; ++k)
+                m[j][k] = (uint32_t)pt[SUMMED ? ENG::encoded_pos(j, k, tid) : ENG::coef_pos(k, tid)];
     }
     if (!ENG::PINGPONG) {
         __syncthreads();
         stage_encrypt_samples<ENG>(stage, tid, DOM_ENC_U, party, group, ct_base + c, rc);
     }
     __syncthreads();
-    SmallTriple<ENG> smp;                   // of a fused transform's start; e0 of pass 0's otherwise
+    SmallTriple<ENG> smp;
     smp.load(stage, tid);
-    uint32_t e0[2];
-    if constexpr (ENG::FUSE > 0) {
+    constexpr bool OWN_E0 = ENG::FUSE > 0 && (ENG::LOGP > 0 || !SUMMED);
+    uint32_t e0[MS][2];                     // bytes: e0 at the positions of m, where they are not those of smp
+    if constexpr (OWN_E0) {
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-            const uint32_t b = (stage[ENG::coef_pos(k, tid)] >> 8) & 0xffu;
-            e0[k / 4] = k % 4 ? e0[k / 4] | b << (8 * (k % 4)) : b;
-        }
+        for (int j = 0; j < MS; ++j)
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                const uint32_t b = (stage[SUMMED ? ENG::encoded_pos(j, k, tid) : ENG::coef_pos(k, tid)] >> 8) & 0xffu;
+                e0[j][k / 4] = k % 4 ? e0[j][k / 4] | b << (8 * (k % 4)) : b;
+            }
     }
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
@@ -851,10 +870,10 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const typename A::Twid lam = A::tw(tb.lambda);
-        const size_t off = (size_t)limb * ENG::NB;
+        const size_t off = (size_t)limb * ENG::N;
         const uint64_t *p0 = pk + off, *p0s = pk + LN + off;
         const uint64_t *p1 = pk + 2 * LN + off, *p1s = pk + 3 * LN + off;
-        const int tl = opaque(tid);
+        const int tl = opaque(tid), el = ENG::eval_lane(tl, blk);
         // With 16 coefficients per thread NTT(mu) is parked (lazy, as raw bits) in the c1 slot of the
         // output, which every thread re-reads at its own positions and overwrites last: keeping
         // it in 32 registers across the next two transforms would halve the occupancy.  With 8
@@ -864,29 +883,47 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
         elem u[E];
         int32_t sv[ENG::SS][E];         // the samples of this transform as plain small integers
         smp.template get<0>(sv);
-        ENG::forward_chained_small(sv, u, lds, turn, tl, tb.fwd, md);
+        ENG::forward_chained_small(sv, u, lds, turn, tl, blk, tb.fwd, md);
         if (STASH) {
 #pragma unroll
             for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
+        }
+        elem x[E];
+        if constexpr (SUMMED) {
+            uint32_t mm[2][E];
+            int32_t e[2][E];
+            if constexpr (!OWN_E0) {
+                smp.template get<1>(e);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int k = 0; k < E; ++k) e[j][k] = sbyte(opaque(e0[j][k / 4]), k % 4);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int k = 0; k < E; ++k) mm[j][k] = opaque(m[j][k]);
+            ENG::forward_chained_encoded(mm, e, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
+        } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                int32_t e;
+                if constexpr (OWN_E0) e = sbyte(opaque(e0[0][k / 4]), k % 4);
+                else e = sbyte(opaque(smp.w[k]), 1);
+                x[k] = A::add_small(A::mul_u32(opaque(m[0][k]), lam, md), e, md);
+            }
+            ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
         }
         typename A::Factor f[E];
         if (!STASH) {
 #pragma unroll
             for (int k = 0; k < E; ++k) f[k] = A::factor(u[k], md);
         }
-        elem x[E];
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            int32_t e;
-            if constexpr (ENG::FUSE > 0) e = sbyte(opaque(e0[k / 4]), k % 4);
-            else e = sbyte(opaque(smp.w[k]), 1);
-            x[k] = A::add_small(A::mul_u32(opaque(m[k]), lam, md), e, md);
-        }
-        ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, el, md);
         smp.template get<2>(sv);
-        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, tl, md);
+        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, el, md);
     }
 }
 
@@ -897,29 +934,31 @@ template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, uint32_t ct_base, const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
-    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS + SMALL_LDS_WORDS<ENG>];
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
     uint32_t turn = 0;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, L = rc.L;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
     const RoundJob job = round_job(jobs, blockIdx.y);
-    const size_t LN = (size_t)L * ENG::NB;
+    const size_t LN = (size_t)L * ENG::N;
     const uint64_t *sk = (const uint64_t *)job.src;
     const uint64_t *c1 = job.key + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = job.out + (size_t)c * LN;
     SmallPoly<ENG> e;
-    small_cbd<ENG>(e, lds + ENG::LDS_CHAIN_WORDS, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
+    static_assert(SMALL_LDS_WORDS<ENG> <= ENG::LDS_WORDS, "in the buffer the first transform leaves alone");
+    small_cbd<ENG>(e, lds, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
+    if (ENG::WAVE_CHAIN) __syncthreads();
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
-        const size_t off = (size_t)limb * ENG::NB;
+        const size_t off = (size_t)limb * ENG::N;
         const int tl = opaque(tid);
         typename A::elem x[E];
         int32_t sv[ENG::SS][E];
         const typename A::Factor none[E] = {};
         e.get(sv);
-        ENG::forward_chained_small(sv, x, lds, turn, tl, tb.fwd, md);
-        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, tl, md);
+        ENG::forward_chained_small(sv, x, lds, turn, tl, blk, tb.fwd, md);
+        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, ENG::eval_lane(tl, blk), md);
     }
 }
 
@@ -1212,7 +1251,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
             int32_t sv[ENG::SS][E];
             e.get(sv);
             typename A::elem x[E];
-            ENG::forward_chained_small(sv, x, lds, turn, opaque(tid), tb.fwd, md);
+            ENG::forward_chained_small(sv, x, lds, turn, opaque(tid), 0, tb.fwd, md);
             const uint64_t *sk = jobs.sk[who];
             typename A::Key kv[E];
 #pragma unroll
@@ -1333,8 +1372,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, job = blockIdx.y, L = rc.L;
-    const size_t LN = (size_t)L * ENG::NB;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), job = blockIdx.y, L = rc.L;
+    const size_t LN = (size_t)L * ENG::N;
     const uint64_t *sk = jobs.sk[job], *pk = jobs.pk[job];
     const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
@@ -1347,18 +1386,18 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
-        const size_t off = (size_t)limb * ENG::NB;
-        const int tl = opaque(tid);
+        const size_t off = (size_t)limb * ENG::N;
+        const int tl = opaque(tid), el = ENG::eval_lane(tl, blk);
         // as in Encrypt: with 16 coefficients per thread NTT(mu) is parked in the h1 slot of the output
         constexpr bool STASH = E > 8;
         uint64_t *stash = out + LN + off;
         elem u[E];
         int32_t sv[ENG::SS][E];
         smp.template get<0>(sv);
-        ENG::forward_chained_small(sv, u, lds, turn, tl, tb.fwd, md);
+        ENG::forward_chained_small(sv, u, lds, turn, tl, blk, tb.fwd, md);
         if (STASH) {
 #pragma unroll
-            for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
+            for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)el, 8u * ENG::T * k, to_bits<A>(u[k]));
         }
         typename A::Factor f[E];
         if (!STASH) {
@@ -1367,7 +1406,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
         }
         elem x[E];
         smp.template get<1>(sv);
-        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
+        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
         // h0: two products per slot, each reduced on its own; first x <- s c1 + x (loads only, eight slots at a time)
         constexpr int BATCH = E < 8 ? E : 8;
 #pragma unroll
@@ -1376,17 +1415,17 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
             uint64_t cv[BATCH];
 #pragma unroll
             for (int k = 0; k < BATCH; ++k) {
-                kv[k] = A::key(sk + off, sk + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * (k0 + k));
-                cv[k] = ld64(c1 + off, 8u * (uint32_t)tl, 8u * ENG::T * (k0 + k));
+                kv[k] = A::key(sk + off, sk + LN + off, 8u * (uint32_t)el, 8u * ENG::T * (k0 + k));
+                cv[k] = ld64(c1 + off, 8u * (uint32_t)el, 8u * ENG::T * (k0 + k));
             }
 #pragma unroll
             for (int k = 0; k < BATCH; ++k)
                 x[k0 + k] = A::renorm(A::mul_key_add(A::from_canon(cv[k], md), kv[k], x[k0 + k], md), md);
         }
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, f, x, tl, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, pk + off, pk + LN + off, stash, f, x, el, md);
         smp.template get<2>(sv);
-        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, pk + 2 * LN + off, pk + 3 * LN + off, stash, f, x, tl, md);
+        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
+        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, pk + 2 * LN + off, pk + 3 * LN + off, stash, f, x, el, md);
     }
 }
 

@@ -80,6 +80,7 @@ struct Engine {
     typedef typename A::Twid Twid;
     static constexpr int LOGN = LOGN_, ELOG = ELOG_, LOGB = LOGB_;
     static constexpr int NB = 1 << LOGB;
+    static constexpr int N = 1 << LOGN, LOGP = LOGN - LOGB;      // the whole polynomial; its blocks: 2^LOGP
     static constexpr int E = 1 << ELOG;
     static constexpr int T = NB / E;
     static constexpr int NPASS = (LOGB + ELOG - 1) / ELOG;
@@ -121,28 +122,44 @@ struct Engine {
     static constexpr int sbit(int p) { return p < PARTIAL ? LOGB - ELOG * (p + 1) : ELOG * (NPASS - 1 - p); }
     static constexpr int wbase(int p) { return sbit(p) + stages(p) - ELOG; }
 
-    // FUSE = 1: a first pass of one stage, on small inputs, is one sum per coefficient, of SS = 2 samples with a
-    // multiplicand that is the same for the whole wave, in the ownership of pass 1: pass 0 and its exchange go away
-    // (N = 8192: one workgroup barrier per transform instead of three; N = 1024: none, see WAVE_CHAIN).
+    // FUSE > 0: a first pass of one stage, and the stage in front of it that couples two blocks where a workgroup takes
+    // half of the polynomial (LOGP = 1), are on small inputs one sum per coefficient, of SS = 2^FUSE samples with
+    // multiplicands that are the same for the whole wave, in the ownership of pass 1: pass 0 and its exchange go away
+    // (blocks of 8192: one workgroup barrier per transform instead of three; N = 1024: none, see WAVE_CHAIN).
     // Measured with the order of the passes, N = 8192, 4 limbs: rounds with key switching 7.87 -> 7.40 ms, without
     // 19.3 -> 18.9 ms; one node's encryption and share 121 -> 118 us.
-    // Two stages taken together (N = 2048) cost three products per coefficient for the exchange they save: 117 us
-    // instead of 115 for an iteration of 12 nodes.
-    static constexpr int FUSE = A::SUM_SMALL && PARTIAL == 0 && LOGB == LOGN && wbase(1) >= 6 && LOGB % ELOG == 1 ? 1 : 0;
+    // Two stages of one block taken together (N = 2048) cost three products per coefficient for the exchange they
+    // save: 117 us instead of 115 for an iteration of 12 nodes.
+    static constexpr int FUSE =
+        A::SUM_SMALL && PARTIAL == 0 && LOGP <= 1 && wbase(1) >= 6 && LOGB % ELOG == 1 ? 1 + LOGP : 0;
     static constexpr int SS = 1 << FUSE;
     // Such transforms never leave the wave: what brings other waves' data in or out has to put its own barriers
     // around its use of the buffers.
     static constexpr bool WAVE_CHAIN = FUSE > 0 && wbase(1) <= 6;
-    // Position of sample j (of SS) of slot k: the first is in the lower part of the polynomial; own_pos is the one
-    // among them that the thread owns.
-    D2_DEV static int own_pos(int k, int tid)
-    {
-        if constexpr (FUSE > 0) return index_of<1>(k, tid);
-        else return coef_pos(k, tid);
-    }
+    // Position of sample j (of SS) of slot k: one in each of the SS parts of the polynomial.
+    static constexpr int PART = N >> FUSE;
     D2_DEV static int small_pos(int j, int k, int tid)
     {
-        return FUSE > 0 ? (j << (LOGB - FUSE)) | (own_pos(k, tid) & ((1 << (LOGB - FUSE)) - 1)) : own_pos(k, tid);
+        if constexpr (FUSE > 0) return j * PART + (index_of<1>(k, tid) & (PART - 1));
+        else return coef_pos(k, tid);
+    }
+    // SS parts are drawn by the T E / PART threads that start from the same positions, DRAW parts each
+    static constexpr int DRAW = FUSE > 0 ? N / NB : 1;
+    D2_DEV static int draw_part(int r, int tid) { return FUSE > 0 ? tid / (PART / E) * DRAW + r : 0; }
+    // Positions of an encoded message: its first stage is one sum of two coefficients half a polynomial apart, in the
+    // ownership of pass 1, or for a half of the polynomial (its other stages then begin with pass 0) of pass 0.
+    D2_DEV static int encoded_pos(int j, int k, int tid)
+    {
+        if constexpr (LOGP > 0) return j * (N / 2) + coef_pos(k, tid);
+        else return small_pos(j, k, tid);
+    }
+    // Word of slot 0 of a thread in evaluation-form storage, slots T apart (eval_pos).  A half of the polynomial is in
+    // the places its coefficients have in the layout of 2E per thread.
+    D2_DEV static int eval_lane(int tid, uint32_t blk)
+    {
+        static_assert(LOGP == 0 || T == N >> (ELOG + LOGP), "slots of both layouts the same distance apart");
+        if constexpr (LOGP == 1) return (tid & 1) * E * T + (int)(blk * (T / 2)) + (tid >> 1);
+        else return tid;
     }
 
     template <int P>
@@ -402,23 +419,59 @@ struct Engine {
         fwd_from<0, PINGPONG && !WAVE_CHAIN>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
     }
 
+    // Multiplicands of the samples of a fused start.  Entries 1, 2, 3 of the table are I, r, I r with I^2 = -1, r^2 = I.
+    // With h, l the top bits of a position, stage 0 adds (-1)^h I times the sample half a polynomial up, stage 1
+    // (-1)^l r (h = 0) or (-1)^l I r times the one a quarter up.
+    template <class SMALL>
+    D2_DEV static void small_multiplicands(SMALL (&c)[SS], uint32_t blk, const Tw *tw, const Mod &md)
+    {
+        const uint32_t l = wave_uniform((uint32_t)threadIdx.x / (uint32_t)(NB / 2 / E));
+        if constexpr (FUSE == 1) {
+            c[1] = A::small(load_tw_uniform<A>(tw, 1), l != 0, md);
+        } else {
+            c[1] = A::small(load_tw_uniform<A>(tw, 2 + blk), l != 0, md);
+            c[2] = A::small(load_tw_uniform<A>(tw, 1), blk != 0, md);
+            c[3] = A::small(load_tw_uniform<A>(tw, 3 - blk), l != 0, md);
+        }
+    }
+
+    // The next forward transform of a chain, of lam m + e with plaintext coefficients m and small e, both at
+    // encoded_pos(j, k, tid); lam_i = I lam.
+    template <class B = A>
+    D2_DEV static void forward_chained_encoded(const uint32_t (&m)[2][E], const int32_t (&e)[2][E], elem (&x)[E], uint64_t *lds,
+                                               uint32_t &turn, int tid, uint32_t blk, const Tw *tw, const Twid &lam,
+                                               const Twid &lam_i, const Mod &md)
+    {
+        static_assert(FUSE > 0, "shape without a fused start");
+        constexpr int START = LOGP > 0 ? 0 : 1;
+        const bool neg = LOGP > 0 ? blk != 0 : wave_uniform((uint32_t)threadIdx.x / (uint32_t)(NB / 2 / E)) != 0;
+        typename B::Small c[2];
+        c[1] = B::small(load_tw_uniform<B>(tw, 1), neg, md);
+        Twid w[E];
+        load_tw<START, false, true>(w, tid, blk, tw);
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            const uint32_t mk[2] = {m[0][k], m[1][k]};
+            const int32_t ek[2] = {e[0][k], e[1][k]};
+            x[k] = B::sum_encoded(mk, ek, lam, lam_i, neg, c, md);
+        }
+        fwd_from<START, PINGPONG && (START == 1 || !WAVE_CHAIN), false, START>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
+    }
+
     // The next forward transform of a chain for a whole polynomial of small signed coefficients
     // (|v| <= 32: ternary or centred-binomial samples), given as plain integers: v[j][k] is the one at
     // small_pos(j, k, tid).  Without FUSE the first stage multiplies the twiddle by a small number: the policy does
     // that without a modular reduction and without first mapping the inputs into [0, q) (ct_small).
-    // Whole-polynomial engines only.
     D2_DEV static void forward_chained_small(const int32_t (&v)[SS][E], elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid,
-                                             const Tw *tw, const Mod &md)
+                                             uint32_t blk, const Tw *tw, const Mod &md)
     {
-        static_assert(LOGB == LOGN && ahead<0>(), "shape without a separable first stage");
+        static_assert(ahead<0>() && (LOGP == 0 || FUSE > 0), "shape without a separable first stage");
         if constexpr (E > 8) tw = fresh_table(tw);
         Twid w[E];
         if constexpr (FUSE > 0) {
-            // The sample half a polynomial up is added in the lower half of the positions and subtracted in the upper one.
-            const uint32_t top = wave_uniform((uint32_t)threadIdx.x >> wbase(1));
             typename A::Small c[SS];
-            c[1] = A::small(load_tw_uniform<A>(tw, 1), top != 0, md);
-            load_tw<1, false, true>(w, tid, 0, tw);
+            small_multiplicands(c, blk, tw, md);
+            load_tw<1, false, true>(w, tid, blk, tw);
 #pragma unroll
             for (int k = 0; k < E; ++k) {
                 int32_t s[SS];
@@ -426,7 +479,7 @@ struct Engine {
                 for (int j = 0; j < SS; ++j) s[j] = v[j][k];
                 x[k] = A::sum_small(s, c, md);
             }
-            fwd_from<1, PINGPONG, false, 1>(x, w, next_buffer(lds, turn), tid, 0, tw, md);
+            fwd_from<1, PINGPONG, false, 1>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
         } else {
             load_tw<0, false, true>(w, tid, 0, tw);
             constexpr int kb = ELOG - 1;                  // the first stage pairs slots k and k + E/2, one twiddle

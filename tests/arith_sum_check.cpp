@@ -1,6 +1,6 @@
 // Host build of the sums that stand in for the first one or two stages of a transform on small inputs (sum_small of
 // the policies in paper_2207_04604_amd/csrc/arith.hpp) against 128-bit integers: the residue, and the bound the
-// stages that follow start from; and a lazy value as the multiplicand of keys (factor_key_add).  Compiled and run by tests/test_sum_small.py; exits non-zero on a violation.
+// stages that follow start from; the same for an encoded message (sum_encoded); and a lazy value as the multiplicand of keys (factor_key_add).  Compiled and run by tests/test_sum_small.py; exits non-zero on a violation.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -80,6 +80,37 @@ static void check(uint64_t q)
     }
 }
 
+// lam m0 + e0 +- I (lam m1 + e1) with any I
+template <class A>
+static void check_encoded(uint64_t q, uint64_t most_times_q)
+{
+    const typename A::Mod md = Of<A>::mod(q);
+    const uint64_t ends[] = {0, 1, q - 1, q / 2, q / 2 + 1, q - 2};
+    const uint32_t ms[] = {0, 1, (1u << 30) - 1, (1u << 30) - 2, 65536, 12288};
+    for (int rep = 0; rep < 40000; ++rep) {
+        const uint64_t w = rep % 5 < 3 ? ends[rnd() % 6] : rnd() % q, lam = rep % 4 < 2 ? ends[rnd() % 6] : rnd() % q;
+        const uint64_t lam_i = (uint64_t)((u128)w * lam % q);
+        const bool neg = rnd() & 1;
+        const uint32_t cap = (uint32_t)(q < 1u << 30 ? q - 1 : (1u << 30) - 1);
+        uint32_t m[2];
+        int32_t e[2];
+        for (int j = 0; j < 2; ++j) {
+            m[j] = rep % 3 ? ms[rnd() % 6] : (uint32_t)(rnd() >> 34);
+            if (m[j] > cap) m[j] = cap;
+            e[j] = rep % 2 ? (rnd() & 1 ? 32 : -32) : (int)(rnd() % 65) - 32;
+        }
+        typename A::Small c[2];
+        c[1] = A::small(Of<A>::tw(w, q), neg, md);
+        const typename A::elem x = A::sum_encoded(m, e, Of<A>::tw(lam, q), Of<A>::tw(lam_i, q), neg, c, md);
+        const i128 v = Of<A>::value(x), second = (i128)(u128)((u128)lam_i * m[1] % q) + (i128)w * e[1];
+        const i128 want = (i128)(u128)((u128)lam * m[0] % q) + e[0] + (neg ? -second : second);
+        if ((v - want) % (i128)q != 0 || (v < 0 ? -v : v) >= (i128)most_times_q * q) {
+            std::printf("FAILED: encoded, kind %d, q = %llu\n", A::KIND, (unsigned long long)q);
+            std::exit(1);
+        }
+    }
+}
+
 template <class A>
 static void check_factor(uint64_t q, bool wide)
 {
@@ -104,10 +135,10 @@ int main(int argc, char **argv)
     for (int i = 1; i < argc; ++i) {
         const uint64_t q = std::strtoull(argv[i], nullptr, 10);
         int n = 0;
-        if (pm_growth(q, false)) { check<ArithP, 2>(q); check<ArithP, 4>(q); check_factor<ArithP>(q, false); ++n; }
-        if (pm_growth(q, true)) { check<ArithQ, 2>(q); check<ArithQ, 4>(q); check_factor<ArithQ>(q, true); ++n; }
-        if (q < 1ull << 44) { check<ArithF, 2>(q); check<ArithF, 4>(q); ++n; }
-        if (q < 1ull << 30) { check<Arith32, 2>(q); check<Arith32, 4>(q); ++n; }
+        if (pm_growth(q, false)) { check<ArithP, 2>(q); check<ArithP, 4>(q); check_factor<ArithP>(q, false); check_encoded<ArithP>(q, 2 * pm_growth(q, false)); ++n; }
+        if (pm_growth(q, true)) { check<ArithQ, 2>(q); check<ArithQ, 4>(q); check_factor<ArithQ>(q, true); check_encoded<ArithQ>(q, 2 * pm_growth(q, true)); ++n; }
+        if (q < 1ull << 44) { check<ArithF, 2>(q); check<ArithF, 4>(q); check_encoded<ArithF>(q, 18); ++n; }
+        if (q < 1ull << 30) { check<Arith32, 2>(q); check<Arith32, 4>(q); check_encoded<Arith32>(q, 4); ++n; }
         std::printf("%d ", n);
     }
     return 0;
