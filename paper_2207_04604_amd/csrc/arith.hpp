@@ -679,13 +679,13 @@ struct ArithF {
         for (int j = 1; j < SS; ++j) x = __builtin_fma(c[j].w, (double)s[j], x);
         return x;
     }
-    // lam m[0] + e[0] +- I (lam m[1] + e[1]), m below 2^30: the first stage on an encoded message and its error; c as in
-    // sum_small, lam_i = I lam (neg: subtracted).  Two products and 16 q.
-    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
-                                   const Small (&c)[2], const Mod &m)
+    // +-lam m[0] + e[0] +- I (+-lam m[1] + e[1]), m below 2^30: the first stage on an encoded message and its error; c as in
+    // sum_small, lam_i = I lam (n0, n1: the product with m[0], m[1] is subtracted).  Two products and 16 q.
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool n0,
+                                   bool n1, const Small (&c)[2], const Mod &m)
     {
-        const elem t = mul_u32(mm[1], lam_i, m), s = sum_small(e, c, m) + mul_u32(mm[0], lam, m);
-        return neg ? s - t : s + t;
+        const elem t0 = mul_u32(mm[0], lam, m), t1 = mul_u32(mm[1], lam_i, m), s = sum_small(e, c, m);
+        return (n0 ? s - t0 : s + t0) + (n1 ? -t1 : t1);
     }
     // First stage on small signed inputs (|xv|, |yv| <= 32): w*yv is exact in a double (< 2^49), so the
     // stage is one multiplication and two additions.  The values then reach 32q; every later stage adds one
@@ -838,13 +838,13 @@ struct Arith32 {
         }
         return x;
     }
-    // lam m[0] + e[0] +- I (lam m[1] + e[1]), in [0, 4q)
-    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
-                                   const Small (&c)[2], const Mod &m)
+    // +-lam m[0] + e[0] +- I (+-lam m[1] + e[1]), in [0, 4q]
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool n0,
+                                   bool n1, const Small (&c)[2], const Mod &m)
     {
-        const uint32_t t = mul(mm[1], lam_i, m);
-        const uint32_t s = csub32(sum_small(e, c, m), m.two_q) + mul(mm[0], lam, m);
-        return csub32(s, m.two_q) + (neg ? m.two_q - t : t);
+        const uint32_t t0 = mul(mm[0], lam, m), t1 = mul(mm[1], lam_i, m);
+        const uint32_t s = csub32(sum_small(e, c, m), m.two_q) + (n0 ? m.two_q - t0 : t0);
+        return csub32(s, m.two_q) + (n1 ? m.two_q - t1 : t1);
     }
     D2_DEV static void fwd_pass_begin(elem &, const Mod &) {}
     // the last step of a forward transform: [0, 4q) -> [0, 2q)
@@ -971,13 +971,13 @@ D2_DEV uint64_t pm_sum_small(const int32_t (&s)[SS], const SmallPm (&c)[SS], con
     }
     return mul32(m.c2, hi32((uint64_t)b)) + (mul32(m.p2s, lo32((uint64_t)b)) + (uint64_t)a);
 }
-// lam m[0] + e[0] +- I (lam m[1] + e[1]), m below 2^30, |e| <= 32, in the same way (neg is in lam_i and c): here
-// -2^62 < B < 2^62 + 2^37, 2^62 is added, and 2^62 2^s = 2^(b + 31) = 2^31 c is less than k = G q.  The result is below
-// (G + 3 + gamma / 2) q.
+// +-lam m[0] + e[0] +- I (+-lam m[1] + e[1]), m below 2^30, |e| <= 32, in the same way (the signs are in lam, lam_i and
+// c): here |B| < 2^62 + 2^37, 2^63 is added, and 2^63 2^s = 2^(b + 32) = 2^32 c is less than k = G q.  The result is
+// below (G + 3 + gamma / 2) q.
 D2_DEV uint64_t pm_sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const SmallPm &lam, const SmallPm &lam_i,
                                const SmallPm &c, const ModPm &m)
 {
-    uint64_t a = (m.k - (m.c64 << 31)) + (uint64_t)(int64_t)e[0], b = (uint64_t)1 << 62;
+    uint64_t a = (m.k - (m.c64 << 32)) + (uint64_t)(int64_t)e[0], b = (uint64_t)1 << 63;
     a = (uint64_t)((int64_t)c.w0 * e[1]) + a;
     b = (uint64_t)((int64_t)c.w1 * e[1]) + b;
     a = (uint64_t)((int64_t)lam.w0 * (int32_t)mm[0]) + a;
@@ -1079,10 +1079,10 @@ struct ArithP {
     D2_DEV static Small small(const Twid &t, bool neg, const Mod &) { return pm_small(t, neg); }
     template <int SS>
     D2_DEV static elem sum_small(const int32_t (&s)[SS], const Small (&c)[SS], const Mod &m) { return pm_sum_small(s, c, m); }
-    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool neg,
-                                   const Small (&c)[2], const Mod &m)
+    D2_DEV static elem sum_encoded(const uint32_t (&mm)[2], const int32_t (&e)[2], const Twid &lam, const Twid &lam_i, bool n0,
+                                   bool n1, const Small (&c)[2], const Mod &m)
     {
-        return pm_sum_encoded(mm, e, pm_small(lam, false), pm_small(lam_i, neg), c[1], m);
+        return pm_sum_encoded(mm, e, pm_small(lam, n0), pm_small(lam_i, n1), c[1], m);
     }
     // x' = u + t comes out of the multiply-adds, y' = u + G q - t = (2u + G q) - x'
     template <bool SC = false>

@@ -183,7 +183,7 @@ struct Launch {
     static d2mhe_status bootstrap_share(d2mhe_ctx *ctx, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base,
                                         uint32_t C, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_bootstrap_share<ENG>, dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, ctx->d_tabs,
+        hipLaunchKernelGGL(k_bootstrap_share<HALF>, dim3(C << HALF::LOGP, njobs), dim3(HALF::T), 0, st, jobs, ct_base, ctx->d_tabs,
                            ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;

@@ -1497,55 +1497,85 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x, job = blockIdx.y, L = rc.L;
-    const size_t LN = (size_t)L * ENG::NB;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), job = blockIdx.y, L = rc.L;
+    const size_t LN = (size_t)L * ENG::N;
     const uint32_t party = jobs.who[job], group = jobs.group[job];
     const uint64_t *sk = jobs.sk[job];
     const uint64_t *alpha = jobs.pk[job] + (size_t)c * LN;
     const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
-    // staging: words [0, NB) the masks, words [NB, 2 NB) e0 | e1 << 8 (two's complement bytes)
+    // staging: words [0, N) the masks, words [N, 2 N) e0 | e1 << 8 (two's complement bytes)
     const LimbTab tt = load_tab(tabs, L);                 // the entry of the plaintext modulus
-    for (int n = tid; n < ENG::NB; n += ENG::T)
+    for (int n = tid; n < ENG::N; n += ENG::T)
         lds32[n] = (uint32_t)uniform_mod(philox4x32_10(n, ct_base + c, party, counter_tag(DOM_BS_M, 0, group), rc.key), tt);
-    for (int j = tid; j < ENG::NB / 2; j += ENG::T) {
+    for (int j = tid; j < ENG::N / 2; j += ENG::T) {
         int32_t e0[2], e1[2];
         cbd2(philox4x32_10(j, ct_base + c, party, counter_tag(DOM_BS_E0, 0, group), rc.key), rc.eta_mask, e0);
         cbd2(philox4x32_10(j, ct_base + c, party, counter_tag(DOM_BS_E1, 0, group), rc.key), rc.eta_mask, e1);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            lds32[ENG::NB + 2 * j + i] = ((uint32_t)e0[i] & 0xffu) | (((uint32_t)e1[i] & 0xffu) << 8);
+            lds32[ENG::N + 2 * j + i] = ((uint32_t)e0[i] & 0xffu) | (((uint32_t)e1[i] & 0xffu) << 8);
     }
     __syncthreads();
-    uint32_t mv[E], ev[E];
+    static_assert(ENG::N <= ENG::LDS_CHAIN_WORDS, "two words per coefficient");
+    // with a fused start the two coefficients of every sum, the errors as bytes
+    constexpr bool FUSED = ENG::FUSE > 0;
+    constexpr int MS = FUSED ? 2 : 1;
+    uint32_t mv[MS][E], ev[MS][E / (FUSED ? 2 : 1)];
 #pragma unroll
-    for (int k = 0; k < E; ++k) {
-        mv[k] = lds32[ENG::coef_pos(k, tid)];
-        ev[k] = lds32[ENG::NB + ENG::coef_pos(k, tid)];
-    }
+    for (int j = 0; j < MS; ++j)
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            const int pos = FUSED ? ENG::encoded_pos(j, k, tid) : ENG::coef_pos(k, tid);
+            mv[j][k] = lds32[pos];
+            const uint32_t e = lds32[ENG::N + pos];
+            if constexpr (!FUSED) ev[j][k] = e;
+            else ev[j][k / 2] = k & 1 ? ev[j][k / 2] | e << 16 : e;
+        }
+    // the transforms overwrite the samples: both buffers hold some, or their transforms have no barrier
+    if (2 * ENG::LDS_WORDS < 2 * ENG::N || ENG::WAVE_CHAIN) __syncthreads();
     for (uint32_t limb = 0; limb < L; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;
         const typename A::Mod md = A::mod(q, tb.one_s);
         const typename A::Twid lam = A::tw(tb.lambda);
-        const size_t off = (size_t)limb * ENG::NB;
-        const int tl = opaque(tid);
+        const size_t off = (size_t)limb * ENG::N;
+        const int tl = opaque(tid), el = ENG::eval_lane(tl, blk);
         const typename A::Factor none[E] = {};
         uint64_t lm[E];                                     // Lambda M mod q, canonical
-#pragma unroll
-        for (int k = 0; k < E; ++k) lm[k] = A::canon_acc(A::mul_u32(opaque(mv[k]), lam, md), md);
         elem x[E];
+        uint32_t mm[MS][E];
+        int32_t e[MS][E];
+        auto errors = [&](int which) {
 #pragma unroll
-        for (int k = 0; k < E; ++k)
-            x[k] = A::add(A::from_canon(lm[k] ? q - lm[k] : 0, md), A::from_small(sbyte(opaque(ev[k]), 0), md));
-        ENG::forward_chained(x, lds, turn, tl, 0, tb.fwd, md);
-        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, tl, md);
+            for (int j = 0; j < MS; ++j)
 #pragma unroll
-        for (int k = 0; k < E; ++k)
-            x[k] = A::add(A::from_canon(lm[k], md), A::from_small(sbyte(opaque(ev[k]), 1), md));
-        ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
+                for (int k = 0; k < E; ++k) {
+                    mm[j][k] = opaque(mv[j][k]);
+                    e[j][k] = FUSED ? sbyte(opaque(ev[j][k / (FUSED ? 2 : 1)]), 2 * (k & 1) + which) : sbyte(opaque(ev[j][k]), which);
+                }
+        };
+        errors(0);
+        if constexpr (FUSED) {
+            ENG::template forward_chained_encoded<true>(mm, e, x, lds, turn, tl, blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
+        } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k) lm[k] = A::canon_acc(A::mul_u32(mm[0][k], lam, md), md);
+#pragma unroll
+            for (int k = 0; k < E; ++k) x[k] = A::add(A::from_canon(lm[k] ? q - lm[k] : 0, md), A::from_small(e[0][k], md));
+            ENG::forward_chained(x, lds, turn, tl, 0, tb.fwd, md);
+        }
+        mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, el, md);
+        errors(1);
+        if constexpr (FUSED) {
+            ENG::forward_chained_encoded(mm, e, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
+        } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k) x[k] = A::add(A::from_canon(lm[k], md), A::from_small(e[0][k], md));
+            ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
+        }
         // eta1 = Lambda M + e1 - s_k alpha
-        mul_add_store<ENG, SRC_CANON, true>(out + LN + off, sk + off, sk + LN + off, alpha + off, none, x, tl, md, q);
+        mul_add_store<ENG, SRC_CANON, true>(out + LN + off, sk + off, sk + LN + off, alpha + off, none, x, el, md, q);
     }
 }
 

@@ -435,9 +435,9 @@ struct Engine {
         }
     }
 
-    // The next forward transform of a chain, of lam m + e with plaintext coefficients m and small e, both at
+    // The next forward transform of a chain, of lam m + e (NEG: e - lam m) with plaintext coefficients m and small e, both at
     // encoded_pos(j, k, tid); lam_i = I lam.
-    template <class B = A>
+    template <bool NEG = false, class B = A>
     D2_DEV static void forward_chained_encoded(const uint32_t (&m)[2][E], const int32_t (&e)[2][E], elem (&x)[E], uint64_t *lds,
                                                uint32_t &turn, int tid, uint32_t blk, const Tw *tw, const Twid &lam,
                                                const Twid &lam_i, const Mod &md)
@@ -453,7 +453,7 @@ struct Engine {
         for (int k = 0; k < E; ++k) {
             const uint32_t mk[2] = {m[0][k], m[1][k]};
             const int32_t ek[2] = {e[0][k], e[1][k]};
-            x[k] = B::sum_encoded(mk, ek, lam, lam_i, neg, c, md);
+            x[k] = B::sum_encoded(mk, ek, lam, lam_i, NEG, NEG != neg, c, md);
         }
         fwd_from<START, PINGPONG && (START == 1 || !WAVE_CHAIN), false, START>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
     }

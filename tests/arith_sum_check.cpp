@@ -80,7 +80,7 @@ static void check(uint64_t q)
     }
 }
 
-// lam m0 + e0 +- I (lam m1 + e1) with any I
+// +-lam m0 + e0 +- I (+-lam m1 + e1) with any I
 template <class A>
 static void check_encoded(uint64_t q, uint64_t most_times_q)
 {
@@ -90,7 +90,7 @@ static void check_encoded(uint64_t q, uint64_t most_times_q)
     for (int rep = 0; rep < 40000; ++rep) {
         const uint64_t w = rep % 5 < 3 ? ends[rnd() % 6] : rnd() % q, lam = rep % 4 < 2 ? ends[rnd() % 6] : rnd() % q;
         const uint64_t lam_i = (uint64_t)((u128)w * lam % q);
-        const bool neg = rnd() & 1;
+        const bool neg = rnd() & 1, minus = rnd() & 1;          // -I, -lam
         const uint32_t cap = (uint32_t)(q < 1u << 30 ? q - 1 : (1u << 30) - 1);
         uint32_t m[2];
         int32_t e[2];
@@ -101,9 +101,9 @@ static void check_encoded(uint64_t q, uint64_t most_times_q)
         }
         typename A::Small c[2];
         c[1] = A::small(Of<A>::tw(w, q), neg, md);
-        const typename A::elem x = A::sum_encoded(m, e, Of<A>::tw(lam, q), Of<A>::tw(lam_i, q), neg, c, md);
-        const i128 v = Of<A>::value(x), second = (i128)(u128)((u128)lam_i * m[1] % q) + (i128)w * e[1];
-        const i128 want = (i128)(u128)((u128)lam * m[0] % q) + e[0] + (neg ? -second : second);
+        const typename A::elem x = A::sum_encoded(m, e, Of<A>::tw(lam, q), Of<A>::tw(lam_i, q), minus, minus != neg, c, md);
+        const i128 sign = minus ? -1 : 1, second = sign * (i128)((u128)lam_i * m[1] % q) + (i128)w * e[1];
+        const i128 v = Of<A>::value(x), want = sign * (i128)((u128)lam * m[0] % q) + e[0] + (neg ? -second : second);
         if ((v - want) % (i128)q != 0 || (v < 0 ? -v : v) >= (i128)most_times_q * q) {
             std::printf("FAILED: encoded, kind %d, q = %llu\n", A::KIND, (unsigned long long)q);
             std::exit(1);
@@ -138,7 +138,7 @@ int main(int argc, char **argv)
         if (pm_growth(q, false)) { check<ArithP, 2>(q); check<ArithP, 4>(q); check_factor<ArithP>(q, false); check_encoded<ArithP>(q, 2 * pm_growth(q, false)); ++n; }
         if (pm_growth(q, true)) { check<ArithQ, 2>(q); check<ArithQ, 4>(q); check_factor<ArithQ>(q, true); check_encoded<ArithQ>(q, 2 * pm_growth(q, true)); ++n; }
         if (q < 1ull << 44) { check<ArithF, 2>(q); check<ArithF, 4>(q); check_encoded<ArithF>(q, 18); ++n; }
-        if (q < 1ull << 30) { check<Arith32, 2>(q); check<Arith32, 4>(q); check_encoded<Arith32>(q, 4); ++n; }
+        if (q < 1ull << 30) { check<Arith32, 2>(q); check<Arith32, 4>(q); check_encoded<Arith32>(q, 5); ++n; }
         std::printf("%d ", n);
     }
     return 0;
