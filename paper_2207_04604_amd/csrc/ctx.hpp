@@ -40,7 +40,8 @@ inline d2mhe_status hip_fail(d2mhe_ctx *ctx, hipError_t e)
 // Kernel launchers of one ring degree (one engine shape); defined in inst_<log2n>.hip.
 struct EngineOps {
     int elog, logb;
-    bool encodes_ahead;     // encrypt takes plaintexts only: a round encodes its vectors first (encode_parties)
+    bool halves;            // forward kernels take half a polynomial: a round encodes its vectors first (encode_parties),
+                            // and `finish` stops before the combine
     d2mhe_status (*ntt)(d2mhe_ctx *, uint64_t *polys, uint32_t B, bool forward, hipStream_t);
     d2mhe_status (*keygen)(d2mhe_ctx *, uint32_t party, uint64_t *sk, uint64_t *pk0, hipStream_t);
     d2mhe_status (*encode)(d2mhe_ctx *, const float *grad, uint64_t n_values, uint64_t *pt, uint32_t C, hipStream_t);
@@ -57,7 +58,7 @@ struct EngineOps {
                             uint64_t *pt, hipStream_t);
     d2mhe_status (*combine_decode)(d2mhe_ctx *, const GroupJobs &jobs, uint32_t njobs, size_t stride, uint32_t C,
                                    uint64_t n_values, hipStream_t);
-    // sum, shares, combine and decode of whole groups in one launch; null where the shape has no such kernel
+    // sum, shares and (unless `halves`) combine and decode of whole groups in one launch; null where the shape has no such kernel
     d2mhe_status (*finish)(d2mhe_ctx *, const FinishJobs &jobs, uint32_t ngroups, const uint64_t *cts, uint64_t *agg,
                            uint64_t *shares, uint32_t ct_base, uint32_t C, uint64_t n_values, hipStream_t);
     // MBFV.Convert

@@ -907,7 +907,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             order[d->members[j]] = (uint32_t)vectors.size();
             vectors.push_back(d->grads[d->members[j]]);
         }
-    const bool ahead = ops->encodes_ahead ||
+    const bool ahead = ops->halves ||
                        (!ctx->rc.coeff_packing && J >= 2 * vectors.size() && (uint64_t)J * C >= 1024);
     uint32_t *pt = (uint32_t *)shares;
     if (ahead) {
@@ -940,6 +940,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     // A table that does not hold all groups means one launch after the other: each then has to be twice as large.
     const bool split = ev && (ev[2] || ev[3]);
     const uint64_t full = ctx->N >= 2048 ? 256 : 1024;
+    bool shared = false;            // sums and shares are done
     if (!conv && ops->finish && !split && (uint64_t)G * C >= full) {
         FinishJobs jobs;
         uint32_t n = fill_finish_jobs(jobs, d, 0, slot), launches = 1;
@@ -952,13 +953,16 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
                                              shares + j0 * sh_words, d->ct_base, C, d->n_values, st);
                 if (s != D2MHE_OK) return s;
             }
-            if (ev && ev[4]) D2_HIP(ctx, hipEventRecord(ev[4], st));
-            return D2MHE_OK;
+            shared = true;
+            if (!ops->halves) {
+                if (ev && ev[4]) D2_HIP(ctx, hipEventRecord(ev[4], st));
+                return D2MHE_OK;
+            }
         }
     }
 
     // phase 2: homomorphic sum per group
-    for (uint32_t g0 = 0; g0 < G; g0 += JOB_CHUNK) {
+    for (uint32_t g0 = 0; !shared && g0 < G; g0 += JOB_CHUNK) {
         const uint32_t n = G - g0 < (uint32_t)JOB_CHUNK ? G - g0 : (uint32_t)JOB_CHUNK;
         GroupJobs jobs;
         for (uint32_t i = 0; i < n; ++i) {
@@ -976,7 +980,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
 
     if (!conv) {
         // phase 3: every member's decryption share of its group's aggregate
-        for (uint32_t j0 = 0, n; j0 < J; j0 += n) {
+        for (uint32_t j0 = 0, n; !shared && j0 < J; j0 += n) {
             RoundJobs jobs;
             n = fill_round_jobs(jobs, d, j0, per_launch, slot, shares + j0 * sh_words, sh_words,
                                 [&](uint32_t party) -> const void * { return d->sk_shares[party]; },
@@ -1183,20 +1187,20 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     shr.set_group(0, agg, group);
     uint32_t *pt = (uint32_t *)shares;       // plaintexts made ahead wait in the space of the shares (see run_round)
     for (uint32_t k = 0; k < K; ++k) {
-        enc.set_party(k, ops->encodes_ahead ? (const void *)(pt + (size_t)k * C * ctx->N) : grads[k], members[k]);
+        enc.set_party(k, ops->halves ? (const void *)(pt + (size_t)k * C * ctx->N) : grads[k], members[k]);
         enc.set_job(k, k, 0);
         shr.set_party(k, sk_shares[k], members[k]);
         shr.set_job(k, k, 0);
     }
     d2mhe_status s = D2MHE_OK;
-    if (ops->encodes_ahead) {
+    if (ops->halves) {
         static_assert(MAX_GROUP <= ENCODE_CHUNK, "a group must fit one launch");
         EncodeJobs vectors;
         std::copy(grads, grads + K, vectors.src);
         s = ops->encode_parties(&local, vectors, K, n_values, pt, C, st);
     }
     if (s == D2MHE_OK)
-        s = ops->encrypt(&local, ops->encodes_ahead ? FROM_WORDS32 : FROM_VECTOR, enc, K, 0, n_values, C, st);
+        s = ops->encrypt(&local, ops->halves ? FROM_WORDS32 : FROM_VECTOR, enc, K, 0, n_values, C, st);
     if (s == D2MHE_OK) {
         GroupJobs sum;
         sum.first[0] = cts;

@@ -84,7 +84,7 @@ struct Launch {
     {
         const dim3 grid(C << HALF::LOGP, njobs), block(HALF::T);
         if (from == FROM_VECTOR) {
-            if constexpr (HALF::LOGP > 0) return D2MHE_ERR_RANGE;       // the caller encodes first (encodes_ahead)
+            if constexpr (HALF::LOGP > 0) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
             else
                 hipLaunchKernelGGL((k_encrypt<HALF, FROM_VECTOR>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
         } else if (from == FROM_WORDS32) {
@@ -125,14 +125,14 @@ struct Launch {
                                uint64_t *agg, uint64_t *shares, uint32_t ct_base, uint32_t C, uint64_t n_values,
                                hipStream_t st)
     {
-        hipLaunchKernelGGL(k_finish<ENG>, dim3(C, ngroups), dim3(ENG::T), 0, st, jobs, cts, agg, shares,
-                           (size_t)C * 2 * ctx->L * ENG::NB, ct_base, n_values, ctx->d_tabs, ctx->rc);
+        hipLaunchKernelGGL((k_finish<HALF, HALF::LOGP == 0>), dim3(C << HALF::LOGP, ngroups), dim3(HALF::T), 0, st, jobs, cts,
+                           agg, shares, (size_t)C * 2 * ctx->L * HALF::N, ct_base, n_values, ctx->d_tabs, ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
     static constexpr auto finish_or_null()
     {
-        if constexpr (ENG::E == 8) return &finish;
+        if constexpr (HALF::E == 8) return &finish;
         else return nullptr;
     }
 

@@ -1193,8 +1193,10 @@ D2_DEV void sum_members(uint64_t (&s)[ENG::E], const uint64_t *p, size_t stride,
 // The error samples of a member are drawn once and kept as bytes where its share of the last limb will go.
 // Measured (sum + shares + combine, 32 groups of 7, N = 8192, 4 limbs, 153 indices): 10.3 ms as three launches, 7.0 ms
 // in one.  The chain of K + 1 transforms per limb in one workgroup needs a full chip: see the rule in run_round.
+// COMBINE = false: the sum and the shares only.  A half of a polynomial can't be transformed back by itself, so N = 2^14
+// ends with k_combine_decode (8 nodes, 8 limbs, 684 indices: round 15.33 -> 14.93 ms).
 // -------------------------------------------------------------------------------------
-template <class ENG>
+template <class ENG, bool COMBINE>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, const uint64_t *cts, uint64_t *agg,
                                                                uint64_t *shares, size_t ct_words, uint32_t ct_base,
                                                                uint64_t n_values, const LimbTab *tabs, RoundConst rc)
@@ -1202,13 +1204,15 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
     typedef typename ENG::A A;
     constexpr int E = ENG::E;
     static_assert(E == 8, "the samples of a thread are kept in SS 8-byte words");
-    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS + SMALL_LDS_WORDS<ENG>];
+    static_assert(!COMBINE || ENG::LOGP == 0, "the inverse transform takes the whole polynomial");
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
     const int tid = threadIdx.x;
     uint32_t turn = 0;
     // from the last to the first: what the encryption wrote last is still in the memory-side cache
-    const uint32_t c = gridDim.x - 1 - blockIdx.x, job = gridDim.y - 1 - blockIdx.y, L = rc.L, t = (uint32_t)rc.t;
+    const uint32_t b = gridDim.x - 1 - blockIdx.x, c = b >> ENG::LOGP, blk = b & ((1u << ENG::LOGP) - 1u);
+    const uint32_t job = gridDim.y - 1 - blockIdx.y, L = rc.L, t = (uint32_t)rc.t;
     const uint32_t m0 = jobs.first[job], K = jobs.first[job + 1] - m0, group = jobs.group[job];
-    const size_t LN = (size_t)L * ENG::NB, sh_words = ct_words / 2;
+    const size_t LN = (size_t)L * ENG::N, sh_words = ct_words / 2;
     cts += (size_t)m0 * ct_words + (size_t)c * 2 * LN;
     agg += (size_t)job * ct_words + (size_t)c * 2 * LN;
     shares += (size_t)m0 * sh_words + (size_t)c * LN;
@@ -1223,8 +1227,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;
         const typename A::Mod md = A::mod(q, tb.one_s);
-        const size_t off = (size_t)limb * ENG::NB;
-        const uint32_t lo = 8u * (uint32_t)opaque(tid);
+        const size_t off = (size_t)limb * ENG::N;
+        const uint32_t lo = 8u * (uint32_t)ENG::eval_lane(opaque(tid), blk);
         uint64_t y[E], z[E];                        // sums of c0 (and of the shares) and of c1
         sum_members<ENG>(z, cts + LN + off, ct_words, K, lo, md, q);
         sum_members<ENG>(y, cts + off, ct_words, K, lo, md, q);
@@ -1235,10 +1239,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         }
         for (uint32_t j = 0; j < K; ++j) {
             const uint32_t who = jobs.member[m0 + j];
-            uint64_t *share = shares + (size_t)j * sh_words, *kept = share + (size_t)(L - 1) * ENG::NB;
+            uint64_t *share = shares + (size_t)j * sh_words, *kept = share + (size_t)(L - 1) * ENG::N;
             SmallPoly<ENG> e;
             if (limb == 0) {
-                small_cbd<ENG>(e, lds + ENG::LDS_CHAIN_WORDS, opaque(tid), DOM_DEC_E, jobs.party[who], group, ct_base + c, rc);
+                // through the buffer that the next transform leaves alone
+                small_cbd<ENG>(e, ENG::PINGPONG ? lds + turn * (uint32_t)ENG::LDS_WORDS : lds, opaque(tid), DOM_DEC_E, jobs.party[who], group, ct_base + c, rc);
                 if (L > 1) {
 #pragma unroll
                     for (int i = 0; i < ENG::SS; ++i)
@@ -1251,7 +1256,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
             int32_t sv[ENG::SS][E];
             e.get(sv);
             typename A::elem x[E];
-            ENG::forward_chained_small(sv, x, lds, turn, opaque(tid), 0, tb.fwd, md);
+            ENG::forward_chained_small(sv, x, lds, turn, opaque(tid), blk, tb.fwd, md);
             const uint64_t *sk = jobs.sk[who];
             typename A::Key kv[E];
 #pragma unroll
@@ -1262,29 +1267,33 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
 #pragma unroll
             for (int k = 0; k < E; ++k) {
                 st64_stream(share + off, lo, 8u * ENG::T * k, h[k]);
-                y[k] = A::sum(y[k], h[k], q);
+                if (COMBINE) y[k] = A::sum(y[k], h[k], q);
             }
-            if (j == 31) {                          // a sum never holds more than 33 terms
+            if (COMBINE && j == 31) {                          // a sum never holds more than 33 terms
 #pragma unroll
                 for (int k = 0; k < E; ++k) y[k] = A::sum_end(y[k], md);
             }
         }
+        if constexpr (COMBINE) {
 #pragma unroll
-        for (int k = 0; k < E; ++k) y[k] = A::sum_end(y[k], md);
-        // the inverse side of the table, fetched here so that it is not held in scalar registers across the shares
-        const LimbTab ti = load_tab(fresh_table(tabs), limb);
-        typename A::elem x[E];
+            for (int k = 0; k < E; ++k) y[k] = A::sum_end(y[k], md);
+            // the inverse side of the table, fetched here so that it is not held in scalar registers across the shares
+            const LimbTab ti = load_tab(fresh_table(tabs), limb);
+            typename A::elem x[E];
 #pragma unroll
-        for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
-        ENG::template inverse<true>(x, ENG::next_buffer(lds, turn), opaque(tid), 0, ti.inv, md, A::tw(ti.ninvg), A::tw(ti.wng));
+            for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
+            ENG::template inverse<true>(x, ENG::next_buffer(lds, turn), opaque(tid), 0, ti.inv, md, A::tw(ti.ninvg), A::tw(ti.wng));
 #pragma unroll
-        for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), ti, t, acc_int[k], acc_frac[k]);
-        if (ENG::WAVE_CHAIN) __syncthreads();       // the next shares' transforms have no barrier of their own
+            for (int k = 0; k < E; ++k) scale_term(A::canon_inv(x[k], md), ti, t, acc_int[k], acc_frac[k]);
+            if (ENG::WAVE_CHAIN) __syncthreads();       // the next shares' transforms have no barrier of their own
+        }
     }
-    uint32_t m[E];
+    if constexpr (COMBINE) {
+        uint32_t m[E];
 #pragma unroll
-    for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], t);
-    decode_from_regs<ENG>(m, lds, tid, jobs.out[job], (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
+        for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], t);
+        decode_from_regs<ENG>(m, lds, tid, jobs.out[job], (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
+    }
 }
 
 // -------------------------------------------------------------------------------------

@@ -28,6 +28,9 @@ def ring(parties, reach):
     (30, 10, 2, ring(32, 1), 32, 0),
     (54, 12, 3, ring(16, 2), 16, 0),
     (36, 13, 2, ring(8, 1), 32, 0),
+    (54, 14, 2, ring(8, 1), 32, 0),            # halves of polynomials: sum and shares, then the combine
+    (44, 14, 1, [list(range(k)) for k in (1, 2, 5)], 86, 0),
+    (60, 14, 2, ring(9, 2), 29, 1),
 ])
 def test_one_launch_equals_three(bits, log2n, L, groups, C, packing):
     N, K = 1 << log2n, max(len(g) for g in groups)
