@@ -621,12 +621,12 @@ d2mhe_status d2mhe_convert_share(d2mhe_ctx *ctx, const uint64_t *sk_share, const
         return D2MHE_ERR_RANGE;
     if (C == 0) return D2MHE_OK;
     ConvJobs jobs;
-    jobs.sk[0] = sk_share;
-    jobs.pk[0] = pk_recv;
-    jobs.ct[0] = ct;
-    jobs.out[0] = share;
-    jobs.who[0] = party | (receiver << 16);
-    jobs.group[0] = group;
+    jobs.out = share;
+    jobs.stride = 0;
+    jobs.set_member(0, sk_share, party);
+    jobs.set_receiver(0, pk_recv, receiver);
+    jobs.set_group(0, ct, group);
+    jobs.job[0] = 0;
     return engine_ops(ctx)->convert_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
 }
 
@@ -686,12 +686,12 @@ d2mhe_status d2mhe_bootstrap_share(d2mhe_ctx *ctx, const uint64_t *sk_share, con
     if (party > 0xffffu || group > 0xffffu || (uint64_t)ct_base + C > 0xffffffffull) return D2MHE_ERR_RANGE;
     if (C == 0) return D2MHE_OK;
     ConvJobs jobs;
-    jobs.sk[0] = sk_share;
-    jobs.pk[0] = alpha;
-    jobs.ct[0] = ct;
-    jobs.out[0] = share;
-    jobs.who[0] = party;
-    jobs.group[0] = group;
+    jobs.out = share;
+    jobs.stride = 0;
+    jobs.set_member(0, sk_share, party);
+    jobs.set_receiver(0, alpha, 0);
+    jobs.set_group(0, ct, group);
+    jobs.job[0] = 0;
     return engine_ops(ctx)->bootstrap_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
 }
 
@@ -1020,21 +1020,38 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             first_share[r] = refs.size();
             for (uint32_t j = d->group_offsets[g]; j < d->group_offsets[g + 1]; ++j) refs.push_back(ShareRef{g, r, j});
         }
-    for (size_t s0 = 0; s0 < refs.size(); s0 += CONV_CHUNK) {
-        const uint32_t n = (uint32_t)(refs.size() - s0 < (size_t)CONV_CHUNK ? refs.size() - s0 : (size_t)CONV_CHUNK);
+    std::vector<uint16_t> rslot(ids);           // as slot, for receivers
+    const size_t launches = (refs.size() + CJ_JOBS - 1) / CJ_JOBS, limit = (refs.size() + launches - 1) / launches;
+    for (size_t s0 = 0; s0 < refs.size();) {
         ConvJobs jobs;
-        for (uint32_t i = 0; i < n; ++i) {
-            const ShareRef &f = refs[s0 + i];
+        jobs.out = shares + s0 * ct_words;
+        jobs.stride = ct_words;
+        std::fill(slot.begin(), slot.end(), (uint16_t)0);
+        std::fill(rslot.begin(), rslot.end(), (uint16_t)0);
+        uint32_t n = 0, members = 0, receivers = 0, groups = 0, listed = G;
+        for (; n < limit && s0 + n < refs.size(); ++n) {
+            const ShareRef &f = refs[s0 + n];
             const uint32_t member = d->members[f.j], receiver = conv->receivers[f.r];
-            jobs.sk[i] = d->sk_shares[member];
-            jobs.pk[i] = conv->recv_pks[receiver];
-            jobs.ct[i] = agg + (size_t)f.g * ct_words;
-            jobs.out[i] = shares + (s0 + i) * ct_words;
-            jobs.who[i] = member | (receiver << 16);
-            jobs.group[i] = d->group_ids ? d->group_ids[f.g] : f.g;
+            if ((!slot[member] && members == (uint32_t)CJ_PARTIES) || (!rslot[receiver] && receivers == (uint32_t)CJ_PARTIES) ||
+                (f.g != listed && groups == (uint32_t)CJ_GROUPS))
+                break;
+            if (!slot[member]) {
+                jobs.set_member(members, d->sk_shares[member], member);
+                slot[member] = (uint16_t)++members;
+            }
+            if (!rslot[receiver]) {
+                jobs.set_receiver(receivers, conv->recv_pks[receiver], receiver);
+                rslot[receiver] = (uint16_t)++receivers;
+            }
+            if (f.g != listed) {
+                jobs.set_group(groups++, agg + (size_t)f.g * ct_words, d->group_ids ? d->group_ids[f.g] : f.g);
+                listed = f.g;
+            }
+            jobs.job[n] = (slot[member] - 1u) | (rslot[receiver] - 1u) << 8 | (groups - 1) << 16;
         }
         d2mhe_status s = ops->convert_share(ctx, jobs, n, d->ct_base, C, st);
         if (s != D2MHE_OK) return s;
+        s0 += n;
     }
     if (ev && ev[3]) D2_HIP(ctx, hipEventRecord(ev[3], st));
 

@@ -127,15 +127,38 @@ constexpr int ENCODE_CHUNK = 448;
 struct EncodeJobs {                    // one job = one party's vector
     const float *src[ENCODE_CHUNK];
 };
-constexpr int CONV_CHUNK = 80;         // 80 * 40 B of table
-struct ConvJobs {                      // one job = one member's conversion shares towards one receiver
-    const uint64_t *sk[CONV_CHUNK];    // the member's prepared secret share
-    const uint64_t *pk[CONV_CHUNK];    // the receiver's prepared public key
-    const uint64_t *ct[CONV_CHUNK];    // aggregate [C][2][L][N]
-    uint64_t *out[CONV_CHUNK];         // shares [C][2][L][N]
-    uint32_t who[CONV_CHUNK];          // member | receiver << 16: the party word of the counters
-    uint32_t group[CONV_CHUNK];
+// Conversion shares in the same way: one job = one member's shares towards one receiver, three indices.
+// Measured, 80 rows of pointers to a launch and this: 100 users in neighbourhoods of some 20, N = 4096, 5 indices, 2 limbs
+// 2.35 -> 2.15 ms; 32 nodes of 7, N = 8192, 37 indices (three launches anyway full) 7.20 ms both.
+constexpr int CJ_PARTIES = 104, CJ_GROUPS = 64, CJ_JOBS = 320;       // 4,016 bytes
+struct ConvJobs {
+    const uint64_t *sk[CJ_PARTIES];    // prepared secret share of a member
+    const uint64_t *pk[CJ_PARTIES];    // prepared public key of a receiver
+    const uint64_t *ct[CJ_GROUPS];     // aggregate of a group [C][2][L][N]
+    uint64_t *out;                     // shares [C][2][L][N] of the first job
+    size_t stride;                     // words
+    uint32_t member[CJ_PARTIES / 2];   // ids, two to a word
+    uint32_t receiver[CJ_PARTIES / 2];
+    uint32_t group[CJ_GROUPS / 2];
+    uint32_t job[CJ_JOBS];             // index into sk | into pk << 8 | into ct << 16
+
+    void set_member(uint32_t i, const uint64_t *p, uint32_t id) { sk[i] = p; member[i / 2] = RoundJobs::half(id, i, member[i / 2]); }
+    void set_receiver(uint32_t i, const uint64_t *p, uint32_t id) { pk[i] = p; receiver[i / 2] = RoundJobs::half(id, i, receiver[i / 2]); }
+    void set_group(uint32_t i, const uint64_t *p, uint32_t id) { ct[i] = p; group[i / 2] = RoundJobs::half(id, i, group[i / 2]); }
 };
+static_assert(sizeof(ConvJobs) <= 4016, "with the other arguments of a launch under 4 KB");
+struct ConvJob {                       // one entry, uniform over the workgroup
+    const uint64_t *sk, *pk, *ct;
+    uint64_t *out;
+    uint32_t who, group;               // member | receiver << 16: the party word of the counters
+};
+D2_DEV ConvJob conv_job(const ConvJobs &t, uint32_t i)
+{
+    auto half = [](const uint32_t *v, uint32_t k) { return (v[k >> 1] >> (16 * (k & 1))) & 0xffffu; };
+    const uint32_t e = t.job[i], si = e & 0xffu, pi = (e >> 8) & 0xffu, gi = e >> 16;
+    return ConvJob{t.sk[si], t.pk[pi], t.ct[gi], t.out + (size_t)i * t.stride, half(t.member, si) | half(t.receiver, pi) << 16,
+                   half(t.group, gi)};
+}
 struct GroupJobs {                     // one job = one group: K buffers laid out at a fixed stride
     const uint64_t *first[JOB_CHUNK];  // buffer of the group's first member
     const uint64_t *ct[JOB_CHUNK];     // aggregate (combine) / unused (sum)
@@ -151,6 +174,7 @@ struct FinishJobs {                    // one job = one group
     uint16_t first[FIN_GROUPS + 2];    // members of group g: entries [first[g], first[g + 1]) of
     uint8_t member[FIN_MEMBERS];       // indices into sk and party
 };
+constexpr int CONV_CHUNK = 80;         // 80 * 36 B of table
 struct RecvJobs {                      // one job = one receiver of one group (MBFV.Convert)
     const uint64_t *first[CONV_CHUNK]; // conversion shares of the group's first member for this receiver
     const uint64_t *ct[CONV_CHUNK];    // aggregate
@@ -1381,12 +1405,13 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), job = blockIdx.y, L = rc.L;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
+    const ConvJob job = conv_job(jobs, blockIdx.y);
     const size_t LN = (size_t)L * ENG::N;
-    const uint64_t *sk = jobs.sk[job], *pk = jobs.pk[job];
-    const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
-    uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
-    stage_encrypt_samples<ENG>(lds32, tid, DOM_CVT_U, jobs.who[job], jobs.group[job], ct_base + c, rc);
+    const uint64_t *sk = job.sk, *pk = job.pk;
+    const uint64_t *c1 = job.ct + ((size_t)c * 2 + 1) * LN;
+    uint64_t *out = job.out + (size_t)c * 2 * LN;
+    stage_encrypt_samples<ENG>(lds32, tid, DOM_CVT_U, job.who, job.group, ct_base + c, rc);
     __syncthreads();
     SmallTriple<ENG> smp;
     smp.load(lds32, tid);
@@ -1506,13 +1531,14 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), job = blockIdx.y, L = rc.L;
+    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
+    const ConvJob job = conv_job(jobs, blockIdx.y);
     const size_t LN = (size_t)L * ENG::N;
-    const uint32_t party = jobs.who[job], group = jobs.group[job];
-    const uint64_t *sk = jobs.sk[job];
-    const uint64_t *alpha = jobs.pk[job] + (size_t)c * LN;
-    const uint64_t *c1 = jobs.ct[job] + ((size_t)c * 2 + 1) * LN;
-    uint64_t *out = jobs.out[job] + (size_t)c * 2 * LN;
+    const uint32_t party = job.who, group = job.group;
+    const uint64_t *sk = job.sk;
+    const uint64_t *alpha = job.pk + (size_t)c * LN;
+    const uint64_t *c1 = job.ct + ((size_t)c * 2 + 1) * LN;
+    uint64_t *out = job.out + (size_t)c * 2 * LN;
     // staging: words [0, N) the masks, words [N, 2 N) e0 | e1 << 8 (two's complement bytes)
     const LimbTab tt = load_tab(tabs, L);                 // the entry of the plaintext modulus
     for (int n = tid; n < ENG::N; n += ENG::T)

@@ -79,3 +79,45 @@ def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
         assert torch.equal(total, agg[g]), f"aggregate of group {g}"
     torch.cuda.synchronize()
     ctx.close()
+
+
+# conversion shares: 320 jobs, 104 members, 104 receivers, 64 groups to a launch
+@pytest.mark.parametrize("bits,log2n,L,parties,reach,C", [
+    (54, 10, 1, 130, 1, 1),          # 390 jobs; more members, receivers and groups than a table lists
+    (36, 10, 2, 64, 2, 1),           # exactly 320, 64 groups
+    (54, 11, 1, 65, 2, 2),           # 325
+    (30, 10, 1, 12, 5, 2),           # 11 members each, 132
+    (54, 14, 1, 7, 1, 2),            # halves of polynomials
+])
+def test_round_convert_equals_per_call(bits, log2n, L, parties, reach, C):
+    N, LN, groups = 1 << log2n, L << log2n, ring(parties, reach)
+    K, P = len(groups[0]), parties
+    q, t = O.find_primes(bits, log2n, L), 12289 if log2n <= 11 else 65537
+    n = C * N - 3
+    ctx = make_ctx(log2n, q, t, f=3, max_group=K, seed=9)
+    sk, pk0 = [dzeros(2 * LN) for _ in range(P)], [dzeros(LN) for _ in range(P)]
+    rsk, rpk = [dzeros(2 * LN) for _ in range(P)], [dzeros(4 * LN) for _ in range(P)]
+    for k in range(P):
+        ctx.keygen_share(k, sk[k], pk0[k])
+        ctx.receiver_keygen(k, rsk[k], rpk[k])
+    pks = [dzeros(4 * LN) for _ in groups]
+    for g, pk in zip(groups, pks):
+        ctx.aggregate_pk([pk0[k] for k in g], pk)
+    vec = to_dev(np.random.default_rng(bits).normal(0, 2.0, n + 4 * P).astype(np.float32))
+    grads = [vec[4 * k:4 * k + n] for k in range(P)]
+    outs = [torch.zeros((n + 3) // 4 * 4, dtype=torch.float32, device=DEV) for _ in groups]
+    ids, receivers = [3 + 2 * g for g in range(P)], [[g] for g in range(P)]
+    desc = ctx.make_round(groups, pks, sk, grads, outs, n, group_ids=ids, ct_base=7)
+    conv = ctx.make_convert(desc, receivers, rpk, rsk, outs)
+    nbytes = ctx.round_convert_scratch_bytes(K * P, P, conv.num_shares, n)
+    scratch = dzeros(nbytes // 8)
+    ctx.round_convert(desc, conv, scratch, nbytes)
+    agg = scratch[K * P * C * 2 * LN:(K + 1) * P * C * 2 * LN].view(P, C * 2 * LN)
+    shares = scratch[(K + 1) * P * C * 2 * LN:].view(K * P, C * 2 * LN)
+    share = dzeros(C * 2 * LN)
+    for g, members in enumerate(groups):
+        for i, k in enumerate(members):
+            ctx.convert_share(sk[k], rpk[g], agg[g], C, k, g, ids[g], 7, share)
+            assert torch.equal(share, shares[g * K + i]), f"share of party {k} in group {g}"
+    torch.cuda.synchronize()
+    ctx.close()
