@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0                      # MI355X HBM3E
 VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12   # 256 CUs x 64 lanes x 2.4 GHz = 39.3 T lane-ops/s
-JOBS_PER_LAUNCH = 112                      # (party, group) pairs one launch of a phase takes
+JOBS_PER_LAUNCH = 880                      # (party, group) pairs one launch of the encryption takes
 
 
 def ops_per_butterfly(qmax):
@@ -174,7 +174,11 @@ def main():
             self.scratch = dz(self.nbytes // 8)
             self.desc = self.ctx.make_round(self.groups, self.pks, self.sks, self.grads, self.outs, cfg.n_values)
             self.opb, self.arith = ops_for_moduli(cfg.q)
-            self.launches = math.ceil(self.J / JOBS_PER_LAUNCH)          # launches of one phase
+            self.launches = math.ceil(self.J / JOBS_PER_LAUNCH)          # launches of the encryption
+            # transforms modulo t per ciphertext index: one per party where the vectors are encoded ahead of the
+            # encryption, else one per (party, group) pair
+            ahead = cfg.log2_n == 14 or (self.J >= 2 * self.P and self.J * self.C >= 1024)
+            self.encodings = self.P if ahead else self.J
             torch.cuda.synchronize()
 
         def make_keys(self):
@@ -206,10 +210,10 @@ def main():
             S = 16 * L * N                                    # bytes of one ciphertext
             bf_per_transform = (N // 2) * cfg.log2_n
             # whole round, algorithmic: (4K+1) L transforms per aggregated ciphertext + (K+1) mod-t transforms
-            round_bf = sum(((4 * len(g) + 1) * L + len(g) + 1) for g in self.groups) * C_ * bf_per_transform
+            round_bf = (sum((4 * len(g) + 1) * L + 1 for g in self.groups) + self.encodings) * C_ * bf_per_transform
             round_bytes = sum(S * (3.5 * len(g) + 1.5) for g in self.groups) * C_
-            # the fused encode+encrypt kernel: 3 L transforms mod q_i + 1 mod t per fresh ciphertext
-            enc_bf = fresh * (3 * L + 1) * bf_per_transform / self.launches
+            # encode and encrypt: 3 L transforms mod q_i per fresh ciphertext and the encodings
+            enc_bf = (fresh * 3 * L + self.encodings * C_) * bf_per_transform / self.launches
             enc_bytes = (fresh * S + fresh * 4 * N) / self.launches
             enc_rate = enc_bf * self.opb / (enc_launch_ms * 1e-3) / 1e12
             sec = ms * 1e-3
@@ -244,7 +248,7 @@ def main():
                       "shares": sum(k * S for k in ks) * C_,                       # c1 read per member, share written
                       "combine_decode": sum((k + 1) * S / 2 + 4 * N for k in ks) * C_}
             # transforms modulo q_i at the context's instruction count, the ones modulo t on 32-bit residues (8)
-            ops = {"encode_encrypt": sum(k * (3 * L * self.opb + 8) for k in ks) * C_ * bf,
+            ops = {"encode_encrypt": (sum(k * 3 * L * self.opb for k in ks) + 8 * self.encodings) * C_ * bf,
                    "aggregate": 0,
                    "shares": sum(k * L * self.opb for k in ks) * C_ * bf,
                    "combine_decode": len(ks) * (L * self.opb + 8) * C_ * bf}
