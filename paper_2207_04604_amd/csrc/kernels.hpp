@@ -770,7 +770,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_keygen(uint32_t party, u
 // exceed the register budget), and the loads of a batch are issued before the stores of the
 // previous one.
 // -------------------------------------------------------------------------------------
-// NEG: dst = x - u * key instead.
+// NEG (canonical u): dst = x - u * key instead, as x + (q - u) key, so that nothing but the product is added to x: the
+// ranges of ArithQ leave no room for more.
 enum { SRC_REGS = 0, SRC_PARKED = 1, SRC_CANON = 2 };
 template <class ENG, int SRC, bool NEG = false>
 D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps, const uint64_t *src,
@@ -778,6 +779,7 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
                           const typename ENG::A::Mod &md, uint64_t q = 0 /* the modulus, for NEG */)
 {
     typedef typename ENG::A A;
+    static_assert(!NEG || SRC == SRC_CANON, "q - u");
     constexpr int E = ENG::E, BATCH = E < 8 ? E : 8, NB = E / BATCH;
     const uint32_t lo = 8u * (uint32_t)tl;
     typename A::Key kv[BATCH];
@@ -794,18 +796,12 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
         for (int k = 0; k < BATCH; ++k) {
             const typename A::elem xx = x[b * BATCH + k];
             if constexpr (SRC == SRC_REGS) {
-                static_assert(!NEG, "not needed");
                 r[k] = A::canon_acc(A::factor_key_add(u[b * BATCH + k], kv[k], xx, md), md);
             } else {
                 typename A::elem uu;
                 if constexpr (SRC == SRC_PARKED) uu = from_bits<A>(ub[k]);
-                else uu = A::from_canon(ub[k], md);
-                if constexpr (NEG) {
-                    const uint64_t prod = A::canon_acc(A::mul_key_add(uu, kv[k], A::from_canon(0, md), md), md);
-                    r[k] = A::canon_acc(A::add(xx, A::from_canon(prod ? q - prod : 0, md)), md);
-                } else {
-                    r[k] = A::canon_acc(A::mul_key_add(uu, kv[k], xx, md), md);
-                }
+                else uu = A::from_canon(NEG ? q - ub[k] : ub[k], md);
+                r[k] = A::canon_acc(A::mul_key_add(uu, kv[k], xx, md), md);
             }
         }
         if (b + 1 < NB) {

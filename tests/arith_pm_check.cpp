@@ -14,8 +14,22 @@ static inline double __longlong_as_double(long long v) { double d; std::memcpy(&
 static inline long long __double_as_longlong(double d) { long long v; std::memcpy(&v, &d, 8); return v; }
 static inline uint32_t __umulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
 static inline uint64_t __umul64hi(uint64_t a, uint64_t b) { return (uint64_t)(((unsigned __int128)a * b) >> 64); }
+// the rest of what the kernels' header names; nothing here is run by more than one thread
+#define __global__
+#define __shared__ static
+#define __launch_bounds__(...)
+static struct { uint32_t x, y; } threadIdx, blockIdx, gridDim;
+static inline void __syncthreads() {}
+static inline int __shfl_xor(int v, int) { return v; }
+static inline int __popc(uint32_t v) { return __builtin_popcount(v); }
+static inline uint32_t __brev(uint32_t v)
+{
+    uint32_t r = 0;
+    for (int i = 0; i < 32; ++i) r |= ((v >> i) & 1u) << (31 - i);
+    return r;
+}
 
-#include "../paper_2207_04604_amd/csrc/arith.hpp"
+#include "../paper_2207_04604_amd/csrc/kernels.hpp"
 #include "../paper_2207_04604_amd/csrc/pm_growth.hpp"
 
 typedef unsigned __int128 u128;
@@ -146,6 +160,38 @@ static void check(uint64_t q, bool wide)
             }
 }
 
+// x +- u key as the kernels store it (a share, a refresh share), x at the largest value a forward transform can leave,
+// u and the key at the ends of [0, q).
+template <class A, bool NEG>
+static void check_store(uint64_t q, bool wide)
+{
+    const uint32_t G = pm_growth(q, wide);
+    if (!G) return;
+    typedef Engine<A, 10, 3> ENG;
+    constexpr int E = ENG::E, T = ENG::T;
+    const typename A::Mod md = A::mod(q, G * q);
+    const uint64_t c = ((uint64_t)1 << (64 - __builtin_clzll(q))) - q;
+    // wide: 1 + 2G and the excess of a folded value; narrow: a small first stage and 15 further ones
+    const uint64_t most = wide ? (1 + 2 * (uint64_t)G) * q + (3 + 2 * (uint64_t)G) * c : (64 + 15 * (uint64_t)G) * q;
+    std::vector<uint64_t> dst(E * T), key(E * T), src(E * T);
+    const typename A::Factor none[E] = {};
+    for (uint64_t x : {most, most - 1, most - (3 + 2 * (uint64_t)G) * c + 1, most - q, (uint64_t)0})
+        for (uint64_t k : {(uint64_t)0, (uint64_t)1, q - 1, q / 2, rnd() % q}) {
+            const uint64_t us[] = {0, 1, q - 1, q - 2, q / 2, rnd() % q, rnd() % q, rnd() % q};
+            uint64_t xs[E];
+            for (int i = 0; i < E; ++i) {
+                xs[i] = x;
+                key[i * T] = k;
+                src[i * T] = us[i];
+            }
+            mul_add_store<ENG, SRC_CANON, NEG>(dst.data(), key.data(), key.data(), src.data(), none, xs, 0, md, q);
+            for (int i = 0; i < E; ++i) {
+                const uint64_t p = (uint64_t)((u128)us[i] * k % q);
+                CHECK(dst[i * T] == (x % q + (NEG ? q - p : p)) % q, NEG ? "x - u key" : "x + u key", q);
+            }
+        }
+}
+
 int main(int argc, char **argv)
 {
     int narrow = 0, wide = 0;
@@ -155,6 +201,10 @@ int main(int argc, char **argv)
         wide += pm_growth(q, true) != 0;
         check<ArithP>(q, false);
         check<ArithQ>(q, true);
+        check_store<ArithP, false>(q, false);
+        check_store<ArithP, true>(q, false);
+        check_store<ArithQ, false>(q, true);
+        check_store<ArithQ, true>(q, true);
     }
     std::printf("%d moduli, %d fit ArithP, %d fit ArithQ\n", argc - 1, narrow, wide);
     return 0;

@@ -10,7 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("bits", [34, 45, 50, 54, 55, 56, 60, 61])
+@pytest.mark.parametrize("bits", [34, 45, 50, 54, 55, 56, 59, 60, 61])
 def test_contracts_of_moduli_just_below_a_power_of_two(tmp_path, bits):
     """tests/arith_pm_check.cpp on 2^bits - c for the smallest c, ones as the prime search gives them, and c up to
     what 2c < 2^32 and the range of the policies let through (55 bits: the end of ArithP, 60: of ArithQ)."""
