@@ -194,9 +194,7 @@ void one_job(RoundJobs &jobs, const void *src, uint32_t party, const uint64_t *k
 {
     jobs.out = out;
     jobs.stride = 0;
-    jobs.set_party(0, src, party);
-    jobs.set_group(0, key, group);
-    jobs.set_job(0, 0, 0);
+    jobs.set_row(0, src, party, key, group);
 }
 
 d2mhe_status launch_ntt(d2mhe_ctx *ctx, uint64_t *polys, uint32_t B, bool forward, hipStream_t st)
@@ -623,10 +621,7 @@ d2mhe_status d2mhe_convert_share(d2mhe_ctx *ctx, const uint64_t *sk_share, const
     ConvJobs jobs;
     jobs.out = share;
     jobs.stride = 0;
-    jobs.set_member(0, sk_share, party);
-    jobs.set_receiver(0, pk_recv, receiver);
-    jobs.set_group(0, ct, group);
-    jobs.job[0] = 0;
+    jobs.set_row(0, sk_share, party, pk_recv, receiver, ct, group);
     return engine_ops(ctx)->convert_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
 }
 
@@ -688,10 +683,7 @@ d2mhe_status d2mhe_bootstrap_share(d2mhe_ctx *ctx, const uint64_t *sk_share, con
     ConvJobs jobs;
     jobs.out = share;
     jobs.stride = 0;
-    jobs.set_member(0, sk_share, party);
-    jobs.set_receiver(0, alpha, 0);
-    jobs.set_group(0, ct, group);
-    jobs.job[0] = 0;
+    jobs.set_row(0, sk_share, party, alpha, 0, ct, group);
     return engine_ops(ctx)->bootstrap_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
 }
 
@@ -748,6 +740,27 @@ size_t round_words(const d2mhe_ctx *ctx, uint64_t J, uint64_t G, uint64_t S, uin
     return (size_t)C * ((size_t)J * 2 * LN + (size_t)G * 2 * LN + shares);
 }
 
+// The different ids of a list in order of their first appearance, and the place of every entry's id among them.  (A
+// table by id would cost more than a small round where ids are large.)
+struct Places {
+    std::vector<uint32_t> ids, place;
+    Places(const uint32_t *list, uint32_t n) : place(n)
+    {
+        int bits = 4;
+        while (((uint64_t)1 << bits) < 2 * (uint64_t)n) ++bits;
+        std::vector<uint32_t> seen((size_t)1 << bits, 0u);              // 1 + place, open addressing
+        for (uint32_t i = 0; i < n; ++i) {
+            size_t h = (list[i] * 0x9E3779B1u) >> (32 - bits);
+            while (seen[h] && ids[seen[h] - 1] != list[i]) h = (h + 1) & (seen.size() - 1);
+            if (!seen[h]) {
+                ids.push_back(list[i]);
+                seen[h] = (uint32_t)ids.size();
+            }
+            place[i] = seen[h] - 1;
+        }
+    }
+};
+
 // A round's J jobs in as few launches as their table allows, of equal size.
 uint32_t jobs_per_launch(uint32_t J)
 {
@@ -756,37 +769,45 @@ uint32_t jobs_per_launch(uint32_t J)
 }
 
 // The table of a launch over jobs j0, j0 + 1, ..., at most `limit` of them and as far as it holds their parties and
-// groups; returns their number (at least one).  src(party) and key(group index): the pointers of a job.  slot: scratch
-// of num_parties entries (1 + a party's place in this table).
+// groups; returns their number (at least one).  src(job) and key(group index): the pointers of a job.  slot: scratch of
+// one zero per party (1 + its place in this table).
 extern "C++" template <class SRC, class KEY>
-uint32_t fill_round_jobs(RoundJobs &jobs, const d2mhe_round_desc *d, uint32_t j0, uint32_t limit,
+uint32_t fill_round_jobs(RoundJobs &jobs, const d2mhe_round_desc *d, const Places &who, uint32_t j0, uint32_t limit,
                          std::vector<uint16_t> &slot, uint64_t *out, size_t stride, SRC src, KEY key)
 {
     const uint32_t J = d->group_offsets[d->num_groups];
+    const bool rows = J <= (uint32_t)RJ_ROWS;
     uint32_t n = 0, parties = 0, groups = 0, g = 0, listed = d->num_groups;
     std::fill(slot.begin(), slot.end(), (uint16_t)0);
     jobs.out = out;
     jobs.stride = stride;
     for (; n < limit && j0 + n < J; ++n) {
-        const uint32_t party = d->members[j0 + n];
-        while (d->group_offsets[g + 1] <= j0 + n) ++g;
-        if ((g != listed && groups == (uint32_t)RJ_GROUPS) || (!slot[party] && parties == (uint32_t)RJ_PARTIES)) break;
+        const uint32_t j = j0 + n, party = d->members[j];
+        while (d->group_offsets[g + 1] <= j) ++g;
+        const uint32_t id = d->group_ids ? d->group_ids[g] : g;
+        if (rows) {
+            jobs.set_row(n, src(j), party, key(g), id);
+            continue;
+        }
+        uint16_t &s = slot[who.place[j]];
+        if ((g != listed && groups == (uint32_t)RJ_GROUPS) || (!s && parties == (uint32_t)RJ_PARTIES)) break;
         if (g != listed) {
-            jobs.set_group(groups++, key(g), d->group_ids ? d->group_ids[g] : g);
+            jobs.set_group(groups++, key(g), id);
             listed = g;
         }
-        if (!slot[party]) {
-            jobs.set_party(parties, src(party), party);
-            slot[party] = (uint16_t)++parties;
+        if (!s) {
+            jobs.set_party(parties, src(j), party);
+            s = (uint16_t)++parties;
         }
-        jobs.set_job(n, slot[party] - 1u, groups - 1);
+        jobs.set_job(n, s - 1u, groups - 1);
     }
     return n;
 }
 
 // The table of a k_finish launch: groups g0, g0 + 1, ... as far as it holds them; returns their number (at least
-// one).  slot: scratch of num_parties entries (1 + a party's place in this table).
-uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, uint32_t g0, std::vector<uint16_t> &slot)
+// one).  slot: scratch of one zero per party (1 + its place in this table).
+uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Places &who, uint32_t g0,
+                          std::vector<uint16_t> &slot)
 {
     static_assert(MAX_GROUP <= FIN_PARTIES && MAX_GROUP <= FIN_MEMBERS, "a group must fit one launch");
     uint32_t n = 0, members = 0, parties = 0;
@@ -795,16 +816,17 @@ uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, uint32_t 
     for (; g0 + n < d->num_groups && n < (uint32_t)FIN_GROUPS; ++n) {
         const uint32_t g = g0 + n, first = d->group_offsets[g], K = d->group_offsets[g + 1] - first;
         uint32_t fresh = 0;
-        for (uint32_t i = 0; i < K; ++i) fresh += slot[d->members[first + i]] == 0;
+        for (uint32_t i = 0; i < K; ++i) fresh += slot[who.place[first + i]] == 0;
         if (members + K > (uint32_t)FIN_MEMBERS || parties + fresh > (uint32_t)FIN_PARTIES) break;
         for (uint32_t i = 0; i < K; ++i) {
-            const uint32_t party = d->members[first + i];
-            if (!slot[party]) {
+            uint16_t &s = slot[who.place[first + i]];
+            if (!s) {
+                const uint32_t party = d->members[first + i];
                 jobs.sk[parties] = d->sk_shares[party];
                 jobs.party[parties] = (uint16_t)party;
-                slot[party] = (uint16_t)++parties;
+                s = (uint16_t)++parties;
             }
-            jobs.member[members + i] = (uint8_t)(slot[party] - 1);
+            jobs.member[members + i] = (uint8_t)(s - 1);
         }
         members += K;
         jobs.first[n + 1] = (uint16_t)members;
@@ -898,23 +920,16 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     // Measured, encoded per group and ahead: 32 parties in 7 groups each, N = 8192, 4 limbs 20.2 / 19.1 ms; 16 in 5, N =
     // 4096, 3 limbs 0.391 / 0.375 ms.  Below two groups per party, or where the launches do not fill the chip, the
     // extra launch costs what it saves.
-    const uint32_t ids = std::min(d->num_parties, 0x10000u);
-    std::vector<uint16_t> slot(ids);
-    std::vector<uint32_t> order(ids, ~0u);               // a party's place among those that take part
-    std::vector<const float *> vectors;
-    for (uint32_t j = 0; j < J; ++j)
-        if (order[d->members[j]] == ~0u) {
-            order[d->members[j]] = (uint32_t)vectors.size();
-            vectors.push_back(d->grads[d->members[j]]);
-        }
-    const bool ahead = ops->halves ||
-                       (!ctx->rc.coeff_packing && J >= 2 * vectors.size() && (uint64_t)J * C >= 1024);
+    const Places who(d->members, J);
+    const size_t V = who.ids.size();                     // parties that take part
+    std::vector<uint16_t> slot(V);
+    const bool ahead = ops->halves || (!ctx->rc.coeff_packing && J >= 2 * V && (uint64_t)J * C >= 1024);
     uint32_t *pt = (uint32_t *)shares;
     if (ahead) {
-        for (size_t p0 = 0; p0 < vectors.size(); p0 += ENCODE_CHUNK) {
-            const uint32_t n = (uint32_t)std::min(vectors.size() - p0, (size_t)ENCODE_CHUNK);
+        for (size_t p0 = 0; p0 < V; p0 += ENCODE_CHUNK) {
+            const uint32_t n = (uint32_t)std::min(V - p0, (size_t)ENCODE_CHUNK);
             EncodeJobs jobs;
-            std::copy(vectors.begin() + p0, vectors.begin() + p0 + n, jobs.src);
+            for (uint32_t i = 0; i < n; ++i) jobs.src[i] = d->grads[who.ids[p0 + i]];
             d2mhe_status s = ops->encode_parties(ctx, jobs, n, d->n_values, pt + p0 * C * ctx->N, C, st);
             if (s != D2MHE_OK) return s;
         }
@@ -922,9 +937,9 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     const uint32_t per_launch = jobs_per_launch(J);
     for (uint32_t j0 = 0, n; j0 < J; j0 += n) {
         RoundJobs jobs;
-        n = fill_round_jobs(jobs, d, j0, per_launch, slot, cts + j0 * ct_words, ct_words,
-                            [&](uint32_t party) -> const void * {
-                                return ahead ? (const void *)(pt + (size_t)order[party] * C * ctx->N) : d->grads[party];
+        n = fill_round_jobs(jobs, d, who, j0, per_launch, slot, cts + j0 * ct_words, ct_words,
+                            [&](uint32_t j) -> const void * {
+                                return ahead ? (const void *)(pt + (size_t)who.place[j] * C * ctx->N) : d->grads[d->members[j]];
                             },
                             [&](uint32_t g) { return d->pks[g]; });
         d2mhe_status s = ops->encrypt(ctx, ahead ? FROM_WORDS32 : FROM_VECTOR, jobs, n, d->ct_base, d->n_values, C, st);
@@ -943,11 +958,11 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     bool shared = false;            // sums and shares are done
     if (!conv && ops->finish && !split && (uint64_t)G * C >= full) {
         FinishJobs jobs;
-        uint32_t n = fill_finish_jobs(jobs, d, 0, slot), launches = 1;
-        for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, g0, slot);
+        uint32_t n = fill_finish_jobs(jobs, d, who, 0, slot), launches = 1;
+        for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, who, g0, slot);
         if (launches == 1 || (uint64_t)G * C >= 2 * full * launches) {
             for (uint32_t g0 = 0; g0 < G; g0 += n) {
-                if (launches > 1) n = fill_finish_jobs(jobs, d, g0, slot);
+                if (launches > 1) n = fill_finish_jobs(jobs, d, who, g0, slot);
                 const size_t j0 = d->group_offsets[g0];
                 d2mhe_status s = ops->finish(ctx, jobs, n, cts + j0 * ct_words, agg + (size_t)g0 * ct_words,
                                              shares + j0 * sh_words, d->ct_base, C, d->n_values, st);
@@ -982,8 +997,8 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
         // phase 3: every member's decryption share of its group's aggregate
         for (uint32_t j0 = 0, n; !shared && j0 < J; j0 += n) {
             RoundJobs jobs;
-            n = fill_round_jobs(jobs, d, j0, per_launch, slot, shares + j0 * sh_words, sh_words,
-                                [&](uint32_t party) -> const void * { return d->sk_shares[party]; },
+            n = fill_round_jobs(jobs, d, who, j0, per_launch, slot, shares + j0 * sh_words, sh_words,
+                                [&](uint32_t j) -> const void * { return d->sk_shares[d->members[j]]; },
                                 [&](uint32_t g) { return agg + (size_t)g * ct_words; });
             d2mhe_status s = ops->share(ctx, jobs, n, d->ct_base, C, st);
             if (s != D2MHE_OK) return s;
@@ -1020,8 +1035,10 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             first_share[r] = refs.size();
             for (uint32_t j = d->group_offsets[g]; j < d->group_offsets[g + 1]; ++j) refs.push_back(ShareRef{g, r, j});
         }
-    std::vector<uint16_t> rslot(ids);           // as slot, for receivers
+    const Places to(conv->receivers, R);
+    std::vector<uint16_t> rslot(to.ids.size());          // as slot, for receivers
     const size_t launches = (refs.size() + CJ_JOBS - 1) / CJ_JOBS, limit = (refs.size() + launches - 1) / launches;
+    const bool rows = refs.size() <= (size_t)CJ_ROWS;
     for (size_t s0 = 0; s0 < refs.size();) {
         ConvJobs jobs;
         jobs.out = shares + s0 * ct_words;
@@ -1032,22 +1049,29 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
         for (; n < limit && s0 + n < refs.size(); ++n) {
             const ShareRef &f = refs[s0 + n];
             const uint32_t member = d->members[f.j], receiver = conv->receivers[f.r];
-            if ((!slot[member] && members == (uint32_t)CJ_PARTIES) || (!rslot[receiver] && receivers == (uint32_t)CJ_PARTIES) ||
+            const uint32_t id = d->group_ids ? d->group_ids[f.g] : f.g;
+            const uint64_t *sk = d->sk_shares[member], *pk = conv->recv_pks[receiver], *ct = agg + (size_t)f.g * ct_words;
+            if (rows) {
+                jobs.set_row(n, sk, member, pk, receiver, ct, id);
+                continue;
+            }
+            uint16_t &ms = slot[who.place[f.j]], &rs = rslot[to.place[f.r]];
+            if ((!ms && members == (uint32_t)CJ_PARTIES) || (!rs && receivers == (uint32_t)CJ_PARTIES) ||
                 (f.g != listed && groups == (uint32_t)CJ_GROUPS))
                 break;
-            if (!slot[member]) {
-                jobs.set_member(members, d->sk_shares[member], member);
-                slot[member] = (uint16_t)++members;
+            if (!ms) {
+                jobs.set_member(members, sk, member);
+                ms = (uint16_t)++members;
             }
-            if (!rslot[receiver]) {
-                jobs.set_receiver(receivers, conv->recv_pks[receiver], receiver);
-                rslot[receiver] = (uint16_t)++receivers;
+            if (!rs) {
+                jobs.set_receiver(receivers, pk, receiver);
+                rs = (uint16_t)++receivers;
             }
             if (f.g != listed) {
-                jobs.set_group(groups++, agg + (size_t)f.g * ct_words, d->group_ids ? d->group_ids[f.g] : f.g);
+                jobs.set_group(groups++, ct, id);
                 listed = f.g;
             }
-            jobs.job[n] = (slot[member] - 1u) | (rslot[receiver] - 1u) << 8 | (groups - 1) << 16;
+            jobs.set_job(n, ms - 1u, rs - 1u, groups - 1);
         }
         d2mhe_status s = ops->convert_share(ctx, jobs, n, d->ct_base, C, st);
         if (s != D2MHE_OK) return s;
@@ -1169,7 +1193,7 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     D2_NEED_SCHEME(ctx);
     if (!pk || !sk_shares || !grads || !members || !out_sum) return D2MHE_ERR_NULL;
     if (K == 0 || K > (uint32_t)MAX_GROUP || K > ctx->max_group || group > 0xffffu) return D2MHE_ERR_RANGE;
-    static_assert(MAX_GROUP <= RJ_PARTIES && MAX_GROUP <= JOB_CHUNK, "a group must fit one launch");
+    static_assert(MAX_GROUP <= RJ_ROWS && MAX_GROUP <= JOB_CHUNK, "a group must fit one launch");
     if (misaligned(pk) || misaligned(out_sum)) return D2MHE_ERR_ALIGN;
     for (uint32_t k = 0; k < K; ++k) {
         if (members[k] > 0xffffu) return D2MHE_ERR_RANGE;
@@ -1198,16 +1222,12 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
     RoundJobs enc, shr;
     enc.out = cts;
     enc.stride = ct_words;
-    enc.set_group(0, pk, group);
     shr.out = shares;
     shr.stride = sh_words;
-    shr.set_group(0, agg, group);
     uint32_t *pt = (uint32_t *)shares;       // plaintexts made ahead wait in the space of the shares (see run_round)
     for (uint32_t k = 0; k < K; ++k) {
-        enc.set_party(k, ops->halves ? (const void *)(pt + (size_t)k * C * ctx->N) : grads[k], members[k]);
-        enc.set_job(k, k, 0);
-        shr.set_party(k, sk_shares[k], members[k]);
-        shr.set_job(k, k, 0);
+        enc.set_row(k, ops->halves ? (const void *)(pt + (size_t)k * C * ctx->N) : grads[k], members[k], pk, group);
+        shr.set_row(k, sk_shares[k], members[k], agg, group);
     }
     d2mhe_status s = D2MHE_OK;
     if (ops->halves) {

@@ -94,7 +94,10 @@ constexpr int JOB_CHUNK = 112;   // 112 * 32 B of table + the other arguments st
 // round: with a row of pointers per job (112 to a launch) the 2,060 jobs of 100 users in 100 groups were 19 launches of
 // barely more than one chip's worth of workgroups each.
 // Measured, that round (N = 4096, 5 indices, 2 limbs of 54 bits), with the vectors encoded ahead: 1.98 -> 1.42 ms.
-constexpr int RJ_PARTIES = 112, RJ_GROUPS = 112, RJ_JOBS = 880;      // 4,016 bytes
+// Launches of few jobs list each in a row of its own, entry i of every array, so that a workgroup requests all it needs at
+// once: two dependent reads of the arguments cost
+// 0.3 to 0.5 us of a launch (a share of 60 indices, N = 1024, 30 bits 5.0 -> 4.8 us; N = 2048, 60 bits 10.3 -> 10.0 us).
+constexpr int RJ_PARTIES = 112, RJ_GROUPS = 112, RJ_JOBS = 880, RJ_ROWS = 112;      // 4,016 bytes
 struct RoundJobs {
     const void *src[RJ_PARTIES];       // gradient, plaintext polynomials or prepared secret share of a party
     const uint64_t *key[RJ_GROUPS];    // prepared public key or aggregate of a group
@@ -108,6 +111,12 @@ struct RoundJobs {
     void set_party(uint32_t i, const void *p, uint32_t id) { src[i] = p; party[i / 2] = half(id, i, party[i / 2]); }
     void set_group(uint32_t i, const uint64_t *p, uint32_t id) { key[i] = p; group[i / 2] = half(id, i, group[i / 2]); }
     void set_job(uint32_t i, uint32_t si, uint32_t ki) { job[i / 2] = half(si | (ki << 8), i, job[i / 2]); }
+    void set_row(uint32_t i, const void *s, uint32_t party_id, const uint64_t *k, uint32_t group_id)
+    {
+        set_party(i, s, party_id);
+        set_group(i, k, group_id);
+        set_job(i, i, i);
+    }
 };
 static_assert(sizeof(RoundJobs) <= 4016, "with the other arguments of a launch under 4 KB");
 struct RoundJob {                      // one entry, uniform over the workgroup
@@ -116,11 +125,29 @@ struct RoundJob {                      // one entry, uniform over the workgroup
     uint64_t *out;
     uint32_t party, group;
 };
+D2_DEV uint32_t half_word(uint32_t w, uint32_t i) { return (w >> (16 * (i & 1))) & 0xffffu; }
 D2_DEV RoundJob round_job(const RoundJobs &t, uint32_t i)
 {
-    auto half = [](const uint32_t *v, uint32_t k) { return (v[k >> 1] >> (16 * (k & 1))) & 0xffffu; };
-    const uint32_t e = half(t.job, i), si = e & 0xffu, ki = e >> 8;
-    return RoundJob{t.src[si], t.key[ki], t.out + (size_t)i * t.stride, half(t.party, si), half(t.group, ki)};
+    const uint32_t row = i < (uint32_t)RJ_ROWS ? i : 0;
+    uint32_t job = t.job[i >> 1], party = t.party[row >> 1], group = t.group[row >> 1];
+    RoundJob r = {t.src[row], t.key[row], t.out, 0, 0};
+    size_t stride = t.stride;
+#if D2_GCN_ASM
+    // all requested here: the compiler would move them below the branch
+    asm volatile("" : "+s"(job), "+s"(party), "+s"(group), "+s"(r.src), "+s"(r.key), "+s"(r.out), "+s"(stride));
+#endif
+    const uint32_t e = half_word(job, i);
+    r.out += (size_t)i * stride;
+    r.party = half_word(party, row);
+    r.group = half_word(group, row);
+    if (e != (row | row << 8)) {
+        const uint32_t si = e & 0xffu, ki = e >> 8;
+        r.src = t.src[si];
+        r.key = t.key[ki];
+        r.party = half_word(t.party[si >> 1], si);
+        r.group = half_word(t.group[ki >> 1], ki);
+    }
+    return r;
 }
 enum { FROM_WORDS64 = 0, FROM_WORDS32 = 1, FROM_VECTOR = 2 };   // what Encrypt reads
 constexpr int ENCODE_CHUNK = 448;
@@ -130,7 +157,7 @@ struct EncodeJobs {                    // one job = one party's vector
 // Conversion shares in the same way: one job = one member's shares towards one receiver, three indices.
 // Measured, 80 rows of pointers to a launch and this: 100 users in neighbourhoods of some 20, N = 4096, 5 indices, 2 limbs
 // 2.35 -> 2.15 ms; 32 nodes of 7, N = 8192, 37 indices (three launches anyway full) 7.20 ms both.
-constexpr int CJ_PARTIES = 104, CJ_GROUPS = 64, CJ_JOBS = 320;       // 4,016 bytes
+constexpr int CJ_PARTIES = 104, CJ_GROUPS = 64, CJ_JOBS = 320, CJ_ROWS = 64;       // 4,016 bytes
 struct ConvJobs {
     const uint64_t *sk[CJ_PARTIES];    // prepared secret share of a member
     const uint64_t *pk[CJ_PARTIES];    // prepared public key of a receiver
@@ -145,6 +172,15 @@ struct ConvJobs {
     void set_member(uint32_t i, const uint64_t *p, uint32_t id) { sk[i] = p; member[i / 2] = RoundJobs::half(id, i, member[i / 2]); }
     void set_receiver(uint32_t i, const uint64_t *p, uint32_t id) { pk[i] = p; receiver[i / 2] = RoundJobs::half(id, i, receiver[i / 2]); }
     void set_group(uint32_t i, const uint64_t *p, uint32_t id) { ct[i] = p; group[i / 2] = RoundJobs::half(id, i, group[i / 2]); }
+    void set_job(uint32_t i, uint32_t si, uint32_t pi, uint32_t gi) { job[i] = si | pi << 8 | gi << 16; }
+    void set_row(uint32_t i, const uint64_t *s, uint32_t member_id, const uint64_t *p, uint32_t receiver_id, const uint64_t *c,
+                 uint32_t group_id)
+    {
+        set_member(i, s, member_id);
+        set_receiver(i, p, receiver_id);
+        set_group(i, c, group_id);
+        set_job(i, i, i, i);
+    }
 };
 static_assert(sizeof(ConvJobs) <= 4016, "with the other arguments of a launch under 4 KB");
 struct ConvJob {                       // one entry, uniform over the workgroup
@@ -154,10 +190,26 @@ struct ConvJob {                       // one entry, uniform over the workgroup
 };
 D2_DEV ConvJob conv_job(const ConvJobs &t, uint32_t i)
 {
-    auto half = [](const uint32_t *v, uint32_t k) { return (v[k >> 1] >> (16 * (k & 1))) & 0xffffu; };
-    const uint32_t e = t.job[i], si = e & 0xffu, pi = (e >> 8) & 0xffu, gi = e >> 16;
-    return ConvJob{t.sk[si], t.pk[pi], t.ct[gi], t.out + (size_t)i * t.stride, half(t.member, si) | half(t.receiver, pi) << 16,
-                   half(t.group, gi)};
+    const uint32_t row = i < (uint32_t)CJ_ROWS ? i : 0;
+    uint32_t e = t.job[i], member = t.member[row >> 1], receiver = t.receiver[row >> 1], group = t.group[row >> 1];
+    ConvJob r = {t.sk[row], t.pk[row], t.ct[row], t.out, 0, 0};
+    size_t stride = t.stride;
+#if D2_GCN_ASM
+    asm volatile("" : "+s"(e), "+s"(member), "+s"(receiver), "+s"(group), "+s"(r.sk), "+s"(r.pk), "+s"(r.ct), "+s"(r.out),
+                      "+s"(stride));
+#endif
+    r.out += (size_t)i * stride;
+    r.who = half_word(member, row) | half_word(receiver, row) << 16;
+    r.group = half_word(group, row);
+    if (e != (row | row << 8 | row << 16)) {
+        const uint32_t si = e & 0xffu, pi = (e >> 8) & 0xffu, gi = e >> 16;
+        r.sk = t.sk[si];
+        r.pk = t.pk[pi];
+        r.ct = t.ct[gi];
+        r.who = half_word(t.member[si >> 1], si) | half_word(t.receiver[pi >> 1], pi) << 16;
+        r.group = half_word(t.group[gi >> 1], gi);
+    }
+    return r;
 }
 struct GroupJobs {                     // one job = one group: K buffers laid out at a fixed stride
     const uint64_t *first[JOB_CHUNK];  // buffer of the group's first member

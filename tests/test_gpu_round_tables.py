@@ -1,4 +1,5 @@
-"""Rounds whose job tables do not fit one launch (880 jobs, 112 parties, 112 groups) and rounds whose parties are in
+"""Rounds whose job tables do not fit one launch (880 jobs, 112 parties, 112 groups), rounds of as many jobs as a table
+lists in rows (112, 64 conversion shares) and one more, and rounds whose parties are in
 many groups, so that their vectors are encoded once ahead of the encryption: every message against the per-call entry
 points, which the other tests hold to the oracle."""
 import numpy as np
@@ -16,6 +17,10 @@ def ring(parties, reach):
     return [sorted((i + d) % parties for d in range(-reach, reach + 1)) for i in range(parties)]
 
 
+def pairs(n):
+    return [[g, g + 1] for g in range(n)]
+
+
 def shuffled(groups, seed):
     rng = np.random.default_rng(seed)
     return [[int(k) for k in rng.permutation(g)] for g in groups]
@@ -27,8 +32,13 @@ def shuffled(groups, seed):
     (36, 10, 2, shuffled(ring(41, 10), 1), 2, 0, True),         # 861 jobs: one launch; members in any order
     (30, 10, 1, shuffled(ring(42, 10), 2), 2, 0, True),         # 882: two
     (54, 11, 1, ring(125, 3), 2, 0, False),                     # 875 jobs, parties beyond the table before the jobs are
-    (60, 13, 1, ring(26, 19), 1, 0, False),                     # exactly 39 members each
-    (54, 14, 1, ring(23, 5), 5, 0, False),                      # 16 coefficients per thread
+    (60, 13, 1, ring(39, 19), 1, 0, False),                     # 39 groups of the same 39 members: 1,521 jobs
+    (54, 14, 1, ring(23, 5), 5, 0, False),                      # encryption in halves of polynomials
+    (30, 14, 1, ring(23, 5), 5, 0, False),                      # whole ones, 16 coefficients per thread
+    (54, 10, 1, pairs(56), 2, 0, True),                         # 112 jobs: rows of the table
+    (36, 11, 1, pairs(57), 2, 0, True),                         # 114: parties and groups listed once
+    (60, 10, 1, [[65535, 7, 40000], [7, 9], [40000, 65528]], 2, 0, True),       # ids far apart, two pairs of which collide
+    (30, 10, 1, [[(40503 * k) % 65521 for k in range(g, g + 5)] for g in range(30)], 1, 0, True),
     (44, 11, 1, ring(130, 3), 2, 1, True),                      # coefficient packing: never encoded ahead
     (54, 10, 1, [[0, 1, 2], [3, 4]], 300, 0, True),             # nobody in two groups
 ])
@@ -37,22 +47,22 @@ def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
     groups = [list(dict.fromkeys(g)) for g in groups]
     K = max(len(g) for g in groups)
     q, t = O.find_primes(bits, log2n, L), 12289 if log2n <= 11 else 65537
-    P, J, G = 1 + max(max(g) for g in groups), sum(len(g) for g in groups), len(groups)
+    ids, J, G = sorted({k for g in groups for k in g}), sum(len(g) for g in groups), len(groups)
     n, LN = C * N - 5, L * N
     ctx = make_ctx(log2n, q, t, f=3, max_group=K, seed=5)
-    sk, pk0 = [dzeros(2 * LN) for _ in range(P)], [dzeros(LN) for _ in range(P)]
-    for k in range(P):
+    sk, pk0 = {k: dzeros(2 * LN) for k in ids}, {k: dzeros(LN) for k in ids}
+    for k in ids:
         ctx.keygen_share(k, sk[k], pk0[k])
     pks = [dzeros(4 * LN) for _ in groups]
     for g, pk in zip(groups, pks):
         ctx.aggregate_pk([pk0[k] for k in g], pk)
-    vec = to_dev(np.random.default_rng(bits).normal(0, 2.0, n + 4 * P).astype(np.float32))
-    grads = [vec[4 * k:4 * k + n] for k in range(P)]
+    vec = to_dev(np.random.default_rng(bits).normal(0, 2.0, n + 4 * len(ids)).astype(np.float32))
+    grads = {k: vec[4 * i:4 * i + n] for i, k in enumerate(ids)}
     outs = [torch.zeros((n + 3) // 4 * 4, dtype=torch.float32, device=DEV) for _ in groups]
     nbytes = ctx.round_scratch_bytes(J, G, n)
     scratch = dzeros(nbytes // 8)
-    ids = [3 + 2 * g for g in range(G)]
-    desc = ctx.make_round(groups, pks, sk, grads, outs, n, group_ids=ids, ct_base=7, packing=packing)
+    gids = [3 + 2 * g for g in range(G)]
+    desc = ctx.make_round(groups, pks, sk, grads, outs, n, group_ids=gids, ct_base=7, packing=packing)
     events = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
     for e in events:
         e.record()
@@ -60,20 +70,20 @@ def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
     cts = scratch[:J * C * 2 * LN].view(J, C * 2 * LN)
     agg = scratch[J * C * 2 * LN:(J + G) * C * 2 * LN].view(G, C * 2 * LN)
     shares = scratch[(J + G) * C * 2 * LN:].view(J, C * LN)
-    pts = [dzeros(C * N) for _ in range(P)]
-    for k in range(P):
+    pts = {k: dzeros(C * N) for k in ids}
+    for k in ids:
         (ctx.encode_coefficients if packing else ctx.encode)(grads[k], n, pts[k], C)
     ct, share, j = dzeros(C * 2 * LN), dzeros(C * LN), 0
     for g, members in enumerate(groups):
         total = None
         for k in members:
-            ctx.encrypt(pks[g], pts[k], C, k, ids[g], 7, ct)
+            ctx.encrypt(pks[g], pts[k], C, k, gids[g], 7, ct)
             assert torch.equal(ct, cts[j]), f"ciphertext of party {k} in group {g}"
             if total is None:
                 total = ct.clone()
             else:
                 ctx.add(total, ct, C)
-            ctx.partial_decrypt(sk[k], agg[g], C, k, ids[g], 7, share)
+            ctx.partial_decrypt(sk[k], agg[g], C, k, gids[g], 7, share)
             assert torch.equal(share, shares[j]), f"share of party {k} in group {g}"
             j += 1
         assert torch.equal(total, agg[g]), f"aggregate of group {g}"
@@ -81,13 +91,15 @@ def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
     ctx.close()
 
 
-# conversion shares: 320 jobs, 104 members, 104 receivers, 64 groups to a launch
+# conversion shares: 320 jobs, 104 members, 104 receivers, 64 groups to a launch; rows up to 64 jobs
 @pytest.mark.parametrize("bits,log2n,L,parties,reach,C", [
     (54, 10, 1, 130, 1, 1),          # 390 jobs; more members, receivers and groups than a table lists
     (36, 10, 2, 64, 2, 1),           # exactly 320, 64 groups
     (54, 11, 1, 65, 2, 2),           # 325
     (30, 10, 1, 12, 5, 2),           # 11 members each, 132
     (54, 14, 1, 7, 1, 2),            # halves of polynomials
+    (60, 10, 1, 21, 1, 2),           # 63: rows of the table
+    (54, 10, 1, 13, 2, 2),           # 65
 ])
 def test_round_convert_equals_per_call(bits, log2n, L, parties, reach, C):
     N, LN, groups = 1 << log2n, L << log2n, ring(parties, reach)
