@@ -396,6 +396,8 @@ struct ArithS {
     // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
     D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
     D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
+    // minus a product
+    D2_DEV static elem neg(elem x, const Mod &m) { return 4 * m.q - x; }
     // x + v for a small signed v (|v| <= 32), as a forward input: q is added instead of mapping v into
     // [0, q) first (the forward range has room for it)
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + (m.q + (uint64_t)(int64_t)v); }
@@ -513,6 +515,7 @@ struct ArithB {
     D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
     D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul(y, w, m); }
+    D2_DEV static elem neg(elem x, const Mod &m) { return 2 * m.q - x; }           // minus a product
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
 
     // x, y in [0, 4q) -> [0, 4q)
@@ -641,6 +644,7 @@ struct ArithF {
     D2_DEV static elem from_small(int32_t v, const Mod &) { return (double)v; }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return u2d(v); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul((double)y, w, m); }
+    D2_DEV static elem neg(elem x, const Mod &) { return -x; }
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &) { return x + (double)v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
     // u * key + x, lazy (x: a forward output); a sum of that kind as the x of another one
@@ -797,6 +801,7 @@ struct Arith32 {
     D2_DEV static elem mul_key_add(elem u, const Key &k, elem x, const Mod &m) { return add(mul(u, k, m), x); }
     D2_DEV static elem renorm(elem x, const Mod &m) { return from_canon(canon_acc(x, m), m); }
     D2_DEV static elem mul_u32(uint32_t y, const Twid &w, const Mod &m) { return mul(y, w, m); }
+    D2_DEV static elem neg(elem x, const Mod &m) { return m.two_q - x; }           // minus a product
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + from_small(v, m); }
 
     // x, y in [0, 4q) -> [0, 4q)
@@ -1073,6 +1078,7 @@ struct ArithP {
     }
     D2_DEV static elem from_canon(uint64_t v, const Mod &) { return v; }
     D2_DEV static elem add(elem a, elem b) { return a + b; }
+    D2_DEV static elem neg(elem x, const Mod &m) { return m.k - x; }               // minus a product
     D2_DEV static elem add_small(elem x, int32_t v, const Mod &m) { return x + (m.q + (uint64_t)(int64_t)v); }
     static constexpr bool SUM_SMALL = true;
     typedef SmallPm Small;

@@ -976,7 +976,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int k = 0; k < E; ++k) mm[j][k] = opaque(m[j][k]);
-            ENG::forward_chained_encoded(mm, e, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
+            auto at = [&](int j, int k, uint32_t &m_jk, int32_t &e_jk) {
+                m_jk = mm[j][k];
+                e_jk = e[j][k];
+            };
+            ENG::forward_chained_encoded(at, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
         } else {
 #pragma unroll
             for (int k = 0; k < E; ++k) {
@@ -1601,8 +1605,9 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
     }
     __syncthreads();
     static_assert(ENG::N <= ENG::LDS_CHAIN_WORDS, "two words per coefficient");
-    // with a fused start the two coefficients of every sum, the errors as bytes
-    constexpr bool FUSED = ENG::FUSE > 0;
+    // with a fused start (for the shapes that k_encrypt starts its messages so) the two coefficients of every sum, the errors
+    // as bytes.  Fused and not: N = 8192, 2 limbs, 900 indices of 36 bits 217 / 173 us; N = 1024, 60 of 30 bits 13.7 / 12.6 us.
+    constexpr bool FUSED = ENG::FUSE > 0 && (ENG::LOGP > 0 || A::KIND >= 4);
     constexpr int MS = FUSED ? 2 : 1;
     uint32_t mv[MS][E], ev[MS][E / (FUSED ? 2 : 1)];
 #pragma unroll
@@ -1625,38 +1630,35 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
         const size_t off = (size_t)limb * ENG::N;
         const int tl = opaque(tid), el = ENG::eval_lane(tl, blk);
         const typename A::Factor none[E] = {};
-        uint64_t lm[E];                                     // Lambda M mod q, canonical
         elem x[E];
-        uint32_t mm[MS][E];
-        int32_t e[MS][E];
-        auto errors = [&](int which) {
-#pragma unroll
-            for (int j = 0; j < MS; ++j)
+        // coefficient and error `which` of a slot, unpacked where they are used
+        auto fetch = [&](int which) {
+            return [&, which](int j, int k, uint32_t &m, int32_t &e) {
+                m = opaque(mv[j][k]);
+                e = FUSED ? sbyte(opaque(ev[j][k / (FUSED ? 2 : 1)]), 2 * (k & 1) + which) : sbyte(opaque(ev[j][k]), which);
+            };
+        };
+        auto transform = [&](auto neg, auto at, int tid0) {
+            if constexpr (FUSED) {
+                ENG::template forward_chained_encoded<decltype(neg)::value>(at, x, lds, turn, tid0, blk, tb.fwd, lam,
+                                                                            A::tw(tb.lambda_i), md);
+            } else {
+                // the product again for the second transform: kept, its words cost 32 registers across the first (N = 2^14,
+                // 2 limbs, 250 indices, ArithS 167 -> 127 us, ArithB 196 -> 152 us)
 #pragma unroll
                 for (int k = 0; k < E; ++k) {
-                    mm[j][k] = opaque(mv[j][k]);
-                    e[j][k] = FUSED ? sbyte(opaque(ev[j][k / (FUSED ? 2 : 1)]), 2 * (k & 1) + which) : sbyte(opaque(ev[j][k]), which);
+                    uint32_t m;
+                    int32_t e;
+                    at(0, k, m, e);
+                    const elem v = A::mul_u32(m, lam, md);
+                    x[k] = A::add_small(decltype(neg)::value ? A::neg(v, md) : v, e, md);
                 }
+                ENG::forward_chained(x, lds, turn, tid0, 0, tb.fwd, md);
+            }
         };
-        errors(0);
-        if constexpr (FUSED) {
-            ENG::template forward_chained_encoded<true>(mm, e, x, lds, turn, tl, blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) lm[k] = A::canon_acc(A::mul_u32(mm[0][k], lam, md), md);
-#pragma unroll
-            for (int k = 0; k < E; ++k) x[k] = A::add(A::from_canon(lm[k] ? q - lm[k] : 0, md), A::from_small(e[0][k], md));
-            ENG::forward_chained(x, lds, turn, tl, 0, tb.fwd, md);
-        }
+        transform(std::true_type(), fetch(0), tl);
         mul_add_store<ENG, SRC_CANON>(out + off, sk + off, sk + LN + off, c1 + off, none, x, el, md);
-        errors(1);
-        if constexpr (FUSED) {
-            ENG::forward_chained_encoded(mm, e, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) x[k] = A::add(A::from_canon(lm[k], md), A::from_small(e[0][k], md));
-            ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
-        }
+        transform(std::false_type(), fetch(1), opaque(tl));
         // eta1 = Lambda M + e1 - s_k alpha
         mul_add_store<ENG, SRC_CANON, true>(out + LN + off, sk + off, sk + LN + off, alpha + off, none, x, el, md, q);
     }

@@ -435,12 +435,11 @@ struct Engine {
         }
     }
 
-    // The next forward transform of a chain, of lam m + e (NEG: e - lam m) with plaintext coefficients m and small e, both at
-    // encoded_pos(j, k, tid); lam_i = I lam.
-    template <bool NEG = false, class B = A>
-    D2_DEV static void forward_chained_encoded(const uint32_t (&m)[2][E], const int32_t (&e)[2][E], elem (&x)[E], uint64_t *lds,
-                                               uint32_t &turn, int tid, uint32_t blk, const Tw *tw, const Twid &lam,
-                                               const Twid &lam_i, const Mod &md)
+    // The next forward transform of a chain, of lam m + e (NEG: e - lam m) with plaintext coefficients m and small e;
+    // at(j, k, m, e) fetches the ones at encoded_pos(j, k, tid); lam_i = I lam.
+    template <bool NEG = false, class B = A, class AT>
+    D2_DEV static void forward_chained_encoded(AT at, elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid, uint32_t blk,
+                                               const Tw *tw, const Twid &lam, const Twid &lam_i, const Mod &md)
     {
         static_assert(FUSE > 0, "shape without a fused start");
         constexpr int START = LOGP > 0 ? 0 : 1;
@@ -451,8 +450,10 @@ struct Engine {
         load_tw<START, false, true>(w, tid, blk, tw);
 #pragma unroll
         for (int k = 0; k < E; ++k) {
-            const uint32_t mk[2] = {m[0][k], m[1][k]};
-            const int32_t ek[2] = {e[0][k], e[1][k]};
+            uint32_t mk[2];
+            int32_t ek[2];
+            at(0, k, mk[0], ek[0]);
+            at(1, k, mk[1], ek[1]);
             x[k] = B::sum_encoded(mk, ek, lam, lam_i, NEG, NEG != neg, c, md);
         }
         fwd_from<START, PINGPONG && (START == 1 || !WAVE_CHAIN), false, START>(x, w, next_buffer(lds, turn), tid, blk, tw, md);

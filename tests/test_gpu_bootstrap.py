@@ -6,10 +6,12 @@ import pytest
 import torch
 
 from paper_2207_04604_amd import binding as B
-from paper_2207_04604_amd.synth import CONFIGS
+from oracle import oracle as O
+from paper_2207_04604_amd.synth import CONFIGS, toy_config
 
 from gpu_util import DEV, Keys, dzeros, make_pair, to_dev, to_eval, to_host
 from test_gpu_parity import fixed_point_sum
+from test_pm_policies import primes_away_from_powers_of_two
 
 pytestmark = pytest.mark.gpu
 
@@ -80,8 +82,6 @@ def test_bootstrap_C2_one_group_every_coefficient():
 
 
 def test_bootstrap_wide_primes_ragged_tail_and_extreme_ids():
-    from oracle import oracle as O
-    from paper_2207_04604_amd.synth import toy_config
     for bits, log2n, L in ((54, 11, 2), (60, 10, 2), (36, 13, 2), (54, 14, 2), (60, 14, 1), (44, 14, 1)):
         cfg = toy_config(log2n, O.find_primes(bits, log2n, L), 65537, 3, (1 << log2n) + 77, frac_bits=6)
         o, ctx, perm = make_pair(cfg)
@@ -91,6 +91,21 @@ def test_bootstrap_wide_primes_ragged_tail_and_extreme_ids():
         keys = Keys(o, ctx, perm, members, check=False)
         refresh_and_compare(cfg, o, ctx, perm, keys, members, 65535, grads, ct_base=2**32 - 4)
         ctx.close()
+
+
+# the shapes that the primes above, all just below a power of two, do not reach: quotients (54, 60 bits) with 8 and with 16
+# coefficients per thread, 32-bit words with 16, doubles and 32-bit words where the scheme's other transforms start fused
+@pytest.mark.parametrize("bits,log2n,L", [(54, 10, 1), (60, 10, 2), (54, 11, 2), (60, 11, 1), (60, 12, 1), (54, 13, 1), (54, 14, 1),
+                                          (60, 14, 1), (30, 14, 2), (30, 13, 2), (36, 10, 2)])
+def test_bootstrap_other_shapes(bits, log2n, L):
+    q = primes_away_from_powers_of_two(bits, log2n, L) if bits > 44 else O.find_primes(bits, log2n, L)
+    cfg = toy_config(log2n, q, 12289 if log2n <= 11 else 65537, 3, (1 << log2n) + 77, frac_bits=6)
+    o, ctx, perm = make_pair(cfg)
+    rng = np.random.default_rng(bits + log2n)
+    members = [0, 40000, 65535]
+    grads = {k: rng.normal(0, 3.0, cfg.n_values).astype(np.float32) for k in members}
+    refresh_and_compare(cfg, o, ctx, perm, Keys(o, ctx, perm, members, check=False), members, 65535, grads, ct_base=2**32 - 4)
+    ctx.close()
 
 
 def test_bootstrap_argument_checks():
