@@ -886,8 +886,11 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     uint32_t *lds32 = (uint32_t *)lds;
     constexpr int E = ENG::E;
     // The message's first stage as a sum (forward_chained_encoded) wants two coefficients from far apart: read from memory,
-    // not brought through LDS after an encoding in place (25.9 instead of 25.7 us for the smallest round).
-    constexpr bool SUMMED = ENG::FUSE > 0 && FROM != FROM_VECTOR;
+    // not brought through LDS after an encoding in place (25.9 instead of 25.7 us for the smallest round).  On doubles and
+    // 32-bit words it takes two products and corrections where the transform takes one, and saves an exchange that costs
+    // less (summed and not: N = 1024, 36 bits, 2 limbs, 60 indices 12.1 / 10.6 us; N = 8192, 900 indices 148 / 142 us,
+    // 30 bits 152 / 145 us): for halves of a polynomial only, which have no other way.
+    constexpr bool SUMMED = ENG::FUSE > 0 && FROM != FROM_VECTOR && (ENG::LOGP > 0 || A::KIND >= 4);
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
     const RoundJob job = round_job(jobs, blockIdx.y);
