@@ -72,7 +72,8 @@ D2_DEV typename A::Twid load_tw_uniform(const Tw *tw, uint32_t i)
     else return A::load_v(tw, i);
 }
 
-template <class A_, int LOGN_, int ELOG_, int LOGB_ = LOGN_>
+// LAST_: the pass with fewer stages is the last one (see PARTIAL).
+template <class A_, int LOGN_, int ELOG_, int LOGB_ = LOGN_, bool LAST_ = false>
 struct Engine {
     typedef A_ A;
     typedef typename A::elem elem;
@@ -117,10 +118,23 @@ struct Engine {
     // uniform over the wave, the per-lane ones of the last six stages come to 14 instead of 18 to 20, and on small
     // inputs it takes no exchange at all (FUSE below).  With 16 it is the last but one: 3 + 15 per-lane twiddles
     // instead of 15 + 12 (N = 2^14, 8 limbs, 8 nodes: round 17.34 -> 16.88 ms).
-    static constexpr int PARTIAL = LOGB % ELOG == 0 ? -1 : ELOG > 3 ? NPASS - 2 : 0;
+    static constexpr bool LAST = LAST_;
+    static constexpr int PARTIAL = LOGB % ELOG == 0 ? -1 : LAST ? NPASS - 1 : ELOG > 3 ? NPASS - 2 : 0;
     static constexpr int stages(int p) { return p == PARTIAL ? LOGB % ELOG : ELOG; }
     static constexpr int sbit(int p) { return p < PARTIAL ? LOGB - ELOG * (p + 1) : ELOG * (NPASS - 1 - p); }
-    static constexpr int wbase(int p) { return sbit(p) + stages(p) - ELOG; }
+    static constexpr int wbase(int p) { return sbit(p) + stages(p) > ELOG ? sbit(p) + stages(p) - ELOG : 0; }
+    // Transforms on their own (not the chains of small inputs, which start fused or share their twiddles) for which the
+    // shorter pass is better last; a transform starts and ends with the same owners either way.  Measured, shorter pass
+    // first and last, N = 8192 in polynomials per launch:
+    //   inverse  32-bit 16.1 / 15.5 us (512), 51.2 / 50.5 (2048);  ArithS 110.3 / 107.7, ArithB 114.5 / 112.1 (2048);
+    //            doubles 60.4 / 62.1: first;  the encoding of 900 vectors 32.2 / 30.6 us
+    //   forward  doubles 7.1 / 6.8 (2), 15.5 / 14.9 (512);  ArithS 9.9 / 9.6 (2), ArithB 11.8 / 11.6 (2), 51.7 / 50.6
+    //            (1024);  32-bit 50.9 / 51.4 (2048): first
+    // and of N = 2^14 (last but one and last) the encoding, a 32-bit inverse: 18.9 / 18.6 us (60).
+    static constexpr bool INVERSE_LAST =
+        !LAST && LOGP == 0 && LOGB >= 13 && LOGB % ELOG != 0 && (A::KIND == 3 || (LOGB == 13 && (A::KIND == 1 || A::KIND == 2)));
+    static constexpr bool FORWARD_LAST = !LAST && LOGP == 0 && LOGB == 13 && ELOG == 3 && A::KIND <= 2;
+    typedef Engine<A_, LOGN_, ELOG_, LOGB_, true> PartialLast;
 
     // FUSE > 0: a first pass of one stage, and the stage in front of it that couples two blocks where a workgroup takes
     // half of the polynomial (LOGP = 1), are on small inputs one sum per coefficient, of SS = 2^FUSE samples with
@@ -401,9 +415,13 @@ struct Engine {
     // is of that kind and has its barrier; later ones stay inside the wave.
     D2_DEV static void forward(elem (&x)[E], uint64_t *lds, int tid, uint32_t blk, const Tw *tw, const Mod &md)
     {
-        Twid w[E];
-        load_tw<0, false, true>(w, tid, blk, tw);
-        fwd_from<0>(x, w, lds, tid, blk, tw, md);
+        if constexpr (FORWARD_LAST) {
+            PartialLast::forward(x, lds, tid, blk, tw, md);
+        } else {
+            Twid w[E];
+            load_tw<0, false, true>(w, tid, blk, tw);
+            fwd_from<0>(x, w, lds, tid, blk, tw, md);
+        }
     }
 
     // The next forward transform of a chain (see PINGPONG); `lds` holds LDS_CHAIN_WORDS words.
@@ -560,12 +578,16 @@ struct Engine {
     D2_DEV static void inverse(elem (&x)[E], uint64_t *lds, int tid, uint32_t blk, const Tw *tw, const Mod &md,
                                const Twid &ninv, const Twid &wn)
     {
-        Twid w[E];
-        load_tw<NPASS - 1, FOLD, false>(w, tid, blk, tw);
-        if constexpr (NPASS > 1) {
-            if (intra_wave<NPASS - 1, NPASS - 2>()) __syncthreads();
+        if constexpr (INVERSE_LAST) {
+            PartialLast::template inverse<FOLD>(x, lds, tid, blk, tw, md, ninv, wn);
+        } else {
+            Twid w[E];
+            load_tw<NPASS - 1, FOLD, false>(w, tid, blk, tw);
+            if constexpr (NPASS > 1) {
+                if (intra_wave<NPASS - 1, NPASS - 2>()) __syncthreads();
+            }
+            inv_from<NPASS - 1, FOLD>(x, w, lds, tid, blk, tw, md, ninv, wn);
         }
-        inv_from<NPASS - 1, FOLD>(x, w, lds, tid, blk, tw, md, ninv, wn);
     }
 };
 
