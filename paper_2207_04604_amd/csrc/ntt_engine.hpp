@@ -425,13 +425,15 @@ struct Engine {
     }
 
     // The next forward transform of a chain (see PINGPONG); `lds` holds LDS_CHAIN_WORDS words.
-    // With 16 coefficients per thread the scalar twiddles of two passes fill the scalar registers: transforms that
-    // follow one another fetch them again (the constant cache has them) instead of keeping them in lanes
-    // of vector registers (290 of 6,290 vector instructions of k_encrypt for N = 2^14 moved them there and back).
+    // With 16 coefficients per thread the scalar twiddles of two passes fill the scalar registers where one takes four of
+    // them: transforms that follow one another fetch them again (the constant cache has them) instead of keeping them in
+    // lanes of vector registers (290 of 6,290 vector instructions of k_encrypt for N = 2^14 moved them there and back).
+    // Twiddles of two registers fit: fetched again and kept, 30-bit primes, 2 limbs, 500 indices 204 / 189 us.
+    static constexpr bool FRESH_TABLE = E > 8 && sizeof(Twid) > 8;
     D2_DEV static void forward_chained(elem (&x)[E], uint64_t *lds, uint32_t &turn, int tid, uint32_t blk, const Tw *tw,
                                        const Mod &md)
     {
-        if constexpr (E > 8) tw = fresh_table(tw);
+        if constexpr (FRESH_TABLE) tw = fresh_table(tw);
         Twid w[E];
         load_tw<0, false, true>(w, tid, blk, tw);
         fwd_from<0, PINGPONG && !WAVE_CHAIN>(x, w, next_buffer(lds, turn), tid, blk, tw, md);
@@ -485,7 +487,7 @@ struct Engine {
                                              uint32_t blk, const Tw *tw, const Mod &md)
     {
         static_assert(ahead<0>() && (LOGP == 0 || FUSE > 0), "shape without a separable first stage");
-        if constexpr (E > 8) tw = fresh_table(tw);
+        if constexpr (FRESH_TABLE) tw = fresh_table(tw);
         Twid w[E];
         if constexpr (FUSE > 0) {
             typename A::Small c[SS];
