@@ -8,8 +8,42 @@ namespace d2 {
 // where the policy can take the stage that couples the halves as a sum of samples: with 16 coefficients per thread one
 // workgroup filled a CU without room for a second exchange buffer (two barriers per transform, NTT(mu) parked in memory)
 // and kept the vector ALU busy 55 % of the time.  Measured, 8 nodes, 8 limbs, 684 indices: 16.83 -> 15.40 ms.
+//
+// Either half draws all samples of its polynomial, which costs most where a kernel does little else, and n polynomials
+// take turns(2n) turns of half workgroups on the chip instead of turns(n) of whole ones.  Measured, us for whole / halves
+// (54 bits unless stated; one kernel):
+//   n = 60 (one turn of either)  encrypt 52 / 29, share 19.5 / 14.1, conversion 53 / 32, refresh 56 / 45 with one limb;
+//                                172 / 86, 64 / 39, 181 / 96, 147 / 100 with four
+//   n = 300 (two and three)      encrypt 113 / 88, 397 / 256;  share 42.4 / 41.4, 156 / 114;  refresh 116 / 133, 338 / 325
+//   n = 160 (one and two)        share 20.3 / 26.7, 65 / 75;  refresh 57 / 88, 150 / 196;  encrypt 55 / 59, 176 / 167
+//   n = 900 (four and eight)     share 88 / 106, 328 / 344;  refresh 237 / 349, 749 / 875;  encrypt 238 / 233, 811 / 702
+//   36 bits, eight limbs         share 148 / 133 (n = 160), 276 / 225 (300);  refresh 338 / 412 (160), 684 / 850 (400)
+//   44 bits, one limb            encrypt 52 / 58 (160), 212 / 223 (900), 103 / 86 (300);  conversion 55 / 60, 234 / 235
 template <class ENG, class HALF = ENG>
 struct Launch {
+    static constexpr bool HALVES = HALF::LOGP > 0;
+    static uint64_t turns(uint64_t workgroups) { return (workgroups + 255) / 256; }
+    // the turns of halves take less time than those of whole polynomials, a turn of halves being two thirds as long
+    static bool turns_pay(uint64_t n) { return 2 * turns(2 * n) <= 3 * turns(n); }
+    static bool encrypt_in_halves(const d2mhe_ctx *ctx, uint64_t n) { return ENG::A::KIND != 0 || ctx->L > 1 || turns_pay(n); }
+    static bool share_in_halves(const d2mhe_ctx *ctx, uint64_t n) { return ctx->L >= 8 || turns_pay(n); }
+    static bool refresh_in_halves(uint64_t n) { return turns(2 * n) == 1; }
+    template <class E>
+    struct Shape {
+        typedef E type;
+    };
+    // launch(Shape<engine>) with the one to take
+    template <bool BOTH, class F>
+    static void choose(bool half, F launch)
+    {
+        if constexpr (BOTH) {
+            if (half) launch(Shape<HALF>());
+            else launch(Shape<ENG>());
+        } else {
+            launch(Shape<HALF>());
+        }
+    }
+
     static d2mhe_status ntt(d2mhe_ctx *ctx, uint64_t *polys, uint32_t B, bool forward, hipStream_t st)
     {
         const uint32_t L = ctx->L, polys_n = B * L;
@@ -82,15 +116,20 @@ struct Launch {
     static d2mhe_status encrypt(d2mhe_ctx *ctx, int from, const RoundJobs &jobs, uint32_t njobs,
                                 uint32_t ct_base, uint64_t n_values, uint32_t C, hipStream_t st)
     {
-        const dim3 grid(C << HALF::LOGP, njobs), block(HALF::T);
         if (from == FROM_VECTOR) {
-            if constexpr (HALF::LOGP > 0) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
+            if constexpr (HALVES) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
             else
-                hipLaunchKernelGGL((k_encrypt<HALF, FROM_VECTOR>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
-        } else if (from == FROM_WORDS32) {
-            hipLaunchKernelGGL((k_encrypt<HALF, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+                hipLaunchKernelGGL((k_encrypt<ENG, FROM_VECTOR>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, n_values,
+                                   ctx->d_tabs, ctx->rc);
         } else {
-            hipLaunchKernelGGL((k_encrypt<HALF, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+            choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
+                typedef typename decltype(shape)::type E;
+                const dim3 grid(C << E::LOGP, njobs), block(E::T);
+                if (from == FROM_WORDS32)
+                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+                else
+                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+            });
         }
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
@@ -99,7 +138,10 @@ struct Launch {
     static d2mhe_status share(d2mhe_ctx *ctx, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
                               hipStream_t st)
     {
-        hipLaunchKernelGGL(k_share<HALF>, dim3(C << HALF::LOGP, njobs), dim3(HALF::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+        choose<HALVES>(share_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
+            typedef typename decltype(shape)::type E;
+            hipLaunchKernelGGL(k_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+        });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
@@ -147,8 +189,10 @@ struct Launch {
     static d2mhe_status convert_share(d2mhe_ctx *ctx, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base,
                                       uint32_t C, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_convert_share<HALF>, dim3(C << HALF::LOGP, njobs), dim3(HALF::T), 0, st, jobs, ct_base, ctx->d_tabs,
-                           ctx->rc);
+        choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
+            typedef typename decltype(shape)::type E;
+            hipLaunchKernelGGL(k_convert_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+        });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
@@ -183,8 +227,10 @@ struct Launch {
     static d2mhe_status bootstrap_share(d2mhe_ctx *ctx, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base,
                                         uint32_t C, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_bootstrap_share<HALF>, dim3(C << HALF::LOGP, njobs), dim3(HALF::T), 0, st, jobs, ct_base, ctx->d_tabs,
-                           ctx->rc);
+        choose<HALVES>(refresh_in_halves((uint64_t)C * njobs), [&](auto shape) {
+            typedef typename decltype(shape)::type E;
+            hipLaunchKernelGGL(k_bootstrap_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+        });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
@@ -201,7 +247,7 @@ struct Launch {
     // full set (ring degrees a single workgroup can hold)
     static EngineOps full()
     {
-        return EngineOps{ENG::ELOG, ENG::LOGB, HALF::LOGP > 0, &ntt, &keygen, &encode, &decode, &encode_parties, &encrypt, &share,
+        return EngineOps{ENG::ELOG, ENG::LOGB, HALVES, &ntt, &keygen, &encode, &decode, &encode_parties, &encrypt, &share,
                          &combine, &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &convert_combine,
                          &convert_combine_decode, &bootstrap_alpha, &bootstrap_share, &bootstrap_combine};
     }

@@ -98,6 +98,7 @@ def test_round_equals_per_call(bits, log2n, L, groups, C, packing, split):
     (54, 11, 1, 65, 2, 2),           # 325
     (30, 10, 1, 12, 5, 2),           # 11 members each, 132
     (54, 14, 1, 7, 1, 2),            # halves of polynomials
+    (44, 14, 1, 7, 1, 7),            # 147 polynomials of one limb: whole
     (60, 10, 1, 21, 1, 2),           # 63: rows of the table
     (54, 10, 1, 13, 2, 2),           # 65
 ])
@@ -131,5 +132,35 @@ def test_round_convert_equals_per_call(bits, log2n, L, parties, reach, C):
         for i, k in enumerate(members):
             ctx.convert_share(sk[k], rpk[g], agg[g], C, k, g, ids[g], 7, share)
             assert torch.equal(share, shares[g * K + i]), f"share of party {k} in group {g}"
+    torch.cuda.synchronize()
+    ctx.close()
+
+
+# N = 2^14 where a launch may take whole polynomials or halves of them: 130 (two turns of the chip in halves, one in whole
+# polynomials) against 65 and 65 (halves)
+@pytest.mark.parametrize("bits,L", [(44, 1), (36, 2), (54, 1), (60, 1)])
+def test_whole_polynomials_equal_halves(bits, L):
+    log2n, C, LN = 14, 130, L << 14
+    ctx = make_ctx(log2n, O.find_primes(bits, log2n, L), 65537, f=3, max_group=2, seed=21)
+    sk, pk0, pk, rsk, rpk = (dzeros(n * LN) for n in (2, 1, 4, 2, 4))
+    ctx.keygen_share(1, sk, pk0)
+    ctx.aggregate_pk([pk0], pk)
+    ctx.receiver_keygen(2, rsk, rpk)
+    pt = to_dev(np.random.default_rng(bits).integers(0, 65537, C << log2n, dtype=np.uint64))
+    ct, alpha = dzeros(C * 2 * LN), dzeros(C * LN)
+    ctx.encrypt(pk, pt, C, 1, 5, 3, ct)
+    ctx.bootstrap_alpha(5, 3, C, alpha)
+    calls = {
+        "ciphertexts": (2, lambda c, n, out: ctx.encrypt(pk, pt[c << log2n:], n, 1, 5, 3 + c, out)),
+        "shares": (1, lambda c, n, out: ctx.partial_decrypt(sk, ct[c * 2 * LN:], n, 1, 5, 3 + c, out)),
+        "conversion shares": (2, lambda c, n, out: ctx.convert_share(sk, rpk, ct[c * 2 * LN:], n, 1, 2, 5, 3 + c, out)),
+        "refresh shares": (2, lambda c, n, out: ctx.bootstrap_share(sk, ct[c * 2 * LN:], alpha[c * LN:], n, 1, 5, 3 + c, out)),
+    }
+    for name, (polys, call) in calls.items():
+        whole, parts, half = dzeros(C * polys * LN), dzeros(C * polys * LN), C // 2
+        call(0, C, whole)
+        call(0, half, parts)
+        call(half, C - half, parts[half * polys * LN:])
+        assert torch.equal(whole, parts), name
     torch.cuda.synchronize()
     ctx.close()
