@@ -804,16 +804,16 @@ uint32_t fill_round_jobs(RoundJobs &jobs, const d2mhe_round_desc *d, const Place
     return n;
 }
 
-// The table of a k_finish launch: groups g0, g0 + 1, ... as far as it holds them; returns their number (at least
-// one).  slot: scratch of one zero per party (1 + its place in this table).
-uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Places &who, uint32_t g0,
+// The table of a k_finish launch: groups g0, g0 + 1, ..., at most `limit` of them and as far as it holds them; returns
+// their number (at least one).  slot: scratch of one zero per party (1 + its place in this table).
+uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Places &who, uint32_t g0, uint32_t limit,
                           std::vector<uint16_t> &slot)
 {
     static_assert(MAX_GROUP <= FIN_PARTIES && MAX_GROUP <= FIN_MEMBERS, "a group must fit one launch");
     uint32_t n = 0, members = 0, parties = 0;
     std::fill(slot.begin(), slot.end(), (uint16_t)0);
     jobs.first[0] = 0;
-    for (; g0 + n < d->num_groups && n < (uint32_t)FIN_GROUPS; ++n) {
+    for (; g0 + n < d->num_groups && n < (uint32_t)FIN_GROUPS && n < limit; ++n) {
         const uint32_t g = g0 + n, first = d->group_offsets[g], K = d->group_offsets[g + 1] - first;
         uint32_t fresh = 0;
         for (uint32_t i = 0; i < K; ++i) fresh += slot[who.place[first + i]] == 0;
@@ -834,6 +834,41 @@ uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Pla
         jobs.group[n] = (uint16_t)(d->group_ids ? d->group_ids[g] : g);
     }
     return n;
+}
+
+// Whether a k_finish launch over `groups` groups of `members` members in all is faster than the separate launches.  One
+// of its workgroups walks through the K + 1 transforms of every limb of its ciphertext index, so the launch has to fill
+// the chip and to leave no compute unit idle at its end: with W workgroups on 256 units, W / 256 rounded up has to
+// be more than 13/16 used.  The fewer threads a workgroup has, the more of them a unit needs for itself; with
+// four members or fewer the launches saved weigh more.
+// Measured (36, 54 and 60 bits, two limbs, K = 2 to 32), three launches' time over one's:
+//   N = 8192   W = 256 1.04-1.11,  290 0.90-1.02,  350 0.95-1.04,  420 0.99-1.06,  512 1.05-1.12,  576 (3/4) 0.98-1.06,
+//              640 (5/6) 1.01-1.07,  768 1.06-1.12
+//   N = 4096   256 0.99-1.12,  320 0.91-1.07,  384 0.98-1.09,  448 1.00-1.10,  512 1.04-1.11,  576 0.94-1.06,  640 1.02-1.07
+//   N = 2048   256 0.84-0.99 (K = 2, 4: 1.00-1.12),  384 0.90-1.08,  448 0.97-1.09,  512 1.00-1.11,  576 0.94-1.10,  832
+//              (13/16) 0.98-1.09,  896 1.02-1.10
+//   N = 1024   1024 0.91-1.02 (K = 2, 4: 1.00-1.15),  1280 0.98-1.04,  1536 0.97-1.03,  1792 1.04-1.06
+//   N = 2^14   (halves: twice the workgroups; sums and shares only, against a sum and shares in halves or whole, see
+//              engine_inst.hpp) eight limbs 256 1.02-1.06, 512 1.02-1.08, 896 1.02-1.05;  four 512 0.96-1.05, 768 1.00-1.05,
+//              896 (7/8) 0.97-1.04, 1024 0.99-1.07, 1280 1.04-1.05;  three 512 0.98-1.03, 896 0.96-1.02, 1024 1.01-1.05, 1536
+//              1.02-1.05;  one and two 512 0.96-1.02, 1024 0.95-1.01, 1800 0.96-1.01
+bool finish_pays(const d2mhe_ctx *ctx, uint32_t groups, uint32_t members, uint32_t C)
+{
+    const bool few = members <= 4 * groups;
+    uint64_t W = (uint64_t)groups * C, least, sixteenths = 13;
+    switch (ctx->log2n) {
+    case 14:
+        if (ctx->L < 3) return false;
+        W *= 2;
+        least = ctx->L >= 8 ? 256 : ctx->L >= 4 ? 512 : 1024;
+        sixteenths = 14;
+        break;
+    case 13:
+    case 12: least = 256; break;
+    case 11: least = few ? 256 : 512; break;
+    default: least = few ? 1024 : 1792;
+    }
+    return W >= least && 16 * W > sixteenths * 256 * ((W + 255) / 256);
 }
 
 // One exchange round; conv == nullptr: collective decryption of every aggregate, otherwise key
@@ -947,32 +982,32 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     }
     if (ev && ev[1]) D2_HIP(ctx, hipEventRecord(ev[1], st));
 
-    // Phases 2 to 4 in one launch, or in as many as its table needs, unless the caller wants an event between them.
-    // One workgroup then walks through the K + 1 transforms of every limb of its ciphertext index, which pays where the
-    // launch fills the chip.  Measured over groups of 3 to 15 members, one launch against three: N = 8192 with 128 / 256 /
-    // 1024 workgroups 0.95-1.01 / 1.09-1.15 / 1.10-1.23 times as fast, N = 4096 0.87-0.95 / 1.05-1.09 / 1.04-1.07, N = 2048
-    // 0.82-0.93 / 0.99-1.05 / 1.05-1.08, N = 1024 with 512 / 1024 workgroups 0.90-0.99 / 1.02-1.10.
-    // A table that does not hold all groups means one launch after the other: each then has to be twice as large.
+    // Phases 2 to 4 in one launch, unless the caller wants an event between them: see finish_pays.  Groups that its table
+    // does not hold go in several launches of equal size, each of which has to pay by itself.
     const bool split = ev && (ev[2] || ev[3]);
-    const uint64_t full = ctx->N >= 2048 ? 256 : 1024;
     bool shared = false;            // sums and shares are done
-    if (!conv && ops->finish && !split && (uint64_t)G * C >= full) {
+    if (!conv && ops->finish && !split && finish_pays(ctx, G, J, C)) {
         FinishJobs jobs;
-        uint32_t n = fill_finish_jobs(jobs, d, who, 0, slot), launches = 1;
-        for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, who, g0, slot);
-        if (launches == 1 || (uint64_t)G * C >= 2 * full * launches) {
-            for (uint32_t g0 = 0; g0 < G; g0 += n) {
-                if (launches > 1) n = fill_finish_jobs(jobs, d, who, g0, slot);
-                const size_t j0 = d->group_offsets[g0];
-                d2mhe_status s = ops->finish(ctx, jobs, n, cts + j0 * ct_words, agg + (size_t)g0 * ct_words,
-                                             shares + j0 * sh_words, d->ct_base, C, d->n_values, st);
-                if (s != D2MHE_OK) return s;
+        uint32_t n = fill_finish_jobs(jobs, d, who, 0, G, slot), launches = 1, limit = G;
+        shared = true;
+        if (n < G) {
+            for (uint32_t g0 = n; g0 < G; ++launches) g0 += fill_finish_jobs(jobs, d, who, g0, G, slot);
+            limit = (G + launches - 1) / launches;
+            for (uint32_t g0 = 0; shared && g0 < G; g0 += n) {
+                n = fill_finish_jobs(jobs, d, who, g0, limit, slot);
+                shared = finish_pays(ctx, n, d->group_offsets[g0 + n] - d->group_offsets[g0], C);
             }
-            shared = true;
-            if (!ops->halves) {
-                if (ev && ev[4]) D2_HIP(ctx, hipEventRecord(ev[4], st));
-                return D2MHE_OK;
-            }
+        }
+        for (uint32_t g0 = 0; shared && g0 < G; g0 += n) {
+            if (limit < G) n = fill_finish_jobs(jobs, d, who, g0, limit, slot);
+            const size_t j0 = d->group_offsets[g0];
+            d2mhe_status s = ops->finish(ctx, jobs, n, cts + j0 * ct_words, agg + (size_t)g0 * ct_words,
+                                         shares + j0 * sh_words, d->ct_base, C, d->n_values, st);
+            if (s != D2MHE_OK) return s;
+        }
+        if (shared && !ops->halves) {
+            if (ev && ev[4]) D2_HIP(ctx, hipEventRecord(ev[4], st));
+            return D2MHE_OK;
         }
     }
 

@@ -1,6 +1,9 @@
-"""The launch that sums, makes the shares, combines and decodes (taken by d2mhe_round where it fills the chip and no
-event between those phases is asked for) against the separate launches, which the other tests hold to the oracle:
-every word of the scratch and every decoded value."""
+"""The launch that sums, makes the shares, combines and decodes (taken by d2mhe_round where it leaves no part of the
+chip idle and no event between those phases is asked for) against the separate launches, which the other tests hold to
+the oracle: every word of the scratch and every decoded value; and which of the two a round takes, from the nodes of
+the graph that a capture of it makes."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -10,31 +13,67 @@ pytestmark = pytest.mark.gpu
 from oracle import oracle as O
 
 from gpu_util import DEV, dzeros, make_ctx, to_dev
+from test_pm_policies import primes_away_from_powers_of_two
 
 
 def ring(parties, reach):
     return [sorted((i + d) % parties for d in range(-reach, reach + 1)) for i in range(parties)]
 
 
-# (prime bits, log2 N, limbs, groups, ciphertexts, packing): groups of one member, and around the 32 terms after which
-# a lazy sum is reduced; more parties, more members and more groups than one launch's table holds (128, 1400, 64); the
-# chip exactly filled (256 workgroups, 1024 for N = 1024) on every kind of arithmetic
-@pytest.mark.parametrize("bits,log2n,L,groups,C,packing", [
-    (54, 11, 2, [list(range(k)) for k in (1, 2, 32, 33, 64)], 52, 0),
-    (44, 11, 2, [list(range(k)) for k in (31, 33, 64)], 86, 0),
-    (60, 11, 1, [list(range(k)) for k in (1, 33, 64)], 86, 0),
-    (54, 11, 1, ring(200, 4), 12, 1),
-    (36, 11, 1, ring(100, 15), 16, 0),
-    (30, 10, 2, ring(32, 1), 32, 0),
-    (54, 12, 3, ring(16, 2), 16, 0),
-    (36, 13, 2, ring(8, 1), 32, 0),
-    (54, 14, 2, ring(8, 1), 32, 0),            # halves of polynomials: sum and shares, then the combine
-    (44, 14, 1, [list(range(k)) for k in (1, 2, 5)], 86, 0),
-    (60, 14, 2, ring(9, 2), 29, 1),
+def sizes(*ks):
+    return [list(range(k)) for k in ks]
+
+
+def launches(call):
+    """Nodes of the graph that `call` makes under capture: its kernel launches."""
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            call(side.cuda_stream)
+    n = ctypes.c_size_t()
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# (prime bits, a: far from a power of two; log2 N, limbs, groups, ciphertexts, packing, taken): every kind of arithmetic;
+# groups of one member, and around the 32 terms after which a lazy sum is reduced; more parties, more members and more
+# groups than one launch's table holds (128, 1400, 64); the chip exactly filled, and the edges of the rule
+@pytest.mark.parametrize("bits,log2n,L,groups,C,packing,taken", [
+    ("54", 11, 2, sizes(1, 32, 33, 64), 128, 0, True),
+    ("54a", 11, 2, sizes(1, 32, 33, 64), 128, 0, True),
+    ("60a", 11, 1, sizes(1, 32, 33, 64), 128, 0, True),
+    ("44", 11, 2, sizes(31, 33, 64), 171, 0, False),       # 513 workgroups: a third turn of the chip for one of them
+    ("44", 11, 2, sizes(31, 33, 64), 209, 0, True),        # 627 of 768
+    ("60", 11, 1, sizes(1, 33, 64, 2), 128, 0, True),
+    ("54", 11, 1, ring(200, 4), 13, 1, True),
+    ("54", 11, 1, ring(200, 4), 12, 1, False),             # four launches of 50 groups: 600 of 768 workgroups each
+    ("36", 11, 1, ring(100, 15), 20, 0, True),
+    ("36", 11, 1, ring(32, 1), 8, 0, True),                # three members each: 256 are enough
+    ("36", 11, 1, ring(32, 2), 8, 0, False),
+    ("30", 10, 2, ring(32, 1), 32, 0, True),
+    ("30", 10, 1, ring(32, 2), 32, 0, False),
+    ("54a", 10, 2, ring(32, 1), 32, 0, True),
+    ("60a", 10, 1, ring(32, 2), 56, 0, True),
+    ("54", 12, 3, ring(16, 2), 16, 0, True),
+    ("54", 12, 2, ring(16, 2), 20, 0, False),              # 320 of 512
+    ("60a", 12, 1, sizes(1, 2, 33, 64), 64, 0, True),
+    ("54a", 12, 2, ring(16, 2), 16, 0, True),
+    ("36", 13, 2, ring(8, 1), 32, 0, True),
+    ("54a", 13, 2, ring(8, 1), 32, 0, True),
+    ("60a", 13, 1, ring(8, 1), 32, 1, True),
+    ("54", 14, 4, ring(8, 1), 32, 0, True),                # halves of polynomials: sum and shares, then the combine
+    ("54", 14, 2, ring(8, 1), 64, 0, False),
+    ("44", 14, 3, sizes(1, 2, 5), 192, 0, True),
+    ("60", 14, 8, ring(5, 1), 51, 1, True),
+    ("54a", 14, 3, ring(8, 1), 64, 0, False),              # whole polynomials: no such kernel
 ])
-def test_one_launch_equals_three(bits, log2n, L, groups, C, packing):
+def test_one_launch_equals_three(bits, log2n, L, groups, C, packing, taken):
+    find = primes_away_from_powers_of_two if bits.endswith("a") else O.find_primes
+    bits = int(bits.rstrip("a"))
     N, K = 1 << log2n, max(len(g) for g in groups)
-    q, t = O.find_primes(bits, log2n, L), 12289 if log2n <= 11 else 65537
+    q, t = find(bits, log2n, L), 12289 if log2n <= 11 else 65537
     P, J, G = 1 + max(max(g) for g in groups), sum(len(g) for g in groups), len(groups)
     n = C * N - 13
     ctx = make_ctx(log2n, q, t, f=3, max_group=K, seed=11)
@@ -65,4 +104,7 @@ def test_one_launch_equals_three(bits, log2n, L, groups, C, packing):
     assert torch.equal(scratch, want)
     for g, (a, b) in enumerate(zip(outs, sums)):
         assert torch.equal(a, b), f"group {g}"
+    split = launches(lambda stream: ctx.round(desc, scratch, nbytes, [e.cuda_event for e in events], stream))
+    fused = launches(lambda stream: ctx.round(desc, scratch, nbytes, None, stream))
+    assert fused < split if taken else fused == split, (fused, split)
     ctx.close()
