@@ -954,11 +954,12 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     // vector many times: its plaintexts are then made first, in the space the shares take later, and read from there.
     // Measured, encoded per group and ahead: 32 parties in 7 groups each, N = 8192, 4 limbs 20.2 / 19.1 ms; 16 in 5, N =
     // 4096, 3 limbs 0.391 / 0.375 ms.  Below two groups per party, or where the launches do not fill the chip, the
-    // extra launch costs what it saves.
+    // extra launch costs what it saves: N = 2048 with 960 / 1080 / 1920 jobs times indices 0.97-1.00 / 1.00-1.02 / 1.00-1.02 times
+    // as fast, N = 1024 with 1600 / 1920 / 2880 0.97-0.99 / 0.96-1.00 / 1.00-1.03.
     const Places who(d->members, J);
     const size_t V = who.ids.size();                     // parties that take part
     std::vector<uint16_t> slot(V);
-    const bool ahead = ops->halves || (!ctx->rc.coeff_packing && J >= 2 * V && (uint64_t)J * C >= 1024);
+    const bool ahead = ops->halves || (!ctx->rc.coeff_packing && J >= 2 * V && (uint64_t)J * C >= (ctx->log2n == 10 ? 2560u : 1024u));
     uint32_t *pt = (uint32_t *)shares;
     if (ahead) {
         for (size_t p0 = 0; p0 < V; p0 += ENCODE_CHUNK) {
