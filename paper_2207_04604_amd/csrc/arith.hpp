@@ -351,12 +351,12 @@ struct ArithS {
     {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
-    // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
     // a value that several keys multiply
     typedef elem Factor;
     D2_DEV static Factor factor(elem u, const Mod &) { return u; }
     D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = false;
+    // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
     {
@@ -479,12 +479,12 @@ struct ArithB {
     {
         return tw(ld64(v, lane_off, slot_off), ld64(vs, lane_off, slot_off));
     }
-    // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
     // a value that several keys multiply
     typedef elem Factor;
     D2_DEV static Factor factor(elem u, const Mod &) { return u; }
     D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
     static constexpr bool SUM_SMALL = false;
+    // table entry i: per-lane index / wave-uniform index (scalar registers, see mul<true>)
     static constexpr bool SCALAR_TW = true;
     D2_DEV static Twid load_v(const Tw *table, uint32_t i)
     {
@@ -638,7 +638,7 @@ struct ArithF {
         const double r = __builtin_fma(-b, m.q, h);
         return r + l;
     }
-    // sums of canonical words (at most 65 of them), left unreduced until sum_end
+    // sums of canonical words (at most 64 of them: canon_wide), left unreduced until sum_end
     D2_DEV static uint64_t sum(uint64_t a, uint64_t b, uint64_t) { return a + b; }
     D2_DEV static uint64_t sum_end(uint64_t s, const Mod &m) { return canon_wide(u2d(s), m); }
     D2_DEV static elem from_small(int32_t v, const Mod &) { return (double)v; }
@@ -821,11 +821,11 @@ struct Arith32 {
         y = from_small(yv, m);
         ct<SC>(x, y, w, m);
     }
-    // s[0] + sum of c[j] s[j], |s| <= 32, in [0, 4q)
     // a value that several keys multiply
     typedef elem Factor;
     D2_DEV static Factor factor(elem u, const Mod &) { return u; }
     D2_DEV static elem factor_key_add(const Factor &u, const Key &k, elem x, const Mod &m) { return mul_key_add(u, k, x, m); }
+    // s[0] + sum of c[j] s[j], |s| <= 32, in [0, 4q)
     static constexpr bool SUM_SMALL = true;
     struct Small {
         Twid w;

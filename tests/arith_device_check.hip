@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../paper_2207_04604_amd/csrc/arith.hpp"
+#include "../paper_2207_04604_amd/csrc/pm_growth.hpp"
 
 typedef unsigned __int128 u128;
 typedef __int128 i128;
@@ -335,6 +336,124 @@ static void check_f(uint64_t q, Item *d_in, Out *d_out)
     }
 }
 
+// ---------------------------------------------------------------- moduli just below a power of two (ArithP, ArithQ)
+struct PmItem {
+    uint64_t x, y, key;         // x, y: lazy values; key: canonical
+    Tw w;                       // table entry of the multiplicand
+    int32_t s[4];
+    uint32_t m[2];
+};
+struct PmOut {
+    uint64_t mul, key_add, factor, m32, ct_x[2], ct_y[2], gs_x[2], gs_y[2], gl_x, gl_y, canon, sum2, sum4, encoded, kept;
+};
+template <class A>
+__global__ void k_pm(const PmItem *in, PmOut *out, int n, uint64_t q, uint64_t k)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const PmItem it = in[i];
+    const typename A::Mod md = A::mod(q, k);
+    typename A::Twid tw = A::tw(it.w);
+    PmOut o;
+    o.mul = A::mul(it.y, tw, md);
+    o.key_add = A::mul_key_add(it.y, A::key_of(it.key, 0), it.x, md);
+    o.factor = A::factor_key_add(A::factor(it.y, md), A::key_of(it.key, 0), it.x, md);
+    o.m32 = A::mul_u32(it.m[0], tw, md);
+    for (int s = 0; s < 2; ++s) {
+        o.ct_x[s] = it.x;
+        o.ct_y[s] = it.y;
+        A::ct(o.ct_x[s], o.ct_y[s], tw, md, s);
+        // of values up to what an inverse pass lets through (ArithP 8 G q, ArithQ G q)
+        o.gs_x[s] = it.x % (k * (A::INV_LIM / A::INV_PROD));
+        o.gs_y[s] = it.y % (k * (A::INV_LIM / A::INV_PROD));
+        if (s == 0) {
+            o.gl_x = o.gs_x[0];
+            o.gl_y = o.gs_y[0];
+            A::gs_last(o.gl_x, o.gl_y, tw, tw, md);
+        }
+        A::gs(o.gs_x[s], o.gs_y[s], tw, md, s != 0);
+    }
+    o.canon = A::canon_wide(it.x, md);
+    const int32_t s2[2] = {it.s[0], it.s[1]};
+    typename A::Small c2[2], c4[4];
+    c2[1] = c4[1] = A::small(tw, (it.x & 1) != 0, md);
+    c4[2] = A::small(tw, (it.x & 2) != 0, md);
+    c4[3] = A::small(tw, (it.x & 4) != 0, md);
+    o.sum2 = A::sum_small(s2, c2, md);
+    o.sum4 = A::sum_small(it.s, c4, md);
+    o.encoded = A::sum_encoded(it.m, s2, tw, tw, (it.y & 1) != 0, (it.y & 2) != 0, c2, md);
+    pin_multiplicand(tw);
+    o.kept = A::mul(it.x, tw, md);
+    out[i] = o;
+}
+
+template <class A>
+static int check_pm(const char *name, uint64_t q, bool wide)
+{
+    const uint64_t G = pm_growth(q, wide);
+    if (!G) return 0;
+    const int b = 64 - __builtin_clzll(q), s = b - 31;
+    const uint64_t c = ((uint64_t)1 << b) - q, low = ((uint64_t)1 << s) - 1;
+    const uint64_t top = wide ? (1 + 2 * G) * q + (3 + 2 * G) * c : (64 + 15 * G) * q;      // the largest forward output
+    std::vector<PmItem> items;
+    std::vector<uint64_t> ws = multiplicands(q, 20), vs = probes(top, q, 60);
+    for (uint64_t w : ws)
+        for (uint64_t y : vs)
+            for (int r = 0; r < 12; ++r) {
+                PmItem it;
+                const uint64_t v = (uint64_t)(((u128)w << 32) % q);
+                it.w = Tw{(w & low) | (w >> s) << 32, (v & low) | (v >> s) << 32};
+                it.x = r == 0 ? top : vs[rnd() % vs.size()];
+                it.y = y;
+                it.key = r < 2 ? q - 1 : ws[rnd() % ws.size()];
+                for (int32_t &e : it.s) e = r == 0 ? 32 : r == 1 ? -32 : (int32_t)(rnd() % 65) - 32;
+                for (uint32_t &m : it.m) m = r == 0 ? (1u << 30) - 1 : (uint32_t)below(1u << 30);
+                items.push_back(it);
+            }
+    const int n = (int)items.size();
+    PmItem *d_items;
+    PmOut *d_outs;
+    std::vector<PmOut> outs(n);
+    HIP_OK(hipMalloc(&d_items, n * sizeof(PmItem)));
+    HIP_OK(hipMalloc(&d_outs, n * sizeof(PmOut)));
+    HIP_OK(hipMemcpy(d_items, items.data(), n * sizeof(PmItem), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_pm<A>, dim3((n + 255) / 256), dim3(256), 0, 0, (const PmItem *)d_items, d_outs, n, q, G * q);
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipMemcpy(outs.data(), d_outs, n * sizeof(PmOut), hipMemcpyDeviceToHost));
+    HIP_OK(hipFree(d_items));
+    HIP_OK(hipFree(d_outs));
+    const uint64_t lim = G * q * (A::INV_LIM / A::INV_PROD);
+    for (int i = 0; i < n; ++i) {
+        const PmItem &it = items[i];
+        const PmOut &o = outs[i];
+        const uint64_t w = (it.w.w >> 32 << s) + (uint32_t)it.w.w;
+        auto prod = [&](uint64_t v) { return (uint64_t)((u128)w * (v % q) % q); };
+        const uint64_t t = prod(it.y), kt = (uint64_t)((u128)it.key * (it.y % q) % q), x = it.x % q;
+        bool ok = o.mul < G * q && o.mul % q == t && o.kept == o.kept % (G * q) && o.kept % q == prod(it.x);
+        ok = ok && o.key_add % q == (x + kt) % q && o.factor % q == (x + kt) % q;
+        ok = ok && o.m32 < G * q && o.m32 % q == prod(it.m[0]) && o.canon == x;
+        for (int st = 0; st < 2; ++st) {
+            // an even stage of ArithQ takes values that an odd one left
+            if (!(wide && st == 0 && it.x > (1 + G) * q))
+                ok = ok && o.ct_x[st] % q == (x + t) % q && o.ct_y[st] % q == (x + q - t) % q;
+            const uint64_t a = it.x % lim, d = it.y % lim, diff = (a % q + q - d % q) % q;
+            ok = ok && o.gs_x[st] % q == (a % q + d % q) % q && o.gs_y[st] < G * q && o.gs_y[st] % q == prod(diff);
+            ok = ok && o.gl_x % q == prod((a % q + d % q) % q) && o.gl_y % q == prod(diff) && o.gl_x < G * q && o.gl_y < G * q;
+        }
+        auto sign = [](uint64_t v, int bit) { return (v >> bit) & 1 ? -1 : 1; };
+        i128 sum = (i128)it.s[0] + (i128)w * it.s[1] * sign(it.x, 0);
+        ok = ok && o.sum2 < 4 * q && o.sum2 % q == mod_of(sum, q);
+        sum += (i128)w * it.s[2] * sign(it.x, 1) + (i128)w * it.s[3] * sign(it.x, 2);
+        ok = ok && o.sum4 < 4 * q && o.sum4 % q == mod_of(sum, q);
+        const i128 enc = (i128)w * it.m[0] * sign(it.y, 0) + it.s[0] + (i128)w * it.m[1] * sign(it.y, 1) + (i128)w * it.s[1] * sign(it.x, 0);
+        // below (G + 3 + gamma / 2) q, gamma = c 2^32 / 2^b
+        ok = ok && (u128)o.encoded < (u128)(G + 4) * q + ((u128)c << 31) && o.encoded % q == mod_of(enc, q);
+        CHECK(ok, "%s q=%llu w=%llu x=%llu y=%llu key=%llu", name, (unsigned long long)q, (unsigned long long)w,
+              (unsigned long long)it.x, (unsigned long long)it.y, (unsigned long long)it.key);
+    }
+    return 1;
+}
+
 int main()
 {
     Item *d_in;
@@ -355,6 +474,15 @@ int main()
     for (uint64_t q : {(1ull << 44) - 1, 68719403009ull, 12289ull, 1073707009ull})
         check_f(q, d_in, d_out);
     std::printf("ArithF ok\n");
+    int narrow = 0, wide = 0;
+    for (int b : {45, 50, 54, 55, 56, 59, 60})
+        for (uint64_t c : {1ull, 77823ull, 36044799ull, (1ull << 26) - 1, (1ull << 31) - 1}) {
+            narrow += check_pm<ArithP>("ArithP", (1ull << b) - c, false);
+            wide += check_pm<ArithQ>("ArithQ", (1ull << b) - c, true);
+        }
+    // at least the two smallest c of every size that the policy takes
+    CHECK(narrow >= 8 && wide >= 14, "%d moduli fit ArithP, %d ArithQ", narrow, wide);
+    std::printf("ArithP, ArithQ ok\n");
     HIP_OK(hipFree(d_in));
     HIP_OK(hipFree(d_out));
     if (failures) return 1;

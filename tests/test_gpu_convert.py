@@ -11,6 +11,7 @@ from paper_2207_04604_amd.synth import CONFIGS, toy_config
 
 from gpu_util import DEV, Keys, dzeros, make_pair, to_dev, to_eval, to_host
 from test_gpu_parity import fixed_point_sum
+from test_pm_policies import primes_away_from_powers_of_two
 
 pytestmark = pytest.mark.gpu
 
@@ -105,7 +106,7 @@ def test_convert_C2_two_groups_every_coefficient():
 
 
 def test_convert_wide_primes_ragged_tail_and_extreme_ids():
-    """54- and 60-bit primes (the integer back-ends), a ragged last ciphertext, ids at their limits,
+    """54- and 60-bit primes (just below a power of two: ArithP and ArithQ), doubles, a ragged last ciphertext, ids at their limits,
     a receiver that is not a member, and the plain single-key path (encrypt under a receiver key)."""
     from oracle import oracle as O
     from paper_2207_04604_amd.synth import toy_config
@@ -130,6 +131,22 @@ def test_convert_wide_primes_ragged_tail_and_extreme_ids():
         ctx.decrypt(rkeys.sk[7], dct, 2, dout)
         assert np.array_equal(to_host(dout, (2, N)), m)
         ctx.close()
+
+
+# the shapes that the primes above, all just below a power of two, do not reach: quotients (54, 60 bits) with 8 and with 16
+# coefficients per thread, 32-bit words with 16
+@pytest.mark.parametrize("bits,log2n,L", [(54, 10, 1), (60, 10, 2), (54, 11, 2), (60, 11, 1), (60, 12, 1), (54, 13, 1), (54, 14, 1),
+                                          (60, 14, 1), (30, 14, 2), (30, 13, 2), (36, 10, 2)])
+def test_convert_other_shapes(bits, log2n, L):
+    q = primes_away_from_powers_of_two(bits, log2n, L) if bits > 44 else O.find_primes(bits, log2n, L)
+    cfg = toy_config(log2n, q, 12289 if log2n <= 11 else 65537, 3, (1 << log2n) + 77, frac_bits=6)
+    o, ctx, perm = make_pair(cfg)
+    rng = np.random.default_rng(bits + log2n)
+    members = [1, 40000, 65535]
+    grads = {k: rng.normal(0, 3.0, cfg.n_values).astype(np.float32) for k in members}
+    keys, rkeys = Keys(o, ctx, perm, members, check=False), RecvKeys(o, ctx, perm, [7])
+    convert_calls_and_compare(cfg, o, ctx, perm, keys, rkeys, members, 7, 65535, grads, ct_base=2**32 - 4)
+    ctx.close()
 
 
 @pytest.mark.parametrize("name,share_sample,ct_sample", [("C1", [(0, 0, 0), (0, 3, 2)], (0, 3)),
@@ -216,8 +233,8 @@ def test_convert_argument_checks():
 
 
 def test_rounds_with_more_groups_than_one_launch_takes():
-    """130 two-member groups over 131 parties: more jobs, groups, conversion shares and receivers than one
-    launch's table holds (112 / 112 / 80 / 80), so every phase of both rounds is split over several launches.
+    """130 two-member groups over 131 parties: more parties and groups than one launch's table holds (112 and 112 of a
+    round, 104 and 64 of conversion shares, 80 receivers), so every phase of both rounds is split over several launches.
     Every group's result against the fixed-point sum, sampled objects against the oracle."""
     P, G = 131, 130
     cfg = toy_config(10, O.find_primes(36, 10, 2), 12289, P, 1024 + 11, frac_bits=4)
