@@ -838,16 +838,21 @@ uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Pla
 
 // Whether a k_finish launch over `groups` groups of `members` members in all is faster than the separate launches.  One
 // of its workgroups walks through the K + 1 transforms of every limb of its ciphertext index, so the launch has to fill
-// the chip and to leave no compute unit idle at its end: with W workgroups on 256 units, W / 256 rounded up has to
-// be more than 13/16 used.  The fewer threads a workgroup has, the more of them a unit needs for itself; with
-// four members or fewer the launches saved weigh more.
-// Measured (36, 54 and 60 bits, two limbs, K = 2 to 32), three launches' time over one's:
-//   N = 8192   W = 256 1.04-1.11,  290 0.90-1.02,  350 0.95-1.04,  420 0.99-1.06,  512 1.05-1.12,  576 (3/4) 0.98-1.06,
-//              640 (5/6) 1.01-1.07,  768 1.06-1.12
-//   N = 4096   256 0.99-1.12,  320 0.91-1.07,  384 0.98-1.09,  448 1.00-1.10,  512 1.04-1.11,  576 0.94-1.06,  640 1.02-1.07
-//   N = 2048   256 0.84-0.99 (K = 2, 4: 1.00-1.12),  384 0.90-1.08,  448 0.97-1.09,  512 1.00-1.11,  576 0.94-1.10,  832
-//              (13/16) 0.98-1.09,  896 1.02-1.10
-//   N = 1024   1024 0.91-1.02 (K = 2, 4: 1.00-1.15),  1280 0.98-1.04,  1536 0.97-1.03,  1792 1.04-1.06
+// the chip and to leave few units idle at its end: W workgroups take W / 256 turns of the 256 compute units, rounded up.
+// How much of the last one may be missing depends on what else a unit has to do: a workgroup of N = 8192 has it for
+// itself, two of N = 4096 and four of N = 2048 share it.  With few members the launches saved weigh more.
+// Measured (30 to 60 bits, one or two limbs, groups of K = 2 / 4 / 8 to 32), three launches' time over one's:
+//   N = 8192   W = 256 1.02-1.09 / 1.05-1.12 / 1.05-1.13,  290 0.98-1.02 / 0.93-0.98 / 0.90-0.96,  350 0.99-1.04 / 0.98-1.02 /
+//              0.95-1.00,  384 1.00-1.07 / 0.99-1.05 / 0.99-1.05,  420 1.04-1.06 / 1.01-1.05 / 0.99-1.05,  512 1.05-1.13,
+//              576 1.02-1.06 / 1.00-1.04 / 0.98-1.03,  640 and more 1.01-1.12
+//   N = 4096   256 1.06-1.15 / 1.03-1.09 / 0.99-1.07,  320 1.01-1.07 / 0.96-0.98 / 0.91-0.96,  384 1.03-1.09 / 1.00-1.04 /
+//              0.98-1.03,  400 (K = 5, 36 bits) 1.06,  448 1.06-1.11 / 1.03-1.08 / 1.00-1.06,  512 1.06-1.12 / 1.04-1.09 / 1.03-1.08,
+//              576 1.03-1.06 / 0.98-1.02 / 0.94-1.00,  640 and more 1.00-1.12
+//   N = 2048   256 1.04-1.16 / 0.99-1.08 / 0.84-1.00,  320 1.00-1.06 / 0.93-0.99 / 0.86-0.93,  372 (K = 3, 44 bits) 1.03,  384
+//              1.01-1.08 / 0.97-1.02 / 0.90-0.98,  448 1.06-1.09 / 1.02-1.05 / 0.97-1.04,  512 1.06-1.14 / 1.03-1.09 / 0.99-1.05,
+//              576 1.04-1.10 / 0.99-1.06 / 0.94-0.99,  640 and more 0.98-1.15
+//   N = 1024   1024 1.09-1.17 / 1.00-1.08 / 0.91-1.01,  1280 1.08-1.14 / 1.05-1.07 / 0.98-1.04,  1536 1.03-1.15 / 1.02-1.07 /
+//              0.97-1.04,  1792 1.07-1.12 / 1.04-1.07 / 1.04-1.06
 //   N = 2^14   (halves: twice the workgroups; sums and shares only, against a sum and shares in halves or whole, see
 //              engine_inst.hpp) eight limbs 256 1.02-1.06, 512 1.02-1.08, 896 1.02-1.05;  four 512 0.96-1.05, 768 1.00-1.05,
 //              896 (7/8) 0.97-1.04, 1024 0.99-1.07, 1280 1.04-1.05;  three 512 0.98-1.03, 896 0.96-1.02, 1024 1.01-1.05, 1536
@@ -855,19 +860,27 @@ uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Pla
 bool finish_pays(const d2mhe_ctx *ctx, uint32_t groups, uint32_t members, uint32_t C)
 {
     const bool few = members <= 4 * groups;
-    uint64_t W = (uint64_t)groups * C, least, sixteenths = 13;
+    uint64_t W = (uint64_t)groups * C, least;
+    uint32_t sixteenths = 12;               // of all turns, to be used by more than that
     switch (ctx->log2n) {
     case 14:
         if (ctx->L < 3) return false;
         W *= 2;
         least = ctx->L >= 8 ? 256 : ctx->L >= 4 ? 512 : 1024;
-        sixteenths = 14;
         break;
     case 13:
-    case 12: least = 256; break;
+        least = 256;
+        sixteenths = 11;
+        break;
+    case 12:
+        least = 256;
+        if (W <= 512) sixteenths = 11;
+        break;
     case 11: least = few ? 256 : 512; break;
     default: least = few ? 1024 : 1792;
     }
+    if (few) sixteenths = members <= 3 * groups ? 10 : 11;
+    if (ctx->log2n == 14) sixteenths = 14;
     return W >= least && 16 * W > sixteenths * 256 * ((W + 255) / 256);
 }
 

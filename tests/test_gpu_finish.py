@@ -48,7 +48,8 @@ def launches(call):
     ("44", 11, 2, sizes(31, 33, 64), 209, 0, True),        # 627 of 768
     ("60", 11, 1, sizes(1, 33, 64, 2), 128, 0, True),
     ("54", 11, 1, ring(200, 4), 13, 1, True),
-    ("54", 11, 1, ring(200, 4), 12, 1, False),             # four launches of 50 groups: 600 of 768 workgroups each
+    ("54", 11, 1, ring(200, 4), 11, 1, False),             # four launches of 50 groups: 550 of 768 workgroups each
+    ("44", 11, 2, ring(12, 1), 31, 1, True),               # three members each: 372 of 512
     ("36", 11, 1, ring(100, 15), 20, 0, True),
     ("36", 11, 1, ring(32, 1), 8, 0, True),                # three members each: 256 are enough
     ("36", 11, 1, ring(32, 2), 8, 0, False),
@@ -58,6 +59,9 @@ def launches(call):
     ("60a", 10, 1, ring(32, 2), 56, 0, True),
     ("54", 12, 3, ring(16, 2), 16, 0, True),
     ("54", 12, 2, ring(16, 2), 20, 0, False),              # 320 of 512
+    ("36", 12, 3, ring(16, 2), 25, 0, True),               # 400
+    ("36", 12, 1, ring(16, 2), 36, 0, False),              # 576 of 768
+    ("30", 13, 2, ring(16, 2), 24, 0, True),               # 384 of 512
     ("60a", 12, 1, sizes(1, 2, 33, 64), 64, 0, True),
     ("54a", 12, 2, ring(16, 2), 16, 0, True),
     ("36", 13, 2, ring(8, 1), 32, 0, True),
