@@ -126,8 +126,17 @@ struct RoundJob {                      // one entry, uniform over the workgroup
     uint32_t party, group;
 };
 D2_DEV uint32_t half_word(uint32_t w, uint32_t i) { return (w >> (16 * (i & 1))) & 0xffffu; }
+// ROWS: look at row i together with the job's entry.  The branch costs as much as the second read where the kernel
+// has more to wait for (rows and not: encryption of 60 indices, N = 4096, 36 bits 18.9 / 18.5 us, N = 2048, 60 bits, quotients
+// 23.9 / 23.5; share, N = 4096, 36 bits 8.7 / 8.5; but N = 8192, 54 bits 69.5 / 70.2 and 29.1 / 29.3).
+template <bool ROWS>
 D2_DEV RoundJob round_job(const RoundJobs &t, uint32_t i)
 {
+    if constexpr (!ROWS) {
+        const uint32_t e = half_word(t.job[i >> 1], i), si = e & 0xffu, ki = e >> 8;
+        return RoundJob{t.src[si], t.key[ki], t.out + (size_t)i * t.stride, half_word(t.party[si >> 1], si),
+                        half_word(t.group[ki >> 1], ki)};
+    }
     const uint32_t row = i < (uint32_t)RJ_ROWS ? i : 0;
     uint32_t job = t.job[i >> 1], party = t.party[row >> 1], group = t.group[row >> 1];
     RoundJob r = {t.src[row], t.key[row], t.out, 0, 0};
@@ -893,7 +902,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     constexpr bool SUMMED = ENG::FUSE > 0 && FROM != FROM_VECTOR && (ENG::LOGP > 0 || A::KIND >= 4);
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
-    const RoundJob job = round_job(jobs, blockIdx.y);
+    const RoundJob job = round_job<(ENG::LOGN > 12)>(jobs, blockIdx.y);
     const uint32_t party = job.party, group = job.group;
     const uint64_t *pk = job.key;
     const size_t LN = (size_t)L * ENG::N;
@@ -1018,7 +1027,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
-    const RoundJob job = round_job(jobs, blockIdx.y);
+    const RoundJob job = round_job<ENG::LOGN != 12>(jobs, blockIdx.y);
     const size_t LN = (size_t)L * ENG::N;
     const uint64_t *sk = (const uint64_t *)job.src;
     const uint64_t *c1 = job.key + ((size_t)c * 2 + 1) * LN;
