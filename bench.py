@@ -177,7 +177,7 @@ def main():
             self.launches = math.ceil(self.J / JOBS_PER_LAUNCH)          # launches of the encryption
             # transforms modulo t per ciphertext index: one per party where the vectors are encoded ahead of the
             # encryption, else one per (party, group) pair
-            ahead = cfg.log2_n == 14 or (self.J >= 2 * self.P and self.J * self.C >= 1024)
+            ahead = cfg.log2_n == 14 or (self.J >= 2 * self.P and self.J * self.C >= (2560 if cfg.log2_n == 10 else 1024))
             self.encodings = self.P if ahead else self.J
             torch.cuda.synchronize()
 

@@ -1280,7 +1280,7 @@ D2_DEV void sum_members(uint64_t (&s)[ENG::E], const uint64_t *p, size_t stride,
 //   aggregate of the first group, shares of its first member.
 // The error samples of a member are drawn once and kept as bytes where its share of the last limb will go.
 // Measured (sum + shares + combine, 32 groups of 7, N = 8192, 4 limbs, 153 indices): 10.3 ms as three launches, 7.0 ms
-// in one.  The chain of K + 1 transforms per limb in one workgroup needs a full chip: see the rule in run_round.
+// in one.  The chain of K + 1 transforms per limb in one workgroup needs a full chip: see finish_pays.
 // COMBINE = false: the sum and the shares only.  A half of a polynomial can't be transformed back by itself, so N = 2^14
 // ends with k_combine_decode (8 nodes, 8 limbs, 684 indices: round 15.33 -> 14.93 ms).
 // -------------------------------------------------------------------------------------
