@@ -857,9 +857,13 @@ uint32_t fill_finish_jobs(FinishJobs &jobs, const d2mhe_round_desc *d, const Pla
 //              engine_inst.hpp) eight limbs 256 1.02-1.06, 512 1.02-1.08, 896 1.02-1.05;  four 512 0.96-1.05, 768 1.00-1.05,
 //              896 (7/8) 0.97-1.04, 1024 0.99-1.07, 1280 1.04-1.05;  three 512 0.98-1.03, 896 0.96-1.02, 1024 1.01-1.05, 1536
 //              1.02-1.05;  one and two 512 0.96-1.02, 1024 0.95-1.01, 1800 0.96-1.01
-bool finish_pays(const d2mhe_ctx *ctx, uint32_t groups, uint32_t members, uint32_t C)
+// One of several such launches (`several`) ends by itself and makes the next one wait, where the separate ones go over all
+// groups at once: twice the workgroups, and 7/8 of all turns.  Measured, one kind of launch's time over the other's: 300
+// groups of three, N = 2048, five launches of 240 / 360 workgroups 0.91-0.96 / 0.94; N = 4096, five of 240 1.01-1.03; 150 of 17,
+// N = 2048, three of 400 0.96-0.98.
+bool finish_pays(const d2mhe_ctx *ctx, uint32_t groups, uint32_t members, uint32_t C, bool several)
 {
-    const bool few = members <= 4 * groups;
+    const bool few = members <= 4 * groups && !several;
     uint64_t W = (uint64_t)groups * C, least;
     uint32_t sixteenths = 12;               // of all turns, to be used by more than that
     switch (ctx->log2n) {
@@ -880,7 +884,8 @@ bool finish_pays(const d2mhe_ctx *ctx, uint32_t groups, uint32_t members, uint32
     default: least = few ? 1024 : 1792;
     }
     if (few) sixteenths = members <= 3 * groups ? 10 : 11;
-    if (ctx->log2n == 14) sixteenths = 14;
+    if (several) least *= 2;
+    if (several || ctx->log2n == 14) sixteenths = 14;
     return W >= least && 16 * W > sixteenths * 256 * ((W + 255) / 256);
 }
 
@@ -1000,7 +1005,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
     // does not hold go in several launches of equal size, each of which has to pay by itself.
     const bool split = ev && (ev[2] || ev[3]);
     bool shared = false;            // sums and shares are done
-    if (!conv && ops->finish && !split && finish_pays(ctx, G, J, C)) {
+    if (!conv && ops->finish && !split && finish_pays(ctx, G, J, C, false)) {
         FinishJobs jobs;
         uint32_t n = fill_finish_jobs(jobs, d, who, 0, G, slot), launches = 1, limit = G;
         shared = true;
@@ -1009,7 +1014,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             limit = (G + launches - 1) / launches;
             for (uint32_t g0 = 0; shared && g0 < G; g0 += n) {
                 n = fill_finish_jobs(jobs, d, who, g0, limit, slot);
-                shared = finish_pays(ctx, n, d->group_offsets[g0 + n] - d->group_offsets[g0], C);
+                shared = finish_pays(ctx, n, d->group_offsets[g0 + n] - d->group_offsets[g0], C, true);
             }
         }
         for (uint32_t g0 = 0; shared && g0 < G; g0 += n) {

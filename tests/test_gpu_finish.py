@@ -47,10 +47,11 @@ def launches(call):
     ("44", 11, 2, sizes(31, 33, 64), 171, 0, False),       # 513 workgroups: a third turn of the chip for one of them
     ("44", 11, 2, sizes(31, 33, 64), 209, 0, True),        # 627 of 768
     ("60", 11, 1, sizes(1, 33, 64, 2), 128, 0, True),
-    ("54", 11, 1, ring(200, 4), 13, 1, True),
-    ("54", 11, 1, ring(200, 4), 11, 1, False),             # four launches of 50 groups: 550 of 768 workgroups each
+    ("54", 11, 1, ring(200, 4), 24, 1, True),              # four launches of 50 groups: 1,200 of 1,280 workgroups each
+    ("54", 11, 1, ring(200, 4), 13, 1, False),             # 650 of 768
     ("44", 11, 2, ring(12, 1), 31, 1, True),               # three members each: 372 of 512
-    ("36", 11, 1, ring(100, 15), 20, 0, True),
+    ("36", 11, 1, ring(100, 15), 36, 0, True),             # 34, 34 and 32 groups
+    ("30", 12, 1, ring(100, 1), 10, 0, False),             # two launches of 500
     ("36", 11, 1, ring(32, 1), 8, 0, True),                # three members each: 256 are enough
     ("36", 11, 1, ring(32, 2), 8, 0, False),
     ("30", 10, 2, ring(32, 1), 32, 0, True),
