@@ -26,7 +26,20 @@ struct Launch {
     // the turns of halves take less time than those of whole polynomials, a turn of halves being two thirds as long
     static bool turns_pay(uint64_t n) { return 2 * turns(2 * n) <= 3 * turns(n); }
     static bool encrypt_in_halves(const d2mhe_ctx *ctx, uint64_t n) { return ENG::A::KIND != 0 || ctx->L > 1 || turns_pay(n); }
-    static bool share_in_halves(const d2mhe_ctx *ctx, uint64_t n) { return ctx->L >= 8 || turns_pay(n); }
+    // Where the last turn of whole polynomials is at most half full, halves save half of it: with limbs enough that is
+    // more than the samples drawn twice cost.  Measured shares, us for whole / halves, n = 520 (three turns and five),
+    // 780 (four, seven), 1040 (five, nine), 1300 (six, eleven):
+    //   36 bits  two limbs 106 / 103, 154 / 144, 198 / 187, 242 / 246;
+    //            three limbs 148 / 141, 226 / 221, 290 / 293, 346 / 356;  four 219 / 186, 299 / 285, 377 / 366, 455 / 448;
+    //            seven 378 / 333, 508 / 480, 637 / 602, 765 / 734
+    //   54 bits  two limbs 107 / 108, 141 / 150, 182 / 196, 239 / 261;  four 205 / 196, 304 / 297, 391 / 390, 472 / 469;
+    //            six 339 / 308, 455 / 436, 583 / 548, 688 / 689
+    // and with that turn fuller, n = 660, seven limbs of 36 bits: 388 / 400.
+    static bool share_in_halves(const d2mhe_ctx *ctx, uint64_t n)
+    {
+        const uint64_t most = ctx->L > 3 ? UINT64_MAX : ctx->L == 3 ? 4 : ctx->L == 2 && ENG::A::KIND == 0 ? 5 : 0;
+        return ctx->L >= 8 || turns_pay(n) || (turns(2 * n) < 2 * turns(n) && turns(n) <= most);
+    }
     static bool refresh_in_halves(uint64_t n) { return turns(2 * n) == 1; }
     template <class E>
     struct Shape {

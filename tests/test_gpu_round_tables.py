@@ -137,10 +137,12 @@ def test_round_convert_equals_per_call(bits, log2n, L, parties, reach, C):
 
 
 # N = 2^14 where a launch may take whole polynomials or halves of them: 130 (two turns of the chip in halves, one in whole
-# polynomials) against 65 and 65 (halves)
-@pytest.mark.parametrize("bits,L", [(44, 1), (36, 2), (54, 1), (60, 1)])
-def test_whole_polynomials_equal_halves(bits, L):
-    log2n, C, LN = 14, 130, L << 14
+# polynomials) against 65 and 65 (halves); with four limbs also shares of 520 (five turns in halves, three in whole
+# polynomials: halves) against four times 130 (whole)
+@pytest.mark.parametrize("bits,L,C,part", [(44, 1, 130, 65), (36, 2, 130, 65), (54, 1, 130, 65), (60, 1, 130, 65),
+                                           (36, 4, 520, 130)])
+def test_whole_polynomials_equal_halves(bits, L, C, part):
+    log2n, LN = 14, L << 14
     ctx = make_ctx(log2n, O.find_primes(bits, log2n, L), 65537, f=3, max_group=2, seed=21)
     sk, pk0, pk, rsk, rpk = (dzeros(n * LN) for n in (2, 1, 4, 2, 4))
     ctx.keygen_share(1, sk, pk0)
@@ -157,10 +159,10 @@ def test_whole_polynomials_equal_halves(bits, L):
         "refresh shares": (2, lambda c, n, out: ctx.bootstrap_share(sk, ct[c * 2 * LN:], alpha[c * LN:], n, 1, 5, 3 + c, out)),
     }
     for name, (polys, call) in calls.items():
-        whole, parts, half = dzeros(C * polys * LN), dzeros(C * polys * LN), C // 2
+        whole, parts = dzeros(C * polys * LN), dzeros(C * polys * LN)
         call(0, C, whole)
-        call(0, half, parts)
-        call(half, C - half, parts[half * polys * LN:])
+        for c in range(0, C, part):
+            call(c, part, parts[c * polys * LN:])
         assert torch.equal(whole, parts), name
     torch.cuda.synchronize()
     ctx.close()
