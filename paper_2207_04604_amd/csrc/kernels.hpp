@@ -128,7 +128,9 @@ struct RoundJob {                      // one entry, uniform over the workgroup
 D2_DEV uint32_t half_word(uint32_t w, uint32_t i) { return (w >> (16 * (i & 1))) & 0xffffu; }
 // ROWS: look at row i together with the job's entry.  The branch costs as much as the second read where the kernel
 // has more to wait for (rows and not: encryption of 60 indices, N = 4096, 36 bits 18.9 / 18.5 us, N = 2048, 60 bits, quotients
-// 23.9 / 23.5; share, N = 4096, 36 bits 8.7 / 8.5; but N = 8192, 54 bits 69.5 / 70.2 and 29.1 / 29.3).
+// 23.9 / 23.5; share, N = 4096, 36 bits 8.7 / 8.5; but N = 8192, 54 bits 69.5 / 70.2 and 29.1 / 29.3).  Shares in halves of
+// N = 2^14 on doubles gain 0.2 us by rows on an empty chip and lose by them over several turns (1,040 shares of eight limbs,
+// 36 bits 689 / 675; 54 bits 714 both).
 template <bool ROWS>
 D2_DEV RoundJob round_job(const RoundJobs &t, uint32_t i)
 {
@@ -1027,7 +1029,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     constexpr int E = ENG::E;
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
-    const RoundJob job = round_job<ENG::LOGN != 12>(jobs, blockIdx.y);
+    const RoundJob job = round_job<(ENG::LOGN != 12 && !(ENG::A::KIND == 0 && ENG::LOGP > 0))>(jobs, blockIdx.y);
     const size_t LN = (size_t)L * ENG::N;
     const uint64_t *sk = (const uint64_t *)job.src;
     const uint64_t *c1 = job.key + ((size_t)c * 2 + 1) * LN;
