@@ -1,6 +1,7 @@
 // Launchers for one engine shape; included by inst_<log2n>.hip, which instantiates them.
 #pragma once
 #include "ctx.hpp"
+#include "limb_split.hpp"
 
 namespace d2 {
 
@@ -45,6 +46,14 @@ struct Launch {
     struct Shape {
         typedef E type;
     };
+    // What every part of a split polynomial repeats, in limbs: the samples (all of them for either half of a polynomial),
+    // for an encryption of a vector also its encoding.
+    static constexpr float SAMPLES = 0.5f, ENCODING = 0.7f, MASKS = 1.2f;
+    template <class E>
+    static LimbSplit split(const d2mhe_ctx *ctx, uint64_t n, float fixed)
+    {
+        return split_limbs(ctx->L, n << E::LOGP, 1024 / E::T, E::LOGP ? 2 * fixed : fixed);
+    }
     // launch(Shape<engine>) with the one to take
     template <bool BOTH, class F>
     static void choose(bool half, F launch)
@@ -131,17 +140,22 @@ struct Launch {
     {
         if (from == FROM_VECTOR) {
             if constexpr (HALVES) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
-            else
-                hipLaunchKernelGGL((k_encrypt<ENG, FROM_VECTOR>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, ct_base, n_values,
-                                   ctx->d_tabs, ctx->rc);
+            else {
+                const LimbSplit sp = split<ENG>(ctx, (uint64_t)C * njobs, ctx->rc.coeff_packing ? SAMPLES : SAMPLES + ENCODING);
+                hipLaunchKernelGGL((k_encrypt<ENG, FROM_VECTOR>), dim3(C, njobs, sp.parts), dim3(ENG::T), 0, st, jobs, ct_base,
+                                   sp.word, n_values, ctx->d_tabs, ctx->rc);
+            }
         } else {
             choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
                 typedef typename decltype(shape)::type E;
-                const dim3 grid(C << E::LOGP, njobs), block(E::T);
+                const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
+                const dim3 grid(C << E::LOGP, njobs, sp.parts), block(E::T);
                 if (from == FROM_WORDS32)
-                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, sp.word, n_values, ctx->d_tabs,
+                                       ctx->rc);
                 else
-                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, n_values, ctx->d_tabs, ctx->rc);
+                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, sp.word, n_values, ctx->d_tabs,
+                                       ctx->rc);
             });
         }
         D2_LAUNCHED(ctx);
@@ -153,7 +167,9 @@ struct Launch {
     {
         choose<HALVES>(share_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            hipLaunchKernelGGL(k_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
+            hipLaunchKernelGGL(k_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
+                               ctx->rc);
         });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
@@ -204,7 +220,9 @@ struct Launch {
     {
         choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            hipLaunchKernelGGL(k_convert_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
+            hipLaunchKernelGGL(k_convert_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
+                               ctx->rc);
         });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
@@ -242,7 +260,9 @@ struct Launch {
     {
         choose<HALVES>(refresh_in_halves((uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            hipLaunchKernelGGL(k_bootstrap_share<E>, dim3(C << E::LOGP, njobs), dim3(E::T), 0, st, jobs, ct_base, ctx->d_tabs, ctx->rc);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, MASKS);
+            hipLaunchKernelGGL(k_bootstrap_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
+                               ctx->rc);
         });
         D2_LAUNCHED(ctx);
         return D2MHE_OK;

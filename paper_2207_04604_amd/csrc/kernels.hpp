@@ -260,6 +260,18 @@ D2_DEV int opaque(int v)
 }
 D2_DEV uint32_t opaque(uint32_t v) { return (uint32_t)opaque((int)v); }
 
+// The limbs [first, end) of a workgroup where a launch splits every polynomial over gridDim.z workgroups: `split` holds
+// the limbs of part 0 and, from bit 16, those of each further part.
+struct LimbRange {
+    uint32_t first, end;
+};
+D2_DEV LimbRange limb_range(uint32_t split, uint32_t L)
+{
+    const uint32_t z = blockIdx.z, head = split & 0xffffu, rest = split >> 16;
+    const uint32_t first = z ? head + (z - 1) * rest : 0, end = first + (z ? rest : head);
+    return LimbRange{first, end < L ? end : L};
+}
+
 // -------------------------------------------------------------------------------------
 // Plain batched transforms: polys [B][L][N] in place, one workgroup per (b, limb).
 // -------------------------------------------------------------------------------------
@@ -886,7 +898,7 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
 // member's gradient, encoded on the fly.
 // -------------------------------------------------------------------------------------
 template <class ENG, int FROM>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, uint32_t ct_base, uint64_t n_values,
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, uint32_t ct_base, uint32_t split, uint64_t n_values,
                                                     const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
@@ -952,7 +964,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     }
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
-    for (uint32_t limb = 0; limb < L; ++limb) {
+    const LimbRange lr = limb_range(split, L);
+    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const typename A::Twid lam = A::tw(tb.lambda);
@@ -1021,7 +1034,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
 // Decryption share h = s c1 + e in evaluation form.  grid = (C, jobs).
 // -------------------------------------------------------------------------------------
 template <class ENG>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, uint32_t ct_base, const LimbTab *tabs, RoundConst rc)
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, uint32_t ct_base, uint32_t split,
+                                                                    const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
     __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
@@ -1038,7 +1052,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     static_assert(SMALL_LDS_WORDS<ENG> <= ENG::LDS_WORDS, "in the buffer the first transform leaves alone");
     small_cbd<ENG>(e, lds, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
     if (ENG::WAVE_CHAIN) __syncthreads();
-    for (uint32_t limb = 0; limb < L; ++limb) {
+    const LimbRange lr = limb_range(split, L);
+    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const size_t off = (size_t)limb * ENG::N;
@@ -1461,8 +1476,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_receiver_keygen(uint32_t
 //   h0 = s_k c1 + NTT(mu) p0_i + NTT(e0),   h1 = NTT(mu) p1_i + NTT(e1)
 // mu ternary, e0, e1 from chi, counters (block, ciphertext, member | receiver << 16, domain | group << 16).
 template <class ENG>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs jobs, uint32_t ct_base, const LimbTab *tabs,
-                                                          RoundConst rc)
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs jobs, uint32_t ct_base, uint32_t split,
+                                                          const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
     typedef typename A::elem elem;
@@ -1483,7 +1498,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     smp.load(lds32, tid);
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
-    for (uint32_t limb = 0; limb < L; ++limb) {
+    const LimbRange lr = limb_range(split, L);
+    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const size_t off = (size_t)limb * ENG::N;
@@ -1587,8 +1603,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_alpha(uint64_t
 //   eta0 = s_k c1 + NTT(e0 - Lambda M),   eta1 = NTT(Lambda M + e1) - s_k alpha
 // M uniform mod t (one block per coefficient), e0, e1 from chi.
 template <class ENG>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs jobs, uint32_t ct_base, const LimbTab *tabs,
-                                                            RoundConst rc)
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs jobs, uint32_t ct_base, uint32_t split,
+                                                            const LimbTab *tabs, RoundConst rc)
 {
     typedef typename ENG::A A;
     typedef typename A::elem elem;
@@ -1636,7 +1652,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
         }
     // the transforms overwrite the samples: both buffers hold some, or their transforms have no barrier
     if (2 * ENG::LDS_WORDS < 2 * ENG::N || ENG::WAVE_CHAIN) __syncthreads();
-    for (uint32_t limb = 0; limb < L; ++limb) {
+    const LimbRange lr = limb_range(split, L);
+    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;
         const typename A::Mod md = A::mod(q, tb.one_s);
