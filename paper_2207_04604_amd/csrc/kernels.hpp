@@ -265,9 +265,17 @@ D2_DEV uint32_t opaque(uint32_t v) { return (uint32_t)opaque((int)v); }
 struct LimbRange {
     uint32_t first, end;
 };
+D2_DEV uint32_t launch_part()
+{
+#if D2_GCN_ASM
+    return __builtin_amdgcn_workgroup_id_z();
+#else
+    return 0;                           // a host build that runs the kernels takes polynomials whole
+#endif
+}
 D2_DEV LimbRange limb_range(uint32_t split, uint32_t L)
 {
-    const uint32_t z = blockIdx.z, head = split & 0xffffu, rest = split >> 16;
+    const uint32_t z = launch_part(), head = split & 0xffffu, rest = split >> 16;
     const uint32_t first = z ? head + (z - 1) * rest : 0, end = first + (z ? rest : head);
     return LimbRange{first, end < L ? end : L};
 }
