@@ -136,6 +136,33 @@ D2_DEV uint64_t ld64_stream(const void *base, uint32_t lane_off, uint32_t slot_o
     return *(const uint64_t *)((const char *)base + lane_off + slot_off);
 #endif
 }
+// The same for pairs of words.
+D2_DEV U128 ld128_stream(const void *base, uint32_t lane_off, uint32_t slot_off)
+{
+#if D2_GCN_ASM
+    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0xffffffff, 0x00020000);
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, slot_off, 2 /* nt */);
+    return U128{((uint64_t)v.y << 32) | v.x, ((uint64_t)v.w << 32) | v.z};
+#else
+    return ld128(base, lane_off, slot_off);
+#endif
+}
+D2_DEV void st128_stream(void *base, uint32_t lane_off, uint32_t slot_off, U128 val)
+{
+#if D2_GCN_ASM
+    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xffffffff, 0x00020000);
+    u32x4 v;
+    v.x = (uint32_t)val.lo;
+    v.y = (uint32_t)(val.lo >> 32);
+    v.z = (uint32_t)val.hi;
+    v.w = (uint32_t)(val.hi >> 32);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, lane_off, slot_off, 2 /* nt */);
+#else
+    uint64_t *p = (uint64_t *)((char *)base + lane_off + slot_off);
+    p[0] = val.lo;
+    p[1] = val.hi;
+#endif
+}
 // The same store marked non-temporal (streaming): for data the kernel never reads again, so that it
 // does not displace what the kernel does re-read (parked words, keys, twiddles) from the caches.
 D2_DEV void st64_stream(void *base, uint32_t lane_off, uint32_t slot_off, uint64_t val)

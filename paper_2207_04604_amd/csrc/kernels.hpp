@@ -1076,6 +1076,114 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
 }
 
 // -------------------------------------------------------------------------------------
+// Sums over members.  A sum does not care which thread adds which word, so its loads are of 16 bytes: of two slots whose
+// words lie side by side in two lanes (eval_lane), the even lane takes both words of the first, the odd lane those of the
+// second, and only the finished sum goes back to its owners.  One compute unit reads 70 bytes/ns from its L2 with 8-byte loads
+// and 127 with these, 40 and 49 from memory while half of the units read.
+// -------------------------------------------------------------------------------------
+template <class ENG>
+struct Pairs {
+    static constexpr int E = ENG::E, BIT = 1 << ENG::LOGP, B = 8;       // slots go in batches, or more than 8 spill
+    static_assert(E % B == 0, "whole batches");
+    // byte offset of a thread's two words of slots 0 and 1
+    D2_DEV static uint32_t lane(int tid, uint32_t blk)
+    {
+        return 8u * (uint32_t)(ENG::eval_lane(tid & ~BIT, blk) + (tid & BIT ? ENG::T : 0));
+    }
+    template <bool STREAM>
+    D2_DEV static void load(uint64_t (&v)[B], const uint64_t *p, uint32_t lo, int k0)
+    {
+#pragma unroll
+        for (int k = 0; k < B; k += 2) {
+            const U128 w = STREAM ? ld128_stream(p, lo, 8u * ENG::T * (k0 + k)) : ld128(p, lo, 8u * ENG::T * (k0 + k));
+            v[k] = w.lo;
+            v[k + 1] = w.hi;
+        }
+    }
+    D2_DEV static void store(uint64_t *p, const uint64_t (&v)[B], uint32_t lo, int k0)
+    {
+#pragma unroll
+        for (int k = 0; k < B; k += 2) st128_stream(p, lo, 8u * ENG::T * (k0 + k), U128{v[k], v[k + 1]});
+    }
+    // v of the other lane of a pair
+    D2_DEV static uint32_t other(uint32_t v)
+    {
+#if D2_GCN_ASM
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, BIT == 1 ? 0xb1 /* quad_perm [1,0,3,2] */ : 0x4e /* [2,3,0,1] */, 0xf,
+                                                     0xf, true);
+#else
+        return (uint32_t)__shfl_xor((int)v, BIT);
+#endif
+    }
+    // from the loaded order to the owners', and back
+    D2_DEV static void swap(uint64_t (&v)[B], int tid)
+    {
+        const bool odd = (tid & BIT) != 0;
+#pragma unroll
+        for (int k = 0; k < B; k += 2) {
+            const uint64_t give = odd ? v[k] : v[k + 1];
+            const uint64_t got = ((uint64_t)other(hi32(give)) << 32) | other(lo32(give));
+            v[k] = odd ? got : v[k];
+            v[k + 1] = odd ? v[k + 1] : got;
+        }
+    }
+    // a sum of K + 1 canonical words made canonical
+    D2_DEV static void reduce(uint64_t (&s)[B], uint32_t K, const typename ENG::A::Mod &md, uint64_t q)
+    {
+        typedef typename ENG::A A;
+        if (A::KIND == 0 && K >= (uint32_t)MAX_GROUP) {      // 65 terms: one more than ArithF's sum_end takes
+#pragma unroll
+            for (int k = 0; k < B; ++k) s[k] = csub(s[k], 32 * q);
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) s[k] = A::sum_end(s[k], md);
+    }
+    // s + the sum of K polynomials, at(j) being the j-th, all canonical and in loaded order (s: up to 65 terms, not reduced
+    // where the policy puts that off).  RING: the words of two members are always under way; else those of three are requested
+    // together and then added, for kernels that have no registers for the other.  RING against three together, combine of
+    // N = 4096, 36 bits, 3 limbs: 512 indices, two members 41.0 / 40.5 us, twelve 113.6 / 112.2; 400, five 51.5 / 54.1; N = 8192,
+    // 54 bits, 4 limbs, 400 of two 112.9 / 120.5 us.
+    template <bool STREAM, bool RING, class AT>
+    D2_DEV static void add(uint64_t (&s)[B], AT at, uint32_t K, uint32_t lo, int k0, uint64_t q)
+    {
+        typedef typename ENG::A A;
+        if constexpr (RING) {
+            constexpr int DEPTH = 2;
+            uint64_t v[DEPTH][B];
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d)
+                if ((uint32_t)d < K) load<STREAM>(v[d], at(d), lo, k0);
+            for (uint32_t j = 0; j < K; j += DEPTH) {
+#pragma unroll
+                for (int d = 0; d < DEPTH; ++d) {
+                    if (j + d < K) {
+#pragma unroll
+                        for (int k = 0; k < B; ++k) s[k] = A::sum(s[k], v[d][k], q);
+                        if (j + d + DEPTH < K) load<STREAM>(v[d], at(j + d + DEPTH), lo, k0);
+                    }
+                }
+            }
+        } else {
+            auto batch = [&](uint32_t j, auto n) {
+                constexpr int D = decltype(n)::value;
+                uint64_t v[D][B];
+#pragma unroll
+                for (int d = 0; d < D; ++d) load<STREAM>(v[d], at(j + d), lo, k0);
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+#pragma unroll
+                    for (int k = 0; k < B; ++k) s[k] = A::sum(s[k], v[d][k], q);
+            };
+            constexpr int DEPTH = ENG::E > 8 ? 2 : 3;
+            uint32_t j = 0;
+            for (; j + DEPTH <= K; j += DEPTH) batch(j, std::integral_constant<int, DEPTH>());
+            if (DEPTH > 2 && K - j == 2) batch(j, std::integral_constant<int, 2>());
+            else if (j < K) batch(j, std::integral_constant<int, 1>());
+        }
+    }
+};
+
+// -------------------------------------------------------------------------------------
 // Combine: y = c0 + sum_k h_k, back to coefficient form, then pt = round(t y / Q) mod t
 // by summing t * y_i' / q_i over the limbs with y_i' = y_i (Q/q_i)^-1 mod q_i: integer
 // parts exactly, fractional parts in 64-bit fixed point (each term is truncated by less
@@ -1125,6 +1233,13 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
     const size_t share_ct = (MODE == COMBINE_COLLECTIVE ? 1 : 2) * LN;       // words of one share per ciphertext index
     const uint64_t *c0 = ct + (size_t)c * 2 * LN;
     const uint32_t t = (uint32_t)rc.t;
+    typedef Pairs<ENG> PR;
+    // Shares that fit the caches may still be there, or be wanted again; a launch that fills the chip is faster without
+    // leaving them there.  Kept and streamed, N = 4096, 36 bits, 3 limbs, shares read again / made just before: 25 indices of five
+    // members (14 MB) 22.0 / 24.8 and 27.5 / 27.8 us, 128 of twelve (156 MB) 35.8 / 44.2 and 48.6 / 47.8, 256 of twelve (312 MB)
+    // 64.4 / 61.2 and 72.5 / 65.6; N = 2048, 256 of two (48 MB) 19.8 / 18.3 and 23.4 / 22.5.
+    const uint32_t units = gridDim.x * gridDim.y;
+    const bool stream = units > 128 || (uint64_t)units * (K + 1) * share_ct > (192u << 20) / 8;
     // (a zero of its own: shared with the limb counter's it would move the counter, and with it every buffer
     // descriptor, to vector registers)
     const uint32_t zero = opaque(0u);
@@ -1138,50 +1253,34 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
         const typename A::Mod md = A::mod(q, tb.one_s);
         const size_t off = (size_t)limb * ENG::NB;
         const int tl = opaque(tid);
-        // c0 + sum of the shares, one batch of loads per member; with 8 coefficients per thread the
-        // next member's values are already in flight while this one's are added
-        constexpr bool PIPE = E <= 8 && !CONVERT;
-        uint64_t y[E], hv[E];
+        const uint32_t lo = 8u * (uint32_t)tl, lp = PR::lane(tl, 0);
+        // `from` (none: zero) and a polynomial of every member
+        auto sum = [&](uint64_t (&s)[E], const uint64_t *from, auto at) {
 #pragma unroll
-        for (int k = 0; k < E; ++k) y[k] = ld64_stream(c0 + off, 8u * (uint32_t)tl, 8u * ENG::T * k);
-        if (PIPE && K > 0) {
-            const uint64_t *h = share_of(0) + (size_t)c * share_ct + off;
+            for (int k0 = 0; k0 < E; k0 += PR::B) {
+                uint64_t v[PR::B];
+                if (from) {
+                    PR::template load<true>(v, from, lp, k0);
+                } else {
 #pragma unroll
-            for (int k = 0; k < E; ++k) hv[k] = ld64_stream(h, 8u * (uint32_t)tl, 8u * ENG::T * k);
-        }
-        for (uint32_t j = 0; j < K; ++j) {
-            if constexpr (PIPE) {
-                uint64_t nv[E];
-                if (j + 1 < K) {
-                    const uint64_t *h = share_of(j + 1) + (size_t)c * share_ct + off;
-#pragma unroll
-                    for (int k = 0; k < E; ++k) nv[k] = ld64_stream(h, 8u * (uint32_t)tl, 8u * ENG::T * k);
+                    for (int k = 0; k < PR::B; ++k) v[k] = 0;
                 }
+                constexpr bool RING = E <= 8 && !CONVERT;
+                if (stream) PR::template add<true, RING>(v, at, K, lp, k0, q);
+                else PR::template add<false, RING>(v, at, K, lp, k0, q);
+                PR::reduce(v, K, md, q);
+                PR::swap(v, tl);
 #pragma unroll
-                for (int k = 0; k < E; ++k) {
-                    y[k] = add_mod(y[k], hv[k], q);
-                    hv[k] = nv[k];
-                }
-            } else {
-                const uint64_t *h = share_of(j) + (size_t)c * share_ct + off;
-#pragma unroll
-                for (int k = 0; k < E; ++k) hv[k] = ld64_stream(h, 8u * (uint32_t)tl, 8u * ENG::T * k);
-#pragma unroll
-                for (int k = 0; k < E; ++k) y[k] = add_mod(y[k], hv[k], q);
+                for (int k = 0; k < PR::B; ++k) s[k0 + k] = v[k];
             }
-        }
+        };
+        auto share = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + off; };
+        uint64_t y[E];
+        sum(y, c0 + off, share);
         typename A::elem x[E];
         if constexpr (CONVERT) {
             uint64_t z[E];
-#pragma unroll
-            for (int k = 0; k < E; ++k) z[k] = keep_c1 ? ld64_stream(c0 + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * k) : 0;
-            for (uint32_t j = 0; j < K; ++j) {
-                const uint64_t *h = share_of(j) + (size_t)c * share_ct + LN + off;
-#pragma unroll
-                for (int k = 0; k < E; ++k) hv[k] = ld64_stream(h, 8u * (uint32_t)tl, 8u * ENG::T * k);
-#pragma unroll
-                for (int k = 0; k < E; ++k) z[k] = add_mod(z[k], hv[k], q);
-            }
+            sum(z, keep_c1 ? c0 + LN + off : nullptr, [&](uint32_t j) { return share(j) + LN; });
             typename A::Key kv[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) kv[k] = A::key(skr + off, skr + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * k);
@@ -1216,21 +1315,20 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
 #pragma unroll
             for (int k = 0; k < E; ++k) x[k] = A::mul_u32(opaque(m[k]), lam, md);
             ENG::forward(x, lds, tl, 0, tb.fwd, md);
-            uint64_t y[E], hv[E];
+            const uint32_t lp = PR::lane(tl, 0);
+            auto second = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + LN + off; };
 #pragma unroll
-            for (int k = 0; k < E; ++k) y[k] = A::canon_fwd(x[k], md);
-            for (uint32_t j = 0; j < K; ++j) {
-                const uint64_t *h = share_of(j) + (size_t)c * share_ct + LN + off;
+            for (int k0 = 0; k0 < E; k0 += PR::B) {
+                uint64_t v[PR::B];
 #pragma unroll
-                for (int k = 0; k < E; ++k) hv[k] = ld64_stream(h, 8u * (uint32_t)tl, 8u * ENG::T * k);
-#pragma unroll
-                for (int k = 0; k < E; ++k) y[k] = add_mod(y[k], hv[k], q);
-            }
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const uint32_t lo = 8u * (uint32_t)tl, so = 8u * ENG::T * k;
-                st64(ct_out + off, lo, so, y[k]);
-                st64(ct_out + LN + off, lo, so, ld64(alpha + off, lo, so));
+                for (int k = 0; k < PR::B; ++k) v[k] = A::canon_fwd(x[k0 + k], md);
+                PR::swap(v, tl);
+                if (stream) PR::template add<true, false>(v, second, K, lp, k0, q);
+                else PR::template add<false, false>(v, second, K, lp, k0, q);
+                PR::reduce(v, K, md, q);
+                PR::store(ct_out + off, v, lp, k0);
+                PR::template load<false>(v, alpha + off, lp, k0);
+                PR::store(ct_out + LN + off, v, lp, k0);
             }
         }
     } else if (DECODE) {
@@ -1262,38 +1360,6 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine_decode(GroupJobs
     combine_body<ENG, true, COMBINE_COLLECTIVE>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
                                    jobs.K[job], (const uint64_t *)nullptr, false, (uint64_t *)nullptr,
                                    (float *)jobs.out[job], n_values, tabs, rc);
-}
-
-// Sum of K canonical polynomials `stride` words apart, canonical, for the slots of a thread: the next one's words are
-// in flight while one's are added.
-template <class ENG>
-D2_DEV void sum_members(uint64_t (&s)[ENG::E], const uint64_t *p, size_t stride, uint32_t K, uint32_t lo,
-                        const typename ENG::A::Mod &md, uint64_t q)
-{
-    typedef typename ENG::A A;
-    constexpr int E = ENG::E;
-    uint64_t v[E], n[E];
-#pragma unroll
-    for (int k = 0; k < E; ++k) s[k] = ld64_stream(p, lo, 8u * ENG::T * k);
-    if (K > 1) {
-        p += stride;
-#pragma unroll
-        for (int k = 0; k < E; ++k) v[k] = ld64_stream(p, lo, 8u * ENG::T * k);
-    }
-    for (uint32_t j = 1; j < K; ++j) {
-        if (j + 1 < K) {
-            p += stride;
-#pragma unroll
-            for (int k = 0; k < E; ++k) n[k] = ld64_stream(p, lo, 8u * ENG::T * k);
-        }
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            s[k] = A::sum(s[k], v[k], q);
-            v[k] = n[k];
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < E; ++k) s[k] = A::sum_end(s[k], md);
 }
 
 // -------------------------------------------------------------------------------------
@@ -1343,12 +1409,20 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         const size_t off = (size_t)limb * ENG::N;
         const uint32_t lo = 8u * (uint32_t)ENG::eval_lane(opaque(tid), blk);
         uint64_t y[E], z[E];                        // sums of c0 (and of the shares) and of c1
-        sum_members<ENG>(z, cts + LN + off, ct_words, K, lo, md, q);
-        sum_members<ENG>(y, cts + off, ct_words, K, lo, md, q);
+        {
+            const int tp = opaque(tid);
+            const uint32_t lp = Pairs<ENG>::lane(tp, blk);
+            auto sum = [&](uint64_t (&s)[E], size_t at) {
+                const uint64_t *p = cts + at + off;
+                Pairs<ENG>::template load<true>(s, p, lp, 0);
+                Pairs<ENG>::template add<true, false>(s, [&](uint32_t j) { return p + (size_t)(j + 1) * ct_words; }, K - 1, lp, 0, q);
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-            st64_stream(agg + off, lo, 8u * ENG::T * k, y[k]);
-            st64_stream(agg + LN + off, lo, 8u * ENG::T * k, z[k]);
+                for (int k = 0; k < E; ++k) s[k] = A::sum_end(s[k], md);
+                Pairs<ENG>::store(agg + at + off, s, lp, 0);
+                Pairs<ENG>::swap(s, tp);
+            };
+            sum(z, LN);
+            sum(y, 0);
         }
         for (uint32_t j = 0; j < K; ++j) {
             const uint32_t who = jobs.member[m0 + j];

@@ -1,0 +1,56 @@
+"""Sums over members inside the combining kernels (16-byte loads, their words brought back to their owners; two or three members
+under way; kept in the caches or streamed): shares of K members against one share that is their sum modulo q, which takes
+no loop; with words at the ends of their range, whose sums are multiples of q."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import oracle as O
+
+from gpu_util import DEV, dzeros, make_ctx
+from test_pm_policies import primes_away_from_powers_of_two
+
+
+# C = 129 or 200: streamed; 64 members: as many as there can be
+@pytest.mark.parametrize("bits,log2n,L,C,Ks", [
+    ("30", 10, 2, 3, (2, 3, 64)), ("36", 11, 2, 2, (2, 3, 4, 5, 63, 64)), ("44", 12, 1, 200, (6, 64)), ("36", 14, 2, 2, (3, 64)),
+    ("54", 12, 2, 129, (3, 8)), ("54", 13, 2, 3, (2, 7, 64)), ("60", 13, 2, 2, (5, 64)), ("54a", 13, 1, 2, (4, 64)),
+    ("60a", 11, 2, 2, (3, 64)), ("54", 14, 2, 1, (2, 3, 64)), ("60a", 14, 1, 130, (5,)),
+])
+def test_members_equal_their_sum(bits, log2n, L, C, Ks):
+    N, t = 1 << log2n, 12289 if log2n <= 11 else 65537
+    q = primes_away_from_powers_of_two(int(bits[:-1]), log2n, L) if bits.endswith("a") else O.find_primes(int(bits), log2n, L)
+    ctx = make_ctx(log2n, q, t, f=3, max_group=64, seed=12)
+    qs = torch.tensor(q, dtype=torch.int64, device=DEV).view(1, 1, L, 1)
+    gen = torch.Generator(device=DEV).manual_seed(log2n)
+
+    def words(polys):
+        w = torch.randint(0, 1 << 62, (C, polys, L, N), generator=gen, dtype=torch.int64, device=DEV) % qs
+        end = torch.randint(0, 4, (C, polys, 1, N), generator=gen, device=DEV)           # half of the words at an end
+        return torch.where(end == 0, qs - 1, torch.where(end == 1, torch.zeros_like(qs), w)).contiguous()
+
+    ct, alpha = words(2), words(1)
+    for K in Ks:
+        shares, pairs = [words(1) for _ in range(K)], [words(2) for _ in range(K)]
+
+        def total(parts):
+            s = parts[0]
+            for p in parts[1:]:
+                s = s + p - torch.where(s >= qs - p, qs, torch.zeros_like(qs))
+            return s.contiguous()
+
+        if K == 64:     # c0 and the shares add up to 64 q
+            shares = [(qs - 1).expand(C, 1, L, N).contiguous() for _ in range(K)]
+            ct[:, 0] = 64
+        got, want = dzeros(C * N), dzeros(C * N)
+        ctx.combine(ct, shares, C, got)
+        ctx.combine(ct, [total(shares)], C, want)
+        assert torch.equal(got, want), f"combine of {K}"
+        got, want = dzeros(C * 2 * L * N), dzeros(C * 2 * L * N)
+        ctx.bootstrap_combine(ct, alpha, pairs, C, got)
+        ctx.bootstrap_combine(ct, alpha, [total(pairs)], C, want)
+        assert torch.equal(got, want), f"refresh by {K}"
+    torch.cuda.synchronize()
+    ctx.close()
