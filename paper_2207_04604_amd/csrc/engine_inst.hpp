@@ -66,6 +66,28 @@ struct Launch {
         }
     }
 
+    // Members that a workgroup of the tail takes in turn, for `groups` groups of B.  The twiddles it fetches first cost about two
+    // members' time; the workgroups take ceil(W / places) turns of the chip.  Always eight and this, N = 2^16, 60 bits, us:
+    // L = 1, B = 8 32.6 / 12.8;  4, 8 43.9 / 27.8;  4, 16 41.0 / 31.3;  4, 24 46.7 / 41.7;  16, 2 26.0 / 25.5;  N = 2^15, 60 bits:
+    // 1, 32 36.0 / 16.2;  4, 16 37.9 / 21.2;  7, 48 75.8 / 67.8.  More than eight gain where they fill a turn of the chip, of N =
+    // 2^16 also two, if all are equal (L = 16: B = 32 194 / 176, 48 286 / 273, 64 398 / 383; in part of two, L = 4, B = 200 305 / 317; N = 2^15, L = 16,
+    // B = 128 397 / 420).
+    static uint32_t tail_tiles(uint32_t groups, uint32_t B)
+    {
+        constexpr uint64_t PLACES = 256 * (1024 / ENG::T);
+        uint32_t best = 1;
+        uint64_t least = ~(uint64_t)0;
+        for (uint32_t m = 1; m <= 16 && m <= B; ++m) {
+            const uint64_t W = (uint64_t)groups * ((B + m - 1) / m), n = (W + PLACES - 1) / PLACES;
+            if (m > 8 && n > 1 && !(ENG::LOGN == 16 && n == 2 && B % m == 0 && 16 * W >= 15 * 2 * PLACES)) continue;
+            if (n * (m + 2) <= least) {
+                least = n * (m + 2);
+                best = m;
+            }
+        }
+        return best;
+    }
+
     static d2mhe_status ntt(d2mhe_ctx *ctx, uint64_t *polys, uint32_t B, bool forward, hipStream_t st)
     {
         const uint32_t L = ctx->L, polys_n = B * L;
@@ -84,14 +106,16 @@ struct Launch {
                 const uint32_t nb = B - b0 < chunk_b ? B - b0 : chunk_b, n = nb * L;
                 uint64_t *base = polys + ((size_t)b0 * L << LOGN);
                 dim3 hgrid((1u << (LOGN - LOGH)) / 256, n);
-                dim3 tgrid(L * (1u << LOGH) * ((nb + TAIL_TILES - 1) / TAIL_TILES));
+                const uint32_t tiles = tail_tiles(L << LOGH, nb);
+                const uint32_t wpg = (nb + tiles - 1) / tiles;
+                dim3 tgrid(L * (1u << LOGH) * wpg);
                 if (forward) {
                     hipLaunchKernelGGL((k_head_forward<typename ENG::A, LOGN, LOGH>), hgrid, dim3(256), 0, st, base,
                                        ctx->d_tabs, L, 0u);
                     D2_LAUNCHED(ctx);
-                    hipLaunchKernelGGL(k_tail_forward<ENG>, tgrid, dim3(ENG::T), 0, st, base, ctx->d_tabs, L, nb);
+                    hipLaunchKernelGGL(k_tail_forward<ENG>, tgrid, dim3(ENG::T), 0, st, base, ctx->d_tabs, L, nb, tiles, wpg);
                 } else {
-                    hipLaunchKernelGGL(k_tail_inverse<ENG>, tgrid, dim3(ENG::T), 0, st, base, ctx->d_tabs, L, nb);
+                    hipLaunchKernelGGL(k_tail_inverse<ENG>, tgrid, dim3(ENG::T), 0, st, base, ctx->d_tabs, L, nb, tiles, wpg);
                     D2_LAUNCHED(ctx);
                     hipLaunchKernelGGL((k_head_inverse<typename ENG::A, LOGN, LOGH>), hgrid, dim3(256), 0, st, base,
                                        ctx->d_tabs, L, 0u);

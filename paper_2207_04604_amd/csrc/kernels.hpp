@@ -395,20 +395,18 @@ __global__ void __launch_bounds__(256) k_head_inverse(uint64_t *polys, const Lim
 }
 
 // Tail of a long transform over polys [B][L][N].  Tiles that share twiddles -- the same (limb, block)
-// of every polynomial of the batch, a "group" of B members -- are given to one workgroup TAIL_TILES
+// of every polynomial of the batch, a "group" of B members -- are given to one workgroup `tiles`
 // members at a time: it fetches the twiddles once (scalar registers for the uniform passes, 56
 // vector registers for the rest with 16-byte entries) and walks its members with the next member's
 // coefficients already requested.  Without this the twiddles are twice the bytes of the data.
 // Workgroups are handed to the 8 XCDs round-robin by linear id: XCD x = i % 8 walks the contiguous
 // slot range [x * grid/8, (x+1) * grid/8), so that the workgroups of a group also share an L2.
-constexpr int TAIL_TILES = 8;
 
 struct TailTile {
     uint32_t limb, blk, m0, m1;       // members [m0, m1) of group (limb, blk)
 };
-D2_DEV TailTile tail_tile(uint32_t i, uint32_t grid, uint32_t B, uint32_t nblk)
+D2_DEV TailTile tail_tile(uint32_t i, uint32_t grid, uint32_t B, uint32_t tiles, uint32_t wpg, uint32_t nblk)
 {
-    const uint32_t wpg = (B + TAIL_TILES - 1) / TAIL_TILES;      // workgroups per group
     uint32_t slot = i;
     if ((grid & 7u) == 0) slot = (i & 7u) * (grid >> 3) + (i >> 3);
     const uint32_t group = slot / wpg, part = slot % wpg;
@@ -417,21 +415,21 @@ D2_DEV TailTile tail_tile(uint32_t i, uint32_t grid, uint32_t B, uint32_t nblk)
     TailTile t;
     t.limb = wave_uniform(group / nblk);
     t.blk = wave_uniform(group % nblk);
-    t.m0 = wave_uniform(part * TAIL_TILES);
-    t.m1 = t.m0 + TAIL_TILES < B ? t.m0 + TAIL_TILES : B;
+    t.m0 = wave_uniform(part * tiles);
+    t.m1 = t.m0 + tiles < B ? t.m0 + tiles : B;
     return t;
 }
 
-// grid = L * 2^(LOGN - LOGB) * ceil(B / TAIL_TILES)
+// grid = L * 2^(LOGN - LOGB) * wpg, wpg = ceil(B / tiles) workgroups per group
 template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_tail_forward(uint64_t *polys, const LimbTab *tabs, uint32_t L,
-                                                        uint32_t B)
+                                                        uint32_t B, uint32_t tiles, uint32_t wpg)
 {
     typedef typename ENG::A A;
     constexpr int E = ENG::E;
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     const int tid = threadIdx.x;
-    const TailTile tt = tail_tile(blockIdx.x, gridDim.x, B, 1u << (ENG::LOGN - ENG::LOGB));
+    const TailTile tt = tail_tile(blockIdx.x, gridDim.x, B, tiles, wpg, 1u << (ENG::LOGN - ENG::LOGB));
     if (tt.limb >= L || tt.m0 >= tt.m1) return;
     const LimbTab tb = load_tab(tabs, tt.limb);
     const typename A::Mod md = A::mod(tb.q, tb.one_s);
@@ -459,13 +457,13 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_tail_forward(uint64_t *p
 
 template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_tail_inverse(uint64_t *polys, const LimbTab *tabs, uint32_t L,
-                                                        uint32_t B)
+                                                        uint32_t B, uint32_t tiles, uint32_t wpg)
 {
     typedef typename ENG::A A;
     constexpr int E = ENG::E;
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     const int tid = threadIdx.x;
-    const TailTile tt = tail_tile(blockIdx.x, gridDim.x, B, 1u << (ENG::LOGN - ENG::LOGB));
+    const TailTile tt = tail_tile(blockIdx.x, gridDim.x, B, tiles, wpg, 1u << (ENG::LOGN - ENG::LOGB));
     if (tt.limb >= L || tt.m0 >= tt.m1) return;
     const LimbTab tb = load_tab(tabs, tt.limb);
     const typename A::Mod md = A::mod(tb.q, tb.one_s);

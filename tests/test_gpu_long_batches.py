@@ -1,0 +1,32 @@
+"""Batches of the transforms that take two kernels: how many members a workgroup walks through depends on the batch (one where
+the chip has room, up to sixteen), so every batch is compared with its members transformed one by one."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import oracle as O
+
+from gpu_util import dzeros, make_ctx
+
+
+# members to a workgroup: 1, 2 (remainder), 3, 4, 6, 8 (remainder), 12, 16
+@pytest.mark.parametrize("bits,log2n,L,B", [(54, 15, 2, 31), (60, 15, 3, 37), (36, 15, 8, 24), (30, 16, 1, 97), (54, 16, 2, 90),
+                                            (60, 16, 1, 251), (36, 15, 7, 96), (44, 16, 16, 32)])
+def test_batch_equals_members(bits, log2n, L, B):
+    ctx = make_ctx(log2n, O.find_primes(bits, log2n, L), 0, seed=3)
+    words = L << log2n
+    batch = dzeros(B * words)
+    ctx.bench_polys(batch, B)
+    single, first = batch.clone(), batch.clone()
+    ctx.ntt_forward(batch, B)
+    for b in range(B):
+        ctx.ntt_forward(single[b * words:], 1)
+    assert torch.equal(batch, single), "forward"
+    ctx.ntt_inverse(batch, B)
+    for b in range(B):
+        ctx.ntt_inverse(single[b * words:], 1)
+    assert torch.equal(batch, single), "inverse"
+    assert torch.equal(batch, first), "there and back"
+    torch.cuda.synchronize()
+    ctx.close()
