@@ -1235,9 +1235,10 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
     // Shares that fit the caches may still be there, or be wanted again; a launch that fills the chip is faster without
     // leaving them there.  Kept and streamed, N = 4096, 36 bits, 3 limbs, shares read again / made just before: 25 indices of five
     // members (14 MB) 22.0 / 24.8 and 27.5 / 27.8 us, 128 of twelve (156 MB) 35.8 / 44.2 and 48.6 / 47.8, 256 of twelve (312 MB)
-    // 64.4 / 61.2 and 72.5 / 65.6; N = 2048, 256 of two (48 MB) 19.8 / 18.3 and 23.4 / 22.5.
+    // 64.4 / 61.2 and 72.5 / 65.6; N = 2048, 256 of two (48 MB) 19.8 / 18.3 and 23.4 / 22.5.  With 16 coefficients per thread the
+    // second loop spills (N = 2^14, 60 bits, 160 of five with both 129, streamed only 115 us).
     const uint32_t units = gridDim.x * gridDim.y;
-    const bool stream = units > 128 || (uint64_t)units * (K + 1) * share_ct > (192u << 20) / 8;
+    const bool stream = E > 8 || units > 128 || (uint64_t)units * (K + 1) * share_ct > (192u << 20) / 8;
     // (a zero of its own: shared with the limb counter's it would move the counter, and with it every buffer
     // descriptor, to vector registers)
     const uint32_t zero = opaque(0u);
