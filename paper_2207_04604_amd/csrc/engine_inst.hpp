@@ -92,10 +92,34 @@ struct Launch {
     {
         const uint32_t L = ctx->L, polys_n = B * L;
         if constexpr (ENG::LOGB == ENG::LOGN) {
+            // One workgroup to a compute unit: N = 8192 with multiplicands of four registers (more than 64 registers to a
+            // thread), N = 2^14 always, where those of two leave room for the next polynomial.  One by one and walking, us, 537 MB and
+            // 134 MB:  N = 8192, 54 bits forward 278 / 261, 68.4 / 61.4, inverse 385 / 336, 85 / 79;  60 bits 302 / 298, 73.4 / 70.3,
+            // 405 / 345, 90 / 81;  N = 2^14, 36 bits 278 / 254, 71.7 / 60.6, 344 / 326, 86 / 76;  30 bits 267 / 245, 67.6 / 56.4,
+            // 415 / 289, 80 / 67.  Two to a unit (N = 8192, 36 bits) 261 / 266, 254 / 314; spilling (N = 2^14, 54 bits) 288 / 365, 360 / 449.
+            // Forward transforms with Shoup quotients gain nothing (54 bits, 300 polynomials 19.4 / 19.2, 420 20.3 / 21.2; inverse 25.9 /
+            // 24.3, 27.5 / 26.6).
+            constexpr bool WALK_INV = (ENG::LOGN == 13 && sizeof(typename ENG::Twid) > 8) || (ENG::LOGN == 14 && sizeof(typename ENG::Twid) <= 8);
+            constexpr bool WALK_FWD = WALK_INV && (ENG::LOGN == 14 || ENG::A::KIND >= 4);
+            const dim3 walk(256 / L * L), block(ENG::T);
+            if constexpr (WALK_FWD) {
+                if (forward && polys_n > 256) {
+                    hipLaunchKernelGGL((k_ntt_walk<ENG, false>), walk, block, 0, st, polys, ctx->d_tabs, L, polys_n);
+                    D2_LAUNCHED(ctx);
+                    return D2MHE_OK;
+                }
+            }
+            if constexpr (WALK_INV) {
+                if (!forward && polys_n > 256) {
+                    hipLaunchKernelGGL((k_ntt_walk<ENG, true>), walk, block, 0, st, polys, ctx->d_tabs, L, polys_n);
+                    D2_LAUNCHED(ctx);
+                    return D2MHE_OK;
+                }
+            }
             if (forward)
-                hipLaunchKernelGGL(k_ntt_forward<ENG>, dim3(polys_n), dim3(ENG::T), 0, st, polys, ctx->d_tabs, L);
+                hipLaunchKernelGGL(k_ntt_forward<ENG>, dim3(polys_n), block, 0, st, polys, ctx->d_tabs, L);
             else
-                hipLaunchKernelGGL(k_ntt_inverse<ENG>, dim3(polys_n), dim3(ENG::T), 0, st, polys, ctx->d_tabs, L);
+                hipLaunchKernelGGL(k_ntt_inverse<ENG>, dim3(polys_n), block, 0, st, polys, ctx->d_tabs, L);
             D2_LAUNCHED(ctx);
         } else {
             // head: top stages across blocks; tail: the block-local stages.  The batch is walked in

@@ -317,6 +317,39 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_ntt_inverse(uint64_t *po
     for (int k = 0; k < ENG::E; ++k) p[ENG::coef_pos(k, tid)] = A::canon_inv(x[k], md);
 }
 
+// The same where there is more than one polynomial to a workgroup and one workgroup fills a compute unit: without a
+// second one nothing overlaps loads with butterflies, so every workgroup walks through the polynomials of its limb with the
+// next one's words already requested.  grid: a multiple of L.  See the rule in Launch::ntt.
+template <class ENG, bool INV>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_ntt_walk(uint64_t *polys, const LimbTab *tabs, uint32_t L, uint32_t total)
+{
+    typedef typename ENG::A A;
+    constexpr int E = ENG::E;
+    __shared__ uint64_t lds[ENG::LDS_WORDS];
+    const int tid = threadIdx.x;
+    const uint32_t lane = 8u * (uint32_t)tid;
+    const LimbTab tb = load_tab(tabs, blockIdx.x % L);
+    const typename A::Mod md = A::mod(tb.q, tb.one_s);
+    const size_t stride = (size_t)gridDim.x * ENG::NB;
+    uint64_t *p = polys + (size_t)blockIdx.x * ENG::NB;
+    uint64_t nx[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) nx[k] = ld64(p, lane, 8u * ENG::T * k);
+    for (uint32_t i = blockIdx.x; i < total; i += gridDim.x, p += stride) {
+        typename A::elem x[E];
+#pragma unroll
+        for (int k = 0; k < E; ++k) x[k] = INV ? A::inv_input(nx[k], md) : A::from_canon(nx[k], md);
+        if (total - i > gridDim.x) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) nx[k] = ld64(p + stride, lane, 8u * ENG::T * k);
+        }
+        if constexpr (INV) ENG::template inverse<true>(x, lds, tid, 0, tb.inv, md, A::tw(tb.ninv), A::tw(tb.wn));
+        else ENG::forward(x, lds, tid, 0, tb.fwd, md);
+#pragma unroll
+        for (int k = 0; k < E; ++k) st64(p, lane, 8u * ENG::T * k, INV ? A::canon_inv(x[k], md) : A::canon_fwd(x[k], md));
+    }
+}
+
 // -------------------------------------------------------------------------------------
 // Transforms longer than one workgroup can hold: the top LOGH = LOGN - LOGB stages couple
 // the 2^LOGH blocks of NB coefficients ("head", register-only, strided global access); the

@@ -1,5 +1,6 @@
-"""Batches of the transforms that take two kernels: how many members a workgroup walks through depends on the batch (one where
-the chip has room, up to sixteen), so every batch is compared with its members transformed one by one."""
+"""Batches of transforms: how many polynomials a workgroup walks through depends on the batch (in the transforms of two kernels
+one member where the chip has room, up to sixteen; N = 8192 and 2^14 more than one beyond 256 polynomials), so every batch is
+compared with its members transformed one by one."""
 import pytest
 import torch
 
@@ -12,7 +13,8 @@ from gpu_util import dzeros, make_ctx
 
 # members to a workgroup: 1, 2 (remainder), 3, 4, 6, 8 (remainder), 12, 16
 @pytest.mark.parametrize("bits,log2n,L,B", [(54, 15, 2, 31), (60, 15, 3, 37), (36, 15, 8, 24), (30, 16, 1, 97), (54, 16, 2, 90),
-                                            (60, 16, 1, 251), (36, 15, 7, 96), (44, 16, 16, 32)])
+                                            (60, 16, 1, 251), (36, 15, 7, 96), (44, 16, 16, 32),
+                                            (54, 13, 1, 257), (60, 13, 7, 75), (36, 14, 3, 171), (30, 14, 16, 17)])
 def test_batch_equals_members(bits, log2n, L, B):
     ctx = make_ctx(log2n, O.find_primes(bits, log2n, L), 0, seed=3)
     words = L << log2n
