@@ -183,27 +183,37 @@ struct Launch {
         return D2MHE_OK;
     }
 
+    template <class E, int FROM>
+    static void launch_encrypt(d2mhe_ctx *ctx, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint64_t n_values, uint32_t C,
+                               float fixed, hipStream_t st)
+    {
+        const uint64_t n = (uint64_t)C * njobs;
+        if constexpr (E::E == 8) {
+            const uint32_t L = ctx->L;
+            if ((n << E::LOGP) * 2 * L <= 256) {
+                hipLaunchKernelGGL((k_encrypt<E, FROM, true>), dim3(C << E::LOGP, njobs, 2 * L), dim3(E::T), 0, st, jobs, ct_base,
+                                   1u | 1u << 16, n_values, ctx->d_tabs, ctx->rc);
+                return;
+            }
+        }
+        const LimbSplit sp = split<E>(ctx, n, fixed);
+        hipLaunchKernelGGL((k_encrypt<E, FROM>), dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, n_values,
+                           ctx->d_tabs, ctx->rc);
+    }
+
     static d2mhe_status encrypt(d2mhe_ctx *ctx, int from, const RoundJobs &jobs, uint32_t njobs,
                                 uint32_t ct_base, uint64_t n_values, uint32_t C, hipStream_t st)
     {
         if (from == FROM_VECTOR) {
             if constexpr (HALVES) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
-            else {
-                const LimbSplit sp = split<ENG>(ctx, (uint64_t)C * njobs, ctx->rc.coeff_packing ? SAMPLES : SAMPLES + ENCODING);
-                hipLaunchKernelGGL((k_encrypt<ENG, FROM_VECTOR>), dim3(C, njobs, sp.parts), dim3(ENG::T), 0, st, jobs, ct_base,
-                                   sp.word, n_values, ctx->d_tabs, ctx->rc);
-            }
+            else
+                launch_encrypt<ENG, FROM_VECTOR>(ctx, jobs, njobs, ct_base, n_values, C,
+                                                 ctx->rc.coeff_packing ? SAMPLES : SAMPLES + ENCODING, st);
         } else {
             choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
                 typedef typename decltype(shape)::type E;
-                const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
-                const dim3 grid(C << E::LOGP, njobs, sp.parts), block(E::T);
-                if (from == FROM_WORDS32)
-                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS32>), grid, block, 0, st, jobs, ct_base, sp.word, n_values, ctx->d_tabs,
-                                       ctx->rc);
-                else
-                    hipLaunchKernelGGL((k_encrypt<E, FROM_WORDS64>), grid, block, 0, st, jobs, ct_base, sp.word, n_values, ctx->d_tabs,
-                                       ctx->rc);
+                if (from == FROM_WORDS32) launch_encrypt<E, FROM_WORDS32>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, st);
+                else launch_encrypt<E, FROM_WORDS64>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, st);
             });
         }
         D2_LAUNCHED(ctx);

@@ -273,9 +273,9 @@ D2_DEV uint32_t launch_part()
     return 0;                           // a host build that runs the kernels takes polynomials whole
 #endif
 }
-D2_DEV LimbRange limb_range(uint32_t split, uint32_t L)
+D2_DEV LimbRange limb_range(uint32_t split, uint32_t L, uint32_t z)
 {
-    const uint32_t z = launch_part(), head = split & 0xffffu, rest = split >> 16;
+    const uint32_t head = split & 0xffffu, rest = split >> 16;
     const uint32_t first = z ? head + (z - 1) * rest : 0, end = first + (z ? rest : head);
     return LimbRange{first, end < L ? end : L};
 }
@@ -936,7 +936,11 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
 // FROM says what a job's source is: plaintext polynomials [C][N], the same in 32-bit words (k_encode_parties), or the
 // member's gradient, encoded on the fly.
 // -------------------------------------------------------------------------------------
-template <class ENG, int FROM>
+// TWO: a workgroup for either component, two to a part.  Both make NTT(mu), but only the first encodes the vector and neither does
+// three transforms: for launches that leave every workgroup a compute unit of its own.  One workgroup / two:
+// N = 1024, 30 bits, 16 indices 7.2 / 5.9 us, N = 4096, 36 bits, 3 limbs, 32 12.1 / 9.8, N = 8192, 54 bits, 1 limb, 60 28.1 / 22.8; but
+// 60 of N = 4096 (360 workgroups) 12.2 / 14.8.
+template <class ENG, int FROM, bool TWO = false>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, uint32_t ct_base, uint32_t split, uint64_t n_values,
                                                     const LimbTab *tabs, RoundConst rc)
 {
@@ -960,6 +964,9 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     const uint64_t *pk = job.key;
     const size_t LN = (size_t)L * ENG::N;
     uint64_t *out = job.out + (size_t)c * 2 * LN;
+    static_assert(!TWO || E <= 8, "NTT(mu) is parked where the other component goes");
+    const uint32_t part = launch_part();
+    const bool first = !TWO || (part & 1u) == 0, second = !TWO || (part & 1u) != 0;     // components to make
 
     // With two buffers the samples are staged in the second one, next to the encoding in the first:
     // one barrier then makes them visible and also ends the encoding's reads of the first buffer,
@@ -973,7 +980,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     constexpr int MS = SUMMED ? 2 : 1;
     uint32_t m[MS][E];
     if constexpr (FROM == FROM_VECTOR) {
-        encode_to_regs<ENG>(m[0], lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
+        if (first)
+            encode_to_regs<ENG>(m[0], lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
     } else {
         typedef typename std::conditional<FROM == FROM_WORDS32, uint32_t, uint64_t>::type word;
         const word *pt = (const word *)job.src + (size_t)c * ENG::N;
@@ -1003,7 +1011,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     }
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
-    const LimbRange lr = limb_range(split, L);
+    const LimbRange lr = limb_range(split, L, TWO ? part >> 1 : part);
     for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
@@ -1027,45 +1035,49 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
             for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
         }
         elem x[E];
-        if constexpr (SUMMED) {
-            uint32_t mm[2][E];
-            int32_t e[2][E];
-            if constexpr (!OWN_E0) {
-                smp.template get<1>(e);
-            } else {
+        if (first) {
+            if constexpr (SUMMED) {
+                uint32_t mm[2][E];
+                int32_t e[2][E];
+                if constexpr (!OWN_E0) {
+                    smp.template get<1>(e);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int k = 0; k < E; ++k) e[j][k] = sbyte(opaque(e0[j][k / 4]), k % 4);
+                }
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int k = 0; k < E; ++k) e[j][k] = sbyte(opaque(e0[j][k / 4]), k % 4);
+                    for (int k = 0; k < E; ++k) mm[j][k] = opaque(m[j][k]);
+                auto at = [&](int j, int k, uint32_t &m_jk, int32_t &e_jk) {
+                    m_jk = mm[j][k];
+                    e_jk = e[j][k];
+                };
+                ENG::forward_chained_encoded(at, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
+            } else {
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    int32_t e;
+                    if constexpr (OWN_E0) e = sbyte(opaque(e0[0][k / 4]), k % 4);
+                    else e = sbyte(opaque(smp.w[k]), 1);
+                    x[k] = A::add_small(A::mul_u32(opaque(m[0][k]), lam, md), e, md);
+                }
+                ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
             }
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int k = 0; k < E; ++k) mm[j][k] = opaque(m[j][k]);
-            auto at = [&](int j, int k, uint32_t &m_jk, int32_t &e_jk) {
-                m_jk = mm[j][k];
-                e_jk = e[j][k];
-            };
-            ENG::forward_chained_encoded(at, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                int32_t e;
-                if constexpr (OWN_E0) e = sbyte(opaque(e0[0][k / 4]), k % 4);
-                else e = sbyte(opaque(smp.w[k]), 1);
-                x[k] = A::add_small(A::mul_u32(opaque(m[0][k]), lam, md), e, md);
-            }
-            ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
         }
         typename A::Factor f[E];
         if (!STASH) {
 #pragma unroll
             for (int k = 0; k < E; ++k) f[k] = A::factor(u[k], md);
         }
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, el, md);
-        smp.template get<2>(sv);
-        ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
-        mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, el, md);
+        if (first) mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, el, md);
+        if (second) {
+            smp.template get<2>(sv);
+            ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
+            mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, el, md);
+        }
     }
 }
 
@@ -1091,7 +1103,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     static_assert(SMALL_LDS_WORDS<ENG> <= ENG::LDS_WORDS, "in the buffer the first transform leaves alone");
     small_cbd<ENG>(e, lds, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
     if (ENG::WAVE_CHAIN) __syncthreads();
-    const LimbRange lr = limb_range(split, L);
+    const LimbRange lr = limb_range(split, L, launch_part());
     for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
@@ -1612,7 +1624,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     smp.load(lds32, tid);
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
-    const LimbRange lr = limb_range(split, L);
+    const LimbRange lr = limb_range(split, L, launch_part());
     for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
@@ -1766,7 +1778,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
         }
     // the transforms overwrite the samples: both buffers hold some, or their transforms have no barrier
     if (2 * ENG::LDS_WORDS < 2 * ENG::N || ENG::WAVE_CHAIN) __syncthreads();
-    const LimbRange lr = limb_range(split, L);
+    const LimbRange lr = limb_range(split, L, launch_part());
     for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;

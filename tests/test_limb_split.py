@@ -19,12 +19,12 @@ def test_every_limb_in_one_part(tmp_path):
 
 
 # C indices at once (whole polynomials, or other parts) against runs of `part` of them (one limb, two, or all but one or two to a
-# workgroup): every word
+# workgroup; either component of a ciphertext by itself): every word
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits,log2n,L,C,part", [
     (30, 10, 3, 2050, 205), (54, 10, 6, 2050, 41), (36, 11, 5, 1024, 128), (60, 11, 2, 1024, 64), (44, 12, 3, 512, 150),
     (54, 12, 2, 512, 100), (36, 13, 8, 256, 33), (54, 13, 4, 256, 153), (60, 13, 3, 256, 1), (54, 14, 8, 128, 50),
-    (36, 14, 3, 128, 16),
+    (36, 14, 3, 128, 16), (54, 12, 1, 512, 128), (30, 10, 1, 300, 128), (60, 13, 2, 256, 64), (54, 14, 1, 128, 64),
 ])
 def test_parts_equal_whole_polynomials(bits, log2n, L, C, part):
     from oracle import oracle as O
