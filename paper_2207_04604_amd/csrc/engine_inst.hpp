@@ -67,7 +67,8 @@ struct Launch {
     }
 
     // Members that a workgroup of the tail takes in turn, for `groups` groups of B.  The twiddles it fetches first cost about two
-    // members' time; the workgroups take ceil(W / places) turns of the chip.  Always eight and this, N = 2^16, 60 bits, us:
+    // members' time; the workgroups take ceil(W / places) turns of the chip, and where there are more than two, W / places + 1/2 as they
+    // drift apart (L = 15, B = 37, inverse: sevens, 1,440 workgroups, 225 us, eights, 1,200, 222).  Always eight and this, N = 2^16, 60 bits, us:
     // L = 1, B = 8 32.6 / 12.8;  4, 8 43.9 / 27.8;  4, 16 41.0 / 31.3;  4, 24 46.7 / 41.7;  16, 2 26.0 / 25.5;  N = 2^15, 60 bits:
     // 1, 32 36.0 / 16.2;  4, 16 37.9 / 21.2;  7, 48 75.8 / 67.8.  More than eight gain where they fill a turn of the chip, of N =
     // 2^16 also two, if all are equal (L = 16: B = 32 194 / 176, 48 286 / 273, 64 398 / 383; in part of two, L = 4, B = 200 305 / 317; N = 2^15, L = 16,
@@ -80,8 +81,9 @@ struct Launch {
         for (uint32_t m = 1; m <= 16 && m <= B; ++m) {
             const uint64_t W = (uint64_t)groups * ((B + m - 1) / m), n = (W + PLACES - 1) / PLACES;
             if (m > 8 && n > 1 && !(ENG::LOGN == 16 && n == 2 && B % m == 0 && 16 * W >= 15 * 2 * PLACES)) continue;
-            if (n * (m + 2) <= least) {
-                least = n * (m + 2);
+            const uint64_t time = (n > 2 ? 2 * W + PLACES : 2 * n * PLACES) * (m + 2);
+            if (time <= least) {
+                least = time;
                 best = m;
             }
         }
