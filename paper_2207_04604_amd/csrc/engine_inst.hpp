@@ -328,9 +328,28 @@ struct Launch {
         return D2MHE_OK;
     }
 
+    // Up to how many indices the limbs of refreshed ciphertexts go in a launch of their own.  Measured, us in one launch / in two,
+    // 32, 64, 128 and 200 indices by seven members:
+    //   N = 8192, 54 bits, four limbs 119 / 92, 145 / 114, 158 / 146, 186 / 203;  two 62 / 57, 64 / 63, 87 / 86, 102 / 114;  one 33 / 39
+    //   N = 4096, 36 bits, three limbs 45 / 37, 46 / 42, 51 / 57, 79 / 84;  eight 116 / 86, 147 / 110, 161 / 145, 192 / 196
+    //   N = 2048, 54 bits, six limbs 66 / 46, 67 / 54, 69 / 64, 84 / 83;  N = 1024, 30 bits, two limbs 15 / 15, 15 / 15, 16 / 16, 21 / 21
+    //   N = 2^14, 36 bits, two limbs 140 / 113, 145 / 120, 158 / 144, 186 / 203
+    static uint32_t refresh_apart(const d2mhe_ctx *ctx)
+    {
+        const uint32_t L = ctx->L;
+        return L >= 4 || (L > 1 && ENG::LOGN == 14) ? 128 : L == 3 ? 85 : L == 2 && ENG::LOGN > 10 ? 32 : 0;
+    }
     static d2mhe_status bootstrap_combine(d2mhe_ctx *ctx, const uint64_t *ct, const PtrList &shares, uint32_t K,
                                           const uint64_t *alpha, uint32_t C, uint64_t *ct_out, hipStream_t st)
     {
+        if (C <= refresh_apart(ctx)) {
+            hipLaunchKernelGGL(k_bootstrap_round<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, shares, K, ct_out, ctx->d_tabs, ctx->rc);
+            D2_LAUNCHED(ctx);
+            hipLaunchKernelGGL(k_bootstrap_refresh<ENG>, dim3(C, ctx->L), dim3(ENG::T), 0, st, shares, K, alpha, ct_out, ctx->d_tabs,
+                               ctx->rc);
+            D2_LAUNCHED(ctx);
+            return D2MHE_OK;
+        }
         hipLaunchKernelGGL(k_bootstrap_combine<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, shares, K, alpha, ct_out,
                            ctx->d_tabs, ctx->rc);
         D2_LAUNCHED(ctx);

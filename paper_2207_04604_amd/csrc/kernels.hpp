@@ -1258,7 +1258,40 @@ D2_DEV uint32_t round_mod_t(uint32_t acc_int, uint64_t acc_frac, uint32_t t)
     return v >= t ? v - t : v;
 }
 
-enum { COMBINE_COLLECTIVE = 0, COMBINE_CONVERT = 1, COMBINE_BOOTSTRAP = 2 };
+enum { COMBINE_COLLECTIVE = 0, COMBINE_CONVERT = 1, COMBINE_BOOTSTRAP = 2, COMBINE_REFRESH = 3 };
+
+// One limb of a refreshed ciphertext from the rounded plaintext, which sits where a forward transform takes its input:
+// c0' = NTT(Lambda x) + sum eta1_k, c1' = alpha.  second(j): this limb of the j-th member's eta1.
+template <class ENG, class SH>
+D2_DEV void refresh_limb(uint64_t *lds, const uint32_t (&m)[ENG::E], int tl, const LimbTab &tb, SH second, uint32_t K,
+                         const uint64_t *alpha, uint64_t *c0, uint64_t *c1, bool stream)
+{
+    typedef typename ENG::A A;
+    typedef Pairs<ENG> PR;
+    constexpr int E = ENG::E;
+    const uint64_t q = tb.q;
+    const typename A::Mod md = A::mod(q, tb.one_s);
+    const typename A::Twid lam = A::tw(tb.lambda);
+    typename A::elem x[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) x[k] = A::mul_u32(opaque(m[k]), lam, md);
+    ENG::forward(x, lds, tl, 0, tb.fwd, md);
+    const uint32_t lp = PR::lane(tl, 0);
+#pragma unroll
+    for (int k0 = 0; k0 < E; k0 += PR::B) {
+        uint64_t v[PR::B];
+#pragma unroll
+        for (int k = 0; k < PR::B; ++k) v[k] = A::canon_fwd(x[k0 + k], md);
+        PR::swap(v, tl);
+        if (stream) PR::template add<true, false>(v, second, K, lp, k0, q);
+        else PR::template add<false, false>(v, second, K, lp, k0, q);
+        PR::reduce(v, K, md, q);
+        PR::store(c0, v, lp, k0);
+        PR::template load<false>(v, alpha, lp, k0);
+        PR::store(c1, v, lp, k0);
+    }
+}
+
 template <class ENG, bool DECODE, int MODE, class SH>
 D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_t K, const uint64_t *aux,
                          bool keep_c1, uint64_t *pt, float *out, uint64_t n_values, const LimbTab *tabs,
@@ -1345,35 +1378,20 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
 #pragma unroll
     for (int k = 0; k < E; ++k) m[k] = round_mod_t(acc_int[k], acc_frac[k], t);
     if constexpr (MODE == COMBINE_BOOTSTRAP) {
-        // x sits where a forward transform takes its input: c0' = NTT(Lambda x) + sum eta1_k, c1' = alpha
         uint64_t *ct_out = pt + (size_t)c * 2 * LN;
         const uint64_t *alpha = aux + (size_t)c * LN;
         for (uint32_t limb = 0; limb < L; ++limb) {
-            const LimbTab tb = load_tab(tabs, limb);
-            const uint64_t q = tb.q;
-            const typename A::Mod md = A::mod(q, tb.one_s);
-            const typename A::Twid lam = A::tw(tb.lambda);
             const size_t off = (size_t)limb * ENG::NB;
-            const int tl = opaque(tid);
-            typename A::elem x[E];
+            refresh_limb<ENG>(lds, m, opaque(tid), load_tab(tabs, limb),
+                              [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + LN + off; }, K, alpha + off, ct_out + off,
+                              ct_out + LN + off, stream);
+        }
+    } else if constexpr (MODE == COMBINE_REFRESH) {
+        // a copy for the workgroup of every limb, where that will put its c0'
+        for (uint32_t limb = 0; limb < L; ++limb) {
+            uint32_t *x = (uint32_t *)(pt + (size_t)c * 2 * LN + (size_t)limb * ENG::NB);
 #pragma unroll
-            for (int k = 0; k < E; ++k) x[k] = A::mul_u32(opaque(m[k]), lam, md);
-            ENG::forward(x, lds, tl, 0, tb.fwd, md);
-            const uint32_t lp = PR::lane(tl, 0);
-            auto second = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + LN + off; };
-#pragma unroll
-            for (int k0 = 0; k0 < E; k0 += PR::B) {
-                uint64_t v[PR::B];
-#pragma unroll
-                for (int k = 0; k < PR::B; ++k) v[k] = A::canon_fwd(x[k0 + k], md);
-                PR::swap(v, tl);
-                if (stream) PR::template add<true, false>(v, second, K, lp, k0, q);
-                else PR::template add<false, false>(v, second, K, lp, k0, q);
-                PR::reduce(v, K, md, q);
-                PR::store(ct_out + off, v, lp, k0);
-                PR::template load<false>(v, alpha + off, lp, k0);
-                PR::store(ct_out + LN + off, v, lp, k0);
-            }
+            for (int k = 0; k < E; ++k) x[ENG::coef_pos(k, tid)] = m[k];
         }
     } else if (DECODE) {
         decode_from_regs<ENG>(m, lds, tid, out, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
@@ -1830,6 +1848,33 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_combine(const 
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     combine_body<ENG, false, COMBINE_BOOTSTRAP>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
                                                 alpha, false, ct_out, (float *)nullptr, 0, tabs, rc);
+}
+
+// The same in two launches, for batches that leave compute units idle: the sums of eta0 and the rounding, grid = C, then every limb
+// of the refreshed ciphertexts by itself, grid = (C, L).  One and two, see the rule in Launch::bootstrap_combine.
+template <class ENG>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_round(const uint64_t *ct, PtrList shares, uint32_t K,
+                                                            uint64_t *ct_out, const LimbTab *tabs, RoundConst rc)
+{
+    __shared__ uint64_t lds[ENG::LDS_WORDS];
+    combine_body<ENG, false, COMBINE_REFRESH>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
+                                              (const uint64_t *)nullptr, false, ct_out, (float *)nullptr, 0, tabs, rc);
+}
+template <class ENG>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_refresh(PtrList shares, uint32_t K, const uint64_t *alpha,
+                                                              uint64_t *ct_out, const LimbTab *tabs, RoundConst rc)
+{
+    constexpr int E = ENG::E;
+    __shared__ uint64_t lds[ENG::LDS_WORDS];
+    const int tid = threadIdx.x;
+    const uint32_t c = blockIdx.x, limb = blockIdx.y, L = rc.L;
+    const size_t LN = (size_t)L * ENG::NB, off = (size_t)limb * ENG::NB, at = (size_t)c * 2 * LN + off;
+    uint32_t m[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) m[k] = ((const uint32_t *)(ct_out + at))[ENG::coef_pos(k, tid)];
+    __syncthreads();                                       // they lie where other threads will store
+    refresh_limb<ENG>(lds, m, tid, load_tab(tabs, limb), [&](uint32_t j) { return (const uint64_t *)shares.p[j] + at + LN; }, K,
+                      alpha + (size_t)c * LN + off, ct_out + at, ct_out + LN + at, true);
 }
 
 }  // namespace d2

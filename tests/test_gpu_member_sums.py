@@ -54,3 +54,24 @@ def test_members_equal_their_sum(bits, log2n, L, C, Ks):
         assert torch.equal(got, want), f"refresh by {K}"
     torch.cuda.synchronize()
     ctx.close()
+
+
+# C indices refreshed in one launch against runs of `part` of them (rounding and limbs in a launch each), in place as well
+@pytest.mark.parametrize("bits,log2n,L,C,part", [("30", 11, 2, 64, 32), ("54", 12, 3, 170, 85), ("36", 13, 4, 150, 40), ("60a", 14, 2, 129, 43),
+                                                 ("54", 10, 6, 140, 128)])
+def test_refresh_in_parts(bits, log2n, L, C, part):
+    LN, t, K = L << log2n, 12289 if log2n <= 11 else 65537, 3
+    q = primes_away_from_powers_of_two(int(bits[:-1]), log2n, L) if bits.endswith("a") else O.find_primes(int(bits), log2n, L)
+    ctx = make_ctx(log2n, q, t, f=3, max_group=K, seed=14)
+    words = dzeros((3 + 2 * K) * C * LN)
+    ctx.bench_polys(words, (3 + 2 * K) * C)
+    ct, alpha = words[:2 * C * LN], words[2 * C * LN:3 * C * LN]
+    shares = [words[(3 + 2 * k) * C * LN:(5 + 2 * k) * C * LN] for k in range(K)]
+    whole, parts = dzeros(2 * C * LN), ct.clone()
+    ctx.bootstrap_combine(ct, alpha, shares, C, whole)
+    for c in range(0, C, part):
+        n, at = min(part, C - c), parts[2 * c * LN:]
+        ctx.bootstrap_combine(at, alpha[c * LN:], [s[2 * c * LN:] for s in shares], n, at)
+    assert torch.equal(whole, parts)
+    torch.cuda.synchronize()
+    ctx.close()
