@@ -68,6 +68,26 @@ D2_DEV uint64_t uniform_mod(const Block4 &b, const LimbTab &tb)
     return add_mod(mul_shoup64(hi, tb.pow64.w, tb.pow64.ws, q), mul_shoup64(lo, 1, tb.inv64, q), q);
 }
 
+// The same modulo the plaintext modulus (below 2^30): the words times 2^96, 2^64, 2^32 and 1 modulo t add up to less than 2^64.
+// The masks of refresh shares: 575.6 -> 563.7 us for the refresh above.
+struct UniformT {
+    uint64_t t, inv64;
+    uint32_t p32, p64, p96;
+    D2_DEV explicit UniformT(const LimbTab &tt) : t(tt.q), inv64(tt.inv64)
+    {
+        const uint32_t a = 0u - (uint32_t)tt.one_s * (uint32_t)t;              // one_s = floor(2^32 / t)
+        const uint32_t b = (uint32_t)mul_shoup64((uint64_t)a * a, 1, inv64, t);
+        p32 = wave_uniform(a);
+        p64 = wave_uniform(b);
+        p96 = wave_uniform((uint32_t)mul_shoup64((uint64_t)a * b, 1, inv64, t));
+    }
+    D2_DEV uint32_t operator()(const Block4 &b) const
+    {
+        const uint64_t s = mul32(b.w[3], p96) + (mul32(b.w[2], p64) + (mul32(b.w[1], p32) + b.w[0]));
+        return (uint32_t)mul_shoup64(s, 1, inv64, t);
+    }
+};
+
 struct RoundConst {
     uint64_t t;
     uint32_t L;
@@ -1762,9 +1782,9 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
     const uint64_t *c1 = job.ct + ((size_t)c * 2 + 1) * LN;
     uint64_t *out = job.out + (size_t)c * 2 * LN;
     // staging: words [0, N) the masks, words [N, 2 N) e0 | e1 << 8 (two's complement bytes)
-    const LimbTab tt = load_tab(tabs, L);                 // the entry of the plaintext modulus
+    const UniformT mask(load_tab(tabs, L));               // the entry of the plaintext modulus
     for (int n = tid; n < ENG::N; n += ENG::T)
-        lds32[n] = (uint32_t)uniform_mod(philox4x32_10(n, ct_base + c, party, counter_tag(DOM_BS_M, 0, group), rc.key), tt);
+        lds32[n] = mask(philox4x32_10(n, ct_base + c, party, counter_tag(DOM_BS_M, 0, group), rc.key));
     for (int j = tid; j < ENG::N / 2; j += ENG::T) {
         int32_t e0[2], e1[2];
         cbd2(philox4x32_10(j, ct_base + c, party, counter_tag(DOM_BS_E0, 0, group), rc.key), rc.eta_mask, e0);

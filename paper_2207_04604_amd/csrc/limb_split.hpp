@@ -54,7 +54,7 @@ inline float split_time(uint32_t L, uint32_t n, uint32_t head, uint32_t rest, ui
 //   encryption, 54 bits, N = 8192, 4 limbs   n = 8 69.6 / 24.1 (1 + 1 + 1 + 1), 153 70.2 / 56.0 (3 + 1), 300 139 / 110 (3 + 1)
 //   share       36 bits, N = 4096, 3 limbs   n = 40 11.5 / 6.3 (1 + 1 + 1), 153 11.5 / 8.8 (1 + 1 + 1)
 //   refresh     54 bits, N = 2^14, 8 limbs   n = 16 168 / 49 (by ones), 50 168 / 99 (4 + 4), 153 338 / 274 (6 + 2)
-// Beyond four turns of the chip the last one matters little.
+// (Refresh shares as they were with masks of 1.2 limbs.)  Beyond four turns of the chip the last one matters little.
 inline LimbSplit split_limbs(uint32_t L, uint64_t n, uint32_t resident, float fixed)
 {
     LimbSplit best = {1, L};
