@@ -276,6 +276,17 @@ D2_DEV int opaque(int v)
 }
 D2_DEV uint32_t opaque(uint32_t v) { return (uint32_t)opaque((int)v); }
 
+// A value that is the same in every lane, in a scalar register from here on.  The compiler may keep a loop's counter, and the
+// pointers it derives from it, in vector registers although all lanes agree, and then wraps every buffer access in a loop over the lanes' values
+// (32 of them in k_share<ArithS>: 152 shares, N = 8192, two limbs, 24.7 us; without 21.6).
+D2_DEV uint32_t scalar(uint32_t v)
+{
+#if D2_GCN_ASM
+    asm("" : "+s"(v));
+#endif
+    return v;
+}
+
 // The limbs [first, end) of a workgroup where a launch splits every polynomial over gridDim.z workgroups: `split` holds
 // the limbs of part 0 and, from bit 16, those of each further part.
 struct LimbRange {
@@ -462,9 +473,9 @@ D2_DEV TailTile tail_tile(uint32_t i, uint32_t grid, uint32_t B, uint32_t tiles,
     // the same in every lane (they depend on the workgroup id only): keep them in scalar registers,
     // the divisions above went through the vector ALU
     TailTile t;
-    t.limb = wave_uniform(group / nblk);
-    t.blk = wave_uniform(group % nblk);
-    t.m0 = wave_uniform(part * tiles);
+    t.limb = scalar(wave_uniform(group / nblk));
+    t.blk = scalar(wave_uniform(group % nblk));
+    t.m0 = scalar(wave_uniform(part * tiles));
     t.m1 = t.m0 + tiles < B ? t.m0 + tiles : B;
     return t;
 }
@@ -1028,7 +1039,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, 
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
     const LimbRange lr = limb_range(split, L, TWO ? part >> 1 : part);
-    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
+    for (uint32_t l = lr.first; l < lr.end; ++l) {
+        const uint32_t limb = scalar(l);
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const typename A::Twid lam = A::tw(tb.lambda);
@@ -1120,7 +1132,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_share(RoundJobs jobs, ui
     small_cbd<ENG>(e, lds, tid, DOM_DEC_E, job.party, job.group, ct_base + c, rc);
     if (ENG::WAVE_CHAIN) __syncthreads();
     const LimbRange lr = limb_range(split, L, launch_part());
-    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
+    for (uint32_t l = lr.first; l < lr.end; ++l) {
+        const uint32_t limb = scalar(l);
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const size_t off = (size_t)limb * ENG::N;
@@ -1659,7 +1672,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
 
     const LimbRange lr = limb_range(split, L, launch_part());
-    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
+    for (uint32_t l = lr.first; l < lr.end; ++l) {
+        const uint32_t limb = scalar(l);
         const LimbTab tb = load_tab(tabs, limb);
         const typename A::Mod md = A::mod(tb.q, tb.one_s);
         const size_t off = (size_t)limb * ENG::N;
@@ -1813,7 +1827,8 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_share(ConvJobs
     // the transforms overwrite the samples: both buffers hold some, or their transforms have no barrier
     if (2 * ENG::LDS_WORDS < 2 * ENG::N || ENG::WAVE_CHAIN) __syncthreads();
     const LimbRange lr = limb_range(split, L, launch_part());
-    for (uint32_t limb = lr.first; limb < lr.end; ++limb) {
+    for (uint32_t l = lr.first; l < lr.end; ++l) {
+        const uint32_t limb = scalar(l);
         const LimbTab tb = load_tab(tabs, limb);
         const uint64_t q = tb.q;
         const typename A::Mod md = A::mod(q, tb.one_s);
