@@ -653,9 +653,7 @@ d2mhe_status d2mhe_decrypt(d2mhe_ctx *ctx, const uint64_t *sk, const uint64_t *c
     if (!sk || !ct || !pt) return D2MHE_ERR_NULL;
     if (misaligned(sk) || misaligned(ct) || misaligned(pt)) return D2MHE_ERR_ALIGN;
     if (C == 0) return D2MHE_OK;
-    PtrList none;
-    none.p[0] = nullptr;
-    return engine_ops(ctx)->convert_combine(ctx, ct, none, 0, sk, true, C, pt, (hipStream_t)stream);
+    return engine_ops(ctx)->decrypt(ctx, ct, sk, C, pt, (hipStream_t)stream);
 }
 
 // ---- MBFV.Bootstrap ----------------------------------------------------------------------------

@@ -289,11 +289,9 @@ struct Launch {
         return D2MHE_OK;
     }
 
-    static d2mhe_status convert_combine(d2mhe_ctx *ctx, const uint64_t *ct, const PtrList &shares, uint32_t K,
-                                        const uint64_t *sk, bool keep_c1, uint32_t C, uint64_t *pt, hipStream_t st)
+    static d2mhe_status decrypt(d2mhe_ctx *ctx, const uint64_t *ct, const uint64_t *sk, uint32_t C, uint64_t *pt, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_convert_combine<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, shares, K, sk, keep_c1 ? 1 : 0,
-                           pt, ctx->d_tabs, ctx->rc);
+        hipLaunchKernelGGL(k_decrypt<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, sk, pt, ctx->d_tabs, ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
@@ -361,7 +359,7 @@ struct Launch {
     static EngineOps full()
     {
         return EngineOps{ENG::ELOG, ENG::LOGB, HALVES, &ntt, &keygen, &encode, &decode, &encode_parties, &encrypt, &share,
-                         &combine, &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &convert_combine,
+                         &combine, &combine_decode, finish_or_null(), &receiver_keygen, &convert_share, &decrypt,
                          &convert_combine_decode, &bootstrap_alpha, &bootstrap_share, &bootstrap_combine};
     }
     // transforms only (longer rings)

@@ -276,6 +276,14 @@ D2_DEV int opaque(int v)
 }
 D2_DEV uint32_t opaque(uint32_t v) { return (uint32_t)opaque((int)v); }
 
+// The loads above are issued before anything below.
+D2_DEV void requested()
+{
+#if D2_GCN_ASM
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // A value that is the same in every lane, in a scalar register from here on.  The compiler may keep a loop's counter, and the
 // pointers it derives from it, in vector registers although all lanes agree, and then wraps every buffer access in a loop over the lanes' values
 // (32 of them in k_share<ArithS>: 152 shares, N = 8192, two limbs, 24.7 us; without 21.6).
@@ -1261,11 +1269,11 @@ struct Pairs {
 // parts exactly, fractional parts in 64-bit fixed point (each term is truncated by less
 // than 2^-63, so the rounding is exact unless t y / Q lies within L * 2^-63 of a half-integer).
 // SH(j) returns the share buffer of member j.
-// MODE 1 (MBFV.Convert, Eq. (2)): a share is a pair (h0, h1) [C][2][L][N] and the receiver's
-// single-key decryption is folded in: y = c0 + sum h0_k + (z0 + sum h1_k) sk, where z0 = c1 of
-// `ct` if keep_c1 (plain BFV.Decrypt of `ct` when K = 0) and 0 otherwise (the converted
-// ciphertext drops the old c1).  aux: the receiver's prepared secret key.
-// MODE 2 (MBFV.Bootstrap, Eq. (3)): a share is a pair (eta0, eta1); y = c0 + sum eta0_k is rounded
+// COMBINE_CONVERT (MBFV.Convert, Eq. (2)): a share is a pair (h0, h1) [C][2][L][N] and the receiver's
+// single-key decryption is folded in: y = c0 + sum h0_k + (sum h1_k) sk (the converted ciphertext drops the
+// old c1).  aux: the receiver's prepared secret key.
+// COMBINE_DECRYPT (BFV.Decrypt): y = c0 + c1 sk; no shares.  aux as above.
+// COMBINE_BOOTSTRAP (MBFV.Bootstrap, Eq. (3)): a share is a pair (eta0, eta1); y = c0 + sum eta0_k is rounded
 // to x in R_t, and the refreshed ciphertext (Lambda x + sum eta1_k, alpha) goes to ct_out.
 // aux: alpha [C][L][N] in evaluation form.
 // -------------------------------------------------------------------------------------
@@ -1287,7 +1295,7 @@ D2_DEV uint32_t round_mod_t(uint32_t acc_int, uint64_t acc_frac, uint32_t t)
     return v >= t ? v - t : v;
 }
 
-enum { COMBINE_COLLECTIVE = 0, COMBINE_CONVERT = 1, COMBINE_BOOTSTRAP = 2, COMBINE_REFRESH = 3 };
+enum { COMBINE_COLLECTIVE = 0, COMBINE_CONVERT = 1, COMBINE_BOOTSTRAP = 2, COMBINE_REFRESH = 3, COMBINE_DECRYPT = 4 };
 
 // One limb of a refreshed ciphertext from the rounded plaintext, which sits where a forward transform takes its input:
 // c0' = NTT(Lambda x) + sum eta1_k, c1' = alpha.  second(j): this limb of the j-th member's eta1.
@@ -1323,8 +1331,7 @@ D2_DEV void refresh_limb(uint64_t *lds, const uint32_t (&m)[ENG::E], int tl, con
 
 template <class ENG, bool DECODE, int MODE, class SH>
 D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_t K, const uint64_t *aux,
-                         bool keep_c1, uint64_t *pt, float *out, uint64_t n_values, const LimbTab *tabs,
-                         const RoundConst &rc)
+                         uint64_t *pt, float *out, uint64_t n_values, const LimbTab *tabs, const RoundConst &rc)
 {
     constexpr bool CONVERT = MODE == COMBINE_CONVERT;
     const uint64_t *skr = aux;
@@ -1381,12 +1388,37 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
             }
         };
         auto share = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + off; };
-        uint64_t y[E];
-        sum(y, c0 + off, share);
         typename A::elem x[E];
-        if constexpr (CONVERT) {
+        if constexpr (MODE == COMBINE_DECRYPT) {
+            // The ciphertext's words are requested before anything is multiplied: left alone, the compiler spreads the loads over the products to
+            // save registers.  Left and requested first, 42 indices, N = 2048, eight limbs of 54 bits (ArithS) 49.2 / 43.5 us.
+            // With 16 coefficients per thread they go in batches of eight; there only 32-bit words have registers for more, and ask for two of the
+            // keys with them (196 indices of two limbs 54.8 / 51.9 us).
+#pragma unroll
+            for (int k0 = 0; k0 < E; k0 += 8) {
+                uint64_t z[8], y[8];
+                typename A::Key kv[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) z[k] = ld64_stream(c0 + LN + off, lo, 8u * ENG::T * (k0 + k));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) y[k] = ld64_stream(c0 + off, lo, 8u * ENG::T * (k0 + k));
+                if constexpr (E <= 8) requested();
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    kv[k] = A::key(skr + off, skr + LN + off, lo, 8u * ENG::T * (k0 + k));
+                    if (E > 8 && A::KIND == 3 && k == 1) requested();
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const typename A::elem sum = A::mul_key_add(A::from_canon(z[k], md), kv[k], A::from_canon(y[k], md), md);
+                    x[k0 + k] = A::inv_input(A::canon_acc(sum, md), md);
+                }
+            }
+        } else if constexpr (CONVERT) {
+            uint64_t y[E];
+            sum(y, c0 + off, share);
             uint64_t z[E];
-            sum(z, keep_c1 ? c0 + LN + off : nullptr, [&](uint32_t j) { return share(j) + LN; });
+            sum(z, nullptr, [&](uint32_t j) { return share(j) + LN; });
             typename A::Key kv[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) kv[k] = A::key(skr + off, skr + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * k);
@@ -1396,6 +1428,8 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
                 x[k] = A::inv_input(A::canon_acc(sum, md), md);
             }
         } else {
+            uint64_t y[E];
+            sum(y, c0 + off, share);
 #pragma unroll
             for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
         }
@@ -1437,7 +1471,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine(const uint64_t *
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     combine_body<ENG, false, COMBINE_COLLECTIVE>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
-                                    (const uint64_t *)nullptr, false, pt, (float *)nullptr, 0, tabs, rc);
+                                    (const uint64_t *)nullptr, pt, (float *)nullptr, 0, tabs, rc);
 }
 
 // whole round: grid = (C, groups); the group's shares lie `stride` words apart; decoded floats out
@@ -1449,7 +1483,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine_decode(GroupJobs
     const uint32_t job = gridDim.y - 1 - blockIdx.y;
     const uint64_t *first = jobs.first[job];
     combine_body<ENG, true, COMBINE_COLLECTIVE>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
-                                   jobs.K[job], (const uint64_t *)nullptr, false, (uint64_t *)nullptr,
+                                   jobs.K[job], (const uint64_t *)nullptr, (uint64_t *)nullptr,
                                    (float *)jobs.out[job], n_values, tabs, rc);
 }
 
@@ -1719,19 +1753,18 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_share(ConvJobs j
     }
 }
 
-// The receiver's side of MBFV.Convert fused with BFV.Decrypt(sk_i, .) (Eq. (2)); grid = C.
-// Plaintext polynomials out.  K = 0 and keep_c1: plain single-key decryption of `ct`.
+// BFV.Decrypt(sk_i, .) of ciphertexts under a node's own key; grid = C.  Plaintext polynomials out.
 template <class ENG>
-__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_combine(const uint64_t *ct, PtrList shares, uint32_t K,
-                                                            const uint64_t *skr, int keep_c1, uint64_t *pt,
-                                                            const LimbTab *tabs, RoundConst rc)
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_decrypt(const uint64_t *ct, const uint64_t *skr, uint64_t *pt, const LimbTab *tabs,
+                                                    RoundConst rc)
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
-    combine_body<ENG, false, COMBINE_CONVERT>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K, skr,
-                                   keep_c1 != 0, pt, (float *)nullptr, 0, tabs, rc);
+    combine_body<ENG, false, COMBINE_DECRYPT>(lds, ct, [](uint32_t) { return (const uint64_t *)nullptr; }, 0, skr, pt, (float *)nullptr,
+                                              0, tabs, rc);
 }
 
-// whole round: grid = (C, receivers of all groups); decoded floats out
+// The receiver's side of MBFV.Convert fused with BFV.Decrypt(sk_i, .) (Eq. (2)), whole round:
+// grid = (C, receivers of all groups); decoded floats out
 template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_combine_decode(RecvJobs jobs, size_t stride,
                                                                    uint64_t n_values, const LimbTab *tabs,
@@ -1741,7 +1774,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_combine_decode(R
     const uint32_t job = gridDim.y - 1 - blockIdx.y;
     const uint64_t *first = jobs.first[job];
     combine_body<ENG, true, COMBINE_CONVERT>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
-                                  jobs.K[job], jobs.sk[job], false, (uint64_t *)nullptr, (float *)jobs.out[job],
+                                  jobs.K[job], jobs.sk[job], (uint64_t *)nullptr, (float *)jobs.out[job],
                                   n_values, tabs, rc);
 }
 
@@ -1878,7 +1911,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_combine(const 
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     combine_body<ENG, false, COMBINE_BOOTSTRAP>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
-                                                alpha, false, ct_out, (float *)nullptr, 0, tabs, rc);
+                                                alpha, ct_out, (float *)nullptr, 0, tabs, rc);
 }
 
 // The same in two launches, for batches that leave compute units idle: the sums of eta0 and the rounding, grid = C, then every limb
@@ -1889,7 +1922,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_round(const ui
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     combine_body<ENG, false, COMBINE_REFRESH>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
-                                              (const uint64_t *)nullptr, false, ct_out, (float *)nullptr, 0, tabs, rc);
+                                              (const uint64_t *)nullptr, ct_out, (float *)nullptr, 0, tabs, rc);
 }
 template <class ENG>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_bootstrap_refresh(PtrList shares, uint32_t K, const uint64_t *alpha,

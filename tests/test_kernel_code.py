@@ -1,7 +1,7 @@
 """What the compiler made of the kernels (built library, no GPU)."""
 import re
 
-from kernel_code import instructions
+from kernel_code import instructions, registers
 
 # A buffer access whose base address is in vector registers is wrapped in a loop over the different values that the lanes hold.
 LOOP_OVER_VALUES = r"s_xor_b64 exec, exec, [^\n]*\n[^\n]*s_cbranch_execnz"
@@ -11,3 +11,11 @@ def test_base_addresses_are_in_scalar_registers():
     loops = instructions(lambda body: len(re.findall(LOOP_OVER_VALUES, body)))
     assert len(loops) > 500 and any("ArithS, 13" in k for k in loops)
     assert not {k: n for k, n in loops.items() if n}
+
+
+def test_single_key_decryption_has_room():
+    """It adds up no shares: its registers are not those of the kernels that do."""
+    spilled = {k: v[1] for k, v in registers().items() if k.startswith("k_decrypt<")}
+    assert len(spilled) == 30                       # five ring degrees on six back-ends
+    # N = 2^14 (16 coefficients per thread): sums and accumulators of 24 spilled registers at most
+    assert not {k: n for k, n in spilled.items() if n > (24 if ", 14, 4," in k else 0)}
