@@ -1219,27 +1219,26 @@ struct Pairs {
         for (int k = 0; k < B; ++k) s[k] = A::sum_end(s[k], md);
     }
     // s + the sum of K polynomials, at(j) being the j-th, all canonical and in loaded order (s: up to 65 terms, not reduced
-    // where the policy puts that off).  RING: the words of two members are always under way; else those of three are requested
+    // where the policy puts that off).  RING: the words of two members are always under way; else those of DEPTH are requested
     // together and then added, for kernels that have no registers for the other.  RING against three together, combine of
     // N = 4096, 36 bits, 3 limbs: 512 indices, two members 41.0 / 40.5 us, twelve 113.6 / 112.2; 400, five 51.5 / 54.1; N = 8192,
     // 54 bits, 4 limbs, 400 of two 112.9 / 120.5 us.
-    template <bool STREAM, bool RING, class AT>
+    template <bool STREAM, bool RING, int DEPTH = (ENG::E > 8 ? 2 : 3), class AT>
     D2_DEV static void add(uint64_t (&s)[B], AT at, uint32_t K, uint32_t lo, int k0, uint64_t q)
     {
         typedef typename ENG::A A;
         if constexpr (RING) {
-            constexpr int DEPTH = 2;
-            uint64_t v[DEPTH][B];
+            uint64_t v[2][B];
 #pragma unroll
-            for (int d = 0; d < DEPTH; ++d)
+            for (int d = 0; d < 2; ++d)
                 if ((uint32_t)d < K) load<STREAM>(v[d], at(d), lo, k0);
-            for (uint32_t j = 0; j < K; j += DEPTH) {
+            for (uint32_t j = 0; j < K; j += 2) {
 #pragma unroll
-                for (int d = 0; d < DEPTH; ++d) {
+                for (int d = 0; d < 2; ++d) {
                     if (j + d < K) {
 #pragma unroll
                         for (int k = 0; k < B; ++k) s[k] = A::sum(s[k], v[d][k], q);
-                        if (j + d + DEPTH < K) load<STREAM>(v[d], at(j + d + DEPTH), lo, k0);
+                        if (j + d + 2 < K) load<STREAM>(v[d], at(j + d + 2), lo, k0);
                     }
                 }
             }
@@ -1254,11 +1253,10 @@ struct Pairs {
 #pragma unroll
                     for (int k = 0; k < B; ++k) s[k] = A::sum(s[k], v[d][k], q);
             };
-            constexpr int DEPTH = ENG::E > 8 ? 2 : 3;
             uint32_t j = 0;
             for (; j + DEPTH <= K; j += DEPTH) batch(j, std::integral_constant<int, DEPTH>());
             if (DEPTH > 2 && K - j == 2) batch(j, std::integral_constant<int, 2>());
-            else if (j < K) batch(j, std::integral_constant<int, 1>());
+            else if (DEPTH > 1 && j < K) batch(j, std::integral_constant<int, 1>());
         }
     }
 };
@@ -1333,7 +1331,6 @@ template <class ENG, bool DECODE, int MODE, class SH>
 D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_t K, const uint64_t *aux,
                          uint64_t *pt, float *out, uint64_t n_values, const LimbTab *tabs, const RoundConst &rc)
 {
-    constexpr bool CONVERT = MODE == COMBINE_CONVERT;
     const uint64_t *skr = aux;
     typedef typename ENG::A A;
     constexpr int E = ENG::E;
@@ -1367,26 +1364,6 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
         const size_t off = (size_t)limb * ENG::NB;
         const int tl = opaque(tid);
         const uint32_t lo = 8u * (uint32_t)tl, lp = PR::lane(tl, 0);
-        // `from` (none: zero) and a polynomial of every member
-        auto sum = [&](uint64_t (&s)[E], const uint64_t *from, auto at) {
-#pragma unroll
-            for (int k0 = 0; k0 < E; k0 += PR::B) {
-                uint64_t v[PR::B];
-                if (from) {
-                    PR::template load<true>(v, from, lp, k0);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < PR::B; ++k) v[k] = 0;
-                }
-                constexpr bool RING = E <= 8 && !CONVERT;
-                if (stream) PR::template add<true, RING>(v, at, K, lp, k0, q);
-                else PR::template add<false, RING>(v, at, K, lp, k0, q);
-                PR::reduce(v, K, md, q);
-                PR::swap(v, tl);
-#pragma unroll
-                for (int k = 0; k < PR::B; ++k) s[k0 + k] = v[k];
-            }
-        };
         auto share = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + off; };
         typename A::elem x[E];
         if constexpr (MODE == COMBINE_DECRYPT) {
@@ -1414,14 +1391,44 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
                     x[k0 + k] = A::inv_input(A::canon_acc(sum, md), md);
                 }
             }
-        } else if constexpr (CONVERT) {
-            uint64_t y[E];
-            sum(y, c0 + off, share);
-            uint64_t z[E];
-            sum(z, nullptr, [&](uint32_t j) { return share(j) + LN; });
+        } else if constexpr (MODE == COMBINE_CONVERT) {
+            // Two sums and the keys leave registers for two members at a time, in one loop each (streamed always; three and a second
+            // loop spilled).  One at a time where two spill (ArithB, ArithQ below N = 4096) or gain nothing (N = 4096, 36 bits, three limbs, 25
+            // indices of 16 receivers 102.2 / 103.6 us); two, N = 2048, 44 bits, two limbs, 60 indices 73.6 / 76.7.  With 16 coefficients per
+            // thread there are none left for a second set of addresses: one member, 8 bytes a lane (four nodes, N = 2^14, 54 bits, eight limbs, 80
+            // indices 936 us; the pairs' loads in batches of eight slots 986 with one member and 1,039 with two, of four 1,132).
+            auto second = [&](uint32_t j) { return share(j) + LN; };
+            constexpr int DEPTH = ENG::LOGN == 12 || (ENG::LOGN < 12 && (A::KIND == 2 || A::KIND == 5)) ? 1 : 2;
+            uint64_t y[E], z[E];
+            if constexpr (E <= 8) {
+                PR::template load<true>(z, second(0), lp, 0);
+                PR::template add<true, false, DEPTH>(z, [&](uint32_t j) { return second(j + 1); }, K - 1, lp, 0, q);
+                PR::reduce(z, K - 1, md, q);
+                PR::swap(z, tl);
+                PR::template load<true>(y, c0 + off, lp, 0);
+                PR::template add<true, false, DEPTH>(y, share, K, lp, 0, q);
+                PR::reduce(y, K, md, q);
+                PR::swap(y, tl);
+            } else {
+                auto add = [&](uint64_t (&s)[E], uint64_t first, auto at) {
+                    for (uint32_t j = first; j < K; ++j) {
+                        uint64_t v[E];
+#pragma unroll
+                        for (int k = 0; k < E; ++k) v[k] = ld64_stream(at(j), lo, 8u * ENG::T * k);
+#pragma unroll
+                        for (int k = 0; k < E; ++k) s[k] = add_mod(s[k], v[k], q);
+                    }
+                };
+#pragma unroll
+                for (int k = 0; k < E; ++k) y[k] = ld64_stream(c0 + off, lo, 8u * ENG::T * k);
+                add(y, 0, share);
+#pragma unroll
+                for (int k = 0; k < E; ++k) z[k] = ld64_stream(second(0), lo, 8u * ENG::T * k);
+                add(z, 1, second);
+            }
             typename A::Key kv[E];
 #pragma unroll
-            for (int k = 0; k < E; ++k) kv[k] = A::key(skr + off, skr + LN + off, 8u * (uint32_t)tl, 8u * ENG::T * k);
+            for (int k = 0; k < E; ++k) kv[k] = A::key(skr + off, skr + LN + off, lo, 8u * ENG::T * k);
 #pragma unroll
             for (int k = 0; k < E; ++k) {
                 const typename A::elem sum = A::mul_key_add(A::from_canon(z[k], md), kv[k], A::from_canon(y[k], md), md);
@@ -1429,7 +1436,17 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
             }
         } else {
             uint64_t y[E];
-            sum(y, c0 + off, share);
+#pragma unroll
+            for (int k0 = 0; k0 < E; k0 += PR::B) {
+                uint64_t v[PR::B];
+                PR::template load<true>(v, c0 + off, lp, k0);
+                if (stream) PR::template add<true, (E <= 8)>(v, share, K, lp, k0, q);
+                else PR::template add<false, (E <= 8)>(v, share, K, lp, k0, q);
+                PR::reduce(v, K, md, q);
+                PR::swap(v, tl);
+#pragma unroll
+                for (int k = 0; k < PR::B; ++k) y[k0 + k] = v[k];
+            }
 #pragma unroll
             for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
         }

@@ -75,3 +75,41 @@ def test_refresh_in_parts(bits, log2n, L, C, part):
     assert torch.equal(whole, parts)
     torch.cuda.synchronize()
     ctx.close()
+
+
+# the sums of both halves of conversion shares inside a round (K members, one after another or in pairs) against the same shares
+# added up by d2mhe_convert_combine and decrypted
+@pytest.mark.parametrize("bits,log2n,L,Ks", [
+    ("30", 10, 2, (1, 2, 5, 64)), ("36", 11, 3, (1, 3, 64)), ("44", 13, 2, (1, 2, 4, 5, 64)), ("54", 13, 2, (1, 2, 3, 64)),
+    ("60", 13, 1, (1, 2, 5)), ("54a", 12, 2, (1, 4)), ("60a", 13, 2, (3, 64)), ("36", 14, 2, (1, 2, 5, 64)), ("54", 14, 1, (1, 4)),
+    ("60a", 14, 1, (1, 3)), ("30", 14, 2, (2, 3)),
+])
+def test_conversion_shares_in_a_round(bits, log2n, L, Ks):
+    N, t, C, receiver = 1 << log2n, 12289 if log2n <= 11 else 65537, 2, 0
+    q = primes_away_from_powers_of_two(int(bits[:-1]), log2n, L) if bits.endswith("a") else O.find_primes(int(bits), log2n, L)
+    ctx = make_ctx(log2n, q, t, f=3, max_group=64, seed=15)
+    LN, n = L * N, C * N - 3
+    sks, pk0 = [dzeros(2 * LN) for _ in range(max(Ks))], [dzeros(LN) for _ in range(max(Ks))]
+    for k in range(max(Ks)):
+        ctx.keygen_share(k, sks[k], pk0[k])
+    rsk, rpk = dzeros(2 * LN), dzeros(4 * LN)
+    ctx.receiver_keygen(receiver, rsk, rpk)
+    gen = torch.Generator(device=DEV).manual_seed(L)
+    grads = [torch.randn(C * N, generator=gen, dtype=torch.float32, device=DEV) for _ in range(max(Ks))]
+    for K in Ks:
+        pk = dzeros(4 * LN)
+        ctx.aggregate_pk(pk0[:K], pk)
+        got, want = dzeros(C * N, dtype=torch.float32), dzeros(C * N, dtype=torch.float32)
+        desc = ctx.make_round([list(range(K))], [pk], sks[:K], grads[:K], [None], n)
+        conv = ctx.make_convert(desc, [[receiver]], {receiver: rpk}, {receiver: rsk}, [got])
+        size = ctx.round_convert_scratch_bytes(K, 1, K, n)
+        scratch = dzeros(size // 8 + 2)
+        ctx.round_convert(desc, conv, scratch, size)
+        agg, first = scratch[K * C * 2 * LN:], (K + 1) * C * 2 * LN
+        ct, pt = dzeros(C * 2 * LN), dzeros(C * N)
+        ctx.convert_combine(agg, [scratch[first + k * C * 2 * LN:] for k in range(K)], C, ct)
+        ctx.decrypt(rsk, ct, C, pt)
+        ctx.decode(pt, C, n, want)
+        assert torch.equal(got, want), f"{K} members"
+    torch.cuda.synchronize()
+    ctx.close()

@@ -19,3 +19,11 @@ def test_single_key_decryption_has_room():
     assert len(spilled) == 30                       # five ring degrees on six back-ends
     # N = 2^14 (16 coefficients per thread): sums and accumulators of 24 spilled registers at most
     assert not {k: n for k, n in spilled.items() if n > (24 if ", 14, 4," in k else 0)}
+
+
+def test_receivers_sums_have_room():
+    """Key switching adds up two polynomials of every member next to the receiver's key."""
+    spilled = {k: v[1] for k, v in registers().items() if k.startswith("k_convert_combine_decode<")}
+    assert len(spilled) == 30
+    # N = 2^14: two sums of 32 registers, accumulators of 48; as many again for the quotients of ArithS and ArithB
+    assert not {k: n for k, n in spilled.items() if n > ((80 if re.search("Arith[SB]", k) else 40) if ", 14, 4," in k else 0)}
