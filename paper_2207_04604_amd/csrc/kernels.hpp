@@ -1555,12 +1555,15 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         const uint32_t lo = 8u * (uint32_t)ENG::eval_lane(opaque(tid), blk);
         uint64_t y[E], z[E];                        // sums of c0 (and of the shares) and of c1
         {
+            // Three members at once spilled (32-bit words 21 registers, N = 2048, 80 groups' members of 128 indices 557 us; two 536); ArithP has no
+            // registers for two either (16 spilled against 8; the same time, 0.2 GB of 34 less for 32 groups of 7, N = 8192, four limbs).
+            constexpr int DEPTH = A::KIND == 4 ? 1 : 2;
             const int tp = opaque(tid);
             const uint32_t lp = Pairs<ENG>::lane(tp, blk);
             auto sum = [&](uint64_t (&s)[E], size_t at) {
                 const uint64_t *p = cts + at + off;
                 Pairs<ENG>::template load<true>(s, p, lp, 0);
-                Pairs<ENG>::template add<true, false>(s, [&](uint32_t j) { return p + (size_t)(j + 1) * ct_words; }, K - 1, lp, 0, q);
+                Pairs<ENG>::template add<true, false, DEPTH>(s, [&](uint32_t j) { return p + (size_t)(j + 1) * ct_words; }, K - 1, lp, 0, q);
 #pragma unroll
                 for (int k = 0; k < E; ++k) s[k] = A::sum_end(s[k], md);
                 Pairs<ENG>::store(agg + at + off, s, lp, 0);

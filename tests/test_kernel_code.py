@@ -27,3 +27,12 @@ def test_receivers_sums_have_room():
     assert len(spilled) == 30
     # N = 2^14: two sums of 32 registers, accumulators of 48; as many again for the quotients of ArithS and ArithB
     assert not {k: n for k, n in spilled.items() if n > ((80 if re.search("Arith[SB]", k) else 40) if ", 14, 4," in k else 0)}
+
+
+def test_finish_has_room():
+    """Sum, shares and combine of a round in one kernel: what it spills is written and read again for every limb."""
+    limit = {"Arith32": 0, "ArithF": 0, "ArithS": 13, "ArithB": 13, "ArithP": 9, "ArithQ": 16}
+    spilled = {k: v[1] for k, v in registers().items() if k.startswith("k_finish<")}
+    assert len(spilled) == 27
+    # ArithP at N = 1024 takes two passes of other sizes and 14
+    assert not {k: n for k, n in spilled.items() if n > limit[re.search(r"Arith\w", k).group(0) if "Arith32" not in k else "Arith32"] + 5 * ("ArithP, 10" in k)}
