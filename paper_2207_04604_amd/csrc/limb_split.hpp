@@ -46,6 +46,17 @@ inline float split_time(uint32_t L, uint32_t n, uint32_t head, uint32_t rest, ui
     return time;
 }
 
+// The least that this can be: the work spread evenly over the units of the first shader engine, or the largest part by itself.  Most splits
+// need not be played through (host time in front of a launch, 16 limbs 2 to 5 us, 31 without this).
+inline float split_time_least(uint32_t L, uint32_t n, uint32_t head, uint32_t rest, float alone, float fixed)
+{
+    float work = 0;
+    for (uint32_t done = 0, limbs = head, start = 0; done < L; done += limbs, start += n, limbs = L - done < rest ? L - done : rest)
+        work += (float)((start + n + SHADER_ENGINES - 1) / SHADER_ENGINES - (start + SHADER_ENGINES - 1) / SHADER_ENGINES) * ((float)limbs + fixed);
+    const float even = work / SE_UNITS, part = alone * ((float)head + fixed);
+    return (even > part ? even : part) * 0.9999f;            // (sums in another order)
+}
+
 // The split of L limbs that takes least time by that rule, if it takes 5 % less than whole polynomials do; `n`: workgroups
 // of whole polynomials.  Measured over 752 shapes (encryption, decryption, conversion and refresh shares, N = 2^10 to
 // 2^14, 30 to 60 bits, 2 to 8 limbs, 4 to 1,700 indices): 1.263 times as fast as whole polynomials in the geometric mean, where
@@ -65,7 +76,7 @@ inline LimbSplit split_limbs(uint32_t L, uint64_t n, uint32_t resident, float fi
     for (uint32_t rest = 1; rest < L; ++rest)
         for (int k = 0; k < 2; ++k) {                       // equal parts; all limbs but `rest` in the first
             const uint32_t head = k ? L - rest : rest;
-            if (head < rest || (k && head == rest)) continue;
+            if (head < rest || (k && head == rest) || split_time_least(L, (uint32_t)n, head, rest, alone, fixed) >= least) continue;
             const float t = split_time(L, (uint32_t)n, head, rest, resident, alone, fixed);
             if (t < least) {
                 least = t;

@@ -1,4 +1,6 @@
-// Every limb of a polynomial belongs to exactly one part of a split launch, whatever the sizes.
+// Every limb of a polynomial belongs to exactly one part of a split launch, whatever the sizes, and no split that was passed over
+// is better than the one chosen.
+#include <chrono>
 #include <cstdio>
 #include <initializer_list>
 
@@ -24,10 +26,40 @@ int main()
                     }
                     for (uint32_t i = 0; i < L; ++i)
                         if (seen[i] != 1) return std::printf("limb %u: L %u n %llu\n", i, L, (unsigned long long)n), 1;
+                    if (L > 1 && n <= 4 * 256 * (uint64_t)(resident < 2 ? resident : 2)) {
+                        const float alone = resident >= 8 ? 3.0f : resident >= 4 ? 2.2f : resident >= 2 ? 1.4f : 1.0f;
+                        float least = d2::split_time(L, (uint32_t)n, L, L, resident, alone, fixed) / 1.05f;
+                        for (uint32_t r = 1; r < L; ++r)
+                            for (uint32_t h : {r, L - r}) {
+                                const float t = h < r ? least : d2::split_time(L, (uint32_t)n, h, r, resident, alone, fixed);
+                                least = t < least ? t : least;
+                            }
+                        if (s.parts > 1 && d2::split_time(L, (uint32_t)n, head, rest, resident, alone, fixed) != least)
+                            return std::printf("not the best: L %u n %llu\n", L, (unsigned long long)n), 1;
+                        if (s.parts == 1 && d2::split_time(L, (uint32_t)n, L, L, resident, alone, fixed) / 1.05f != least)
+                            return std::printf("better in parts: L %u n %llu\n", L, (unsigned long long)n), 1;
+                    }
                     if (s.parts == 1) ++whole;
                     else ++splits;
                     if (s.parts > 1 && head != rest) ++uneven;
                 }
-    std::printf("%ld %ld %ld\n", whole, splits, uneven);
+    // host time in front of a launch, the worst of its sizes (least of several runs: the machine may be busy)
+    double worst = 0;
+    for (uint32_t L : {4u, 8u, 16u})
+        for (uint32_t n : {40u, 153u, 500u, 1024u, 1600u, 2048u})
+            for (uint32_t resident : {1u, 2u, 8u}) {
+                double best = 1e9;
+                for (int run = 0; run < 20; ++run) {
+                    const auto t0 = std::chrono::steady_clock::now();
+                    for (int i = 0; i < 10; ++i) {
+                        volatile uint32_t word = d2::split_limbs(L, n, resident, 0.5f).word;
+                        (void)word;
+                    }
+                    const double us = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 10;
+                    best = us < best ? us : best;
+                }
+                worst = best > worst ? best : worst;
+            }
+    std::printf("%ld %ld %ld %.2f\n", whole, splits, uneven, worst);
     return 0;
 }
