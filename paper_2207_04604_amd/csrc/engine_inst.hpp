@@ -236,10 +236,20 @@ struct Launch {
         return D2MHE_OK;
     }
 
+    // Up to how many members a combine reads 8 bytes a lane: with 16 coefficients per thread the registers that pairs take are missed
+    // elsewhere, and pay for many members only.  N = 2^14, times of pairs by those of 8 bytes (geometric mean, some 300 shapes): 36 and 44 bits two
+    // members 1.03, three 1.01, five 0.99, seven 0.98, twelve 0.95; 30 bits 1.04, 1.02, 1.01, 1.00, 0.98.  Shoup and
+    // split multiplicands spill either way (ArithS two members 1.00, three 1.01, five 0.97, twelve 0.92; the others 0.92 to 0.98).
+    static constexpr bool FEW = ENG::E > 8 && (ENG::A::KIND == 0 || ENG::A::KIND == 3);
+    static constexpr uint32_t FEW_MEMBERS = 3;
+
     static d2mhe_status combine(d2mhe_ctx *ctx, const uint64_t *ct, const PtrList &shares, uint32_t K, uint32_t C,
                                 uint64_t *pt, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_combine<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, shares, K, pt, ctx->d_tabs, ctx->rc);
+        if (FEW && K <= FEW_MEMBERS)
+            hipLaunchKernelGGL((k_combine<ENG, FEW>), dim3(C), dim3(ENG::T), 0, st, ct, shares, K, pt, ctx->d_tabs, ctx->rc);
+        else
+            hipLaunchKernelGGL((k_combine<ENG, false>), dim3(C), dim3(ENG::T), 0, st, ct, shares, K, pt, ctx->d_tabs, ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }
@@ -247,8 +257,14 @@ struct Launch {
     static d2mhe_status combine_decode(d2mhe_ctx *ctx, const GroupJobs &jobs, uint32_t njobs, size_t stride,
                                        uint32_t C, uint64_t n_values, hipStream_t st)
     {
-        hipLaunchKernelGGL(k_combine_decode<ENG>, dim3(C, njobs), dim3(ENG::T), 0, st, jobs, stride, n_values,
-                           ctx->d_tabs, ctx->rc);
+        uint32_t most = 0;
+        for (uint32_t j = 0; j < njobs; ++j) most = jobs.K[j] > most ? jobs.K[j] : most;
+        if (FEW && most <= FEW_MEMBERS)
+            hipLaunchKernelGGL((k_combine_decode<ENG, FEW>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, stride, n_values, ctx->d_tabs,
+                               ctx->rc);
+        else
+            hipLaunchKernelGGL((k_combine_decode<ENG, false>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, stride, n_values, ctx->d_tabs,
+                               ctx->rc);
         D2_LAUNCHED(ctx);
         return D2MHE_OK;
     }

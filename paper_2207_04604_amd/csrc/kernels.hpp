@@ -1330,7 +1330,8 @@ D2_DEV void refresh_limb(uint64_t *lds, const uint32_t (&m)[ENG::E], int tl, con
     }
 }
 
-template <class ENG, bool DECODE, int MODE, class SH>
+// FEW: the members' words 8 bytes a lane (see Launch::FEW).
+template <class ENG, bool DECODE, int MODE, bool FEW = false, class SH>
 D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_t K, const uint64_t *aux,
                          uint64_t *pt, float *out, uint64_t n_values, const LimbTab *tabs, const RoundConst &rc)
 {
@@ -1368,6 +1369,37 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
         const int tl = opaque(tid);
         const uint32_t lo = 8u * (uint32_t)tl, lp = PR::lane(tl, 0);
         auto share = [&](uint32_t j) { return share_of(j) + (size_t)c * share_ct + off; };
+        // `from` and a polynomial of every member from the first on, 8 bytes a lane
+        auto one_by_one = [&](uint64_t (&s)[E], const uint64_t *from, auto at, uint32_t first) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) s[k] = ld64_stream(from, lo, 8u * ENG::T * k);
+            for (uint32_t j = first; j < K; ++j) {
+                uint64_t v[E];
+#pragma unroll
+                for (int k = 0; k < E; ++k) v[k] = ld64_stream(at(j), lo, 8u * ENG::T * k);
+#pragma unroll
+                for (int k = 0; k < E; ++k) s[k] = add_mod(s[k], v[k], q);
+            }
+        };
+        // the same in pairs
+        auto in_pairs = [&](uint64_t (&s)[E], const uint64_t *from) {
+#pragma unroll
+            for (int k0 = 0; k0 < E; k0 += PR::B) {
+                uint64_t v[PR::B];
+                if (from) {                                 // (always; without a branch here the loops of N = 2^14 take 5 % longer)
+                    PR::template load<true>(v, from, lp, k0);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < PR::B; ++k) v[k] = 0;
+                }
+                if (stream) PR::template add<true, (E <= 8)>(v, share, K, lp, k0, q);
+                else PR::template add<false, (E <= 8)>(v, share, K, lp, k0, q);
+                PR::reduce(v, K, md, q);
+                PR::swap(v, tl);
+#pragma unroll
+                for (int k = 0; k < PR::B; ++k) s[k0 + k] = v[k];
+            }
+        };
         typename A::elem x[E];
         if constexpr (MODE == COMBINE_DECRYPT) {
             // The ciphertext's words are requested before anything is multiplied: left alone, the compiler spreads the loads over the products to
@@ -1413,21 +1445,8 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
                 PR::reduce(y, K, md, q);
                 PR::swap(y, tl);
             } else {
-                auto add = [&](uint64_t (&s)[E], uint64_t first, auto at) {
-                    for (uint32_t j = first; j < K; ++j) {
-                        uint64_t v[E];
-#pragma unroll
-                        for (int k = 0; k < E; ++k) v[k] = ld64_stream(at(j), lo, 8u * ENG::T * k);
-#pragma unroll
-                        for (int k = 0; k < E; ++k) s[k] = add_mod(s[k], v[k], q);
-                    }
-                };
-#pragma unroll
-                for (int k = 0; k < E; ++k) y[k] = ld64_stream(c0 + off, lo, 8u * ENG::T * k);
-                add(y, 0, share);
-#pragma unroll
-                for (int k = 0; k < E; ++k) z[k] = ld64_stream(second(0), lo, 8u * ENG::T * k);
-                add(z, 1, second);
+                one_by_one(y, c0 + off, share, 0);
+                one_by_one(z, second(0), second, 1);
             }
             typename A::Key kv[E];
 #pragma unroll
@@ -1439,17 +1458,8 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
             }
         } else {
             uint64_t y[E];
-#pragma unroll
-            for (int k0 = 0; k0 < E; k0 += PR::B) {
-                uint64_t v[PR::B];
-                PR::template load<true>(v, c0 + off, lp, k0);
-                if (stream) PR::template add<true, (E <= 8)>(v, share, K, lp, k0, q);
-                else PR::template add<false, (E <= 8)>(v, share, K, lp, k0, q);
-                PR::reduce(v, K, md, q);
-                PR::swap(v, tl);
-#pragma unroll
-                for (int k = 0; k < PR::B; ++k) y[k0 + k] = v[k];
-            }
+            if constexpr (FEW) one_by_one(y, c0 + off, share, 0);
+            else in_pairs(y, c0 + off);
 #pragma unroll
             for (int k = 0; k < E; ++k) x[k] = A::inv_input(y[k], md);
         }
@@ -1485,24 +1495,24 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
 }
 
 // one aggregate, K share buffers anywhere in memory, plaintext polynomials out; grid = C
-template <class ENG>
+template <class ENG, bool FEW>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine(const uint64_t *ct, PtrList shares, uint32_t K, uint64_t *pt,
                                                     const LimbTab *tabs, RoundConst rc)
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
-    combine_body<ENG, false, COMBINE_COLLECTIVE>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
+    combine_body<ENG, false, COMBINE_COLLECTIVE, FEW>(lds, ct, [&](uint32_t j) { return (const uint64_t *)shares.p[j]; }, K,
                                     (const uint64_t *)nullptr, pt, (float *)nullptr, 0, tabs, rc);
 }
 
 // whole round: grid = (C, groups); the group's shares lie `stride` words apart; decoded floats out
-template <class ENG>
+template <class ENG, bool FEW>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_combine_decode(GroupJobs jobs, size_t stride, uint64_t n_values,
                                                            const LimbTab *tabs, RoundConst rc)
 {
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     const uint32_t job = gridDim.y - 1 - blockIdx.y;
     const uint64_t *first = jobs.first[job];
-    combine_body<ENG, true, COMBINE_COLLECTIVE>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
+    combine_body<ENG, true, COMBINE_COLLECTIVE, FEW>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
                                    jobs.K[job], (const uint64_t *)nullptr, (uint64_t *)nullptr,
                                    (float *)jobs.out[job], n_values, tabs, rc);
 }

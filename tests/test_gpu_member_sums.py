@@ -15,7 +15,7 @@ from test_pm_policies import primes_away_from_powers_of_two
 
 # C = 129 or 200: streamed; 64 members: as many as there can be
 @pytest.mark.parametrize("bits,log2n,L,C,Ks", [
-    ("30", 10, 2, 3, (2, 3, 64)), ("36", 11, 2, 2, (2, 3, 4, 5, 63, 64)), ("44", 12, 1, 200, (6, 64)), ("36", 14, 2, 2, (3, 64)),
+    ("30", 10, 2, 3, (2, 3, 64)), ("36", 11, 2, 2, (2, 3, 4, 5, 63, 64)), ("44", 12, 1, 200, (6, 64)), ("36", 14, 2, 2, (3, 4, 64)), ("30", 14, 2, 2, (2, 3, 4, 5)), ("54a", 14, 1, 2, (3, 4)),
     ("54", 12, 2, 129, (3, 8)), ("54", 13, 2, 3, (2, 7, 64)), ("60", 13, 2, 2, (5, 64)), ("54a", 13, 1, 2, (4, 64)),
     ("60a", 11, 2, 2, (3, 64)), ("54", 14, 2, 1, (2, 3, 64)), ("60a", 14, 1, 130, (5,)),
 ])

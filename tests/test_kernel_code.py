@@ -36,3 +36,9 @@ def test_finish_has_room():
     assert len(spilled) == 27
     # ArithP at N = 1024 takes two passes of other sizes and 14
     assert not {k: n for k, n in spilled.items() if n > limit[re.search(r"Arith\w", k).group(0) if "Arith32" not in k else "Arith32"] + 5 * ("ArithP, 10" in k)}
+
+
+def test_combines_of_few_members_have_room():
+    """N = 2^14 on doubles and 32-bit words: as many coefficients per thread as fit, so the loops over members decide."""
+    spilled = {k: v[1] for k, v in registers().items() if re.match(r"k_combine(_decode)?<Engine<Arith(F|32), 14, 4.*, true>", k)}
+    assert len(spilled) == 4 and not any(spilled.values()), spilled
