@@ -194,7 +194,7 @@ struct Launch {
         if constexpr (E::E == 8) {
             const uint32_t L = ctx->L;
             if ((n << E::LOGP) * 2 * L <= 256) {
-                hipLaunchKernelGGL((k_encrypt<E, FROM, true>), dim3(C << E::LOGP, njobs, 2 * L), dim3(E::T), 0, st, jobs, ct_base,
+                hipLaunchKernelGGL((k_encrypt_components<E, FROM>), dim3(C << E::LOGP, njobs, 2 * L), dim3(E::T), 0, st, jobs, ct_base,
                                    1u | 1u << 16, n_values, ctx->d_tabs, ctx->rc);
                 return;
             }

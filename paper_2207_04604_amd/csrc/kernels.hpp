@@ -971,150 +971,38 @@ D2_DEV void mul_add_store(uint64_t *dst, const uint64_t *kp, const uint64_t *kps
 // FROM says what a job's source is: plaintext polynomials [C][N], the same in 32-bit words (k_encode_parties), or the
 // member's gradient, encoded on the fly.
 // -------------------------------------------------------------------------------------
-// TWO: a workgroup for either component, two to a part.  Both make NTT(mu), but only the first encodes the vector and neither does
-// three transforms: for launches that leave every workgroup a compute unit of its own.  One workgroup / two:
-// N = 1024, 30 bits, 16 indices 7.2 / 5.9 us, N = 4096, 36 bits, 3 limbs, 32 12.1 / 9.8, N = 8192, 54 bits, 1 limb, 60 28.1 / 22.8; but
-// 60 of N = 4096 (360 workgroups) 12.2 / 14.8.
-template <class ENG, int FROM, bool TWO = false>
+// One component, of the limbs in part `part`.
+template <class ENG, int FROM, bool FIRST>
+D2_DEV void encrypt_component(uint64_t *lds, const RoundJobs &jobs, uint32_t ct_base, uint32_t split, uint32_t part, uint64_t n_values,
+                              const LimbTab *tabs, const RoundConst &rc)
+{
+    constexpr bool SECOND = !FIRST;
+#include "encrypt_body.inc"
+}
+template <class ENG, int FROM>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt(RoundJobs jobs, uint32_t ct_base, uint32_t split, uint64_t n_values,
                                                     const LimbTab *tabs, RoundConst rc)
 {
-    typedef typename ENG::A A;
-    typedef typename A::elem elem;
-    static_assert(FROM != FROM_VECTOR || ENG::LOGP == 0, "an encoding takes the whole polynomial");
     __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
-    uint32_t turn = 0;      // the buffer used last; the transforms take the two buffers in turn
-    uint32_t *lds32 = (uint32_t *)lds;
-    constexpr int E = ENG::E;
-    // The message's first stage as a sum (forward_chained_encoded) wants two coefficients from far apart: read from memory,
-    // not brought through LDS after an encoding in place (25.9 instead of 25.7 us for the smallest round).  On doubles and
-    // 32-bit words it takes two products and corrections where the transform takes one, and saves an exchange that costs
-    // less (summed and not: N = 1024, 36 bits, 2 limbs, 60 indices 12.1 / 10.6 us; N = 8192, 900 indices 148 / 142 us,
-    // 30 bits 152 / 145 us): for halves of a polynomial only, which have no other way.
-    constexpr bool SUMMED = ENG::FUSE > 0 && FROM != FROM_VECTOR && (ENG::LOGP > 0 || A::KIND >= 4);
-    const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x >> ENG::LOGP, blk = blockIdx.x & ((1u << ENG::LOGP) - 1u), L = rc.L;
-    const RoundJob job = round_job<(ENG::LOGN > 12)>(jobs, blockIdx.y);
-    const uint32_t party = job.party, group = job.group;
-    const uint64_t *pk = job.key;
-    const size_t LN = (size_t)L * ENG::N;
-    uint64_t *out = job.out + (size_t)c * 2 * LN;
-    static_assert(!TWO || E <= 8, "NTT(mu) is parked where the other component goes");
+    constexpr bool FIRST = true, SECOND = true;
     const uint32_t part = launch_part();
-    const bool first = !TWO || (part & 1u) == 0, second = !TWO || (part & 1u) != 0;     // components to make
+#include "encrypt_body.inc"
+}
 
-    // With two buffers the samples are staged in the second one, next to the encoding in the first:
-    // one barrier then makes them visible and also ends the encoding's reads of the first buffer,
-    // which the first transform of the chain takes.
-    static_assert(ENG::N <= 2 * ENG::LDS_WORDS, "one word per sample fits a buffer");
-    uint32_t *stage = ENG::PINGPONG ? lds32 + 2 * ENG::LDS_WORDS : lds32;
-    if (ENG::PINGPONG) {
-        stage_encrypt_samples<ENG>(stage, tid, DOM_ENC_U, party, group, ct_base + c, rc);
-        turn = 1;
-    }
-    constexpr int MS = SUMMED ? 2 : 1;
-    uint32_t m[MS][E];
-    if constexpr (FROM == FROM_VECTOR) {
-        if (first)
-            encode_to_regs<ENG>(m[0], lds, tid, (const float *)job.src, (uint64_t)c * ENG::NB, n_values, load_tab(tabs, L), rc);
-    } else {
-        typedef typename std::conditional<FROM == FROM_WORDS32, uint32_t, uint64_t>::type word;
-        const word *pt = (const word *)job.src + (size_t)c * ENG::N;
-#pragma unroll
-        for (int j = 0; j < MS; ++j)
-#pragma unroll
-            for (int k = 0; k < E; ++k)
-                m[j][k] = (uint32_t)pt[SUMMED ? ENG::encoded_pos(j, k, tid) : ENG::coef_pos(k, tid)];
-    }
-    if (!ENG::PINGPONG) {
-        __syncthreads();
-        stage_encrypt_samples<ENG>(stage, tid, DOM_ENC_U, party, group, ct_base + c, rc);
-    }
-    __syncthreads();
-    SmallTriple<ENG> smp;
-    smp.load(stage, tid);
-    constexpr bool OWN_E0 = ENG::FUSE > 0 && (ENG::LOGP > 0 || !SUMMED);
-    uint32_t e0[MS][2];                     // bytes: e0 at the positions of m, where they are not those of smp
-    if constexpr (OWN_E0) {
-#pragma unroll
-        for (int j = 0; j < MS; ++j)
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const uint32_t b = (stage[SUMMED ? ENG::encoded_pos(j, k, tid) : ENG::coef_pos(k, tid)] >> 8) & 0xffu;
-                e0[j][k / 4] = k % 4 ? e0[j][k / 4] | b << (8 * (k % 4)) : b;
-            }
-    }
-    if (ENG::WAVE_CHAIN) __syncthreads();   // before a wave's second transform writes where others read samples
-
-    const LimbRange lr = limb_range(split, L, TWO ? part >> 1 : part);
-    for (uint32_t l = lr.first; l < lr.end; ++l) {
-        const uint32_t limb = scalar(l);
-        const LimbTab tb = load_tab(tabs, limb);
-        const typename A::Mod md = A::mod(tb.q, tb.one_s);
-        const typename A::Twid lam = A::tw(tb.lambda);
-        const size_t off = (size_t)limb * ENG::N;
-        const uint64_t *p0 = pk + off, *p0s = pk + LN + off;
-        const uint64_t *p1 = pk + 2 * LN + off, *p1s = pk + 3 * LN + off;
-        const int tl = opaque(tid), el = ENG::eval_lane(tl, blk);
-        // With 16 coefficients per thread NTT(mu) is parked (lazy, as raw bits) in the c1 slot of the
-        // output, which every thread re-reads at its own positions and overwrites last: keeping
-        // it in 32 registers across the next two transforms would halve the occupancy.  With 8
-        // per thread it stays in registers (no extra memory traffic).
-        constexpr bool STASH = E > 8;
-        uint64_t *stash = out + LN + off;
-        elem u[E];
-        int32_t sv[ENG::SS][E];         // the samples of this transform as plain small integers
-        smp.template get<0>(sv);
-        ENG::forward_chained_small(sv, u, lds, turn, tl, blk, tb.fwd, md);
-        if (STASH) {
-#pragma unroll
-            for (int k = 0; k < E; ++k) st64(stash, 8u * (uint32_t)tl, 8u * ENG::T * k, to_bits<A>(u[k]));
-        }
-        elem x[E];
-        if (first) {
-            if constexpr (SUMMED) {
-                uint32_t mm[2][E];
-                int32_t e[2][E];
-                if constexpr (!OWN_E0) {
-                    smp.template get<1>(e);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int k = 0; k < E; ++k) e[j][k] = sbyte(opaque(e0[j][k / 4]), k % 4);
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int k = 0; k < E; ++k) mm[j][k] = opaque(m[j][k]);
-                auto at = [&](int j, int k, uint32_t &m_jk, int32_t &e_jk) {
-                    m_jk = mm[j][k];
-                    e_jk = e[j][k];
-                };
-                ENG::forward_chained_encoded(at, x, lds, turn, opaque(tl), blk, tb.fwd, lam, A::tw(tb.lambda_i), md);
-            } else {
-#pragma unroll
-                for (int k = 0; k < E; ++k) {
-                    int32_t e;
-                    if constexpr (OWN_E0) e = sbyte(opaque(e0[0][k / 4]), k % 4);
-                    else e = sbyte(opaque(smp.w[k]), 1);
-                    x[k] = A::add_small(A::mul_u32(opaque(m[0][k]), lam, md), e, md);
-                }
-                ENG::forward_chained(x, lds, turn, opaque(tl), 0, tb.fwd, md);
-            }
-        }
-        typename A::Factor f[E];
-        if (!STASH) {
-#pragma unroll
-            for (int k = 0; k < E; ++k) f[k] = A::factor(u[k], md);
-        }
-        if (first) mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(out + off, p0, p0s, stash, f, x, el, md);
-        if (second) {
-            smp.template get<2>(sv);
-            ENG::forward_chained_small(sv, x, lds, turn, opaque(tl), blk, tb.fwd, md);
-            mul_add_store<ENG, STASH ? SRC_PARKED : SRC_REGS>(stash, p1, p1s, stash, f, x, el, md);
-        }
-    }
+// A workgroup for either component, two to a part.  Both make NTT(mu), but only the first encodes the vector and neither does
+// three transforms: for launches that leave every workgroup a compute unit of its own.  One workgroup / two: N = 1024, 30 bits,
+// 16 indices 7.2 / 5.7 us, N = 4096, 36 bits, 3 limbs, 32 12.1 / 9.5; but 60 of N = 4096 (360 workgroups) 12.2 / 14.8.
+// A body for each: both in one, with the component a run-time switch, kept the other's registers (from 54 bits up to 41 spilled, now 16).
+// Switch / bodies: N = 8192, 54 bits, 3 limbs, 25 indices 24.2 / 17.8 us, N = 2^14, 54 bits, 40 32.1 / 23.6, N = 1024, 60 bits,
+// 4 limbs, 30 10.3 / 7.4;  N = 4096, 60 bits, 2 limbs, 16 12.5 / 13.0, the only ones slower.
+template <class ENG, int FROM>
+__global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_encrypt_components(RoundJobs jobs, uint32_t ct_base, uint32_t split,
+                                                                           uint64_t n_values, const LimbTab *tabs, RoundConst rc)
+{
+    __shared__ uint64_t lds[ENG::LDS_CHAIN_WORDS];
+    const uint32_t z = launch_part();
+    if (z & 1u) encrypt_component<ENG, FROM, false>(lds, jobs, ct_base, split, z >> 1, n_values, tabs, rc);
+    else encrypt_component<ENG, FROM, true>(lds, jobs, ct_base, split, z >> 1, n_values, tabs, rc);
 }
 
 // -------------------------------------------------------------------------------------

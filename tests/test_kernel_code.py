@@ -39,6 +39,13 @@ def test_finish_has_room():
     assert not {k: n for k, n in spilled.items() if n > limit[re.search(r"Arith\w", k).group(0) if "Arith32" not in k else "Arith32"] + 5 * ("ArithP, 10" in k)}
 
 
+def test_encryption_by_components_has_room():
+    """A workgroup that makes one component of a ciphertext keeps nothing of the other (24 to 41 registers were spilled for it)."""
+    spilled = {k: v[1] for k, v in registers().items() if k.startswith("k_encrypt_components<")}
+    assert len(spilled) >= 50
+    assert not {k: n for k, n in spilled.items() if n > (0 if ", 14, 3," in k else 16)}
+
+
 def test_combines_of_few_members_have_room():
     """N = 2^14 on doubles and 32-bit words: as many coefficients per thread as fit, so the loops over members decide."""
     spilled = {k: v[1] for k, v in registers().items() if re.match(r"k_combine(_decode)?<Engine<Arith(F|32), 14, 4.*, true>", k)}
