@@ -101,19 +101,28 @@ struct Launch {
             // 405 / 345, 90 / 81;  N = 2^14, 36 bits 278 / 254, 71.7 / 60.6, 344 / 326, 86 / 76;  30 bits 267 / 245, 67.6 / 56.4,
             // 415 / 289, 80 / 67.  Two to a unit (N = 8192, 36 bits) 261 / 266, 254 / 314; spilling (N = 2^14, 54 bits) 288 / 365, 360 / 449.
             // Forward transforms with Shoup quotients gain nothing (54 bits, 300 polynomials 19.4 / 19.2, 420 20.3 / 21.2; inverse 25.9 /
-            // 24.3, 27.5 / 26.6).
+            // 24.3, 27.5 / 26.6).  What walking costs within the same turns: forward, N = 8192, seven limbs, batch of 60 3 %.
+            // A workgroup keeps its limb, so up to eight units stay idle, and just below a multiple of 256 polynomials that takes
+            // a turn more, which only many turns make up for.  One by one / walking, seven limbs, N = 8192 54 bits inverse, 60 bits forward,
+            // N = 2^14 36 bits forward and inverse, batch of
+            //   73 (two turns / three) 24.0 / 30.6, 21.2 / 25.4, 37.8 / 42.8, 46.4 / 55.4;  109 35.6 / 40.3, 30.5 / 32.0, 55.5 / 56.0, 68.2 / 73.6
+            //   145 (four / five) 47.0 / 50.7, 39.3 / 41.2, 73.0 / 68.8, 90.0 / 91.0;  182 57.8 / 60.3, 49.0 / 51.0, 91.5 / 84.1, 111.6 / 109.4
+            //   218 (six / seven) 68.1 / 69.6, 58.2 / 57.8;  254 77.8 / 78.2, 65.3 / 65.4;  292 (eight / nine) 87.6 / 87.0, 72.8 / 70.8
             constexpr bool WALK_INV = (ENG::LOGN == 13 && sizeof(typename ENG::Twid) > 8) || (ENG::LOGN == 14 && sizeof(typename ENG::Twid) <= 8);
             constexpr bool WALK_FWD = WALK_INV && (ENG::LOGN == 14 || ENG::A::KIND >= 4);
-            const dim3 walk(256 / L * L), block(ENG::T);
+            constexpr uint32_t MAKE_UP = ENG::LOGN == 14 ? 4 : 7;      // turns of 256
+            const uint32_t grid = 256 / L * L, full = (polys_n + 255) / 256;
+            const bool walks = polys_n > 256 && (full >= MAKE_UP || (polys_n + grid - 1) / grid == full);
+            const dim3 walk(grid), block(ENG::T);
             if constexpr (WALK_FWD) {
-                if (forward && polys_n > 256) {
+                if (forward && walks) {
                     hipLaunchKernelGGL((k_ntt_walk<ENG, false>), walk, block, 0, st, polys, ctx->d_tabs, L, polys_n);
                     D2_LAUNCHED(ctx);
                     return D2MHE_OK;
                 }
             }
             if constexpr (WALK_INV) {
-                if (!forward && polys_n > 256) {
+                if (!forward && walks) {
                     hipLaunchKernelGGL((k_ntt_walk<ENG, true>), walk, block, 0, st, polys, ctx->d_tabs, L, polys_n);
                     D2_LAUNCHED(ctx);
                     return D2MHE_OK;
