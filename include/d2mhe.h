@@ -140,7 +140,8 @@ d2mhe_status d2mhe_aggregate_pk(d2mhe_ctx *ctx, const uint64_t *const *pk0_share
 d2mhe_status d2mhe_encode(d2mhe_ctx *ctx, const float *grad, uint64_t n_values, uint64_t *pt,
                           uint32_t C, void *stream);
 /* BFV.Encrypt (Sec. 3.2 item 3) under the collective key: ct_c = (Lambda m_c + mu p0 + e0,
- * mu p1 + e1) for c = 0..C-1, randomness indexed by (party, group, ct_base + c).          */
+ * mu p1 + e1) for c = 0..C-1, randomness indexed by (party, group, ct_base + c).  ct may not
+ * overlap pt, unless C is 1 and N at most 8192.                                            */
 d2mhe_status d2mhe_encrypt(d2mhe_ctx *ctx, const uint64_t *pk, const uint64_t *pt, uint32_t C,
                            uint32_t party, uint32_t group, uint32_t ct_base, uint64_t *ct,
                            void *stream);

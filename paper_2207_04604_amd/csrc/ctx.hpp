@@ -50,10 +50,11 @@ struct EngineOps {
     d2mhe_status (*encode_parties)(d2mhe_ctx *, const EncodeJobs &jobs, uint32_t nparties, uint64_t n_values, uint32_t *pt,
                                    uint32_t C, hipStream_t);
     // from: FROM_VECTOR, FROM_WORDS32, FROM_WORDS64
+    // whole (here and below): one workgroup makes all limbs of a polynomial, as it reads what another would overwrite
     d2mhe_status (*encrypt)(d2mhe_ctx *, int from, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base,
-                            uint64_t n_values, uint32_t C, hipStream_t);
+                            uint64_t n_values, uint32_t C, bool whole, hipStream_t);
     d2mhe_status (*share)(d2mhe_ctx *, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
-                          hipStream_t);
+                          bool whole, hipStream_t);
     d2mhe_status (*combine)(d2mhe_ctx *, const uint64_t *ct, const PtrList &shares, uint32_t K, uint32_t C,
                             uint64_t *pt, hipStream_t);
     d2mhe_status (*combine_decode)(d2mhe_ctx *, const GroupJobs &jobs, uint32_t njobs, size_t stride, uint32_t C,
@@ -64,7 +65,7 @@ struct EngineOps {
     // MBFV.Convert
     d2mhe_status (*receiver_keygen)(d2mhe_ctx *, uint32_t party, uint64_t *sk, uint64_t *pk, hipStream_t);
     d2mhe_status (*convert_share)(d2mhe_ctx *, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
-                                  hipStream_t);
+                                  bool whole, hipStream_t);
     // y = c0 + c1 sk, rounded: plaintext polynomials
     d2mhe_status (*decrypt)(d2mhe_ctx *, const uint64_t *ct, const uint64_t *sk, uint32_t C, uint64_t *pt, hipStream_t);
     d2mhe_status (*convert_combine_decode)(d2mhe_ctx *, const RecvJobs &jobs, uint32_t njobs, size_t stride,
@@ -73,9 +74,9 @@ struct EngineOps {
     d2mhe_status (*bootstrap_alpha)(d2mhe_ctx *, uint32_t group, uint32_t ct_base, uint32_t C, uint64_t *alpha,
                                     hipStream_t);
     d2mhe_status (*bootstrap_share)(d2mhe_ctx *, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
-                                    hipStream_t);
+                                    bool whole, hipStream_t);
     d2mhe_status (*bootstrap_combine)(d2mhe_ctx *, const uint64_t *ct, const PtrList &shares, uint32_t K,
-                                      const uint64_t *alpha, uint32_t C, uint64_t *ct_out, hipStream_t);
+                                      const uint64_t *alpha, uint32_t C, uint64_t *ct_out, bool whole, hipStream_t);
 };
 
 const EngineOps *ops_f_10();

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ctx.hpp"
+#include "limb_split.hpp"
 #include "pm_growth.hpp"
 #include "stream_kernels.hpp"
 
@@ -548,7 +549,8 @@ d2mhe_status d2mhe_encrypt(d2mhe_ctx *ctx, const uint64_t *pk, const uint64_t *p
     if (C == 0) return D2MHE_OK;
     RoundJobs jobs;
     one_job(jobs, pt, party, pk, group, ct);
-    return engine_ops(ctx)->encrypt(ctx, FROM_WORDS64, jobs, 1, ct_base, 0, C, (hipStream_t)stream);
+    const bool whole = C == 1 && crosses(ct, 2 * (size_t)ctx->L * ctx->N, pt, ctx->N, 0);
+    return engine_ops(ctx)->encrypt(ctx, FROM_WORDS64, jobs, 1, ct_base, 0, C, whole, (hipStream_t)stream);
 }
 
 d2mhe_status d2mhe_add(d2mhe_ctx *ctx, uint64_t *ct_acc, const uint64_t *ct_in, uint32_t C, void *stream)
@@ -577,7 +579,9 @@ d2mhe_status d2mhe_partial_decrypt(d2mhe_ctx *ctx, const uint64_t *sk_share, con
     if (C == 0) return D2MHE_OK;
     RoundJobs jobs;
     one_job(jobs, sk_share, party, ct, group, share);
-    return engine_ops(ctx)->share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
+    const size_t LN = (size_t)ctx->L * ctx->N;
+    const bool whole = C == 1 && crosses(share, LN, ct, 2 * LN, LN);
+    return engine_ops(ctx)->share(ctx, jobs, 1, ct_base, C, whole, (hipStream_t)stream);
 }
 
 d2mhe_status d2mhe_combine(d2mhe_ctx *ctx, const uint64_t *ct, const uint64_t *const *shares, uint32_t K, uint32_t C,
@@ -622,7 +626,9 @@ d2mhe_status d2mhe_convert_share(d2mhe_ctx *ctx, const uint64_t *sk_share, const
     jobs.out = share;
     jobs.stride = 0;
     jobs.set_row(0, sk_share, party, pk_recv, receiver, ct, group);
-    return engine_ops(ctx)->convert_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
+    const size_t LN = (size_t)ctx->L * ctx->N;
+    const bool whole = C == 1 && crosses(share, 2 * LN, ct, 2 * LN, LN);
+    return engine_ops(ctx)->convert_share(ctx, jobs, 1, ct_base, C, whole, (hipStream_t)stream);
 }
 
 d2mhe_status d2mhe_convert_combine(d2mhe_ctx *ctx, const uint64_t *ct, const uint64_t *const *shares, uint32_t K,
@@ -682,7 +688,9 @@ d2mhe_status d2mhe_bootstrap_share(d2mhe_ctx *ctx, const uint64_t *sk_share, con
     jobs.out = share;
     jobs.stride = 0;
     jobs.set_row(0, sk_share, party, alpha, 0, ct, group);
-    return engine_ops(ctx)->bootstrap_share(ctx, jobs, 1, ct_base, C, (hipStream_t)stream);
+    const size_t LN = (size_t)ctx->L * ctx->N;
+    const bool whole = C == 1 && (crosses(share, 2 * LN, ct, 2 * LN, LN) || crosses(share, 2 * LN, alpha, LN, LN));
+    return engine_ops(ctx)->bootstrap_share(ctx, jobs, 1, ct_base, C, whole, (hipStream_t)stream);
 }
 
 d2mhe_status d2mhe_bootstrap_combine(d2mhe_ctx *ctx, const uint64_t *ct, const uint64_t *alpha,
@@ -700,7 +708,11 @@ d2mhe_status d2mhe_bootstrap_combine(d2mhe_ctx *ctx, const uint64_t *ct, const u
         sh.p[k] = shares[k];
     }
     if (C == 0) return D2MHE_OK;
-    return engine_ops(ctx)->bootstrap_combine(ctx, ct, sh, K, alpha, C, ct_out, (hipStream_t)stream);
+    // in two launches the first leaves plaintexts in ct_out: eta1 and alpha are read after that
+    const size_t LN = (size_t)ctx->L * ctx->N;
+    bool whole = C == 1 && alpha != ct_out + LN && crosses(ct_out, 2 * LN, alpha, LN, 0);
+    for (uint32_t k = 0; k < K && C == 1; ++k) whole = whole || (sh.p[k] != ct_out && crosses(ct_out, 2 * LN, sh.p[k], 2 * LN, 0));
+    return engine_ops(ctx)->bootstrap_combine(ctx, ct, sh, K, alpha, C, ct_out, whole, (hipStream_t)stream);
 }
 
 // ---- the float step of one training iteration (Alg. 2 lines 9-10) -----------------------------
@@ -994,7 +1006,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
                                 return ahead ? (const void *)(pt + (size_t)who.place[j] * C * ctx->N) : d->grads[d->members[j]];
                             },
                             [&](uint32_t g) { return d->pks[g]; });
-        d2mhe_status s = ops->encrypt(ctx, ahead ? FROM_WORDS32 : FROM_VECTOR, jobs, n, d->ct_base, d->n_values, C, st);
+        d2mhe_status s = ops->encrypt(ctx, ahead ? FROM_WORDS32 : FROM_VECTOR, jobs, n, d->ct_base, d->n_values, C, false, st);
         if (s != D2MHE_OK) return s;
     }
     if (ev && ev[1]) D2_HIP(ctx, hipEventRecord(ev[1], st));
@@ -1052,7 +1064,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             n = fill_round_jobs(jobs, d, who, j0, per_launch, slot, shares + j0 * sh_words, sh_words,
                                 [&](uint32_t j) -> const void * { return d->sk_shares[d->members[j]]; },
                                 [&](uint32_t g) { return agg + (size_t)g * ct_words; });
-            d2mhe_status s = ops->share(ctx, jobs, n, d->ct_base, C, st);
+            d2mhe_status s = ops->share(ctx, jobs, n, d->ct_base, C, false, st);
             if (s != D2MHE_OK) return s;
         }
         if (ev && ev[3]) D2_HIP(ctx, hipEventRecord(ev[3], st));
@@ -1125,7 +1137,7 @@ d2mhe_status run_round(d2mhe_ctx *ctx, const d2mhe_round_desc *d, const d2mhe_co
             }
             jobs.set_job(n, ms - 1u, rs - 1u, groups - 1);
         }
-        d2mhe_status s = ops->convert_share(ctx, jobs, n, d->ct_base, C, st);
+        d2mhe_status s = ops->convert_share(ctx, jobs, n, d->ct_base, C, false, st);
         if (s != D2MHE_OK) return s;
         s0 += n;
     }
@@ -1289,7 +1301,7 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
         s = ops->encode_parties(&local, vectors, K, n_values, pt, C, st);
     }
     if (s == D2MHE_OK)
-        s = ops->encrypt(&local, ops->halves ? FROM_WORDS32 : FROM_VECTOR, enc, K, 0, n_values, C, st);
+        s = ops->encrypt(&local, ops->halves ? FROM_WORDS32 : FROM_VECTOR, enc, K, 0, n_values, C, false, st);
     if (s == D2MHE_OK) {
         GroupJobs sum;
         sum.first[0] = cts;
@@ -1304,7 +1316,7 @@ d2mhe_status d2mhe_round_group_static(d2mhe_ctx *ctx, const uint64_t *pk, const 
             s = D2MHE_ERR_HIP;
         }
     }
-    if (s == D2MHE_OK) s = ops->share(&local, shr, K, 0, C, st);
+    if (s == D2MHE_OK) s = ops->share(&local, shr, K, 0, C, false, st);
     if (s == D2MHE_OK) {
         GroupJobs cmb;
         cmb.first[0] = shares;

@@ -51,8 +51,9 @@ struct Launch {
     // decryption shares 11.8, 21.5, 28.4, 36.0; a launch by itself 2.5.)
     static constexpr float SAMPLES = 0.5f, ENCODING = 0.7f, MASKS = 0.7f;
     template <class E>
-    static LimbSplit split(const d2mhe_ctx *ctx, uint64_t n, float fixed)
+    static LimbSplit split(const d2mhe_ctx *ctx, uint64_t n, float fixed, bool whole)
     {
+        if (whole) return LimbSplit{1, ctx->L};
         return split_limbs(ctx->L, n << E::LOGP, 1024 / E::T, E::LOGP ? 2 * fixed : fixed);
     }
     // launch(Shape<engine>) with the one to take
@@ -197,35 +198,35 @@ struct Launch {
 
     template <class E, int FROM>
     static void launch_encrypt(d2mhe_ctx *ctx, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint64_t n_values, uint32_t C,
-                               float fixed, hipStream_t st)
+                               float fixed, bool whole, hipStream_t st)
     {
         const uint64_t n = (uint64_t)C * njobs;
         if constexpr (E::E == 8) {
             const uint32_t L = ctx->L;
-            if ((n << E::LOGP) * 2 * L <= 256) {
+            if (!whole && (n << E::LOGP) * 2 * L <= 256) {
                 hipLaunchKernelGGL((k_encrypt_components<E, FROM>), dim3(C << E::LOGP, njobs, 2 * L), dim3(E::T), 0, st, jobs, ct_base,
                                    1u | 1u << 16, n_values, ctx->d_tabs, ctx->rc);
                 return;
             }
         }
-        const LimbSplit sp = split<E>(ctx, n, fixed);
+        const LimbSplit sp = split<E>(ctx, n, fixed, whole);
         hipLaunchKernelGGL((k_encrypt<E, FROM>), dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, n_values,
                            ctx->d_tabs, ctx->rc);
     }
 
     static d2mhe_status encrypt(d2mhe_ctx *ctx, int from, const RoundJobs &jobs, uint32_t njobs,
-                                uint32_t ct_base, uint64_t n_values, uint32_t C, hipStream_t st)
+                                uint32_t ct_base, uint64_t n_values, uint32_t C, bool whole, hipStream_t st)
     {
         if (from == FROM_VECTOR) {
             if constexpr (HALVES) return D2MHE_ERR_RANGE;       // the caller encodes first (EngineOps::halves)
             else
                 launch_encrypt<ENG, FROM_VECTOR>(ctx, jobs, njobs, ct_base, n_values, C,
-                                                 ctx->rc.coeff_packing ? SAMPLES : SAMPLES + ENCODING, st);
+                                                 ctx->rc.coeff_packing ? SAMPLES : SAMPLES + ENCODING, whole, st);
         } else {
             choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
                 typedef typename decltype(shape)::type E;
-                if (from == FROM_WORDS32) launch_encrypt<E, FROM_WORDS32>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, st);
-                else launch_encrypt<E, FROM_WORDS64>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, st);
+                if (from == FROM_WORDS32) launch_encrypt<E, FROM_WORDS32>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, whole, st);
+                else launch_encrypt<E, FROM_WORDS64>(ctx, jobs, njobs, ct_base, n_values, C, SAMPLES, whole, st);
             });
         }
         D2_LAUNCHED(ctx);
@@ -233,11 +234,11 @@ struct Launch {
     }
 
     static d2mhe_status share(d2mhe_ctx *ctx, const RoundJobs &jobs, uint32_t njobs, uint32_t ct_base, uint32_t C,
-                              hipStream_t st)
+                              bool whole, hipStream_t st)
     {
         choose<HALVES>(share_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES, whole);
             hipLaunchKernelGGL(k_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
                                ctx->rc);
         });
@@ -302,11 +303,11 @@ struct Launch {
     }
 
     static d2mhe_status convert_share(d2mhe_ctx *ctx, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base,
-                                      uint32_t C, hipStream_t st)
+                                      uint32_t C, bool whole, hipStream_t st)
     {
         choose<HALVES && ENG::A::KIND == 0>(encrypt_in_halves(ctx, (uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, SAMPLES, whole);
             hipLaunchKernelGGL(k_convert_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
                                ctx->rc);
         });
@@ -340,11 +341,11 @@ struct Launch {
     }
 
     static d2mhe_status bootstrap_share(d2mhe_ctx *ctx, const ConvJobs &jobs, uint32_t njobs, uint32_t ct_base,
-                                        uint32_t C, hipStream_t st)
+                                        uint32_t C, bool whole, hipStream_t st)
     {
         choose<HALVES>(refresh_in_halves((uint64_t)C * njobs), [&](auto shape) {
             typedef typename decltype(shape)::type E;
-            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, MASKS);
+            const LimbSplit sp = split<E>(ctx, (uint64_t)C * njobs, MASKS, whole);
             hipLaunchKernelGGL(k_bootstrap_share<E>, dim3(C << E::LOGP, njobs, sp.parts), dim3(E::T), 0, st, jobs, ct_base, sp.word, ctx->d_tabs,
                                ctx->rc);
         });
@@ -364,9 +365,9 @@ struct Launch {
         return L >= 4 || (L > 1 && ENG::LOGN == 14) ? 128 : L == 3 ? 85 : L == 2 && ENG::LOGN > 10 ? 32 : 0;
     }
     static d2mhe_status bootstrap_combine(d2mhe_ctx *ctx, const uint64_t *ct, const PtrList &shares, uint32_t K,
-                                          const uint64_t *alpha, uint32_t C, uint64_t *ct_out, hipStream_t st)
+                                          const uint64_t *alpha, uint32_t C, uint64_t *ct_out, bool whole, hipStream_t st)
     {
-        if (C <= refresh_apart(ctx)) {
+        if (!whole && C <= refresh_apart(ctx)) {
             hipLaunchKernelGGL(k_bootstrap_round<ENG>, dim3(C), dim3(ENG::T), 0, st, ct, shares, K, ct_out, ctx->d_tabs, ctx->rc);
             D2_LAUNCHED(ctx);
             hipLaunchKernelGGL(k_bootstrap_refresh<ENG>, dim3(C, ctx->L), dim3(ENG::T), 0, st, shares, K, alpha, ct_out, ctx->d_tabs,

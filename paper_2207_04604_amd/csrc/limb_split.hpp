@@ -1,8 +1,19 @@
 // How many workgroups share the limbs of one polynomial, for launches that leave compute units idle (host code).
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 namespace d2 {
+
+// A polynomial that is read, `in`, lies in whole or in part where `out` is written, other than limb on limb (`LN` words to a polynomial of
+// all limbs; 0: `in` has none): its workgroup may read before it writes, but not while another writes.  Of several ciphertexts this
+// never was defined, as each has its workgroup.
+inline bool crosses(const void *out, size_t out_words, const void *in, size_t in_words, size_t LN)
+{
+    const uintptr_t o = (uintptr_t)out, i = (uintptr_t)in;
+    if (o >= i + 8 * in_words || i >= o + 8 * out_words) return false;
+    return !LN || (o > i ? o - i : i - o) % (8 * LN) != 0;
+}
 
 constexpr uint32_t SE_UNITS = 8, SHADER_ENGINES = 32;     // 256 compute units
 

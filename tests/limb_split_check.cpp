@@ -6,8 +6,21 @@
 
 #include "../paper_2207_04604_amd/csrc/limb_split.hpp"
 
+// Where what is read lies under what is written: only limb on limb may the parts of a polynomial go to several workgroups.
+static bool crossing_known()
+{
+    static uint64_t w[64];
+    const size_t N = 4, LN = 12;
+    const uint64_t *at = w + 16;
+    return !d2::crosses(w, 16, at, 4, 0) && d2::crosses(w, 17, at, 4, 0) && d2::crosses(w + 19, 24, at, 4, 0) && !d2::crosses(w + 20, 24, at, 4, 0) &&
+           d2::crosses(w + 16, 24, at, 4, 0) && !d2::crosses(w + 16, LN, at, 2 * LN, LN) && !d2::crosses(w + 16 + LN, LN, at, 2 * LN, LN) &&
+           d2::crosses(w + 16 + LN - N, LN, at, 2 * LN, LN) && d2::crosses(w + 14, 2 * LN, at, 2 * LN, LN) &&
+           !d2::crosses(w + 4, LN, at, 2 * LN, LN) && d2::crosses(w + 6, LN, at, 2 * LN, LN);
+}
+
 int main()
 {
+    if (!crossing_known()) return std::printf("crosses\n"), 1;
     long splits = 0, uneven = 0, whole = 0;
     for (uint32_t L = 1; L <= 16; ++L)
         for (uint64_t n : {1ull, 2ull, 31ull, 33ull, 64ull, 85ull, 127ull, 128ull, 153ull, 200ull, 255ull, 256ull, 257ull, 300ull, 700ull, 1025ull, 2048ull,

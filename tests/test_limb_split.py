@@ -56,3 +56,46 @@ def test_parts_equal_whole_polynomials(bits, log2n, L, C, part):
         assert torch.equal(whole, parts), name
     torch.cuda.synchronize()
     ctx.close()
+
+
+# One ciphertext whose result lies where an input is read: as if it lay elsewhere, though its limbs and components could go to several workgroups
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,log2n,L", [(30, 10, 1), (54, 10, 6), (36, 11, 5), (60, 12, 2), (54, 13, 4), (60, 13, 1)])
+def test_one_ciphertext_in_place(bits, log2n, L):
+    from oracle import oracle as O
+    import torch
+    from gpu_util import dzeros, make_ctx, to_dev
+    N, LN, t = 1 << log2n, L << log2n, 12289 if log2n <= 11 else 65537
+    ctx = make_ctx(log2n, O.find_primes(bits, log2n, L), t, f=3, max_group=2, seed=34)
+    sk, pk0, pk, rsk, rpk = (dzeros(n * LN) for n in (2, 1, 4, 2, 4))
+    ctx.keygen_share(1, sk, pk0)
+    ctx.aggregate_pk([pk0], pk)
+    ctx.receiver_keygen(2, rsk, rpk)
+    pt = to_dev(np.random.default_rng(bits).integers(0, t, N, dtype=np.uint64))
+    ct, alpha = dzeros(2 * LN), dzeros(LN)
+    ctx.encrypt(pk, pt, 1, 1, 5, 3, ct)
+    ctx.bootstrap_alpha(5, 3, 1, alpha)
+    shares = [dzeros(2 * LN) for _ in range(2)]
+    for k in range(2):
+        ctx.bootstrap_share(sk, ct, alpha, 1, 1 + k, 5, 3, shares[k])
+    room = dzeros(6 * LN)
+
+    def check(what, call, data, words, offsets):
+        """call(data, out): out `offset` words from where data begins"""
+        want = dzeros(words)
+        call(data, want)
+        for offset in offsets:
+            room.zero_()
+            at = room[2 * LN:2 * LN + data.numel()]
+            at.copy_(data)
+            out = room[2 * LN + offset:]
+            call(at, out)
+            assert torch.equal(out[:words], want), (what, offset)
+
+    check("ciphertext", lambda d, out: ctx.encrypt(pk, d, 1, 1, 5, 3, out), pt, 2 * LN, (0, -LN, N - 2 * LN, -N // 2))
+    check("share", lambda d, out: ctx.partial_decrypt(sk, d, 1, 1, 5, 3, out), ct, LN, (0, LN, LN - N))
+    check("conversion share", lambda d, out: ctx.convert_share(sk, rpk, d, 1, 1, 2, 5, 3, out), ct, 2 * LN, (0, -N))
+    check("refresh share", lambda d, out: ctx.bootstrap_share(sk, d, alpha, 1, 1, 5, 3, out), ct, 2 * LN, (0, -N))
+    check("refreshed", lambda d, out: ctx.bootstrap_combine(ct, alpha, [d, shares[1]], 1, out), shares[0], 2 * LN, (0, LN))
+    torch.cuda.synchronize()
+    ctx.close()
