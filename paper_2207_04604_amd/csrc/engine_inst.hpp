@@ -47,8 +47,12 @@ struct Launch {
         typedef E type;
     };
     // What every part of a split polynomial repeats, in limbs: the samples (all of them for either half of a polynomial),
-    // for an encryption of a vector also its encoding.  (Refresh shares, 256 indices of N = 8192, one to four limbs 27.4, 46.1, 62.6, 80.5 us;
-    // decryption shares 11.8, 21.5, 28.4, 36.0; a launch by itself 2.5.)
+    // for an encryption of a vector also its encoding.  Fitted to the choices that are fastest, as the model leaves out what else a part costs:
+    // by itself the fixed work is less (256 indices of N = 8192, one to four limbs: refresh shares 27.4, 46.1, 62.6, 80.5 us, decryption shares
+    // 11.8, 21.5, 28.4, 36.0; a launch 2.5), but with 0.15 limbs shares take up to 15 % longer, refresh shares 24 %.  Time of 28 shapes
+    // (54 and 36 bits, N = 1024 to 2^14, two to eight limbs, 40 to 1,500 indices) with 0.15, 0.3, 0.4, 0.5, 0.7 against 0.5 (refresh shares 0.7):
+    // shares 1.010, 1.002, 0.996, 1.000, 1.004;  encryptions 1.003, 0.997, 0.994, 0.993, 1.002;  conversion shares 0.993, 0.992, 0.993, 0.995,
+    // 1.004;  refresh shares 1.032, 1.014, 0.996, 0.996, 0.997;  two runs with the same value differ by 0.7 %.
     static constexpr float SAMPLES = 0.5f, ENCODING = 0.7f, MASKS = 0.7f;
     template <class E>
     static LimbSplit split(const d2mhe_ctx *ctx, uint64_t n, float fixed, bool whole)
@@ -74,7 +78,7 @@ struct Launch {
     // L = 1, B = 8 32.6 / 12.8;  4, 8 43.9 / 27.8;  4, 16 41.0 / 31.3;  4, 24 46.7 / 41.7;  16, 2 26.0 / 25.5;  N = 2^15, 60 bits:
     // 1, 32 36.0 / 16.2;  4, 16 37.9 / 21.2;  7, 48 75.8 / 67.8.  More than eight gain where they fill a turn of the chip, of N =
     // 2^16 also two, if all are equal (L = 16: B = 32 194 / 176, 48 286 / 273, 64 398 / 383; in part of two, L = 4, B = 200 305 / 317; N = 2^15, L = 16,
-    // B = 128 397 / 420).
+    // B = 128 397 / 420).  What nearly fills two turns otherwise (L = 14, B = 64;  L = 16, B = 62) was not measured and stays with eights.
     static uint32_t tail_tiles(uint32_t groups, uint32_t B)
     {
         constexpr uint64_t PLACES = 256 * (1024 / ENG::T);

@@ -305,7 +305,7 @@ D2_DEV uint32_t launch_part()
 #if D2_GCN_ASM
     return __builtin_amdgcn_workgroup_id_z();
 #else
-    return 0;                           // a host build that runs the kernels takes polynomials whole
+    return 0;                           // the arithmetic's host check includes this file and launches nothing
 #endif
 }
 D2_DEV LimbRange limb_range(uint32_t split, uint32_t L, uint32_t z)
