@@ -1461,8 +1461,9 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_finish(FinishJobs jobs, 
         uint64_t y[E], z[E];                        // sums of c0 (and of the shares) and of c1
         {
             // Three members at once spilled (32-bit words 21 registers, N = 2048, 80 groups' members of 128 indices 557 us; two 536); ArithP has no
-            // registers for two either (16 spilled against 8; the same time, 0.2 GB of 34 less for 32 groups of 7, N = 8192, four limbs).
-            constexpr int DEPTH = A::KIND == 4 ? 1 : 2;
+            // registers for two either (16 spilled against 8; the same time, 0.2 GB of 34 less for 32 groups of 7, N = 8192, four limbs).  Without
+            // the combine (halves of N = 2^14) there is room for three (8 groups of 8, 684 indices, 54 bits, eight limbs: one 5.46 ms, three 5.34).
+            constexpr int DEPTH = ENG::LOGP > 0 ? 3 : A::KIND == 4 ? 1 : 2;
             const int tp = opaque(tid);
             const uint32_t lp = Pairs<ENG>::lane(tp, blk);
             auto sum = [&](uint64_t (&s)[E], size_t at) {
