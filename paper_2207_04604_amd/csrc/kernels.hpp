@@ -1325,7 +1325,8 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
             // Two sums and the keys leave registers for two members at a time, in one loop each (streamed always; three and a second
             // loop spilled).  One at a time where two spill (ArithB, ArithQ below N = 4096) or gain nothing (N = 4096, 36 bits, three limbs, 25
             // indices of 16 receivers 102.2 / 103.6 us); two, N = 2048, 44 bits, two limbs, 60 indices 73.6 / 76.7.  With 16 coefficients per
-            // thread there are none left for a second set of addresses: one member, 8 bytes a lane (four nodes, N = 2^14, 54 bits, eight limbs, 80
+            // thread there are none left for a second set of addresses: one member, 8 bytes a lane (FEW; the rule for launches that leave most units idle, where
+            // spills cost less than narrow loads, is Launch::convert_combine_decode's; four nodes, N = 2^14, 54 bits, eight limbs, 80
             // indices 936 us; the pairs' loads in batches of eight slots 986 with one member and 1,039 with two, of four 1,132).
             auto second = [&](uint32_t j) { return share(j) + LN; };
             constexpr int DEPTH = ENG::LOGN == 12 || (ENG::LOGN < 12 && (A::KIND == 2 || A::KIND == 5)) ? 1 : 2;
@@ -1339,6 +1340,21 @@ D2_DEV void combine_body(uint64_t *lds, const uint64_t *ct, SH share_of, uint32_
                 PR::template add<true, false, DEPTH>(y, share, K, lp, 0, q);
                 PR::reduce(y, K, md, q);
                 PR::swap(y, tl);
+            } else if constexpr (!FEW) {
+                auto pairs = [&](uint64_t (&s)[E], const uint64_t *from, auto at, uint32_t n) {
+#pragma unroll
+                    for (int k0 = 0; k0 < E; k0 += PR::B) {
+                        uint64_t v[PR::B];
+                        PR::template load<true>(v, from, lp, k0);
+                        PR::template add<true, false, DEPTH>(v, at, n, lp, k0, q);
+                        PR::reduce(v, n, md, q);
+                        PR::swap(v, tl);
+#pragma unroll
+                        for (int k = 0; k < PR::B; ++k) s[k0 + k] = v[k];
+                    }
+                };
+                pairs(y, c0 + off, share, K);
+                pairs(z, second(0), [&](uint32_t j) { return second(j + 1); }, K - 1);
             } else {
                 one_by_one(y, c0 + off, share, 0);
                 one_by_one(z, second(0), second, 1);
@@ -1694,7 +1710,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_decrypt(const uint64_t *
 
 // The receiver's side of MBFV.Convert fused with BFV.Decrypt(sk_i, .) (Eq. (2)), whole round:
 // grid = (C, receivers of all groups); decoded floats out
-template <class ENG>
+template <class ENG, bool FEW>
 __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_combine_decode(RecvJobs jobs, size_t stride,
                                                                    uint64_t n_values, const LimbTab *tabs,
                                                                    RoundConst rc)
@@ -1702,7 +1718,7 @@ __global__ void __launch_bounds__(ENG::T, ENG::WAVES) k_convert_combine_decode(R
     __shared__ uint64_t lds[ENG::LDS_WORDS];
     const uint32_t job = gridDim.y - 1 - blockIdx.y;
     const uint64_t *first = jobs.first[job];
-    combine_body<ENG, true, COMBINE_CONVERT>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
+    combine_body<ENG, true, COMBINE_CONVERT, FEW>(lds, jobs.ct[job], [&](uint32_t j) { return first + (size_t)j * stride; },
                                   jobs.K[job], jobs.sk[job], (uint64_t *)nullptr, (float *)jobs.out[job],
                                   n_values, tabs, rc);
 }

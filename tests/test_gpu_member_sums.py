@@ -79,13 +79,14 @@ def test_refresh_in_parts(bits, log2n, L, C, part):
 
 # the sums of both halves of conversion shares inside a round (K members, one after another or in pairs) against the same shares
 # added up by d2mhe_convert_combine and decrypted
-@pytest.mark.parametrize("bits,log2n,L,Ks", [
-    ("30", 10, 2, (1, 2, 5, 64)), ("36", 11, 3, (1, 3, 64)), ("44", 13, 2, (1, 2, 4, 5, 64)), ("54", 13, 2, (1, 2, 3, 64)),
-    ("60", 13, 1, (1, 2, 5)), ("54a", 12, 2, (1, 4)), ("60a", 13, 2, (3, 64)), ("36", 14, 2, (1, 2, 5, 64)), ("54", 14, 1, (1, 4)),
-    ("60a", 14, 1, (1, 3)), ("30", 14, 2, (2, 3)),
+@pytest.mark.parametrize("bits,log2n,L,C,Ks", [
+    ("30", 10, 2, 2, (1, 2, 5, 64)), ("36", 11, 3, 2, (1, 3, 64)), ("44", 13, 2, 2, (1, 2, 4, 5, 64)), ("54", 13, 2, 2, (1, 2, 3, 64)),
+    ("60", 13, 1, 2, (1, 2, 5)), ("54a", 12, 2, 2, (1, 4)), ("60a", 13, 2, 2, (3, 64)), ("36", 14, 2, 2, (1, 2, 5, 64)), ("54", 14, 1, 2, (1, 4)),
+    ("60a", 14, 1, 2, (1, 3)), ("30", 14, 2, 2, (2, 3)),
+    ("54", 14, 2, 64, (3, 5)), ("60", 14, 1, 2, (1, 2, 64)), ("54", 14, 1, 65, (1, 3)), ("60", 14, 2, 65, (4,)),      # N = 2^14: loads in pairs up to C = 64
 ])
-def test_conversion_shares_in_a_round(bits, log2n, L, Ks):
-    N, t, C, receiver = 1 << log2n, 12289 if log2n <= 11 else 65537, 2, 0
+def test_conversion_shares_in_a_round(bits, log2n, L, C, Ks):
+    N, t, receiver = 1 << log2n, 12289 if log2n <= 11 else 65537, 0
     q = primes_away_from_powers_of_two(int(bits[:-1]), log2n, L) if bits.endswith("a") else O.find_primes(int(bits), log2n, L)
     ctx = make_ctx(log2n, q, t, f=3, max_group=64, seed=15)
     LN, n = L * N, C * N - 3
