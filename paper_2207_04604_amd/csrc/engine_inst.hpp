@@ -330,9 +330,10 @@ struct Launch {
                                                uint32_t C, uint64_t n_values, hipStream_t st)
     {
         // N = 2^14, rounds with 16-byte loads of pairs (they spill) and 8-byte loads, us: 54 bits, 10 workgroups of 8 limbs 563.5 / 569.8, 16 of 4 415.6 /
-        // 428.2, 36 of 6 907 / 930, 64 of 3 583 / 592, 120 of 3 941 / 940;  60 bits 586 / 593, 433 / 442, 960 / 981, 621 / 626, 1,003 / 999;  36
-        // bits 596 / 585, 432 / 433, 916 / 920, 585 / 581, 912 / 900.
-        constexpr bool FEW = ENG::E > 8, PAIRS = FEW && ENG::A::KIND >= 4;
+        // 428.2, 36 of 6 907 / 930, 64 of 3 583 / 592, 120 of 3 941 / 940;  60 bits 586 / 593, 433 / 442, 960 / 981, 621 / 626, 1,003 / 999;  Shoup
+        // quotients, 54 bits 679 / 712, 510 / 534, 1,065 / 1,105, 706 / 724, 1,194 / 1,213;  60 bits 761 / 768, 578 / 587, 1,234 / 1,257, 839 / 844, 1,435 /
+        // 1,444;  30 bits 551 / 547, 424 / 425, 878 / 885, 571 / 577, 970 / 968;  36 bits 596 / 585, 432 / 433, 916 / 920, 585 / 581, 912 / 900.
+        constexpr bool FEW = ENG::E > 8, PAIRS = FEW && ENG::A::KIND != 0 && ENG::A::KIND != 3;
         if (PAIRS && (uint64_t)C * njobs <= 64)
             hipLaunchKernelGGL((k_convert_combine_decode<ENG, FEW && !PAIRS>), dim3(C, njobs), dim3(ENG::T), 0, st, jobs, stride,
                                n_values, ctx->d_tabs, ctx->rc);

@@ -83,7 +83,8 @@ def test_refresh_in_parts(bits, log2n, L, C, part):
     ("30", 10, 2, 2, (1, 2, 5, 64)), ("36", 11, 3, 2, (1, 3, 64)), ("44", 13, 2, 2, (1, 2, 4, 5, 64)), ("54", 13, 2, 2, (1, 2, 3, 64)),
     ("60", 13, 1, 2, (1, 2, 5)), ("54a", 12, 2, 2, (1, 4)), ("60a", 13, 2, 2, (3, 64)), ("36", 14, 2, 2, (1, 2, 5, 64)), ("54", 14, 1, 2, (1, 4)),
     ("60a", 14, 1, 2, (1, 3)), ("30", 14, 2, 2, (2, 3)),
-    ("54", 14, 2, 64, (3, 5)), ("60", 14, 1, 2, (1, 2, 64)), ("54", 14, 1, 65, (1, 3)), ("60", 14, 2, 65, (4,)),      # N = 2^14: loads in pairs up to C = 64
+    ("54", 14, 2, 64, (3, 5)), ("60", 14, 1, 2, (1, 2, 64)), ("54", 14, 1, 65, (1, 3)), ("60", 14, 2, 65, (4,)), ("54a", 14, 1, 3, (1, 2, 64)),
+    ("60a", 14, 1, 65, (3,)),      # N = 2^14: loads in pairs up to C = 64
 ])
 def test_conversion_shares_in_a_round(bits, log2n, L, C, Ks):
     N, t, receiver = 1 << log2n, 12289 if log2n <= 11 else 65537, 0
